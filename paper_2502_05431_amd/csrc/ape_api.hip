@@ -52,6 +52,7 @@ int check_shape(const ape_shape* s, ShapeInfo* o) {
     o->group = o->hq / o->hkv;
     o->mfma = !o->force_generic && o->dtype == APE_BF16 && o->d == 128 &&
               (o->group == 1 || o->group == 2 || o->group == 4 || o->group == 8);
+    o->tile = !o->force_generic && !o->mfma && o->hkv <= 1 << 22;   // (more KV heads than that would pass the launch limit of its grid's x)
     return APE_OK;
 }
 
@@ -96,7 +97,22 @@ int check_encode_size(const ShapeInfo& si, int n_chunks, int max_len, long total
     return APE_OK;
 }
 
+hipError_t launch_encode(const ShapeInfo& si, const EncodeArgs& e, hipStream_t s) {
+    if (si.mfma) return launch_flash_encode(e, s);
+    // The tile kernel's grid is contexts x KV heads x row tiles of the longest context; a call whose lengths are so
+    // uneven that this passes the launch limit takes the vector-ALU kernel, whose grid is the rows themselves.
+    const long n_qtiles = ((long)e.max_chunk_len * si.group + 127) / 128;
+    if (si.tile && ((long)e.n_chunks * si.hkv + 7) / 8 * 8 * n_qtiles < kMaxEncodeBlocks) return launch_tile_encode(e, si.dtype, s);
+    return launch_generic_encode(e, si.dtype, s);
+}
+
 namespace {
+
+// The query kernel that serves the shape.
+hipError_t launch_query(const ShapeInfo& si, const QueryArgs& a, int block_rows, hipStream_t s) {
+    if (si.mfma) return launch_flash_prefill(a, block_rows, s);
+    return si.tile ? launch_tile_query(a, si.dtype, block_rows, s) : launch_generic_query(a, si.dtype, s);
+}
 
 KvView to_view(const ape_request* r) {
     KvView v;
@@ -128,6 +144,14 @@ QueryPlan plan_query(int base_workgroups, long max_ctx, int min_len, int target_
     return p;
 }
 
+// Split plan of the tile kernels, queries and decode alike.
+QueryPlan tile_plan(const ShapeInfo& si, int batch, int q_len, long max_ctx) {
+    const int rows = q_len * si.group, bm = tile_query_block_rows(rows);
+    QueryPlan p = plan_query(batch * si.hkv * ceil_div(rows, bm), max_ctx, 128, 512);
+    p.block_rows = bm;
+    return p;
+}
+
 // Split plan of a decode step.  Matrix-core path: one workgroup per (request, KV head, split), two
 // of them resident per CU.  What decides the rate is how evenly the long (context) workgroups fill the
 // 256 CUs: a count that is a multiple of 256 streams at 81-84 % of the HBM peak (256 itself is best:
@@ -138,6 +162,7 @@ QueryPlan plan_query(int base_workgroups, long max_ctx, int min_len, int target_
 // and the count at 2048 or less; otherwise many workgroups (at least 8 splits per request, about
 // 2048 workgroups), where the remainder of the last round matters less.
 QueryPlan decode_plan(const ShapeInfo& si, int batch, long max_ctx) {
+    if (si.tile) return tile_plan(si, batch, 1, max_ctx);
     if (!si.mfma) return plan_query(batch * si.hq, max_ctx, 256, 1024);
     const int base = batch * si.hkv;
     int g = base, r = 256;
@@ -152,6 +177,7 @@ QueryPlan decode_plan(const ShapeInfo& si, int batch, long max_ctx) {
 // Split plan of the query prefill.  Matrix-core path: about one workgroup per CU (two of the narrow
 // tile for contexts of middle length), the query tile chosen by flash_prefill_block_rows.
 QueryPlan prefill_plan(const ShapeInfo& si, int batch, int q_len, long max_ctx) {
+    if (si.tile) return tile_plan(si, batch, q_len, max_ctx);
     const int rows = q_len * si.group;
     const long units = (long)batch * q_len * si.hq;
     const int bm = si.mfma ? flash_prefill_block_rows(rows, max_ctx) : 0;
@@ -337,7 +363,7 @@ int ape_encode_chunks(const ape_shape* shape,
         e.cu = nullptr; e.out = o_prefix; e.lse = lse_prefix;
         e.n_chunks = 1; e.prefix_len = 0; e.total_rows = prefix_len; e.max_chunk_len = prefix_len;
         e.n_q_heads = si.hq; e.n_kv_heads = si.hkv; e.head_dim = si.d;
-        hipError_t he = si.mfma ? launch_flash_encode(e, st) : launch_generic_encode(e, si.dtype, st);
+        hipError_t he = launch_encode(si, e, st);
         if (he != hipSuccess) return fail(APE_ERR_DEVICE, "encode (prefix rows): %s", hipGetErrorString(he));
     }
     if (total > 0) {
@@ -347,7 +373,7 @@ int ape_encode_chunks(const ape_shape* shape,
         e.n_chunks = n_chunks; e.prefix_len = prefix_len; e.total_rows = (int)total; e.max_chunk_len = max_len;
         e.n_q_heads = si.hq; e.n_kv_heads = si.hkv; e.head_dim = si.d;
         e.uniform_chunks = min_len == max_len;
-        hipError_t he = si.mfma ? launch_flash_encode(e, st) : launch_generic_encode(e, si.dtype, st);
+        hipError_t he = launch_encode(si, e, st);
         if (he != hipSuccess) return fail(APE_ERR_DEVICE, "encode: %s", hipGetErrorString(he));
     }
     return APE_OK;
@@ -400,10 +426,7 @@ static int run_query(const ShapeInfo& si, const ape_request* reqs, int batch, in
         a.n_req = nb; a.q_len = q_len; a.n_q_heads = si.hq; a.n_kv_heads = si.hkv; a.head_dim = si.d;
         a.n_ctx_splits = plan.n_ctx_splits; a.ctx_split_len = plan.ctx_split_len;
         a.units_total = (int)units; a.req_base = b0;
-        hipError_t he;
-        // (a decode step is a query of one row: the flash kernel's narrow tile, one wavefront computing)
-        if (si.mfma) he = launch_flash_prefill(a, decode ? 128 : plan.block_rows, st);
-        else he = launch_generic_query(a, si.dtype, st);
+        hipError_t he = launch_query(si, a, plan.block_rows, st);
         if (he != hipSuccess) return fail(APE_ERR_DEVICE, "attention kernel: %s", hipGetErrorString(he));
 
         m.part_o = part_o; m.part_lse = part_lse; m.out = out; m.lse_out = lse_out;
@@ -532,7 +555,7 @@ int ape_attention_tree(const ape_shape* shape, const ape_request* req,
     {
         const long slots = (long)plan.max_splits + 1;
         long blocks;
-        if (si.mfma && q_len > 1) {
+        if (si.tile || (si.mfma && q_len > 1)) {
             const long n_qtiles = ((long)q_len * si.group + plan.block_rows - 1) / plan.block_rows;
             blocks = ((slots - 1) * si.hkv + 7) / 8 * 8 * n_qtiles + ((long)si.hkv + 7) / 8 * 8 * n_qtiles;
         } else if (si.mfma) {
@@ -566,8 +589,7 @@ int ape_attention_tree(const ape_shape* shape, const ape_request* req,
     a.n_ctx_splits = plan.max_splits; a.ctx_split_len = plan.len;
     a.split_ranges = plan_dev + TreePlanLayout{n_nodes, plan.max_splits}.ranges_at();
     a.units_total = (int)units; a.req_base = 0;
-    if (si.mfma) he = launch_flash_prefill(a, q_len == 1 ? 128 : plan.block_rows, st);
-    else he = launch_generic_query(a, si.dtype, st);
+    he = launch_query(si, a, plan.block_rows, st);
     if (he != hipSuccess) return fail(APE_ERR_DEVICE, "attention kernel: %s", hipGetErrorString(he));
 
     m.part_o = part_o; m.part_lse = part_lse; m.out = out; m.lse_out = lse_out; m.nodes = nodes_dev; m.plan = plan_dev;

@@ -957,15 +957,6 @@ __device__ __forceinline__ void init_state(WaveState<RB>& st) {
     }
 }
 
-// XCD-aware work mapping.  Workgroups are dealt round-robin to the 8 XCDs (each with its own
-// L2); a "team" = the workgroups that read the same K/V (all query tiles of one KV range).
-// Teams are dealt to XCDs so that the members of a team run on one XCD back to back.
-__device__ __forceinline__ void team_of_block(int block, int team_size, int& team, int& member) {
-    const int xcd = block & 7, slot = block >> 3;
-    member = slot % team_size;
-    team = (slot / team_size) * 8 + xcd;
-}
-
 // ------------------------------------------------------------------------------------------
 // Query prefill: team = (split, KV head); grid = the context teams (padded to a multiple of 8) times
 // n_qtiles, then the prefix+self teams likewise.

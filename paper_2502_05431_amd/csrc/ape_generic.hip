@@ -1,6 +1,6 @@
 // Generic gfx950 kernels of the APE attention path: any head_dim <= 256, fp32 or bf16 storage,
-// fp32 arithmetic on the vector ALUs.  They serve the fp32 workload and every shape the
-// matrix-core kernels do not cover.  One wavefront (64 lanes) owns one (query row, query head)
+// fp32 arithmetic on the vector ALUs.  They run where the caller asks for them (APE_DTYPE_FLAG_GENERIC, for
+// cross-checks) and where a call's sizes pass the launch limits of the tile kernels.  One wavefront (64 lanes) owns one (query row, query head)
 // and one split of its keys; the split-merge kernel at the end of this file is shared with the
 // matrix-core kernels.
 //

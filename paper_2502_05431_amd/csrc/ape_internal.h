@@ -244,6 +244,15 @@ __device__ __forceinline__ KvView load_view(int rq) {
     v.temperature = ap->req[rq].temperature; v.scale = ap->req[rq].scale;
     return v;
 }
+
+// XCD-aware work mapping.  Workgroups are dealt round-robin to the 8 XCDs (each with its own
+// L2); a "team" = the workgroups that read the same K/V (all query tiles of one KV range).
+// Teams are dealt to XCDs so that the members of a team run on one XCD back to back.
+__device__ __forceinline__ void team_of_block(int block, int team_size, int& team, int& member) {
+    const int xcd = block & 7, slot = block >> 3;
+    member = slot % team_size;
+    team = (slot / team_size) * 8 + xcd;
+}
 #endif
 
 // ---- host helpers of the entry points (defined in ape_api.hip; the layer library, a separate
@@ -251,13 +260,16 @@ __device__ __forceinline__ KvView load_view(int rq) {
 struct ShapeInfo {
     int hq, hkv, d, dtype, group;
     bool force_generic;
-    bool mfma;                  // matrix-core kernels cover this shape
+    bool mfma;                  // the flash kernels cover this shape
+    bool tile;                  // the tile kernels serve it (every other shape, unless the caller asks for the vector-ALU kernels)
 };
 // records the text ape_last_error() returns on this thread, returns `code`
 int fail(int code, const char* fmt, ...) __attribute__((format(printf, 2, 3)));
 int check_shape(const ape_shape* s, ShapeInfo* o);
 // size limits of an encode launch (see the header's general conventions)
 int check_encode_size(const ShapeInfo& si, int n_chunks, int max_len, long total_rows);
+// the encode kernel that serves the shape
+hipError_t launch_encode(const ShapeInfo& si, const EncodeArgs& e, hipStream_t s);
 
 // Split plan shared by ape_workspace_bytes and the launches.
 struct QueryPlan {
@@ -265,12 +277,14 @@ struct QueryPlan {
     int ctx_split_len;
     int n_splits_total;
     int n_bound;           // >= n_ctx_splits of this plan and of the plan for any shorter context with the same base and target
-    int block_rows;        // query tile of the flash prefill this plan was made for (0: not a flash prefill)
+    int block_rows;        // query tile this plan was made for (0: the vector-ALU kernels, which have none)
 };
 
 // ---- launchers (each returns hipGetLastError() of its launch) ------------------------------
 hipError_t launch_generic_query(const QueryArgs& a, int dtype, hipStream_t s);
 hipError_t launch_generic_encode(const EncodeArgs& a, int dtype, hipStream_t s);
+hipError_t launch_tile_query(const QueryArgs& a, int dtype, int block_rows, hipStream_t s);   // any supported shape; block_rows from the plan
+hipError_t launch_tile_encode(const EncodeArgs& a, int dtype, hipStream_t s);
 hipError_t launch_merge(const MergeArgs& a, hipStream_t s);
 hipError_t launch_rope_write(const RopeArgs& a, int dtype, hipStream_t s);
 hipError_t launch_tree_plan(const TreePlanArgs& a, hipStream_t s);
@@ -278,6 +292,8 @@ hipError_t launch_tree_merge(const TreeMergeArgs& a, hipStream_t s);
 hipError_t launch_flash_prefill(const QueryArgs& a, int block_rows, hipStream_t s);     // bf16, d = 128; block_rows from the plan
 hipError_t launch_flash_encode(const EncodeArgs& a, hipStream_t s);     // bf16, d = 128
 
+// rows of (token, group-head) pairs one workgroup of the tile kernels covers
+int tile_query_block_rows(int rows_per_kv_head);
 // rows of (token, group-head) pairs one flash workgroup covers for a given amount of rows
 int flash_block_rows(int rows_per_kv_head);
 // the same for the query prefill, which also looks at the context length (see the definition), and

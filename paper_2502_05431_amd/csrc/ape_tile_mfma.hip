@@ -1,0 +1,595 @@
+// Matrix-core attention for every head shape that the flash kernels (bf16, head_dim 128, 1/2/4/8 query
+// heads per KV head) do not take: bf16 and fp32, any head_dim that is a multiple of 8 up to 256, any number of query heads
+// per KV head.  Query prefill, decode and the block-diagonal encode of the contexts.
+//
+// Math (arXiv 2502.05431): as in the flash kernels -- block results of Appendix C.1, context scores
+// q.k/(T sqrt d) (Section 4.4), the scaling factor applied later by the merge kernel.
+//
+// Precision: that of the vector-ALU kernels, which keep the probabilities in fp32.  fp32 storage runs on the fp32 MFMA
+// (32x32x2); bf16 storage on the bf16 MFMA (32x32x16) with every probability taken as the sum of two bf16
+// values (16 significant bits, beyond what the bf16 output holds), i.e. two MFMAs per V fragment.
+//
+// Tiling: WR x WK wavefronts.  A wavefront owns 32 rows -- a row is a (query token, head of the group) pair -- and
+// every WK-th run of 32 tokens of the stream; the WK partial results of a row are combined in LDS at the
+// end.  Many rows take 4 x 1 (every K/V byte in LDS serves 128 rows), a decode step or a query of a few
+// rows 1 x 4 (the same bytes in flight, all four wavefronts computing).  Tokens pass through a ring of LDS stages
+// of 32 WK tokens filled by direct global->LDS loads.  A stage is a run of consecutive indices of the
+// pooled contexts (or of prefix + own tokens), whatever context they belong to: a stage that crosses the
+// end of a context picks its source row by row, so short and ragged contexts waste no MFMA on padding.
+// head_dim is padded to 64, 128 or 256 inside LDS; the padding of K repeats finite data that meets zeros in Q.
+//
+// What bounds it: the MFMAs once the streams are long (fp32: 64 cycles for 4096 multiply-adds; 1.5 times the
+// attention's own count for bf16), the fixed chain of a launch, first loads and merge for a short query.  Against the
+// vector-ALU kernels, which give a wavefront one row and read every K/V byte once per row (same card, same inputs):
+// fp32 encode of eight contexts of about 512 tokens, 32/8 heads of 128: 2754 -> 231 us (73 TFLOP/s; the vendor's fp32 GEMM
+// reaches 153); 64 bf16 rows over 20 x 512 tokens, 16/8 heads of 256: 14200 -> 64 us; 16 fp32 rows over 4 x 32 tokens,
+// 4/2 heads of 64: 47.8 -> 15.7 us with the merge.
+#include "ape_internal.h"
+
+#include <math.h>
+
+namespace ape {
+namespace {
+
+typedef __attribute__((ext_vector_type(8))) __bf16 bf16x8;
+typedef __attribute__((ext_vector_type(4))) __bf16 bf16x4;
+typedef __attribute__((ext_vector_type(16))) float f32x16;
+typedef __attribute__((ext_vector_type(4))) float f32x4;
+typedef __attribute__((ext_vector_type(4))) short s16x4;
+typedef __attribute__((ext_vector_type(4))) uint32_t u32x4;
+typedef __attribute__((ext_vector_type(2))) uint32_t u32x2;
+
+constexpr float LOG2E = 1.4426950408889634f;
+constexpr float LN2 = 0.6931471805599453f;
+constexpr float kSlack = 10.f;               // a reference moves only when exceeded by this (fp32 sums lose nothing by that)
+constexpr float kUnset = -1.0e30f;           // reference of a row that has not seen a token yet
+
+// 1/(T sqrt d), rounded once.  Scores of |x| = 40 (T = 0.1) turn one rounding of the scale into 2.4e-6 of a probability, so
+// fp32 carries its remainder along and keeps natural-log units (a factor log2 e inside would round once more);
+// bf16 has log2 e inside and a single fused multiply per score.
+template <typename T>
+struct ScoreScale {
+    static constexpr bool F32 = sizeof(T) == 4;
+    float hi, lo;
+    __device__ __forceinline__ ScoreScale(int d, float temperature) {
+        const double x = (F32 ? 1.0 : 1.4426950408889634) / (sqrt((double)d) * (double)temperature);
+        hi = (float)x; lo = (float)(x - (double)hi);
+    }
+    // exp of (difference of references)
+    static __device__ __forceinline__ float exp_of(float x) { return __builtin_amdgcn_exp2f(F32 ? x * LOG2E : x); }
+    __device__ __forceinline__ float prob(float s, float m) const {
+        return exp_of(F32 ? fmaf(s, hi, fmaf(s, lo, -m)) : fmaf(s, hi, -m));
+    }
+    static __device__ __forceinline__ float lse(float m, float l) {
+        const float x = __builtin_amdgcn_logf(l);            // log2
+        return F32 ? fmaf(x, LN2, m) : (m + x) * LN2;
+    }
+};
+
+// Sizes of one instantiation: T storage type, DP padded head_dim, WR x WK wavefronts.
+template <typename T, int DP, int WR, int WK>
+struct Tile {
+    static constexpr int NW = WR * WK, NT = 64 * NW;
+    static constexpr int ROWS = 32 * WR;                    // query rows per workgroup
+    static constexpr int KS = 32 * WK;                      // tokens per stage
+    static constexpr int PITCH = DP * (int)sizeof(T);       // bytes of a K (or V) row in LDS
+    static constexpr int CPR = PITCH / 16;                  // 16-byte chunks of a row
+    static constexpr int PART = KS * PITCH;                 // K part of a stage; V follows
+    static constexpr int STAGE = 2 * PART;
+    // Stages in the ring: two keep one in flight while the other is read; small stages take more, as far as two
+    // workgroups still fit a CU.
+    static constexpr int NSTG = STAGE * 4 <= 80 * 1024 ? 4 : STAGE * 3 <= 80 * 1024 ? 3 : 2;
+    static constexpr int LDS = NSTG * STAGE;
+    static constexpr int LPT = PART / (16 * NT);            // loads per thread and part
+    static constexpr int NB = DP / 32;                      // 32-dim blocks of the output
+    // wavefronts per SIMD, which set the register budget: what LDS has room for, and one for 256-wide rows (Q and the
+    // accumulators alone are 192 registers)
+    static constexpr int WAVES = DP == 256 || 160 * 1024 / LDS * NW < 8 ? 1 : 2;
+    static_assert(PART % (16 * NT) == 0 && LDS <= 160 * 1024, "stage size");
+};
+
+// XOR swizzles of the 16-byte chunk index inside a row (see the reads in `compute`).
+template <typename T, int DP>
+__device__ __forceinline__ int swz_k(int row) {
+    // 16 rows read the same chunk at once: 16 different 16-byte slots of the 256 that LDS serves at a time
+    return DP * sizeof(T) == 128 ? (row >> 1) & 7 : row & 15;
+}
+template <typename T, int DP>
+__device__ __forceinline__ int swz_v(int row) {
+    if (sizeof(T) == 4) return ((row >> 2) & 1) << 3;       // rows r and r + 4, 128 bytes of each at once
+    return DP * sizeof(T) == 128 ? ((row >> 1) & 1) << 2 : (row & 3) << 2;   // four rows, 64 bytes of each
+}
+
+// Where the tokens of a stream are: index t of the stream has its K row at ka + t * stride while t < b
+// and at kb + t * stride for b <= t < e.  Two neighbouring segments are known at any time (two contexts;
+// or the prefix and the own tokens); a stage that reaches beyond the second looks its rows up one by one.
+struct Source {
+    const char *ka, *va, *kb, *vb;
+    int b, e;
+    long stride, head;
+    const int32_t* cu;               // NULL: prefix + own tokens
+    const void* const* kt;
+    const void* const* vt;
+    int n_chunks, c, ca;             // the contexts behind kb and ka
+
+    __device__ __forceinline__ void next_context() {
+        ka = kb; va = vb; b = e; ca = c;
+        while (c + 1 < n_chunks) {
+            ++c;
+            int c1; const void *k, *v;
+            scalar_load_chunk(cu + c + 1, kt + c, vt + c, c1, k, v);
+            if (c1 > b) {
+                kb = (const char*)k + head - (long)b * stride; vb = (const char*)v + head - (long)b * stride; e = c1;
+                return;
+            }
+        }
+    }
+    __device__ __forceinline__ void init_ctx(const KvView& kv, int t0, long stride_, long head_) {
+        cu = kv.cu; kt = kv.k_chunks; vt = kv.v_chunks; n_chunks = kv.n_chunks; stride = stride_; head = head_;
+        c = find_chunk(cu, n_chunks, t0);
+        const int c0 = scalar_load_i32(cu + c);
+        int c1; const void *k, *v;
+        scalar_load_chunk(cu + c + 1, kt + c, vt + c, c1, k, v);
+        kb = (const char*)k + head - (long)c0 * stride; vb = (const char*)v + head - (long)c0 * stride; e = c1;
+        next_context();
+    }
+    __device__ __forceinline__ void init_seq(const void* kp, const void* vp, int np, const void* ks, const void* vs, int ns, long stride_, long head_) {
+        cu = nullptr; kt = vt = nullptr; n_chunks = c = ca = 0; stride = stride_; head = head_;
+        ka = (const char*)kp + head; va = (const char*)vp + head; b = np;
+        kb = (const char*)ks + head - (long)np * stride; vb = (const char*)vs + head - (long)np * stride; e = np + ns;
+    }
+    // K and V rows of index t, looked up in the table from the context behind ka on (t < cu[n_chunks])
+    __device__ __forceinline__ void look_up(int t, const char*& k, const char*& v) const {
+        int lo = ca, hi = n_chunks - 1;
+        while (lo < hi) {
+            const int mid = (lo + hi + 1) >> 1;
+            if (cu[mid] <= t) lo = mid; else hi = mid - 1;
+        }
+        const long off = (long)(t - cu[lo]) * stride + head;
+        k = (const char*)kt[lo] + off; v = (const char*)vt[lo] + off;
+    }
+};
+
+// One direct global->LDS load: lane i's 16 bytes land at (wavefront-uniform) lds + 16 i.  Written as an
+// instruction so that the compiler does not order it (it could only wait for all of them): the waits and
+// barriers of the ring do.
+__device__ __forceinline__ void load_lds16(const char* src, const char* lds) {
+    const uint32_t m0v = (uint32_t)(uintptr_t)(const __attribute__((address_space(3))) char*)lds;
+    asm volatile("s_mov_b32 m0, %1\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %0, off" :: "v"(src), "s"(m0v) : "m0");
+}
+
+template <int N>
+__device__ __forceinline__ void wait_loads() {
+    static_assert(N < 64, "vmcnt is a 6-bit counter");
+    __builtin_amdgcn_s_waitcnt(0x0f70 | (N & 15) | ((N >> 4) << 14));
+}
+__device__ __forceinline__ void stage_barrier() {
+    asm volatile("" ::: "memory");
+    __builtin_amdgcn_s_barrier();
+    asm volatile("" ::: "memory");
+}
+
+// Starts the loads of tokens [t, t + KS) into `stage`; rows past t_end - 1 repeat that token (finite
+// data whose probabilities are zero).
+template <typename T, int DP, int WR, int WK>
+__device__ __forceinline__ void start_stage(Source& src, int t, int t_end, int d, char* stage) {
+    using X = Tile<T, DP, WR, WK>;
+    if (src.cu) while (t >= src.b && src.e > src.b) src.next_context();
+    const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    int lane = threadIdx.x & 63;
+    asm volatile("" : "+v"(lane));                          // the lane's offsets are recomputed here, not kept over the loop
+    const bool beyond = min(t + X::KS, t_end) > src.e;      // a third context begins inside the stage
+#pragma unroll
+    for (int i = 0; i < X::LPT; ++i) {
+        const int at = (i * X::NW + wave) * 64;             // first chunk of this wavefront's load
+        const int row = (at + lane) / X::CPR, pos = lane % X::CPR;
+        const int tt = min(t + row, t_end - 1);
+        const char *k, *v;
+        if (__builtin_expect(beyond, 0)) {
+            src.look_up(tt, k, v);
+        } else {
+            const long off = (long)tt * src.stride;
+            k = (tt < src.b ? src.ka : src.kb) + off;
+            v = (tt < src.b ? src.va : src.vb) + off;
+        }
+        const int ck = pos ^ swz_k<T, DP>(row), cv = pos ^ swz_v<T, DP>(row);
+        load_lds16(k + (ck * 16 < d * (int)sizeof(T) ? ck * 16 : 0), stage + at * 16);
+        load_lds16(v + (cv * 16 < d * (int)sizeof(T) ? cv * 16 : 0), stage + X::PART + at * 16);
+    }
+}
+
+// Per-wavefront state: 32 query rows, row = lane & 31 (both half-wavefronts hold the row: tokens and dims are split
+// between them).
+template <typename T, int DP>
+struct Rows {
+    static constexpr int NQ = sizeof(T) == 2 ? DP / 16 : DP / 8;   // 16-byte pieces of Q per lane
+    u32x4 q[NQ];                 // bf16: dims 16 i + 8 hi .. +7;  fp32: dims 8 i + 4 hi .. +3
+    float m, l;                  // softmax reference (units of ScoreScale) and this lane's share of the sum
+    f32x16 o[DP / 32];           // O^T: dim 32 db + 8 (r / 4) + 4 hi + r % 4
+};
+
+__device__ __forceinline__ float max_halves(float x) {
+    const u32x2 r = __builtin_amdgcn_permlane32_swap(__float_as_uint(x), __float_as_uint(x), false, false);
+    return fmaxf(__uint_as_float(r[0]), __uint_as_float(r[1]));
+}
+__device__ __forceinline__ float sum_halves(float x) {
+    const u32x2 r = __builtin_amdgcn_permlane32_swap(__float_as_uint(x), __float_as_uint(x), false, false);
+    return __uint_as_float(r[0]) + __uint_as_float(r[1]);
+}
+__device__ __forceinline__ bf16x4 lds_read_tr(const char* p) {
+    s16x4 r = __builtin_amdgcn_ds_read_tr16_b64_v4i16((__attribute__((address_space(3))) s16x4*)p);
+    return __builtin_bit_cast(bf16x4, r);
+}
+__device__ __forceinline__ uint32_t pack_bf16(float a, float b) {
+    const __bf16 x = (__bf16)a, y = (__bf16)b;
+    return (uint32_t)__builtin_bit_cast(unsigned short, x) | ((uint32_t)__builtin_bit_cast(unsigned short, y) << 16);
+}
+
+// With 256-wide rows the accumulators and Q take 192 of the 256 registers of a wavefront (two per SIMD): LDS
+// reads may run ahead of their MFMAs by a few fragments only, which the scheduler has to be told.
+template <int DP>
+__device__ __forceinline__ void group_barrier() {
+    if constexpr (DP == 256) __builtin_amdgcn_sched_barrier(0);
+}
+
+// One run of 32 tokens: S^T = K Q^T, softmax, O^T += V^T P^T.  `nvis`: how many of the tokens this lane's
+// row sees.
+template <typename T, int DP>
+__device__ __forceinline__ void compute(const char* kpart, const char* vpart, const ScoreScale<T>& sc, int nvis, Rows<T, DP>& st) {
+    constexpr int PITCH = DP * (int)sizeof(T), NB = DP / 32;
+    const int lane = threadIdx.x & 63, l32 = lane & 31, hi = lane >> 5;
+    // fp32 scores are summed in several chains (every element of a 16-byte piece its own, two where registers are
+    // short): a sum of up to 256 terms of one sign pattern loses fewer bits, at 16 additions a chain.
+    constexpr int NCH = sizeof(T) == 2 ? 1 : DP == 64 ? 4 : 2;
+    f32x16 sc_part[NCH];
+#pragma unroll
+    for (int c = 0; c < NCH; ++c)
+#pragma unroll
+        for (int r = 0; r < 16; ++r) sc_part[c][r] = 0.f;
+    // K: token row l32, chunk 2 i + hi.  The swizzle leaves one address for every i % 8; the lane's offset is made
+    // opaque so that they are recomputed here (an instruction each) and not kept in registers over the loop.
+    int koff = l32 * PITCH + ((hi ^ swz_k<T, DP>(l32)) << 4);
+    asm volatile("" : "+v"(koff));
+#pragma unroll
+    for (int i = 0; i < Rows<T, DP>::NQ; ++i) {
+        if (i % 4 == 0) group_barrier<DP>();
+        const u32x4 a = *(const u32x4*)(kpart + (koff ^ (32 * (i % 8))) + 256 * (i / 8));
+        if constexpr (sizeof(T) == 2) {
+            sc_part[0] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(__builtin_bit_cast(bf16x8, a), __builtin_bit_cast(bf16x8, st.q[i]), sc_part[0], 0, 0, 0);
+        } else {
+#pragma unroll
+            for (int e = 0; e < 4; ++e)
+                sc_part[e % NCH] = __builtin_amdgcn_mfma_f32_32x32x2f32(__uint_as_float(a[e]), __uint_as_float(st.q[i][e]), sc_part[e % NCH], 0, 0, 0);
+        }
+    }
+    f32x16 s = sc_part[0];
+    if constexpr (NCH == 2) {
+#pragma unroll
+        for (int r = 0; r < 16; ++r) s[r] += sc_part[1][r];
+    } else if constexpr (NCH == 4) {
+#pragma unroll
+        for (int r = 0; r < 16; ++r) s[r] = (s[r] + sc_part[1][r]) + (sc_part[2][r] + sc_part[3][r]);
+    }
+    // register r holds token 8 (r / 4) + 4 hi + r % 4
+    const bool masked = __builtin_amdgcn_ballot_w64(nvis < 32) != 0;
+    if (masked) {
+#pragma unroll
+        for (int r = 0; r < 16; ++r) s[r] = 8 * (r >> 2) + 4 * hi + (r & 3) < nvis ? s[r] : -INFINITY;
+    }
+    float mx = s[0];
+#pragma unroll
+    for (int r = 1; r < 16; ++r) mx = fmaxf(mx, s[r]);
+    mx = max_halves(mx) * sc.hi;                             // -inf: the row sees nothing here
+    if (__builtin_amdgcn_ballot_w64(mx > st.m + kSlack) != 0) {
+        const float m_new = mx > st.m + kSlack ? mx : st.m;  // (kUnset + kSlack == kUnset)
+        const float alpha = ScoreScale<T>::exp_of(st.m - m_new);
+        st.m = m_new;
+        st.l *= alpha;
+#pragma unroll
+        for (int db = 0; db < NB; ++db)
+#pragma unroll
+            for (int r = 0; r < 16; ++r) st.o[db][r] *= alpha;
+    }
+    float p[16], sum0 = 0.f, sum1 = 0.f;
+#pragma unroll
+    for (int r = 0; r < 16; ++r) p[r] = sc.prob(s[r], st.m);
+    if (sizeof(T) == 4 && masked) {                          // (-inf times the scale's remainder, which may be 0 or negative)
+#pragma unroll
+        for (int r = 0; r < 16; ++r) p[r] = s[r] > -INFINITY ? p[r] : 0.f;
+    }
+#pragma unroll
+    for (int r = 0; r < 16; r += 2) { sum0 += p[r]; sum1 += p[r + 1]; }
+    st.l += sum0 + sum1;
+    if constexpr (sizeof(T) == 2) {
+        // k-slot e of slab sl is token 16 sl + (e < 4 ? 4 hi + e : 8 + 4 hi + e - 4): the registers 8 sl .. 8 sl + 7
+        u32x4 ph[2], pl[2];
+#pragma unroll
+        for (int sl = 0; sl < 2; ++sl)
+#pragma unroll
+            for (int j = 0; j < 4; ++j) {
+                const float a = p[8 * sl + 2 * j], b = p[8 * sl + 2 * j + 1];
+                const uint32_t h = pack_bf16(a, b);
+                ph[sl][j] = h;
+                pl[sl][j] = pack_bf16(a - __uint_as_float(h << 16), b - __uint_as_float(h & 0xffff0000u));
+            }
+        const int g16 = lane >> 4, s16 = lane & 15;
+        const int row0 = 4 * (g16 >> 1) + (s16 >> 2);
+        int voff = row0 * PITCH + (((2 * (g16 & 1) + ((s16 & 3) >> 1)) ^ swz_v<T, DP>(row0)) << 4) + (s16 & 1) * 8;
+        asm volatile("" : "+v"(voff));
+#pragma unroll
+        for (int sl = 0; sl < 2; ++sl)
+#pragma unroll
+            for (int db = 0; db < NB; ++db) {
+                if (db % 2 == 0) group_barrier<DP>();
+                const char* at = vpart + (voff ^ (64 * (db % 4))) + 256 * (db / 4) + 16 * sl * PITCH;
+                const bf16x4 lo4 = lds_read_tr(at), hi4 = lds_read_tr(at + 8 * PITCH);
+                const bf16x8 a = __builtin_shufflevector(lo4, hi4, 0, 1, 2, 3, 4, 5, 6, 7);
+                st.o[db] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a, __builtin_bit_cast(bf16x8, ph[sl]), st.o[db], 0, 0, 0);
+                st.o[db] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a, __builtin_bit_cast(bf16x8, pl[sl]), st.o[db], 0, 0, 0);
+            }
+    } else {
+        // V: token row 8 (r / 4) + 4 hi + r % 4, dim 32 db + l32
+        int voff = 4 * hi * PITCH + (((l32 >> 2) ^ swz_v<T, DP>(4 * hi)) << 4) + (l32 & 3) * 4;
+        asm volatile("" : "+v"(voff));
+#pragma unroll
+        for (int r = 0; r < 16; ++r) {
+#pragma unroll
+            for (int db = 0; db < NB; ++db) {
+                const float a = *(const float*)(vpart + (voff ^ (128 * (db % 2))) + 256 * (db / 2) + (8 * (r >> 2) + (r & 3)) * PITCH);
+                st.o[db] = __builtin_amdgcn_mfma_f32_32x32x2f32(a, p[r], st.o[db], 0, 0, 0);
+            }
+        }
+    }
+}
+
+// Streams tokens [t_beg, t_end) past the workgroup's rows.  `lim`: this lane's row sees indices up to
+// and including lim; `lim_hi`: the largest lim of the wavefront; `active`: it has rows at all.
+template <typename T, int DP, int WR, int WK>
+__device__ __forceinline__ void stream(Source& src, int t_beg, int t_end, int d, const ScoreScale<T>& sc, int lim, int lim_hi, bool active,
+                                       char* lds, Rows<T, DP>& st) {
+    using X = Tile<T, DP, WR, WK>;
+    const int kw = __builtin_amdgcn_readfirstlane((threadIdx.x >> 6) % WK);
+    const int n = (t_end - t_beg + X::KS - 1) / X::KS;
+    for (int j = 0; j < X::NSTG - 1 && j < n; ++j)
+        start_stage<T, DP, WR, WK>(src, t_beg + j * X::KS, t_end, d, lds + j * X::STAGE);
+    int at = 0, to = X::NSTG - 1;                           // ring positions of stage j and of the one whose loads start
+    for (int j = 0; j < n; ++j) {
+        if (j + X::NSTG - 2 < n) wait_loads<(X::NSTG - 2) * 2 * X::LPT>(); else wait_loads<0>();
+        stage_barrier();                                     // stage j has landed for every wavefront, all of which are done with stage j - 1
+        if (j + X::NSTG - 1 < n) start_stage<T, DP, WR, WK>(src, t_beg + (j + X::NSTG - 1) * X::KS, t_end, d, lds + to * X::STAGE);
+        const int t = t_beg + j * X::KS + 32 * kw;
+        if (active && t <= lim_hi && t < t_end) {
+            const char* part = lds + at * X::STAGE + 32 * kw * X::PITCH;
+            compute<T, DP>(part, part + X::PART, sc, min(lim, t_end - 1) - t + 1, st);
+        }
+        at = at + 1 == X::NSTG ? 0 : at + 1;
+        to = to + 1 == X::NSTG ? 0 : to + 1;
+    }
+}
+
+template <typename T, int DP>
+__device__ __forceinline__ void init_rows(Rows<T, DP>& st, const T* q, int d) {
+    const int hi = (threadIdx.x & 63) >> 5;
+    constexpr int N = 16 / (int)sizeof(T);
+#pragma unroll
+    for (int i = 0; i < Rows<T, DP>::NQ; ++i) {
+        const int c = (2 * i + hi) * N;                      // zeros beyond head_dim (selected, not branched around)
+        const u32x4 w = *(const u32x4*)(q + (c < d ? c : 0));
+#pragma unroll
+        for (int e = 0; e < 4; ++e) st.q[i][e] = c < d ? w[e] : 0;
+    }
+    st.m = kUnset; st.l = 0.f;
+#pragma unroll
+    for (int db = 0; db < DP / 32; ++db)
+#pragma unroll
+        for (int r = 0; r < 16; ++r) st.o[db][r] = 0.f;
+}
+
+// The partial results of a row's WK wavefronts become one, held by the wavefront of the first (others:
+// return false).  Every lane keeps its own dims and its own share of l.
+template <typename T, int DP, int WR, int WK>
+__device__ __forceinline__ bool combine(char* lds, Rows<T, DP>& st) {
+    if constexpr (WK == 1) return true;
+    constexpr int NV = DP / 2 + 2;                          // values per lane
+    static_assert((WK - 1) * WR * NV * 256 <= Tile<T, DP, WR, WK>::LDS, "the ring holds the partial results");
+    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6, kw = wave % WK, wr = wave / WK;
+    float* box = (float*)lds + lane;
+    stage_barrier();                                         // every wavefront is done with the last stage
+    if (kw > 0) {
+        float* to = box + ((kw - 1) * WR + wr) * NV * 64;
+        to[0] = st.m; to[64] = st.l;
+#pragma unroll
+        for (int db = 0; db < DP / 32; ++db)
+#pragma unroll
+            for (int r = 0; r < 16; ++r) to[(2 + 16 * db + r) * 64] = st.o[db][r];
+    }
+    __syncthreads();
+    if (kw > 0) return false;
+#pragma unroll
+    for (int w = 0; w < WK - 1; ++w) {
+        const float* from = box + (w * WR + wr) * NV * 64;
+        const float m = fmaxf(st.m, from[0]);
+        const float a = ScoreScale<T>::exp_of(st.m - m), b = ScoreScale<T>::exp_of(from[0] - m);
+        st.l = st.l * a + from[64] * b;
+        st.m = m;
+#pragma unroll
+        for (int db = 0; db < DP / 32; ++db)
+#pragma unroll
+            for (int r = 0; r < 16; ++r) st.o[db][r] = st.o[db][r] * a + from[(2 + 16 * db + r) * 64] * b;
+    }
+    return true;
+}
+
+// ------------------------------------------------------------------------------------------
+// Query prefill and decode: team = (split, KV head), members = tiles of the query rows; the context
+// teams come first, the prefix + own ones follow.  grid: x as in the flash prefill, y = request.
+template <typename T, int DP, int WR, int WK>
+__global__ __launch_bounds__(64 * WR * WK, (Tile<T, DP, WR, WK>::WAVES)) void tile_query_kernel(const QueryArgs a, int n_qtiles) {
+    using X = Tile<T, DP, WR, WK>;
+    extern __shared__ __attribute__((aligned(16))) char lds[];
+    const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), l32 = lane & 31, hi = lane >> 5;
+    const int d = a.head_dim, hq = a.n_q_heads, hkv = a.n_kv_heads, G = hq / hkv, q_len = a.q_len, rq = blockIdx.y;
+    const int ctx_teams = a.n_ctx_splits * hkv, ctx_blocks = (ctx_teams + 7) / 8 * 8 * n_qtiles;
+    int team, qtile, split;
+    if ((int)blockIdx.x < ctx_blocks) {
+        team_of_block(blockIdx.x, n_qtiles, team, qtile);
+        if (team >= ctx_teams) return;
+        split = team / hkv;
+    } else {
+        team_of_block(blockIdx.x - ctx_blocks, n_qtiles, team, qtile);
+        if (team >= hkv) return;
+        split = a.n_ctx_splits;
+    }
+    const int hk = team % hkv;
+    const KvView kv = load_view<QueryArgs>(rq);
+    const long stride = (long)hkv * d * sizeof(T), head = (long)hk * d * sizeof(T);
+
+    const int rows = q_len * G;
+    const int R0 = qtile * X::ROWS + (wave / WK) * 32, R = R0 + l32;
+    const int tok = min(R, rows - 1) / G, h = hk * G + min(R, rows - 1) % G;
+    const bool valid = R < rows;
+    Source src;
+    int t_beg, t_end, lim, lim_hi;
+    const ScoreScale<T> sc(d, split < a.n_ctx_splits ? kv.temperature : 1.f);
+    if (split < a.n_ctx_splits) {
+        long t0, t1;
+        ctx_split_range(a, kv, split, t0, t1);
+        t1 = min(t1, (long)scalar_load_i32(kv.cu + kv.n_chunks));   // (stay inside the table whatever total_ctx says)
+        if (t0 >= t1) return;                                // an empty split: the merge never looks at it
+        src.init_ctx(kv, (int)t0, stride, head);
+        t_beg = (int)t0; t_end = (int)t1; lim = lim_hi = t_end - 1;
+    } else {
+        const int off = kv.prefix_len + kv.self_len - q_len; // index of query token 0
+        const int tile_hi = min(qtile * X::ROWS + X::ROWS - 1, rows - 1) / G;
+        src.init_seq(kv.k_prefix, kv.v_prefix, kv.prefix_len, kv.k_self, kv.v_self, kv.self_len, stride, head);
+        t_beg = 0; t_end = off + tile_hi + 1;
+        lim = off + tok; lim_hi = off + min(R0 + 31, rows - 1) / G;
+    }
+    Rows<T, DP> st;
+    init_rows<T, DP>(st, (const T*)a.q + (((long)rq * q_len + tok) * hq + h) * d, d);
+    stream<T, DP, WR, WK>(src, t_beg, t_end, d, sc, lim, lim_hi, R0 < rows, lds, st);
+    if (!combine<T, DP, WR, WK>(lds, st)) return;
+
+    const float lt = sum_halves(st.l);
+    if (!valid) return;
+    const float inv = lt > 0.f ? 1.f / lt : 0.f;
+    const long slot = (long)split * a.units_total + ((long)(a.req_base + rq) * q_len + tok) * hq + h;
+    float* o = a.part_o + slot * d;
+#pragma unroll
+    for (int db = 0; db < X::NB; ++db)
+#pragma unroll
+        for (int q4 = 0; q4 < 4; ++q4) {
+            const int c = 32 * db + 8 * q4 + 4 * hi;
+            f32x4 w;
+#pragma unroll
+            for (int e = 0; e < 4; ++e) w[e] = st.o[db][4 * q4 + e] * inv;
+            if (c < d) *(f32x4*)(o + c) = w;
+        }
+    if (hi == 0) a.part_lse[slot] = lt > 0.f ? ScoreScale<T>::lse(st.m, lt) : -INFINITY;
+}
+
+// ------------------------------------------------------------------------------------------
+// Block-diagonal causal encode: team = (context, KV head), members = its row tiles, the heaviest first.
+template <typename T, int DP, int WR>
+__global__ __launch_bounds__(64 * WR, (Tile<T, DP, WR, 1>::WAVES)) void tile_encode_kernel(const EncodeArgs a, int n_qtiles) {
+    using X = Tile<T, DP, WR, 1>;
+    extern __shared__ __attribute__((aligned(16))) char lds[];
+    const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), l32 = lane & 31, hi = lane >> 5;
+    const int d = a.head_dim, hq = a.n_q_heads, hkv = a.n_kv_heads, G = hq / hkv;
+    int team, member;
+    team_of_block(blockIdx.x, n_qtiles, team, member);
+    if (team >= a.n_chunks * hkv) return;
+    const int qtile = n_qtiles - 1 - member, chunk = team / hkv, hk = team % hkv;
+    const int c0 = a.cu ? scalar_load_i32(a.cu + chunk) : 0;
+    const int len = a.cu ? scalar_load_i32(a.cu + chunk + 1) - c0 : a.total_rows;
+    const long rows = (long)len * G;
+    if ((long)qtile * X::ROWS >= rows) return;
+    const long stride = (long)hkv * d * sizeof(T), head = (long)hk * d * sizeof(T);
+    const long R0 = (long)qtile * X::ROWS + wave * 32, R = R0 + l32, Rc = R < rows ? R : rows - 1;
+    const int tok = (int)(Rc / G), h = hk * G + (int)(Rc % G);
+    const bool valid = R < rows;
+    const long tile_last = (long)qtile * X::ROWS + X::ROWS - 1, wave_last = R0 + 31;
+    Source src;
+    src.init_seq(a.k_prefix, a.v_prefix, a.prefix_len, (const T*)a.k + (long)c0 * hkv * d, (const T*)a.v + (long)c0 * hkv * d, len, stride, head);
+    const int t_end = a.prefix_len + (int)((tile_last < rows ? tile_last : rows - 1) / G) + 1;
+    const int lim = a.prefix_len + tok, lim_hi = a.prefix_len + (int)((wave_last < rows ? wave_last : rows - 1) / G);
+    Rows<T, DP> st;
+    init_rows<T, DP>(st, (const T*)a.q + ((long)(c0 + tok) * hq + h) * d, d);
+    stream<T, DP, WR, 1>(src, 0, t_end, d, ScoreScale<T>(d, 1.f), lim, lim_hi, R0 < rows, lds, st);
+
+    const float lt = sum_halves(st.l);
+    if (!valid) return;
+    const float inv = 1.f / lt;                              // a row always sees itself
+    T* o = (T*)a.out + ((long)(c0 + tok) * hq + h) * d;
+#pragma unroll
+    for (int db = 0; db < X::NB; ++db)
+#pragma unroll
+        for (int q4 = 0; q4 < 4; ++q4) {
+            const int c = 32 * db + 8 * q4 + 4 * hi;
+            if (c >= d) continue;
+            if constexpr (sizeof(T) == 4) {
+                f32x4 w;
+#pragma unroll
+                for (int e = 0; e < 4; ++e) w[e] = st.o[db][4 * q4 + e] * inv;
+                *(f32x4*)(o + c) = w;
+            } else {
+                *(u32x2*)(o + c) = u32x2{pack_bf16(st.o[db][4 * q4] * inv, st.o[db][4 * q4 + 1] * inv),
+                                         pack_bf16(st.o[db][4 * q4 + 2] * inv, st.o[db][4 * q4 + 3] * inv)};
+            }
+        }
+    if (a.lse && hi == 0) a.lse[(long)h * a.total_rows + c0 + tok] = ScoreScale<T>::lse(st.m, lt);
+}
+
+template <typename T, int DP, int WR, int WK>
+hipError_t query_with(const QueryArgs& a, hipStream_t s) {
+    using X = Tile<T, DP, WR, WK>;
+    auto kernel = tile_query_kernel<T, DP, WR, WK>;
+    const int rows = a.q_len * (a.n_q_heads / a.n_kv_heads), n_qtiles = (rows + X::ROWS - 1) / X::ROWS;
+    const dim3 grid((unsigned)(((a.n_ctx_splits * a.n_kv_heads + 7) / 8 * 8 + (a.n_kv_heads + 7) / 8 * 8) * n_qtiles), (unsigned)a.n_req);
+    hipError_t e = hipFuncSetAttribute((const void*)kernel, hipFuncAttributeMaxDynamicSharedMemorySize, X::LDS);
+    if (e != hipSuccess) return e;
+    kernel<<<grid, X::NT, X::LDS, s>>>(a, n_qtiles);
+    return hipGetLastError();
+}
+
+// A stage of WK x 32 tokens has to leave room for a second one: the widest rows take fewer wavefronts
+// along the tokens.
+template <typename T, int DP>
+hipError_t query_with_rows(const QueryArgs& a, int block_rows, hipStream_t s) {
+    constexpr int BYTES = DP * (int)sizeof(T);
+    if (block_rows == 128) return query_with<T, DP, 4, 1>(a, s);
+    if (block_rows == 64) return query_with<T, DP, 2, BYTES <= 512 ? 2 : 1>(a, s);
+    return query_with<T, DP, 1, BYTES <= 256 ? 4 : BYTES <= 512 ? 2 : 1>(a, s);
+}
+
+template <typename T, int DP>
+hipError_t encode_with(const EncodeArgs& a, hipStream_t s) {
+    using X = Tile<T, DP, 4, 1>;
+    auto kernel = tile_encode_kernel<T, DP, 4>;
+    const long rows = (long)a.max_chunk_len * (a.n_q_heads / a.n_kv_heads);
+    const int n_qtiles = (int)((rows + X::ROWS - 1) / X::ROWS);
+    hipError_t e = hipFuncSetAttribute((const void*)kernel, hipFuncAttributeMaxDynamicSharedMemorySize, X::LDS);
+    if (e != hipSuccess) return e;
+    kernel<<<(unsigned)((a.n_chunks * a.n_kv_heads + 7) / 8 * 8 * n_qtiles), X::NT, X::LDS, s>>>(a, n_qtiles);
+    return hipGetLastError();
+}
+
+}  // namespace
+
+int tile_query_block_rows(int rows_per_kv_head) { return rows_per_kv_head > 64 ? 128 : rows_per_kv_head > 32 ? 64 : 32; }
+
+hipError_t launch_tile_query(const QueryArgs& a, int dtype, int block_rows, hipStream_t s) {
+    const int d = a.head_dim;
+    if (dtype == APE_F32)
+        return d <= 64 ? query_with_rows<float, 64>(a, block_rows, s) : d <= 128 ? query_with_rows<float, 128>(a, block_rows, s) : query_with_rows<float, 256>(a, block_rows, s);
+    return d <= 64 ? query_with_rows<__bf16, 64>(a, block_rows, s) : d <= 128 ? query_with_rows<__bf16, 128>(a, block_rows, s) : query_with_rows<__bf16, 256>(a, block_rows, s);
+}
+
+hipError_t launch_tile_encode(const EncodeArgs& a, int dtype, hipStream_t s) {
+    if (a.total_rows == 0) return hipSuccess;
+    const int d = a.head_dim;
+    if (dtype == APE_F32) return d <= 64 ? encode_with<float, 64>(a, s) : d <= 128 ? encode_with<float, 128>(a, s) : encode_with<float, 256>(a, s);
+    return d <= 64 ? encode_with<__bf16, 64>(a, s) : d <= 128 ? encode_with<__bf16, 128>(a, s) : encode_with<__bf16, 256>(a, s);
+}
+
+}  // namespace ape

@@ -102,7 +102,7 @@ int run_layer(const ShapeInfo& si, const ape_layer_weights* w, const Contexts& c
     e.cu = c.cu_dev; e.out = attn; e.lse = nullptr;
     e.n_chunks = c.n_chunks; e.prefix_len = c.prefix_len; e.total_rows = (int)rows; e.max_chunk_len = c.max_len;
     e.n_q_heads = si.hq; e.n_kv_heads = si.hkv; e.head_dim = si.d; e.uniform_chunks = c.min_len == c.max_len;
-    he = si.mfma ? launch_flash_encode(e, st) : launch_generic_encode(e, si.dtype, st);
+    he = launch_encode(si, e, st);
     if (he != hipSuccess) return dev_fail("encode attention", he);
     if (gemm_xwT(attn, qd, w->w_o, x, x1, hidden, rows, hidden, qd, si.dtype, st)) return fail(APE_ERR_DEVICE, "output projection (rocBLAS) failed");
 
