@@ -98,7 +98,10 @@ int check_encode_size(const ShapeInfo& si, int n_chunks, int max_len, long total
 }
 
 hipError_t launch_encode(const ShapeInfo& si, const EncodeArgs& e, hipStream_t s) {
-    if (si.mfma) return launch_flash_encode(e, s);
+    if (si.mfma) {
+        const int parts = encode_walk_parts(e);
+        return parts > 0 ? launch_encode_walk(e, parts, s) : launch_flash_encode(e, s);
+    }
     // The tile kernel's grid is contexts x KV heads x row tiles of the longest context; a call whose lengths are so
     // uneven that this passes the launch limit takes the vector-ALU kernel, whose grid is the rows themselves.
     const long n_qtiles = ((long)e.max_chunk_len * si.group + 127) / 128;

@@ -104,17 +104,6 @@ struct LoadOffsetsT {
     static_assert(!(NT && KCOL), "the column-major form gathers 64-byte pieces: not for streams bound by HBM");
 };
 
-// The thread index for a tile's set-up (lane offsets, load offsets, query addresses): a kernel that
-// walks several tiles makes it opaque per tile, so that everything derived from it is recomputed
-// per tile instead of being kept in registers across the whole walk (the compiler would hoist it
-// all out of the tile loop, and the block loop has no registers to spare).  Inside the block loop
-// the few uses of the thread index read threadIdx directly, as a one-tile kernel does.
-__device__ __forceinline__ int tile_thread_index() {
-    int tid = threadIdx.x;
-    asm volatile("" : "+v"(tid));
-    return tid;
-}
-
 template <bool NT, bool KCOL>
 __device__ __forceinline__ LoadOffsetsT<NT, KCOL> load_offsets(long stride_b, int n_valid, int tid) {
     const int lane = tid & 63, wave = tid >> 6;
@@ -1087,7 +1076,7 @@ __global__ __launch_bounds__(NT) void flash_prefill_kernel(const QueryArgs a, in
 // ------------------------------------------------------------------------------------------
 // Block-diagonal causal encode: team = (chunk, KV head), members = query tiles of the chunk,
 // heaviest (last) tile first.  Writes the final bf16 output.  `vblock` is the tile's index in the
-// order team_of_block() defines (the blockIdx of a launch with one workgroup per tile).
+// order team_of_block() defines.
 template <int RB, int G>
 __device__ __forceinline__ void encode_tile(const EncodeArgs a, const int n_qtiles, const int vblock, char* const lds, const int tid) {
     constexpr int BM = NW * 32 * RB;
@@ -1208,31 +1197,11 @@ __device__ __forceinline__ void encode_tile(const EncodeArgs a, const int n_qtil
     }
 }
 
-// Two launch shapes.  One workgroup per tile (rounds == 0): the hardware hands out the tiles.
-// Resident workgroups (rounds > 0; the grid is 8 * slots_per_xcd workgroups, as many as the chip holds
-// at once): each walks `rounds` tiles of its own XCD's list, so the ~3 us between the end of one
-// workgroup and the start of the next on the same CU are paid once, not per tile.  A tile's weight
-// falls with its index inside a team (the last query tile of a chunk sees the most keys), so the
-// direction of the walk alternates from round to round: the workgroup that drew the heaviest tile
-// of a round draws the lightest of the next.  Used when all chunks have the same length, where this
-// static deal is balanced.
+// One workgroup per tile; the hardware hands them out.
 template <int RB, int G>
-__global__ __launch_bounds__(NT) void flash_encode_kernel(const EncodeArgs a, int n_qtiles, int slots_per_xcd, int rounds) {
+__global__ __launch_bounds__(NT) void flash_encode_kernel(const EncodeArgs a, int n_qtiles) {
     extern __shared__ __attribute__((aligned(16))) char lds[];
-    if constexpr (RB == 2) {
-        // (the wide tile always runs one tile per workgroup: its chunks are long, and a tile loop around
-        // its block loop costs it registers it does not have)
-        encode_tile<RB, G>(a, n_qtiles, blockIdx.x, lds, threadIdx.x);
-    } else {
-        if (rounds == 0) { encode_tile<RB, G>(a, n_qtiles, blockIdx.x, lds, threadIdx.x); return; }
-        const int xcd = blockIdx.x & 7, slot = blockIdx.x >> 3;
-        for (int k = 0; k < rounds; ++k) {
-            // (every wavefront has read its output rows back from LDS before the next tile's loads overwrite them)
-            if (k > 0) ring_barrier();
-            const int v = k * slots_per_xcd + ((k & 1) ? slots_per_xcd - 1 - slot : slot);
-            encode_tile<RB, G>(a, n_qtiles, v * 8 + xcd, lds, tile_thread_index());
-        }
-    }
+    encode_tile<RB, G>(a, n_qtiles, blockIdx.x, lds, threadIdx.x);
 }
 
 template <int RB, int G, bool NTL>
@@ -1244,10 +1213,10 @@ hipError_t launch_prefill_t(const QueryArgs& a, dim3 grid, int n_qtiles, hipStre
 }
 
 template <int RB, int G>
-hipError_t launch_encode_t(const EncodeArgs& a, unsigned grid, int n_qtiles, int slots_per_xcd, int rounds, hipStream_t s) {
+hipError_t launch_encode_t(const EncodeArgs& a, unsigned grid, int n_qtiles, hipStream_t s) {
     hipError_t e = hipFuncSetAttribute((const void*)flash_encode_kernel<RB, G>, hipFuncAttributeMaxDynamicSharedMemorySize, Ring<RB>::slots * SLOTB);
     if (e != hipSuccess) return e;
-    flash_encode_kernel<RB, G><<<grid, NT, Ring<RB>::slots * SLOTB, s>>>(a, n_qtiles, slots_per_xcd, rounds);
+    flash_encode_kernel<RB, G><<<grid, NT, Ring<RB>::slots * SLOTB, s>>>(a, n_qtiles);
     return hipGetLastError();
 }
 
@@ -1262,12 +1231,12 @@ hipError_t launch_prefill_g(int group, const QueryArgs& a, dim3 grid, int n_qtil
 }
 
 template <int RB>
-hipError_t launch_encode_g(int group, const EncodeArgs& a, unsigned grid, int n_qtiles, int slots_per_xcd, int rounds, hipStream_t s) {
+hipError_t launch_encode_g(int group, const EncodeArgs& a, unsigned grid, int n_qtiles, hipStream_t s) {
     switch (group) {
-        case 1: return launch_encode_t<RB, 1>(a, grid, n_qtiles, slots_per_xcd, rounds, s);
-        case 2: return launch_encode_t<RB, 2>(a, grid, n_qtiles, slots_per_xcd, rounds, s);
-        case 4: return launch_encode_t<RB, 4>(a, grid, n_qtiles, slots_per_xcd, rounds, s);
-        default: return launch_encode_t<RB, 8>(a, grid, n_qtiles, slots_per_xcd, rounds, s);
+        case 1: return launch_encode_t<RB, 1>(a, grid, n_qtiles, s);
+        case 2: return launch_encode_t<RB, 2>(a, grid, n_qtiles, s);
+        case 4: return launch_encode_t<RB, 4>(a, grid, n_qtiles, s);
+        default: return launch_encode_t<RB, 8>(a, grid, n_qtiles, s);
     }
 }
 
@@ -1321,27 +1290,8 @@ hipError_t launch_flash_encode(const EncodeArgs& a, hipStream_t s) {
     const int bm = a.max_chunk_len > 4096 ? flash_block_rows(rows) : 128;
     const int n_qtiles = (rows + bm - 1) / bm;
     const int teams = a.n_chunks * a.n_kv_heads;
-    unsigned grid = (unsigned)((teams + 7) / 8 * 8 * n_qtiles);
-    // Resident workgroups (two of the narrow tile per CU, walking the tiles in a fixed deal) for many
-    // short chunks of one length: there a tile is a handful of blocks and the ~3 us between two
-    // workgroups on a CU weigh most (measured: 512 x 256 tokens 0.821 -> 0.798 ms, 20 x 512 0.087 ->
-    // 0.084 ms).  Longer chunks are better off with the hardware handing out the tiles: CUs differ in
-    // speed by a few per cent and a fixed deal ends with the slowest (64 x 2048: 2.34 -> 2.41 ms).
-    int slots_per_xcd = 0, rounds = 0;
-    if (a.uniform_chunks && bm == 128 && a.max_chunk_len <= 1024) {
-        int dev = 0, cus = 0;
-        if (hipGetDevice(&dev) == hipSuccess && hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev) == hipSuccess && cus >= 8) {
-            const int resident = cus / 8 * 2;                                // per XCD
-            const int per_xcd = (int)(grid / 8);
-            if (per_xcd >= 4 * resident) {
-                slots_per_xcd = resident;
-                rounds = (per_xcd + resident - 1) / resident;
-                grid = (unsigned)(8 * resident);
-            }
-        }
-    }
-    return bm == 256 ? launch_encode_g<2>(group, a, grid, n_qtiles, slots_per_xcd, rounds, s)
-                     : launch_encode_g<1>(group, a, grid, n_qtiles, slots_per_xcd, rounds, s);
+    const unsigned grid = (unsigned)((teams + 7) / 8 * 8 * n_qtiles);
+    return bm == 256 ? launch_encode_g<2>(group, a, grid, n_qtiles, s) : launch_encode_g<1>(group, a, grid, n_qtiles, s);
 }
 
 }  // namespace ape

@@ -291,6 +291,9 @@ hipError_t launch_tree_plan(const TreePlanArgs& a, hipStream_t s);
 hipError_t launch_tree_merge(const TreeMergeArgs& a, hipStream_t s);
 hipError_t launch_flash_prefill(const QueryArgs& a, int block_rows, hipStream_t s);     // bf16, d = 128; block_rows from the plan
 hipError_t launch_flash_encode(const EncodeArgs& a, hipStream_t s);     // bf16, d = 128
+hipError_t launch_encode_walk(const EncodeArgs& a, int parts, hipStream_t s);   // the same shapes, short contexts
+// workgroups per (context, KV head) of the walk, or 0 where one workgroup per query tile (launch_flash_encode) is faster
+int encode_walk_parts(const EncodeArgs& a);
 
 // rows of (token, group-head) pairs one workgroup of the tile kernels covers
 int tile_query_block_rows(int rows_per_kv_head);

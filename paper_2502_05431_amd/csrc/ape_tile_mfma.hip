@@ -24,25 +24,14 @@
 // fp32 encode of eight contexts of about 512 tokens, 32/8 heads of 128: 2754 -> 231 us (73 TFLOP/s; the vendor's fp32 GEMM
 // reaches 153); 64 bf16 rows over 20 x 512 tokens, 16/8 heads of 256: 14200 -> 64 us; 16 fp32 rows over 4 x 32 tokens,
 // 4/2 heads of 64: 47.8 -> 15.7 us with the merge.
-#include "ape_internal.h"
+#include "ape_mfma.h"
 
 #include <math.h>
 
 namespace ape {
 namespace {
 
-typedef __attribute__((ext_vector_type(8))) __bf16 bf16x8;
-typedef __attribute__((ext_vector_type(4))) __bf16 bf16x4;
-typedef __attribute__((ext_vector_type(16))) float f32x16;
-typedef __attribute__((ext_vector_type(4))) float f32x4;
-typedef __attribute__((ext_vector_type(4))) short s16x4;
-typedef __attribute__((ext_vector_type(4))) uint32_t u32x4;
-typedef __attribute__((ext_vector_type(2))) uint32_t u32x2;
-
-constexpr float LOG2E = 1.4426950408889634f;
-constexpr float LN2 = 0.6931471805599453f;
 constexpr float kSlack = 10.f;               // a reference moves only when exceeded by this (fp32 sums lose nothing by that)
-constexpr float kUnset = -1.0e30f;           // reference of a row that has not seen a token yet
 
 // 1/(T sqrt d), rounded once.  Scores of |x| = 40 (T = 0.1) turn one rounding of the scale into 2.4e-6 of a probability, so
 // fp32 carries its remainder along and keeps natural-log units (a factor log2 e inside would round once more);
@@ -150,25 +139,6 @@ struct Source {
     }
 };
 
-// One direct global->LDS load: lane i's 16 bytes land at (wavefront-uniform) lds + 16 i.  Written as an
-// instruction so that the compiler does not order it (it could only wait for all of them): the waits and
-// barriers of the ring do.
-__device__ __forceinline__ void load_lds16(const char* src, const char* lds) {
-    const uint32_t m0v = (uint32_t)(uintptr_t)(const __attribute__((address_space(3))) char*)lds;
-    asm volatile("s_mov_b32 m0, %1\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %0, off" :: "v"(src), "s"(m0v) : "m0");
-}
-
-template <int N>
-__device__ __forceinline__ void wait_loads() {
-    static_assert(N < 64, "vmcnt is a 6-bit counter");
-    __builtin_amdgcn_s_waitcnt(0x0f70 | (N & 15) | ((N >> 4) << 14));
-}
-__device__ __forceinline__ void stage_barrier() {
-    asm volatile("" ::: "memory");
-    __builtin_amdgcn_s_barrier();
-    asm volatile("" ::: "memory");
-}
-
 // Starts the loads of tokens [t, t + KS) into `stage`; rows past t_end - 1 repeat that token (finite
 // data whose probabilities are zero).
 template <typename T, int DP, int WR, int WK>
@@ -207,23 +177,6 @@ struct Rows {
     float m, l;                  // softmax reference (units of ScoreScale) and this lane's share of the sum
     f32x16 o[DP / 32];           // O^T: dim 32 db + 8 (r / 4) + 4 hi + r % 4
 };
-
-__device__ __forceinline__ float max_halves(float x) {
-    const u32x2 r = __builtin_amdgcn_permlane32_swap(__float_as_uint(x), __float_as_uint(x), false, false);
-    return fmaxf(__uint_as_float(r[0]), __uint_as_float(r[1]));
-}
-__device__ __forceinline__ float sum_halves(float x) {
-    const u32x2 r = __builtin_amdgcn_permlane32_swap(__float_as_uint(x), __float_as_uint(x), false, false);
-    return __uint_as_float(r[0]) + __uint_as_float(r[1]);
-}
-__device__ __forceinline__ bf16x4 lds_read_tr(const char* p) {
-    s16x4 r = __builtin_amdgcn_ds_read_tr16_b64_v4i16((__attribute__((address_space(3))) s16x4*)p);
-    return __builtin_bit_cast(bf16x4, r);
-}
-__device__ __forceinline__ uint32_t pack_bf16(float a, float b) {
-    const __bf16 x = (__bf16)a, y = (__bf16)b;
-    return (uint32_t)__builtin_bit_cast(unsigned short, x) | ((uint32_t)__builtin_bit_cast(unsigned short, y) << 16);
-}
 
 // With 256-wide rows the accumulators and Q take 192 of the 256 registers of a wavefront (two per SIMD): LDS
 // reads may run ahead of their MFMAs by a few fragments only, which the scheduler has to be told.
@@ -274,7 +227,7 @@ __device__ __forceinline__ void compute(const char* kpart, const char* vpart, co
     const bool masked = __builtin_amdgcn_ballot_w64(nvis < 32) != 0;
     if (masked) {
 #pragma unroll
-        for (int r = 0; r < 16; ++r) s[r] = 8 * (r >> 2) + 4 * hi + (r & 3) < nvis ? s[r] : -INFINITY;
+        for (int r = 0; r < 16; ++r) s[r] = 8 * (r >> 2) + (r & 3) < nvis - 4 * hi ? s[r] : -INFINITY;
     }
     float mx = s[0];
 #pragma unroll
