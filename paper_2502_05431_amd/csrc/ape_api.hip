@@ -147,10 +147,17 @@ QueryPlan plan_query(int base_workgroups, long max_ctx, int min_len, int target_
     return p;
 }
 
-// Split plan of the tile kernels, queries and decode alike.
+// Split plan of the tile kernels, queries and decode alike: as many workgroups as fit the chip at once, of splits that are
+// long against a workgroup's fixed cost.  Measured with 64 / 32 rows per tile: 64 bf16 rows over 10240 tokens, 16/8 heads of
+// 256, 512 workgroups 49.9 us, 256 51.4; 12/2 heads of 128, 29.0 / 25.9 (its partial results weigh more than the second
+// workgroup per CU gives); 64 fp32 rows over 4096 tokens, 16/8 heads of 256 (one workgroup per CU), 90.7 / 83.6.
 QueryPlan tile_plan(const ShapeInfo& si, int batch, int q_len, long max_ctx) {
-    const int rows = q_len * si.group, bm = tile_query_block_rows(rows);
-    QueryPlan p = plan_query(batch * si.hkv * ceil_div(rows, bm), max_ctx, 128, 512);
+    const int rows = q_len * si.group, bm = tile_query_block_rows(si, batch, rows, max_ctx);
+    const bool f32 = si.dtype == APE_F32;
+    const int target = (f32 ? si.d > 128 : si.d > 64 && si.d <= 128 && bm < 128) ? 256 : 512;
+    // (16 rows over 2048 tokens, 2/2 fp32 heads of 256: splits of 64 / 128 / 256 tokens 18.9 / 25.8 / 40.2 us; 40 bf16 rows, 6/2
+    // heads of 40: 14.5 / 14.7 / 17.2)
+    QueryPlan p = plan_query(batch * si.hkv * ceil_div(rows, bm), max_ctx, f32 && si.d > 128 ? 64 : 128, target);
     p.block_rows = bm;
     return p;
 }

@@ -296,7 +296,7 @@ hipError_t launch_encode_walk(const EncodeArgs& a, int parts, hipStream_t s);   
 int encode_walk_parts(const EncodeArgs& a);
 
 // rows of (token, group-head) pairs one workgroup of the tile kernels covers
-int tile_query_block_rows(int rows_per_kv_head);
+int tile_query_block_rows(const ShapeInfo& si, int batch, int rows_per_kv_head, long max_ctx);
 // rows of (token, group-head) pairs one flash workgroup covers for a given amount of rows
 int flash_block_rows(int rows_per_kv_head);
 // the same for the query prefill, which also looks at the context length (see the definition), and

@@ -9,10 +9,11 @@
 // (32x32x2); bf16 storage on the bf16 MFMA (32x32x16) with every probability taken as the sum of two bf16
 // values (16 significant bits, beyond what the bf16 output holds), i.e. two MFMAs per V fragment.
 //
-// Tiling: WR x WK wavefronts.  A wavefront owns 32 rows -- a row is a (query token, head of the group) pair -- and
-// every WK-th run of 32 tokens of the stream; the WK partial results of a row are combined in LDS at the
-// end.  Many rows take 4 x 1 (every K/V byte in LDS serves 128 rows), a decode step or a query of a few
-// rows 1 x 4 (the same bytes in flight, all four wavefronts computing).  Tokens pass through a ring of LDS stages
+// Tiling: WR x WK x WD wavefronts.  A wavefront owns 32 rows -- a row is a (query token, head of the group) pair -- every
+// WK-th run of 32 tokens of the stream, and one WD-th of the head's dims; the WK partial results of a row are combined in
+// LDS at the end, the WD partial scores of a run in every stage.  Many rows take 4 x 1 x 1 (every K/V byte in LDS serves 128
+// rows), a decode step or a query of a few rows 1 x 4 x 1 (the same bytes in flight, all four wavefronts computing) or, where
+// rows are so wide that LDS has no room for a ring of four runs, 1 x 1 x 4.  Tokens pass through a ring of LDS stages
 // of 32 WK tokens filled by direct global->LDS loads.  A stage is a run of consecutive indices of the
 // pooled contexts (or of prefix + own tokens), whatever context they belong to: a stage that crosses the
 // end of a context picks its source row by row, so short and ragged contexts waste no MFMA on padding.
@@ -22,8 +23,9 @@
 // attention's own count for bf16), the fixed chain of a launch, first loads and merge for a short query.  Against the
 // vector-ALU kernels, which give a wavefront one row and read every K/V byte once per row (same card, same inputs):
 // fp32 encode of eight contexts of about 512 tokens, 32/8 heads of 128: 2754 -> 231 us (73 TFLOP/s; the vendor's fp32 GEMM
-// reaches 153); 64 bf16 rows over 20 x 512 tokens, 16/8 heads of 256: 14200 -> 64 us; 16 fp32 rows over 4 x 32 tokens,
-// 4/2 heads of 64: 47.8 -> 15.7 us with the merge.
+// reaches 154); 64 bf16 rows over 20 x 512 tokens, 16/8 heads of 256: 14200 -> 52.5 us (1.6 TB/s; 64 with one wavefront per
+// SIMD that held whole rows); a fp32 decode step over 4096 tokens, 16/8 heads of 256: 38 us, 88 by one wavefront per
+// workgroup; 16 fp32 rows over 4 x 32 tokens, 4/2 heads of 64: 47.8 -> 15.7 us with the merge.
 #include "ape_mfma.h"
 
 #include <math.h>
@@ -55,26 +57,27 @@ struct ScoreScale {
     }
 };
 
-// Sizes of one instantiation: T storage type, DP padded head_dim, WR x WK wavefronts.
-template <typename T, int DP, int WR, int WK>
+// Sizes of one instantiation: T storage type, DP padded head_dim, WR x WK x WD wavefronts.
+template <typename T, int DP, int WR, int WK, int WD>
 struct Tile {
-    static constexpr int NW = WR * WK, NT = 64 * NW;
+    static constexpr int NW = WR * WK * WD, NT = 64 * NW;
     static constexpr int ROWS = 32 * WR;                    // query rows per workgroup
     static constexpr int KS = 32 * WK;                      // tokens per stage
     static constexpr int PITCH = DP * (int)sizeof(T);       // bytes of a K (or V) row in LDS
     static constexpr int CPR = PITCH / 16;                  // 16-byte chunks of a row
     static constexpr int PART = KS * PITCH;                 // K part of a stage; V follows
     static constexpr int STAGE = 2 * PART;
-    // Stages in the ring: two keep one in flight while the other is read; small stages take more, as far as two
-    // workgroups still fit a CU.
-    static constexpr int NSTG = STAGE * 4 <= 80 * 1024 ? 4 : STAGE * 3 <= 80 * 1024 ? 3 : 2;
-    static constexpr int LDS = NSTG * STAGE;
+    static constexpr int SUMS = WD > 1 ? NW * 4096 : 0;     // partial scores of the wavefronts that share rows, behind the ring
+    // Stages in the ring: as many as leave room for a second workgroup on the CU, where the registers allow one (Q and the
+    // accumulators of 256-wide rows alone are 192 of them), else as fit.
+    static constexpr int ROOM = (DP / WD == 256 ? 160 : 80) * 1024 - SUMS;
+    static constexpr int NSTG = STAGE * 4 <= ROOM ? 4 : STAGE * 3 <= ROOM ? 3 : 2;
+    static constexpr int LDS = NSTG * STAGE + SUMS;
     static constexpr int LPT = PART / (16 * NT);            // loads per thread and part
-    static constexpr int NB = DP / 32;                      // 32-dim blocks of the output
-    // wavefronts per SIMD, which set the register budget: what LDS has room for, and one for 256-wide rows (Q and the
-    // accumulators alone are 192 registers)
-    static constexpr int WAVES = DP == 256 || 160 * 1024 / LDS * NW < 8 ? 1 : 2;
+    // wavefronts per SIMD, which set the register budget: what LDS has room for
+    static constexpr int WAVES = DP / WD == 256 || 160 * 1024 / LDS * NW < 8 ? 1 : 2;
     static_assert(PART % (16 * NT) == 0 && LDS <= 160 * 1024, "stage size");
+    static_assert(WK == 1 || WD == 1, "one way to share the rows");
 };
 
 // XOR swizzles of the 16-byte chunk index inside a row (see the reads in `compute`).
@@ -141,9 +144,9 @@ struct Source {
 
 // Starts the loads of tokens [t, t + KS) into `stage`; rows past t_end - 1 repeat that token (finite
 // data whose probabilities are zero).
-template <typename T, int DP, int WR, int WK>
+template <typename T, int DP, int WR, int WK, int WD>
 __device__ __forceinline__ void start_stage(Source& src, int t, int t_end, int d, char* stage) {
-    using X = Tile<T, DP, WR, WK>;
+    using X = Tile<T, DP, WR, WK, WD>;
     if (src.cu) while (t >= src.b && src.e > src.b) src.next_context();
     const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
     int lane = threadIdx.x & 63;
@@ -169,14 +172,24 @@ __device__ __forceinline__ void start_stage(Source& src, int t, int t_end, int d
 }
 
 // Per-wavefront state: 32 query rows, row = lane & 31 (both half-wavefronts hold the row: tokens and dims are split
-// between them).
-template <typename T, int DP>
+// between them), and the wavefront's 1 / WD of the head's dims.
+template <typename T, int DW>
 struct Rows {
-    static constexpr int NQ = sizeof(T) == 2 ? DP / 16 : DP / 8;   // 16-byte pieces of Q per lane
+    static constexpr int NQ = sizeof(T) == 2 ? DW / 16 : DW / 8;   // 16-byte pieces of Q per lane
+    static constexpr int NB = DW / 32;                             // 32-dim blocks of the output
     u32x4 q[NQ];                 // bf16: dims 16 i + 8 hi .. +7;  fp32: dims 8 i + 4 hi .. +3
     float m, l;                  // softmax reference (units of ScoreScale) and this lane's share of the sum
-    f32x16 o[DP / 32];           // O^T: dim 32 db + 8 (r / 4) + 4 hi + r % 4
+    f32x16 o[NB];                // O^T: dim 32 db + 8 (r / 4) + 4 hi + r % 4
 };
+
+template <typename T, int DW>
+__device__ __forceinline__ void clear_rows(Rows<T, DW>& st) {
+    st.m = kUnset; st.l = 0.f;
+#pragma unroll
+    for (int db = 0; db < Rows<T, DW>::NB; ++db)
+#pragma unroll
+        for (int r = 0; r < 16; ++r) st.o[db][r] = 0.f;
+}
 
 // With 256-wide rows the accumulators and Q take 192 of the 256 registers of a wavefront (two per SIMD): LDS
 // reads may run ahead of their MFMAs by a few fragments only, which the scheduler has to be told.
@@ -185,15 +198,14 @@ __device__ __forceinline__ void group_barrier() {
     if constexpr (DP == 256) __builtin_amdgcn_sched_barrier(0);
 }
 
-// One run of 32 tokens: S^T = K Q^T, softmax, O^T += V^T P^T.  `nvis`: how many of the tokens this lane's
-// row sees.
-template <typename T, int DP>
-__device__ __forceinline__ void compute(const char* kpart, const char* vpart, const ScoreScale<T>& sc, int nvis, Rows<T, DP>& st) {
-    constexpr int PITCH = DP * (int)sizeof(T), NB = DP / 32;
+// One run of 32 tokens.  S^T = K Q^T over the dims of part `wd`.
+template <typename T, int DP, int WD>
+__device__ __forceinline__ f32x16 scores(const char* kpart, int wd, const Rows<T, DP / WD>& st) {
+    constexpr int PITCH = DP * (int)sizeof(T), DW = DP / WD, NQ = Rows<T, DW>::NQ;
     const int lane = threadIdx.x & 63, l32 = lane & 31, hi = lane >> 5;
     // fp32 scores are summed in several chains (every element of a 16-byte piece its own, two where registers are
     // short): a sum of up to 256 terms of one sign pattern loses fewer bits, at 16 additions a chain.
-    constexpr int NCH = sizeof(T) == 2 ? 1 : DP == 64 ? 4 : 2;
+    constexpr int NCH = sizeof(T) == 2 ? 1 : DW == 64 ? 4 : 2;
     f32x16 sc_part[NCH];
 #pragma unroll
     for (int c = 0; c < NCH; ++c)
@@ -201,11 +213,12 @@ __device__ __forceinline__ void compute(const char* kpart, const char* vpart, co
         for (int r = 0; r < 16; ++r) sc_part[c][r] = 0.f;
     // K: token row l32, chunk 2 i + hi.  The swizzle leaves one address for every i % 8; the lane's offset is made
     // opaque so that they are recomputed here (an instruction each) and not kept in registers over the loop.
-    int koff = l32 * PITCH + ((hi ^ swz_k<T, DP>(l32)) << 4);
+    int koff = (l32 * PITCH + ((hi ^ swz_k<T, DP>(l32)) << 4)) ^ (32 * (wd * NQ % 8));
     asm volatile("" : "+v"(koff));
+    kpart += 256 * (wd * NQ / 8);
 #pragma unroll
-    for (int i = 0; i < Rows<T, DP>::NQ; ++i) {
-        if (i % 4 == 0) group_barrier<DP>();
+    for (int i = 0; i < NQ; ++i) {
+        if (i % 4 == 0) group_barrier<DW>();
         const u32x4 a = *(const u32x4*)(kpart + (koff ^ (32 * (i % 8))) + 256 * (i / 8));
         if constexpr (sizeof(T) == 2) {
             sc_part[0] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(__builtin_bit_cast(bf16x8, a), __builtin_bit_cast(bf16x8, st.q[i]), sc_part[0], 0, 0, 0);
@@ -223,6 +236,36 @@ __device__ __forceinline__ void compute(const char* kpart, const char* vpart, co
 #pragma unroll
         for (int r = 0; r < 16; ++r) s[r] = (s[r] + sc_part[1][r]) + (sc_part[2][r] + sc_part[3][r]);
     }
+    return s;
+}
+
+// The wavefronts that share rows put their partial scores side by side; each adds them up in the same order, so that all
+// go on with the same scores.
+__device__ __forceinline__ void put_scores(char* sums, const f32x16& s) {
+    const int lane = threadIdx.x & 63;
+#pragma unroll
+    for (int i = 0; i < 4; ++i) *(f32x4*)(sums + 1024 * i + 16 * lane) = f32x4{s[4 * i], s[4 * i + 1], s[4 * i + 2], s[4 * i + 3]};
+}
+template <int WD>
+__device__ __forceinline__ f32x16 sum_scores(const char* sums) {
+    const int lane = threadIdx.x & 63;
+    f32x16 s;
+#pragma unroll
+    for (int i = 0; i < 4; ++i) {
+        f32x4 x[WD];
+#pragma unroll
+        for (int w = 0; w < WD; ++w) x[w] = *(const f32x4*)(sums + 4096 * w + 1024 * i + 16 * lane);
+#pragma unroll
+        for (int e = 0; e < 4; ++e) s[4 * i + e] = WD == 2 ? x[0][e] + x[1][e] : (x[0][e] + x[1][e]) + (x[2][e] + x[WD - 1][e]);
+    }
+    return s;
+}
+
+// The softmax of the run's scores and O^T += V^T P^T.  `nvis`: how many of the tokens this lane's row sees.
+template <typename T, int DP, int WD>
+__device__ __forceinline__ void update(f32x16 s, const char* vpart, int wd, const ScoreScale<T>& sc, int nvis, Rows<T, DP / WD>& st) {
+    constexpr int PITCH = DP * (int)sizeof(T), DW = DP / WD, NB = DW / 32;
+    const int lane = threadIdx.x & 63, l32 = lane & 31, hi = lane >> 5;
     // register r holds token 8 (r / 4) + 4 hi + r % 4
     const bool masked = __builtin_amdgcn_ballot_w64(nvis < 32) != 0;
     if (masked) {
@@ -267,13 +310,14 @@ __device__ __forceinline__ void compute(const char* kpart, const char* vpart, co
             }
         const int g16 = lane >> 4, s16 = lane & 15;
         const int row0 = 4 * (g16 >> 1) + (s16 >> 2);
-        int voff = row0 * PITCH + (((2 * (g16 & 1) + ((s16 & 3) >> 1)) ^ swz_v<T, DP>(row0)) << 4) + (s16 & 1) * 8;
+        int voff = (row0 * PITCH + (((2 * (g16 & 1) + ((s16 & 3) >> 1)) ^ swz_v<T, DP>(row0)) << 4) + (s16 & 1) * 8) ^ (64 * (wd * NB % 4));
         asm volatile("" : "+v"(voff));
+        vpart += 256 * (wd * NB / 4);
 #pragma unroll
         for (int sl = 0; sl < 2; ++sl)
 #pragma unroll
             for (int db = 0; db < NB; ++db) {
-                if (db % 2 == 0) group_barrier<DP>();
+                if (db % 2 == 0) group_barrier<DW>();
                 const char* at = vpart + (voff ^ (64 * (db % 4))) + 256 * (db / 4) + 16 * sl * PITCH;
                 const bf16x4 lo4 = lds_read_tr(at), hi4 = lds_read_tr(at + 8 * PITCH);
                 const bf16x8 a = __builtin_shufflevector(lo4, hi4, 0, 1, 2, 3, 4, 5, 6, 7);
@@ -282,8 +326,9 @@ __device__ __forceinline__ void compute(const char* kpart, const char* vpart, co
             }
     } else {
         // V: token row 8 (r / 4) + 4 hi + r % 4, dim 32 db + l32
-        int voff = 4 * hi * PITCH + (((l32 >> 2) ^ swz_v<T, DP>(4 * hi)) << 4) + (l32 & 3) * 4;
+        int voff = (4 * hi * PITCH + (((l32 >> 2) ^ swz_v<T, DP>(4 * hi)) << 4) + (l32 & 3) * 4) ^ (128 * (wd * NB % 2));
         asm volatile("" : "+v"(voff));
+        vpart += 256 * (wd * NB / 2);
 #pragma unroll
         for (int r = 0; r < 16; ++r) {
 #pragma unroll
@@ -297,54 +342,58 @@ __device__ __forceinline__ void compute(const char* kpart, const char* vpart, co
 
 // Streams tokens [t_beg, t_end) past the workgroup's rows.  `lim`: this lane's row sees indices up to
 // and including lim; `lim_hi`: the largest lim of the wavefront; `active`: it has rows at all.
-template <typename T, int DP, int WR, int WK>
+template <typename T, int DP, int WR, int WK, int WD>
 __device__ __forceinline__ void stream(Source& src, int t_beg, int t_end, int d, const ScoreScale<T>& sc, int lim, int lim_hi, bool active,
-                                       char* lds, Rows<T, DP>& st) {
-    using X = Tile<T, DP, WR, WK>;
-    const int kw = __builtin_amdgcn_readfirstlane((threadIdx.x >> 6) % WK);
+                                       char* lds, Rows<T, DP / WD>& st) {
+    using X = Tile<T, DP, WR, WK, WD>;
+    const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), kw = wave / WD % WK, wd = wave % WD;
     const int n = (t_end - t_beg + X::KS - 1) / X::KS;
     for (int j = 0; j < X::NSTG - 1 && j < n; ++j)
-        start_stage<T, DP, WR, WK>(src, t_beg + j * X::KS, t_end, d, lds + j * X::STAGE);
+        start_stage<T, DP, WR, WK, WD>(src, t_beg + j * X::KS, t_end, d, lds + j * X::STAGE);
     int at = 0, to = X::NSTG - 1;                           // ring positions of stage j and of the one whose loads start
     for (int j = 0; j < n; ++j) {
         if (j + X::NSTG - 2 < n) wait_loads<(X::NSTG - 2) * 2 * X::LPT>(); else wait_loads<0>();
         stage_barrier();                                     // stage j has landed for every wavefront, all of which are done with stage j - 1
-        if (j + X::NSTG - 1 < n) start_stage<T, DP, WR, WK>(src, t_beg + (j + X::NSTG - 1) * X::KS, t_end, d, lds + to * X::STAGE);
+        if (j + X::NSTG - 1 < n) start_stage<T, DP, WR, WK, WD>(src, t_beg + (j + X::NSTG - 1) * X::KS, t_end, d, lds + to * X::STAGE);
         const int t = t_beg + j * X::KS + 32 * kw;
-        if (active && t <= lim_hi && t < t_end) {
-            const char* part = lds + at * X::STAGE + 32 * kw * X::PITCH;
-            compute<T, DP>(part, part + X::PART, sc, min(lim, t_end - 1) - t + 1, st);
+        const bool sees = active && t <= lim_hi && t < t_end;
+        const char* part = lds + at * X::STAGE + 32 * kw * X::PITCH;
+        if constexpr (WD == 1) {
+            if (sees) update<T, DP, WD>(scores<T, DP, WD>(part, wd, st), part + X::PART, wd, sc, min(lim, t_end - 1) - t + 1, st);
+        } else {
+            char* sums = lds + X::NSTG * X::STAGE + 4096 * (wave - wd);
+            if (sees) put_scores(sums + 4096 * wd, scores<T, DP, WD>(part, wd, st));
+            asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
+            stage_barrier();
+            if (sees) update<T, DP, WD>(sum_scores<WD>(sums), part + X::PART, wd, sc, min(lim, t_end - 1) - t + 1, st);
         }
         at = at + 1 == X::NSTG ? 0 : at + 1;
         to = to + 1 == X::NSTG ? 0 : to + 1;
     }
 }
 
-template <typename T, int DP>
-__device__ __forceinline__ void init_rows(Rows<T, DP>& st, const T* q, int d) {
+// The query rows and the empty state.  `q`: the row's first element.
+template <typename T, int DP, int WD>
+__device__ __forceinline__ void init_rows(Rows<T, DP / WD>& st, const T* q, int d, int wd) {
     const int hi = (threadIdx.x & 63) >> 5;
-    constexpr int N = 16 / (int)sizeof(T);
+    constexpr int N = 16 / (int)sizeof(T), NQ = Rows<T, DP / WD>::NQ;
 #pragma unroll
-    for (int i = 0; i < Rows<T, DP>::NQ; ++i) {
-        const int c = (2 * i + hi) * N;                      // zeros beyond head_dim (selected, not branched around)
+    for (int i = 0; i < NQ; ++i) {
+        const int c = (2 * (wd * NQ + i) + hi) * N;          // zeros beyond head_dim (selected, not branched around)
         const u32x4 w = *(const u32x4*)(q + (c < d ? c : 0));
 #pragma unroll
         for (int e = 0; e < 4; ++e) st.q[i][e] = c < d ? w[e] : 0;
     }
-    st.m = kUnset; st.l = 0.f;
-#pragma unroll
-    for (int db = 0; db < DP / 32; ++db)
-#pragma unroll
-        for (int r = 0; r < 16; ++r) st.o[db][r] = 0.f;
+    clear_rows(st);
 }
 
 // The partial results of a row's WK wavefronts become one, held by the wavefront of the first (others:
 // return false).  Every lane keeps its own dims and its own share of l.
 template <typename T, int DP, int WR, int WK>
 __device__ __forceinline__ bool combine(char* lds, Rows<T, DP>& st) {
-    if constexpr (WK == 1) return true;
+    if constexpr (WK == 1) return true;                      // (with WD > 1 every wavefront holds its own dims, and all hold m and l)
     constexpr int NV = DP / 2 + 2;                          // values per lane
-    static_assert((WK - 1) * WR * NV * 256 <= Tile<T, DP, WR, WK>::LDS, "the ring holds the partial results");
+    static_assert((WK - 1) * WR * NV * 256 <= Tile<T, DP, WR, WK, 1>::LDS, "the ring holds the partial results");
     const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6, kw = wave % WK, wr = wave / WK;
     float* box = (float*)lds + lane;
     stage_barrier();                                         // every wavefront is done with the last stage
@@ -376,9 +425,9 @@ __device__ __forceinline__ bool combine(char* lds, Rows<T, DP>& st) {
 // ------------------------------------------------------------------------------------------
 // Query prefill and decode: team = (split, KV head), members = tiles of the query rows; the context
 // teams come first, the prefix + own ones follow.  grid: x as in the flash prefill, y = request.
-template <typename T, int DP, int WR, int WK>
-__global__ __launch_bounds__(64 * WR * WK, (Tile<T, DP, WR, WK>::WAVES)) void tile_query_kernel(const QueryArgs a, int n_qtiles) {
-    using X = Tile<T, DP, WR, WK>;
+template <typename T, int DP, int WR, int WK, int WD>
+__global__ __launch_bounds__(64 * WR * WK * WD, (Tile<T, DP, WR, WK, WD>::WAVES)) void tile_query_kernel(const QueryArgs a, int n_qtiles) {
+    using X = Tile<T, DP, WR, WK, WD>;
     extern __shared__ __attribute__((aligned(16))) char lds[];
     const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), l32 = lane & 31, hi = lane >> 5;
     const int d = a.head_dim, hq = a.n_q_heads, hkv = a.n_kv_heads, G = hq / hkv, q_len = a.q_len, rq = blockIdx.y;
@@ -398,7 +447,7 @@ __global__ __launch_bounds__(64 * WR * WK, (Tile<T, DP, WR, WK>::WAVES)) void ti
     const long stride = (long)hkv * d * sizeof(T), head = (long)hk * d * sizeof(T);
 
     const int rows = q_len * G;
-    const int R0 = qtile * X::ROWS + (wave / WK) * 32, R = R0 + l32;
+    const int wd = wave % WD, R0 = qtile * X::ROWS + wave / (WK * WD) * 32, R = R0 + l32;
     const int tok = min(R, rows - 1) / G, h = hk * G + min(R, rows - 1) % G;
     const bool valid = R < rows;
     Source src;
@@ -418,10 +467,10 @@ __global__ __launch_bounds__(64 * WR * WK, (Tile<T, DP, WR, WK>::WAVES)) void ti
         t_beg = 0; t_end = off + tile_hi + 1;
         lim = off + tok; lim_hi = off + min(R0 + 31, rows - 1) / G;
     }
-    Rows<T, DP> st;
-    init_rows<T, DP>(st, (const T*)a.q + (((long)rq * q_len + tok) * hq + h) * d, d);
-    stream<T, DP, WR, WK>(src, t_beg, t_end, d, sc, lim, lim_hi, R0 < rows, lds, st);
-    if (!combine<T, DP, WR, WK>(lds, st)) return;
+    Rows<T, DP / WD> st;
+    init_rows<T, DP, WD>(st, (const T*)a.q + (((long)rq * q_len + tok) * hq + h) * d, d, wd);
+    stream<T, DP, WR, WK, WD>(src, t_beg, t_end, d, sc, lim, lim_hi, R0 < rows, lds, st);
+    if (!combine<T, DP / WD, WR, WK>(lds, st)) return;
 
     const float lt = sum_halves(st.l);
     if (!valid) return;
@@ -429,23 +478,23 @@ __global__ __launch_bounds__(64 * WR * WK, (Tile<T, DP, WR, WK>::WAVES)) void ti
     const long slot = (long)split * a.units_total + ((long)(a.req_base + rq) * q_len + tok) * hq + h;
     float* o = a.part_o + slot * d;
 #pragma unroll
-    for (int db = 0; db < X::NB; ++db)
+    for (int db = 0; db < Rows<T, DP / WD>::NB; ++db)
 #pragma unroll
         for (int q4 = 0; q4 < 4; ++q4) {
-            const int c = 32 * db + 8 * q4 + 4 * hi;
+            const int c = DP / WD * wd + 32 * db + 8 * q4 + 4 * hi;
             f32x4 w;
 #pragma unroll
             for (int e = 0; e < 4; ++e) w[e] = st.o[db][4 * q4 + e] * inv;
             if (c < d) *(f32x4*)(o + c) = w;
         }
-    if (hi == 0) a.part_lse[slot] = lt > 0.f ? ScoreScale<T>::lse(st.m, lt) : -INFINITY;
+    if (hi == 0 && wd == 0) a.part_lse[slot] = lt > 0.f ? ScoreScale<T>::lse(st.m, lt) : -INFINITY;
 }
 
 // ------------------------------------------------------------------------------------------
 // Block-diagonal causal encode: team = (context, KV head), members = its row tiles, the heaviest first.
 template <typename T, int DP, int WR>
-__global__ __launch_bounds__(64 * WR, (Tile<T, DP, WR, 1>::WAVES)) void tile_encode_kernel(const EncodeArgs a, int n_qtiles) {
-    using X = Tile<T, DP, WR, 1>;
+__global__ __launch_bounds__(64 * WR, (Tile<T, DP, WR, 1, 1>::WAVES)) void tile_encode_kernel(const EncodeArgs a, int n_qtiles) {
+    using X = Tile<T, DP, WR, 1, 1>;
     extern __shared__ __attribute__((aligned(16))) char lds[];
     const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), l32 = lane & 31, hi = lane >> 5;
     const int d = a.head_dim, hq = a.n_q_heads, hkv = a.n_kv_heads, G = hq / hkv;
@@ -467,15 +516,15 @@ __global__ __launch_bounds__(64 * WR, (Tile<T, DP, WR, 1>::WAVES)) void tile_enc
     const int t_end = a.prefix_len + (int)((tile_last < rows ? tile_last : rows - 1) / G) + 1;
     const int lim = a.prefix_len + tok, lim_hi = a.prefix_len + (int)((wave_last < rows ? wave_last : rows - 1) / G);
     Rows<T, DP> st;
-    init_rows<T, DP>(st, (const T*)a.q + ((long)(c0 + tok) * hq + h) * d, d);
-    stream<T, DP, WR, 1>(src, 0, t_end, d, ScoreScale<T>(d, 1.f), lim, lim_hi, R0 < rows, lds, st);
+    init_rows<T, DP, 1>(st, (const T*)a.q + ((long)(c0 + tok) * hq + h) * d, d, 0);
+    stream<T, DP, WR, 1, 1>(src, 0, t_end, d, ScoreScale<T>(d, 1.f), lim, lim_hi, R0 < rows, lds, st);
 
     const float lt = sum_halves(st.l);
     if (!valid) return;
     const float inv = 1.f / lt;                              // a row always sees itself
     T* o = (T*)a.out + ((long)(c0 + tok) * hq + h) * d;
 #pragma unroll
-    for (int db = 0; db < X::NB; ++db)
+    for (int db = 0; db < DP / 32; ++db)
 #pragma unroll
         for (int q4 = 0; q4 < 4; ++q4) {
             const int c = 32 * db + 8 * q4 + 4 * hi;
@@ -493,10 +542,10 @@ __global__ __launch_bounds__(64 * WR, (Tile<T, DP, WR, 1>::WAVES)) void tile_enc
     if (a.lse && hi == 0) a.lse[(long)h * a.total_rows + c0 + tok] = ScoreScale<T>::lse(st.m, lt);
 }
 
-template <typename T, int DP, int WR, int WK>
+template <typename T, int DP, int WR, int WK, int WD>
 hipError_t query_with(const QueryArgs& a, hipStream_t s) {
-    using X = Tile<T, DP, WR, WK>;
-    auto kernel = tile_query_kernel<T, DP, WR, WK>;
+    using X = Tile<T, DP, WR, WK, WD>;
+    auto kernel = tile_query_kernel<T, DP, WR, WK, WD>;
     const int rows = a.q_len * (a.n_q_heads / a.n_kv_heads), n_qtiles = (rows + X::ROWS - 1) / X::ROWS;
     const dim3 grid((unsigned)(((a.n_ctx_splits * a.n_kv_heads + 7) / 8 * 8 + (a.n_kv_heads + 7) / 8 * 8) * n_qtiles), (unsigned)a.n_req);
     hipError_t e = hipFuncSetAttribute((const void*)kernel, hipFuncAttributeMaxDynamicSharedMemorySize, X::LDS);
@@ -505,19 +554,19 @@ hipError_t query_with(const QueryArgs& a, hipStream_t s) {
     return hipGetLastError();
 }
 
-// A stage of WK x 32 tokens has to leave room for a second one: the widest rows take fewer wavefronts
-// along the tokens.
+// Few rows: the wavefronts share them.  Where a stage of 32 tokens per wavefront leaves room for a second stage they
+// split the tokens, otherwise (rows of 512 bytes and more) the dims, which takes an exchange of scores per stage.
 template <typename T, int DP>
 hipError_t query_with_rows(const QueryArgs& a, int block_rows, hipStream_t s) {
-    constexpr int BYTES = DP * (int)sizeof(T);
-    if (block_rows == 128) return query_with<T, DP, 4, 1>(a, s);
-    if (block_rows == 64) return query_with<T, DP, 2, BYTES <= 512 ? 2 : 1>(a, s);
-    return query_with<T, DP, 1, BYTES <= 256 ? 4 : BYTES <= 512 ? 2 : 1>(a, s);
+    constexpr bool WIDE = DP * (int)sizeof(T) > 256;
+    if (block_rows == 128) return query_with<T, DP, 4, 1, 1>(a, s);
+    if (block_rows == 64) return query_with<T, DP, 2, WIDE ? 1 : 2, WIDE ? 2 : 1>(a, s);
+    return query_with<T, DP, 1, WIDE ? 1 : 4, WIDE ? 4 : 1>(a, s);
 }
 
 template <typename T, int DP>
 hipError_t encode_with(const EncodeArgs& a, hipStream_t s) {
-    using X = Tile<T, DP, 4, 1>;
+    using X = Tile<T, DP, 4, 1, 1>;
     auto kernel = tile_encode_kernel<T, DP, 4>;
     const long rows = (long)a.max_chunk_len * (a.n_q_heads / a.n_kv_heads);
     const int n_qtiles = (int)((rows + X::ROWS - 1) / X::ROWS);
@@ -529,7 +578,16 @@ hipError_t encode_with(const EncodeArgs& a, hipStream_t s) {
 
 }  // namespace
 
-int tile_query_block_rows(int rows_per_kv_head) { return rows_per_kv_head > 64 ? 128 : rows_per_kv_head > 32 ? 64 : 32; }
+// Rows per workgroup.  128 only for many rows of head_dims up to 128 on enough KV heads (wider rows leave one wavefront per
+// SIMD; 512 fp32 rows over 4096 tokens, 32/8 heads of 128: 128 / 64 rows 368 / 390 us; 256 bf16 rows over 10240, 12/2 heads:
+// 55.3 / 62.9; 512 fp32 rows, 4/2 heads of 64: 77 / 57).  32 where 64 would not give every CU a workgroup (60 fp32 rows per KV
+// head over 1024 tokens, 8 heads of 256: 64 / 32 rows 36 / 28.5 us) or would be half empty (80 bf16 rows: 23.1 / 20.3).
+int tile_query_block_rows(const ShapeInfo& si, int batch, int rows_per_kv_head, long max_ctx) {
+    const long rows = rows_per_kv_head, heads = (long)batch * si.hkv;
+    if (si.d <= 128 && rows >= 1024 && heads * ((rows + 127) / 128) >= 24) return 128;
+    if (rows <= 32 || (rows > 64 && rows <= 96)) return 32;
+    return heads * ((rows + 63) / 64) * ((max_ctx + 127) / 128) >= 256 ? 64 : 32;
+}
 
 hipError_t launch_tile_query(const QueryArgs& a, int dtype, int block_rows, hipStream_t s) {
     const int d = a.head_dim;
