@@ -151,15 +151,25 @@ QueryPlan plan_query(int base_workgroups, long max_ctx, int min_len, int target_
 // long against a workgroup's fixed cost.  Measured with 64 / 32 rows per tile: 64 bf16 rows over 10240 tokens, 16/8 heads of
 // 256, 512 workgroups 49.9 us, 256 51.4; 12/2 heads of 128, 29.0 / 25.9 (its partial results weigh more than the second
 // workgroup per CU gives); 64 fp32 rows over 4096 tokens, 16/8 heads of 256 (one workgroup per CU), 90.7 / 83.6.
-QueryPlan tile_plan(const ShapeInfo& si, int batch, int q_len, long max_ctx) {
+QueryPlan tile_plan(const ShapeInfo& si, int batch, int q_len, long max_ctx, long max_splits = kMaxSplits) {
     const int rows = q_len * si.group, bm = tile_query_block_rows(si, batch, rows, max_ctx);
     const bool f32 = si.dtype == APE_F32;
     const int target = (f32 ? si.d > 128 : si.d > 64 && si.d <= 128 && bm < 128) ? 256 : 512;
     // (16 rows over 2048 tokens, 2/2 fp32 heads of 256: splits of 64 / 128 / 256 tokens 18.9 / 25.8 / 40.2 us; 40 bf16 rows, 6/2
     // heads of 40: 14.5 / 14.7 / 17.2)
-    QueryPlan p = plan_query(batch * si.hkv * ceil_div(rows, bm), max_ctx, f32 && si.d > 128 ? 64 : 128, target);
+    const long base = (long)batch * si.hkv * ceil_div(rows, bm);
+    QueryPlan p = plan_query((int)base, max_ctx, f32 && si.d > 128 ? 64 : 128, (int)(target < base * max_splits ? target : base * max_splits));
     p.block_rows = bm;
     return p;
+}
+
+// ... of a decode step: no more splits than the library's own buffer holds (ape_attention_decode_static), unless the
+// vector-ALU kernels' plan has more itself, so that a step fits the buffer whenever it does under that plan.
+QueryPlan tile_decode_plan(const ShapeInfo& si, int batch, long max_ctx) {
+    const long split_bytes = (long)batch * si.hq * (si.d + 1) * (long)sizeof(float);
+    const long fit = ((long)APE_STATIC_SCRATCH_BYTES - 2 * kWsAlign) / split_bytes - 1;
+    const long other = plan_query(batch * si.hq, max_ctx, 256, 1024).n_bound;
+    return tile_plan(si, batch, 1, max_ctx, fit > other ? fit : other);
 }
 
 // Split plan of a decode step.  Matrix-core path: one workgroup per (request, KV head, split), two
@@ -172,7 +182,7 @@ QueryPlan tile_plan(const ShapeInfo& si, int batch, int q_len, long max_ctx) {
 // and the count at 2048 or less; otherwise many workgroups (at least 8 splits per request, about
 // 2048 workgroups), where the remainder of the last round matters less.
 QueryPlan decode_plan(const ShapeInfo& si, int batch, long max_ctx) {
-    if (si.tile) return tile_plan(si, batch, 1, max_ctx);
+    if (si.tile) return tile_decode_plan(si, batch, max_ctx);
     if (!si.mfma) return plan_query(batch * si.hq, max_ctx, 256, 1024);
     const int base = batch * si.hkv;
     int g = base, r = 256;
