@@ -456,8 +456,9 @@ __global__ __launch_bounds__(64 * WR * WK * WD, (Tile<T, DP, WR, WK, WD>::WAVES)
     if (split < a.n_ctx_splits) {
         long t0, t1;
         ctx_split_range(a, kv, split, t0, t1);
+        if (t0 >= t1) return;                                // an empty split: the merge never looks at it (a request without contexts has no table)
         t1 = min(t1, (long)scalar_load_i32(kv.cu + kv.n_chunks));   // (stay inside the table whatever total_ctx says)
-        if (t0 >= t1) return;                                // an empty split: the merge never looks at it
+        if (t0 >= t1) return;
         src.init_ctx(kv, (int)t0, stride, head);
         t_beg = (int)t0; t_end = (int)t1; lim = lim_hi = t_end - 1;
     } else {
