@@ -114,7 +114,7 @@ namespace {
 // The query kernel that serves the shape.
 hipError_t launch_query(const ShapeInfo& si, const QueryArgs& a, int block_rows, hipStream_t s) {
     if (si.mfma) return launch_flash_prefill(a, block_rows, s);
-    return si.tile ? launch_tile_query(a, si.dtype, block_rows, s) : launch_generic_query(a, si.dtype, s);
+    return si.tile ? launch_tile_query(a, si.dtype, block_rows, false, s) : launch_generic_query(a, si.dtype, s);
 }
 
 KvView to_view(const ape_request* r) {
@@ -170,6 +170,23 @@ QueryPlan tile_decode_plan(const ShapeInfo& si, int batch, long max_ctx) {
     const long fit = ((long)APE_STATIC_SCRATCH_BYTES - 2 * kWsAlign) / split_bytes - 1;
     const long other = plan_query(batch * si.hq, max_ctx, 256, 1024).n_bound;
     return tile_plan(si, batch, 1, max_ctx, fit > other ? fit : other);
+}
+
+// Rows per workgroup of a call that runs without splits, one workgroup taking its rows past the contexts and then past the
+// prefix and the own tokens and writing the output (0: it is split and merged).  Worth it while the longer stream costs less
+// than the second launch, the partial results and their merge, about 4 us: up to 512 context tokens per request with bf16 heads
+// of up to 64, 256 up to 128 (the flash kernels' shapes too), 128 beyond; 128 with fp32 heads of up to 64, 64 up to 128
+// (16 rows, split / whole, us: bf16 heads of 64 over 512 tokens 13.7 / 12.0, 1024 14.1 / 16.9; of 128 over 256 15.4 / 14.5, 512
+// 15.6 / 18.1; of 256 over 128 16.7 / 13.0, 256 17.2 / 19.4; fp32 of 64 over 128 14.0 / 12.9, 256 14.7 / 16.5); and
+// where the requests and heads alone fill the chip and the tile kernels would not split anyway (32 decode steps over 4096 tokens, 16/8
+// bf16 heads of 256: 280 / 228; 32/8 fp32 heads of 128: 366 / 319).
+int whole_block_rows(const ShapeInfo& si, const QueryPlan& plan, int batch, int q_len, long max_ctx) {
+    if (si.force_generic) return 0;
+    const long workgroups = (long)batch * si.hkv * ceil_div((long)q_len * si.group, 32);
+    if (workgroups > 512) return 0;
+    const int width = si.d <= 64 ? 0 : si.d <= 128 ? 1 : 2;
+    const long most = si.dtype == APE_F32 ? (width == 0 ? 128 : width == 1 ? 64 : 0) : 512 >> width;
+    return max_ctx <= most || (si.tile && plan.n_ctx_splits <= 1 && workgroups >= 128) ? 32 : 0;
 }
 
 // Split plan of a decode step.  Matrix-core path: one workgroup per (request, KV head, split), two
@@ -431,6 +448,7 @@ static int run_query(const ShapeInfo& si, const ape_request* reqs, int batch, in
     float* part_o = (float*)workspace;
     float* part_lse = (float*)((char*)workspace + align_up((size_t)units * plan.n_splits_total * si.d * sizeof(float), kWsAlign));
 
+    const int whole = whole_block_rows(si, plan, batch, q_len, max_ctx);
     for (int b0 = 0; b0 < batch; b0 += kMaxReqPerLaunch) {
         const int nb = batch - b0 < kMaxReqPerLaunch ? batch - b0 : kMaxReqPerLaunch;
         QueryArgs a{};
@@ -446,6 +464,12 @@ static int run_query(const ShapeInfo& si, const ape_request* reqs, int batch, in
         a.n_req = nb; a.q_len = q_len; a.n_q_heads = si.hq; a.n_kv_heads = si.hkv; a.head_dim = si.d;
         a.n_ctx_splits = plan.n_ctx_splits; a.ctx_split_len = plan.ctx_split_len;
         a.units_total = (int)units; a.req_base = b0;
+        if (whole) {
+            a.out = out; a.lse_out = lse_out; a.lse_head_major = decode ? 0 : 1;
+            const hipError_t we = launch_tile_query(a, si.dtype, whole, true, st);
+            if (we != hipSuccess) return fail(APE_ERR_DEVICE, "attention kernel: %s", hipGetErrorString(we));
+            continue;
+        }
         hipError_t he = launch_query(si, a, plan.block_rows, st);
         if (he != hipSuccess) return fail(APE_ERR_DEVICE, "attention kernel: %s", hipGetErrorString(he));
 

@@ -48,6 +48,10 @@ struct QueryArgs {
                                 // [split_ranges[2s], split_ranges[2s+1]) of the pooled contexts; empty if equal
     int32_t units_total;        // n_req * q_len * Hq (stride of the split dimension)
     int32_t req_base;           // index of req[0] in the whole batch
+    // a call that takes no merge writes its output itself
+    void* out;                  // [units][d]
+    float* lse_out;             // NULL or fp32
+    int32_t lse_head_major;     // as in MergeArgs
 };
 
 struct MergeArgs {
@@ -283,7 +287,8 @@ struct QueryPlan {
 // ---- launchers (each returns hipGetLastError() of its launch) ------------------------------
 hipError_t launch_generic_query(const QueryArgs& a, int dtype, hipStream_t s);
 hipError_t launch_generic_encode(const EncodeArgs& a, int dtype, hipStream_t s);
-hipError_t launch_tile_query(const QueryArgs& a, int dtype, int block_rows, hipStream_t s);   // any supported shape; block_rows from the plan
+// any supported shape; block_rows from the plan; whole: one workgroup per row tile and KV head, writing the output (32 or 64 rows)
+hipError_t launch_tile_query(const QueryArgs& a, int dtype, int block_rows, bool whole, hipStream_t s);
 hipError_t launch_tile_encode(const EncodeArgs& a, int dtype, hipStream_t s);
 hipError_t launch_merge(const MergeArgs& a, hipStream_t s);
 hipError_t launch_rope_write(const RopeArgs& a, int dtype, hipStream_t s);

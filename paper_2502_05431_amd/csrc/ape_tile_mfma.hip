@@ -422,16 +422,50 @@ __device__ __forceinline__ bool combine(char* lds, Rows<T, DP>& st) {
     return true;
 }
 
+// The contexts' result becomes the state from which the prefix and the own tokens go on (Appendix C.3/C.4): weight S times
+// its LogSumExp, values normalised.
+template <typename T, int DW>
+__device__ __forceinline__ void scale_contexts(Rows<T, DW>& st, float scale) {
+    const float lt = sum_halves(st.l);
+    const bool any = lt > 0.f;                               // (else the state is empty and stays so)
+    const float inv = any ? 1.f / lt : 0.f, w = scale * ScoreScale<T>::lse(st.m, lt);
+    st.m = any ? (sizeof(T) == 4 ? w : w * LOG2E) : kUnset;
+    st.l = any && (threadIdx.x & 32) == 0 ? 1.f : 0.f;
+#pragma unroll
+    for (int db = 0; db < Rows<T, DW>::NB; ++db)
+#pragma unroll
+        for (int r = 0; r < 16; ++r) st.o[db][r] *= inv;
+}
+
+// A row's 4 consecutive output values, in the storage type.
+__device__ __forceinline__ void store4(float* p, const float (&x)[4]) { *(f32x4*)p = f32x4{x[0], x[1], x[2], x[3]}; }
+__device__ __forceinline__ void store4(__bf16* p, const float (&x)[4]) { *(u32x2*)p = u32x2{pack_bf16(x[0], x[1]), pack_bf16(x[2], x[3])}; }
+
+template <typename T, int DP, int WD, typename OUT>
+__device__ __forceinline__ void store_row(const Rows<T, DP / WD>& st, float inv, int d, int wd, OUT* o) {
+    const int hi = (threadIdx.x & 63) >> 5;
+#pragma unroll
+    for (int db = 0; db < Rows<T, DP / WD>::NB; ++db)
+#pragma unroll
+        for (int q4 = 0; q4 < 4; ++q4) {
+            const int c = DP / WD * wd + 32 * db + 8 * q4 + 4 * hi;
+            const float x[4] = {st.o[db][4 * q4] * inv, st.o[db][4 * q4 + 1] * inv, st.o[db][4 * q4 + 2] * inv, st.o[db][4 * q4 + 3] * inv};
+            if (c < d) store4(o + c, x);
+        }
+}
+
 // ------------------------------------------------------------------------------------------
 // Query prefill and decode: team = (split, KV head), members = tiles of the query rows; the context
 // teams come first, the prefix + own ones follow.  grid: x as in the flash prefill, y = request.
-template <typename T, int DP, int WR, int WK, int WD>
+// WHOLE: over short contexts one workgroup takes its rows past the contexts and then past the prefix and the own tokens and
+// writes their output: team = KV head, no partial results, no merge.
+template <typename T, int DP, int WR, int WK, int WD, bool WHOLE>
 __global__ __launch_bounds__(64 * WR * WK * WD, (Tile<T, DP, WR, WK, WD>::WAVES)) void tile_query_kernel(const QueryArgs a, int n_qtiles) {
     using X = Tile<T, DP, WR, WK, WD>;
     extern __shared__ __attribute__((aligned(16))) char lds[];
     const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), l32 = lane & 31, hi = lane >> 5;
     const int d = a.head_dim, hq = a.n_q_heads, hkv = a.n_kv_heads, G = hq / hkv, q_len = a.q_len, rq = blockIdx.y;
-    const int ctx_teams = a.n_ctx_splits * hkv, ctx_blocks = (ctx_teams + 7) / 8 * 8 * n_qtiles;
+    const int ctx_teams = WHOLE ? 0 : a.n_ctx_splits * hkv, ctx_blocks = (ctx_teams + 7) / 8 * 8 * n_qtiles;
     int team, qtile, split;
     if ((int)blockIdx.x < ctx_blocks) {
         team_of_block(blockIdx.x, n_qtiles, team, qtile);
@@ -450,45 +484,60 @@ __global__ __launch_bounds__(64 * WR * WK * WD, (Tile<T, DP, WR, WK, WD>::WAVES)
     const int wd = wave % WD, R0 = qtile * X::ROWS + wave / (WK * WD) * 32, R = R0 + l32;
     const int tok = min(R, rows - 1) / G, h = hk * G + min(R, rows - 1) % G;
     const bool valid = R < rows;
-    Source src;
-    int t_beg, t_end, lim, lim_hi;
-    const ScoreScale<T> sc(d, split < a.n_ctx_splits ? kv.temperature : 1.f);
-    if (split < a.n_ctx_splits) {
-        long t0, t1;
-        ctx_split_range(a, kv, split, t0, t1);
-        if (t0 >= t1) return;                                // an empty split: the merge never looks at it (a request without contexts has no table)
-        t1 = min(t1, (long)scalar_load_i32(kv.cu + kv.n_chunks));   // (stay inside the table whatever total_ctx says)
-        if (t0 >= t1) return;
+    const long unit = ((long)(a.req_base + rq) * q_len + tok) * hq + h;
+    Rows<T, DP / WD> st;
+    auto load_q = [&]() { init_rows<T, DP, WD>(st, (const T*)a.q + (((long)rq * q_len + tok) * hq + h) * d, d, wd); };
+    auto contexts = [&](long t0, long t1) {
+        Source src;
         src.init_ctx(kv, (int)t0, stride, head);
-        t_beg = (int)t0; t_end = (int)t1; lim = lim_hi = t_end - 1;
-    } else {
+        stream<T, DP, WR, WK, WD>(src, (int)t0, (int)t1, d, ScoreScale<T>(d, kv.temperature), (int)t1 - 1, (int)t1 - 1, R0 < rows, lds, st);
+    };
+    auto sequence = [&]() {
         const int off = kv.prefix_len + kv.self_len - q_len; // index of query token 0
         const int tile_hi = min(qtile * X::ROWS + X::ROWS - 1, rows - 1) / G;
+        Source src;
         src.init_seq(kv.k_prefix, kv.v_prefix, kv.prefix_len, kv.k_self, kv.v_self, kv.self_len, stride, head);
-        t_beg = 0; t_end = off + tile_hi + 1;
-        lim = off + tok; lim_hi = off + min(R0 + 31, rows - 1) / G;
-    }
-    Rows<T, DP / WD> st;
-    init_rows<T, DP, WD>(st, (const T*)a.q + (((long)rq * q_len + tok) * hq + h) * d, d, wd);
-    stream<T, DP, WR, WK, WD>(src, t_beg, t_end, d, sc, lim, lim_hi, R0 < rows, lds, st);
-    if (!combine<T, DP / WD, WR, WK>(lds, st)) return;
+        stream<T, DP, WR, WK, WD>(src, 0, off + tile_hi + 1, d, ScoreScale<T>(d, 1.f), off + tok, off + min(R0 + 31, rows - 1) / G, R0 < rows, lds, st);
+    };
 
-    const float lt = sum_halves(st.l);
-    if (!valid) return;
-    const float inv = lt > 0.f ? 1.f / lt : 0.f;
-    const long slot = (long)split * a.units_total + ((long)(a.req_base + rq) * q_len + tok) * hq + h;
-    float* o = a.part_o + slot * d;
-#pragma unroll
-    for (int db = 0; db < Rows<T, DP / WD>::NB; ++db)
-#pragma unroll
-        for (int q4 = 0; q4 < 4; ++q4) {
-            const int c = DP / WD * wd + 32 * db + 8 * q4 + 4 * hi;
-            f32x4 w;
-#pragma unroll
-            for (int e = 0; e < 4; ++e) w[e] = st.o[db][4 * q4 + e] * inv;
-            if (c < d) *(f32x4*)(o + c) = w;
+    if constexpr (WHOLE) {
+        load_q();
+        // (stay inside the table whatever total_ctx says)
+        const int t1 = kv.n_chunks > 0 ? min(kv.total_ctx, scalar_load_i32(kv.cu + kv.n_chunks)) : 0;
+        if (t1 > 0) {
+            contexts(0, t1);
+            const bool first = combine<T, DP / WD, WR, WK>(lds, st);
+            asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
+            stage_barrier();                                 // the results have been read (and every wavefront is done with the last stage)
+            if (first) scale_contexts<T, DP / WD>(st, kernarg<QueryArgs>()->req[rq].scale); else clear_rows(st);
         }
-    if (hi == 0 && wd == 0) a.part_lse[slot] = lt > 0.f ? ScoreScale<T>::lse(st.m, lt) : -INFINITY;
+        sequence();
+        if (!combine<T, DP / WD, WR, WK>(lds, st)) return;
+        const float lt = sum_halves(st.l);                   // (a row always sees itself)
+        if (!valid) return;
+        store_row<T, DP, WD>(st, 1.f / lt, d, wd, (T*)a.out + unit * d);
+        if (a.lse_out && hi == 0 && wd == 0)
+            a.lse_out[a.lse_head_major ? ((long)(a.req_base + rq) * hq + h) * q_len + tok : unit] = ScoreScale<T>::lse(st.m, lt);
+    } else {
+        if (split < a.n_ctx_splits) {
+            long t0, t1;
+            ctx_split_range(a, kv, split, t0, t1);
+            if (t0 >= t1) return;                            // an empty split: the merge never looks at it (a request without contexts has no table)
+            t1 = min(t1, (long)scalar_load_i32(kv.cu + kv.n_chunks));   // (stay inside the table whatever total_ctx says)
+            if (t0 >= t1) return;
+            load_q();
+            contexts(t0, t1);
+        } else {
+            load_q();
+            sequence();
+        }
+        if (!combine<T, DP / WD, WR, WK>(lds, st)) return;
+        const float lt = sum_halves(st.l);
+        if (!valid) return;
+        const long slot = (long)split * a.units_total + unit;
+        store_row<T, DP, WD>(st, lt > 0.f ? 1.f / lt : 0.f, d, wd, a.part_o + slot * d);
+        if (hi == 0 && wd == 0) a.part_lse[slot] = lt > 0.f ? ScoreScale<T>::lse(st.m, lt) : -INFINITY;
+    }
 }
 
 // ------------------------------------------------------------------------------------------
@@ -523,32 +572,17 @@ __global__ __launch_bounds__(64 * WR, (Tile<T, DP, WR, 1, 1>::WAVES)) void tile_
     const float lt = sum_halves(st.l);
     if (!valid) return;
     const float inv = 1.f / lt;                              // a row always sees itself
-    T* o = (T*)a.out + ((long)(c0 + tok) * hq + h) * d;
-#pragma unroll
-    for (int db = 0; db < DP / 32; ++db)
-#pragma unroll
-        for (int q4 = 0; q4 < 4; ++q4) {
-            const int c = 32 * db + 8 * q4 + 4 * hi;
-            if (c >= d) continue;
-            if constexpr (sizeof(T) == 4) {
-                f32x4 w;
-#pragma unroll
-                for (int e = 0; e < 4; ++e) w[e] = st.o[db][4 * q4 + e] * inv;
-                *(f32x4*)(o + c) = w;
-            } else {
-                *(u32x2*)(o + c) = u32x2{pack_bf16(st.o[db][4 * q4] * inv, st.o[db][4 * q4 + 1] * inv),
-                                         pack_bf16(st.o[db][4 * q4 + 2] * inv, st.o[db][4 * q4 + 3] * inv)};
-            }
-        }
+    store_row<T, DP, 1>(st, inv, d, 0, (T*)a.out + ((long)(c0 + tok) * hq + h) * d);
     if (a.lse && hi == 0) a.lse[(long)h * a.total_rows + c0 + tok] = ScoreScale<T>::lse(st.m, lt);
 }
 
-template <typename T, int DP, int WR, int WK, int WD>
-hipError_t query_with(const QueryArgs& a, hipStream_t s) {
+template <typename T, int DP, int WR, int WK, int WD, bool WHOLE>
+hipError_t query_as(const QueryArgs& a, hipStream_t s) {
     using X = Tile<T, DP, WR, WK, WD>;
-    auto kernel = tile_query_kernel<T, DP, WR, WK, WD>;
+    auto kernel = tile_query_kernel<T, DP, WR, WK, WD, WHOLE>;
     const int rows = a.q_len * (a.n_q_heads / a.n_kv_heads), n_qtiles = (rows + X::ROWS - 1) / X::ROWS;
-    const dim3 grid((unsigned)(((a.n_ctx_splits * a.n_kv_heads + 7) / 8 * 8 + (a.n_kv_heads + 7) / 8 * 8) * n_qtiles), (unsigned)a.n_req);
+    const int ctx_teams = WHOLE ? 0 : a.n_ctx_splits * a.n_kv_heads;
+    const dim3 grid((unsigned)(((ctx_teams + 7) / 8 * 8 + (a.n_kv_heads + 7) / 8 * 8) * n_qtiles), (unsigned)a.n_req);
     hipError_t e = hipFuncSetAttribute((const void*)kernel, hipFuncAttributeMaxDynamicSharedMemorySize, X::LDS);
     if (e != hipSuccess) return e;
     kernel<<<grid, X::NT, X::LDS, s>>>(a, n_qtiles);
@@ -558,11 +592,12 @@ hipError_t query_with(const QueryArgs& a, hipStream_t s) {
 // Few rows: the wavefronts share them.  Where a stage of 32 tokens per wavefront leaves room for a second stage they
 // split the tokens, otherwise (rows of 512 bytes and more) the dims, which takes an exchange of scores per stage.
 template <typename T, int DP>
-hipError_t query_with_rows(const QueryArgs& a, int block_rows, hipStream_t s) {
+hipError_t query_with(const QueryArgs& a, int block_rows, bool whole, hipStream_t s) {
     constexpr bool WIDE = DP * (int)sizeof(T) > 256;
-    if (block_rows == 128) return query_with<T, DP, 4, 1, 1>(a, s);
-    if (block_rows == 64) return query_with<T, DP, 2, WIDE ? 1 : 2, WIDE ? 2 : 1>(a, s);
-    return query_with<T, DP, 1, WIDE ? 1 : 4, WIDE ? 4 : 1>(a, s);
+    constexpr int K2 = WIDE ? 1 : 2, D2 = WIDE ? 2 : 1, K4 = WIDE ? 1 : 4, D4 = WIDE ? 4 : 1;
+    if (block_rows == 128) return query_as<T, DP, 4, 1, 1, false>(a, s);
+    if (block_rows == 64) return whole ? query_as<T, DP, 2, K2, D2, true>(a, s) : query_as<T, DP, 2, K2, D2, false>(a, s);
+    return whole ? query_as<T, DP, 1, K4, D4, true>(a, s) : query_as<T, DP, 1, K4, D4, false>(a, s);
 }
 
 template <typename T, int DP>
@@ -590,11 +625,11 @@ int tile_query_block_rows(const ShapeInfo& si, int batch, int rows_per_kv_head, 
     return heads * ((rows + 63) / 64) * ((max_ctx + 127) / 128) >= 256 ? 64 : 32;
 }
 
-hipError_t launch_tile_query(const QueryArgs& a, int dtype, int block_rows, hipStream_t s) {
+hipError_t launch_tile_query(const QueryArgs& a, int dtype, int block_rows, bool whole, hipStream_t s) {
     const int d = a.head_dim;
     if (dtype == APE_F32)
-        return d <= 64 ? query_with_rows<float, 64>(a, block_rows, s) : d <= 128 ? query_with_rows<float, 128>(a, block_rows, s) : query_with_rows<float, 256>(a, block_rows, s);
-    return d <= 64 ? query_with_rows<__bf16, 64>(a, block_rows, s) : d <= 128 ? query_with_rows<__bf16, 128>(a, block_rows, s) : query_with_rows<__bf16, 256>(a, block_rows, s);
+        return d <= 64 ? query_with<float, 64>(a, block_rows, whole, s) : d <= 128 ? query_with<float, 128>(a, block_rows, whole, s) : query_with<float, 256>(a, block_rows, whole, s);
+    return d <= 64 ? query_with<__bf16, 64>(a, block_rows, whole, s) : d <= 128 ? query_with<__bf16, 128>(a, block_rows, whole, s) : query_with<__bf16, 256>(a, block_rows, whole, s);
 }
 
 hipError_t launch_tile_encode(const EncodeArgs& a, int dtype, hipStream_t s) {
