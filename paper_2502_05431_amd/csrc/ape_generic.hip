@@ -198,135 +198,26 @@ __global__ __launch_bounds__(kWave) void generic_encode_kernel(const EncodeArgs 
 // Merge of the split results (Appendix C.1 for splits of one group, C.3/C.4 across the two
 // groups): the context splits are merged first, exactly; only then is the pooled context
 // LogSumExp multiplied by S -- (sum of splits)^S is not the sum of the splits^S.
-// grid: x = unit; a workgroup of kMergeWaves wavefronts per unit.  Every wavefront computes the
-// split weights (one coalesced read of the LogSumExps, a wavefront reduction); the wavefronts
-// then share out the splits, each accumulating its weighted rows with several loads in flight,
-// and are combined through LDS.  (A serial loop over 64 splits cost 61 us at batch 1.)
-constexpr int kMergeWaves = 4;
-constexpr int kMergeWavesFew = 16;
-
-// One group of splits [s0, s1): this wavefront's share of sum_s w_s o_s into acc (lane owns dims
-// lane + 64 r), with w_s = exp(lse_s - max); returns the group's max and sum of weights.
-template <int W>
-__device__ __forceinline__ void merge_group(const MergeArgs& a, long gunit, int s0, int s1, int wave, int lane,
-                                            float (&acc)[kMaxDimRegs], float& m_out, float& z_out) {
-    const int d = a.head_dim;
-    float m = -INFINITY;
-    for (int s = s0 + lane; s < s1; s += kWave) m = fmaxf(m, a.part_lse[(long)s * a.units_total + gunit]);
-    m = wave_max(m);
-    float z = 0.f;
-    if (m > -INFINITY) {
-        for (int c0 = s0; c0 < s1; c0 += kWave) {                   // chunks of 64 splits: lane <-> split
-            const int s_mine = c0 + lane;
-            const float w_mine = s_mine < s1 ? expf(a.part_lse[(long)s_mine * a.units_total + gunit] - m) : 0.f;   // 0 for empty splits
-            z += w_mine;
-            const int cnt = min(kWave, s1 - c0);
-            constexpr int UN = 4;                                       // rows in flight per wavefront
-            for (int i = wave; i < cnt; i += UN * W) {
-                float w[UN], v[UN][kMaxDimRegs];
-#pragma unroll
-                for (int u = 0; u < UN; ++u) {
-                    const int ii = i + u * W;
-                    w[u] = ii < cnt ? __shfl(w_mine, min(ii, kWave - 1)) : 0.f;
-                    const float* o = a.part_o + ((long)(c0 + min(ii, cnt - 1)) * a.units_total + gunit) * d;
-#pragma unroll
-                    for (int r = 0; r < kMaxDimRegs; ++r) {
-                        const int c = lane + kWave * r;
-                        v[u][r] = c < d ? o[c] : 0.f;
-                    }
-                }
-#pragma unroll
-                for (int u = 0; u < UN; ++u)
-#pragma unroll
-                    for (int r = 0; r < kMaxDimRegs; ++r) acc[r] = fmaf(w[u], v[u][r], acc[r]);
-            }
-        }
-        z = wave_sum(z);
-    }
-    m_out = m; z_out = z;
-}
-
-// W wavefronts per unit: kMergeWaves when there are many units (the launch is then bound by its
-// traffic), kMergeWavesFew for a few units with many splits each (decode of a long context at a small
-// batch: 32 units x 64 splits), where the time is a chain of round trips and W x 4 rows in flight
-// cover all splits in one of them.
-template <typename T, int W>
-__global__ __launch_bounds__(kWave * W) void merge_kernel(const MergeArgs a) {
-    __shared__ float part[2][W][kWave * kMaxDimRegs];
-    const int lane = threadIdx.x & (kWave - 1), wave = threadIdx.x / kWave;
-    const int unit = blockIdx.x;                                    // within this launch
-    const int d = a.head_dim, hq = a.n_q_heads;
-    const int rq = unit / (hq * a.q_len);
-    const long gunit = (long)a.req_base * a.q_len * hq + unit;
-    const float S = kernarg<MergeArgs>()->scale[rq];
-
-    float acc_c[kMaxDimRegs], acc_o[kMaxDimRegs];
-#pragma unroll
-    for (int r = 0; r < kMaxDimRegs; ++r) { acc_c[r] = 0.f; acc_o[r] = 0.f; }
-    float mc, zc, mo, zo;
-    // context group: only the splits that hold tokens of THIS request (a shorter context in a
-    // batch leaves the trailing splits untouched)
-    const int tc = kernarg<MergeArgs>()->total_ctx[rq];
-    const int n_ctx = min(a.n_ctx_splits, (tc + a.ctx_split_len - 1) / a.ctx_split_len);
-    merge_group<W>(a, gunit, 0, n_ctx, wave, lane, acc_c, mc, zc);
-    merge_group<W>(a, gunit, a.n_ctx_splits, a.n_splits_total, wave, lane, acc_o, mo, zo);   // prefix + self: never empty
-#pragma unroll
-    for (int r = 0; r < kMaxDimRegs; ++r) {
-        part[0][wave][lane + kWave * r] = acc_c[r];
-        part[1][wave][lane + kWave * r] = acc_o[r];
-    }
-    __syncthreads();
-    if (wave != 0) return;
-#pragma unroll
-    for (int r = 0; r < kMaxDimRegs; ++r) {
-        acc_c[r] = 0.f; acc_o[r] = 0.f;
-#pragma unroll
-        for (int w = 0; w < W; ++w) { acc_c[r] += part[0][w][lane + kWave * r]; acc_o[r] += part[1][w][lane + kWave * r]; }
-    }
-    const float lse_c = mc > -INFINITY ? mc + logf(zc) : -INFINITY;   // log Z_ctx
-    const float inv_zc = zc > 0.f ? 1.f / zc : 0.f;
-    const float lse_o = mo + logf(zo);
-    const float inv_zo = 1.f / zo;
-
-    // softmax over (S * lse_c, lse_o)
-    const float ac = lse_c > -INFINITY ? S * lse_c : -INFINITY;
-    const float mx = fmaxf(ac, lse_o);
-    const float ec = expf(ac - mx), eo = expf(lse_o - mx);
-    const float wc = ec / (ec + eo), wo = eo / (ec + eo);
-
-    T* out = (T*)a.out + gunit * d;
-#pragma unroll
-    for (int r = 0; r < kMaxDimRegs; ++r) {
-        const int c = lane + kWave * r;
-        if (c < d) out[c] = (T)(wc * acc_c[r] * inv_zc + wo * acc_o[r] * inv_zo);
-    }
-    if (a.lse_out && lane == 0) {
-        const float lse = mx + logf(ec + eo);
-        if (a.lse_head_major) {                                     // [request, head, row]
-            const int h = unit % hq, row = (unit / hq) % a.q_len;
-            a.lse_out[((long)(a.req_base + rq) * hq + h) * a.q_len + row] = lse;
-        } else {
-            a.lse_out[gunit] = lse;
-        }
-    }
-}
-
-// The same merge for MANY units of head_dim 128 (a query prefill: 8192 units of 9 splits; a batched
-// decode step): a workgroup per unit spends its time being launched (8192 workgroups took 25 us for
-// 40 MB).  Here half a wavefront owns a unit -- lane j holds dims 4j .. 4j+3, so a split's row is one
-// 16-byte load per lane -- eight units per workgroup, no LDS and no barrier: one round trip for the
-// LogSumExps (lane j reads splits j, j + 32, j + 64), the weights by half-wavefront reductions, then
-// the rows with eight loads in flight.
-constexpr int kMergeUnitsPerBlock = 8;
-template <typename T>
+//
+// A half-wavefront reads rows: lane j holds dims 4j .. 4j+3 (and 128 + 4j .. with NV == 2), so a split's row is one
+// 16-byte load per lane.  H half-wavefronts share a unit's splits and add up in LDS; a workgroup has eight.  What bounds a
+// call with few units is round trips to memory, hence one for everything: the LogSumExps (lane j reads splits j, j + 32,
+// j + 64) and the first UN rows are fetched together, the weights follow by half-wavefront reductions.  With
+// many units the bytes of the partial results bound it.
+// Whole calls, against a workgroup per unit that read the LogSumExps and then the rows of one group after the other (us): a decode
+// step over 20 x 512 tokens, 32 units of 33 splits, 17.8 -> 15.3; 80 units of 33 splits of a 20-row query 25.9 -> 23.6; 64 rows,
+// 32/8 bf16 heads of 64, 30.7 -> 27.4; 256 rows over 128K tokens, 8192 units of 9 splits, 481 -> 480.
+template <typename T, int NV, int H>
 __global__ __launch_bounds__(256) void merge_units_kernel(const MergeArgs a) {
+    constexpr int UN = 8;
+    __shared__ float4 part[H > 1 ? 8 : 1][32 * NV];
     const int lane = threadIdx.x & (kWave - 1), wave = threadIdx.x / kWave;
-    const int half = lane >> 5, j = lane & 31;
+    const int half = lane >> 5, j = lane & 31, hw = 2 * wave + half, share = hw % H;
     const long n_units = (long)a.n_req * a.q_len * a.n_q_heads;
-    const long unit_raw = ((long)blockIdx.x * 4 + wave) * 2 + half;
+    const long unit_raw = (long)blockIdx.x * (8 / H) + hw / H;
     const bool valid = unit_raw < n_units;
     const long unit = valid ? unit_raw : n_units - 1;                // (a spare half-wavefront recomputes the last unit and stores nothing)
-    const int hq = a.n_q_heads;
+    const int hq = a.n_q_heads, d = a.head_dim;
     const int rq = (int)(unit / ((long)hq * a.q_len));
     const long gunit = (long)a.req_base * a.q_len * hq + unit;
     auto ka = kernarg<MergeArgs>();
@@ -334,6 +225,7 @@ __global__ __launch_bounds__(256) void merge_units_kernel(const MergeArgs a) {
     const int tc = ka->total_ctx[rq];
     const int n_split = a.n_ctx_splits;                              // slots of the context group; slot n_split is prefix + self
     const int n_ctx = min(n_split, (tc + a.ctx_split_len - 1) / a.ctx_split_len);   // those this request wrote
+    const int n_slots = n_split + 1;                                 // wavefront-uniform loop bound
     // LogSumExps: slot s lives in lane s % 32 of this half, register s / 32 (at most 65 slots)
     float l[3];
 #pragma unroll
@@ -342,6 +234,20 @@ __global__ __launch_bounds__(256) void merge_units_kernel(const MergeArgs a) {
         const bool used = sl < n_ctx || sl == n_split;
         l[r] = used ? a.part_lse[(long)sl * a.units_total + gunit] : -INFINITY;
     }
+    const long slot_stride = (long)a.units_total * d;
+    const float* base = a.part_o + gunit * d;
+    float4 v[UN][NV], acc[NV];
+    auto load_rows = [&](int s0) {
+#pragma unroll
+        for (int u = 0; u < UN; ++u) {
+            const int sl = s0 + share + H * u;
+            // a slot this request did not write is never read (its weight is 0; read the prefix + self slot instead)
+            const float* o = base + (sl < n_ctx ? sl : n_split) * slot_stride;
+#pragma unroll
+            for (int n = 0; n < NV; ++n) v[u][n] = *(const float4*)(o + (128 * n + 4 * j < d ? 128 * n + 4 * j : 0));
+        }
+    };
+    load_rows(0);
     auto half_max = [](float x) {
 #pragma unroll
         for (int o = 16; o > 0; o >>= 1) x = fmaxf(x, __shfl_xor(x, o));
@@ -356,51 +262,61 @@ __global__ __launch_bounds__(256) void merge_units_kernel(const MergeArgs a) {
 #pragma unroll
     for (int r = 0; r < 3; ++r) lc[r] = (j + 32 * r) < n_ctx ? l[r] : -INFINITY;
     const float mc = half_max(fmaxf(fmaxf(lc[0], lc[1]), lc[2]));
+    const bool any = mc > -INFINITY;
     float e[3];
 #pragma unroll
-    for (int r = 0; r < 3; ++r) e[r] = mc > -INFINITY ? expf(lc[r] - mc) : 0.f;   // 0 for empty and unused slots
+    for (int r = 0; r < 3; ++r) e[r] = any ? expf(lc[r] - mc) : 0.f;               // 0 for empty and unused slots
     const float zc = half_sum(e[0] + e[1] + e[2]);
     const float lse_o = __shfl(l[n_split >> 5], (n_split & 31) + 32 * half);       // prefix + self: never empty
     // the context splits are pooled first; only then is their LogSumExp multiplied by S
-    const float lse_c = zc > 0.f ? mc + logf(zc) : -INFINITY;
-    const float ac = lse_c > -INFINITY ? S * lse_c : -INFINITY;
+    const float ac = any ? S * (mc + logf(zc)) : -INFINITY;
     const float mx = fmaxf(ac, lse_o);
     const float ec = expf(ac - mx), eo = expf(lse_o - mx);
     const float wc = ec / (ec + eo), wo = eo / (ec + eo);
     float w[3];                                                      // weight of this lane's slots in the output
 #pragma unroll
-    for (int r = 0; r < 3; ++r) w[r] = (j + 32 * r) == n_split ? wo : (zc > 0.f ? wc * e[r] / zc : 0.f);
+    for (int r = 0; r < 3; ++r) w[r] = (j + 32 * r) == n_split ? wo : (any ? wc * e[r] / zc : 0.f);
 
-    float4 acc = make_float4(0.f, 0.f, 0.f, 0.f);
-    const float* base = a.part_o + gunit * 128 + 4 * j;
-    const long slot_stride = (long)a.units_total * 128;
-    const int n_slots = n_split + 1;                                 // wavefront-uniform loop bound
-    constexpr int UN = 8;
-    for (int s0 = 0; s0 < n_slots; s0 += UN) {
-        float4 v[UN];
-        float ws[UN];
+#pragma unroll
+    for (int n = 0; n < NV; ++n) acc[n] = make_float4(0.f, 0.f, 0.f, 0.f);
+    for (int s0 = 0; s0 < n_slots; s0 += H * UN) {
+        if (s0 > 0) load_rows(s0);
 #pragma unroll
         for (int u = 0; u < UN; ++u) {
-            const int sl = min(s0 + u, n_slots - 1);
-            const float wl = __shfl(sl < 32 ? w[0] : sl < 64 ? w[1] : w[2], (sl & 31) + 32 * half);
-            ws[u] = s0 + u < n_slots ? wl : 0.f;
-            // a slot this request did not write is never read (its weight is 0; read the prefix + self slot instead)
-            const int src = (sl < n_ctx || sl == n_split) ? sl : n_split;
-            v[u] = *(const float4*)(base + src * slot_stride);
-        }
+            const int sl = s0 + share + H * u, from = min(sl, n_slots - 1);
+            const float wl = __shfl(from < 32 ? w[0] : from < 64 ? w[1] : w[2], (from & 31) + 32 * half);
+            const float ws = sl < n_slots ? wl : 0.f;
 #pragma unroll
-        for (int u = 0; u < UN; ++u) {
-            acc.x = fmaf(ws[u], v[u].x, acc.x); acc.y = fmaf(ws[u], v[u].y, acc.y);
-            acc.z = fmaf(ws[u], v[u].z, acc.z); acc.w = fmaf(ws[u], v[u].w, acc.w);
+            for (int n = 0; n < NV; ++n) {
+                acc[n].x = fmaf(ws, v[u][n].x, acc[n].x); acc[n].y = fmaf(ws, v[u][n].y, acc[n].y);
+                acc[n].z = fmaf(ws, v[u][n].z, acc[n].z); acc[n].w = fmaf(ws, v[u][n].w, acc[n].w);
+            }
         }
     }
-    if (!valid) return;
-    T* out = (T*)a.out + gunit * 128 + 4 * j;
-    if constexpr (sizeof(T) == 4) {
-        *(float4*)out = acc;
-    } else {
-        const T o4[4] = {(T)acc.x, (T)acc.y, (T)acc.z, (T)acc.w};
-        *(uint2*)out = *(const uint2*)o4;
+    if constexpr (H > 1) {
+#pragma unroll
+        for (int n = 0; n < NV; ++n) part[hw][32 * n + j] = acc[n];
+        __syncthreads();
+#pragma unroll
+        for (int n = 0; n < NV; ++n)
+#pragma unroll
+            for (int k = 1; k < H; ++k) {
+                const float4 x = part[hw - share + k][32 * n + j];
+                acc[n].x += x.x; acc[n].y += x.y; acc[n].z += x.z; acc[n].w += x.w;
+            }
+    }
+    if (!valid || share != 0) return;
+#pragma unroll
+    for (int n = 0; n < NV; ++n) {
+        const int c = 128 * n + 4 * j;
+        if (c >= d) continue;
+        T* out = (T*)a.out + gunit * d + c;
+        if constexpr (sizeof(T) == 4) {
+            *(float4*)out = acc[n];
+        } else {
+            const T o4[4] = {(T)acc[n].x, (T)acc[n].y, (T)acc[n].z, (T)acc[n].w};
+            *(uint2*)out = *(const uint2*)o4;
+        }
     }
     if (a.lse_out && j == 0) {
         const float lse = mx + logf(ec + eo);
@@ -422,6 +338,7 @@ __global__ __launch_bounds__(256) void merge_units_kernel(const MergeArgs a) {
 // An exclusive scan over the nodes gives every such node its first split; the ranges of the
 // splits in use are written out, the slots behind them are left empty.
 constexpr int kPlanThreads = 1024;
+constexpr int kMergeWaves = 4;
 __global__ __launch_bounds__(kPlanThreads) void tree_plan_kernel(const TreePlanArgs a) {
     __shared__ int cnt[APE_TREE_MAX_NODES];
     __shared__ int off[APE_TREE_MAX_NODES];
@@ -827,23 +744,26 @@ hipError_t launch_generic_encode(const EncodeArgs& a, int dtype, hipStream_t s) 
     return hipGetLastError();
 }
 
-hipError_t launch_merge(const MergeArgs& a, hipStream_t s) {
-    dim3 grid((unsigned)(a.n_req * a.q_len * a.n_q_heads));
-    const bool few = a.n_ctx_splits >= 32 && (long)grid.x * a.n_splits_total <= 4096;
-    if (!few && a.head_dim == 128 && grid.x >= 256 && a.n_splits_total <= 65) {
-        const unsigned blocks = (grid.x + kMergeUnitsPerBlock - 1) / kMergeUnitsPerBlock;
-        if (a.dtype == APE_F32) merge_units_kernel<float><<<blocks, 256, 0, s>>>(a);
-        else merge_units_kernel<__bf16><<<blocks, 256, 0, s>>>(a);
-        return hipGetLastError();
-    }
-    if (a.dtype == APE_F32) {
-        if (few) merge_kernel<float, kMergeWavesFew><<<grid, kWave * kMergeWavesFew, 0, s>>>(a);
-        else merge_kernel<float, kMergeWaves><<<grid, kWave * kMergeWaves, 0, s>>>(a);
-    } else {
-        if (few) merge_kernel<__bf16, kMergeWavesFew><<<grid, kWave * kMergeWavesFew, 0, s>>>(a);
-        else merge_kernel<__bf16, kMergeWaves><<<grid, kWave * kMergeWaves, 0, s>>>(a);
-    }
+namespace {
+template <typename T, int NV>
+hipError_t launch_merge_t(const MergeArgs& a, hipStream_t s) {
+    const long units = (long)a.n_req * a.q_len * a.n_q_heads;
+    // As many half-wavefronts per unit as take its splits in one round; with enough units to fill the chip (the bytes
+    // bound it then) one.
+    const int slots = a.n_splits_total;
+    const int h = units >= 4096 || slots <= 8 ? 1 : slots <= 16 ? 2 : slots <= 32 ? 4 : 8;
+    const unsigned blocks = (unsigned)((units * h + 7) / 8);
+    if (h == 1) merge_units_kernel<T, NV, 1><<<blocks, 256, 0, s>>>(a);
+    else if (h == 2) merge_units_kernel<T, NV, 2><<<blocks, 256, 0, s>>>(a);
+    else if (h == 4) merge_units_kernel<T, NV, 4><<<blocks, 256, 0, s>>>(a);
+    else merge_units_kernel<T, NV, 8><<<blocks, 256, 0, s>>>(a);
     return hipGetLastError();
+}
+}  // namespace
+
+hipError_t launch_merge(const MergeArgs& a, hipStream_t s) {
+    if (a.dtype == APE_F32) return a.head_dim <= 128 ? launch_merge_t<float, 1>(a, s) : launch_merge_t<float, 2>(a, s);
+    return a.head_dim <= 128 ? launch_merge_t<__bf16, 1>(a, s) : launch_merge_t<__bf16, 2>(a, s);
 }
 
 hipError_t launch_tree_plan(const TreePlanArgs& a, hipStream_t s) {
