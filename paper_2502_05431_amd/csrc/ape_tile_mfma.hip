@@ -422,12 +422,16 @@ __device__ __forceinline__ bool combine(char* lds, Rows<T, DP>& st) {
     return true;
 }
 
+// Whether a row saw any token: a sum of probabilities that is not zero, be it not a number (the compiler is told that there are
+// none, so the bits are asked).
+__device__ __forceinline__ bool seen(float sum) { return __float_as_uint(sum) != 0; }
+
 // The contexts' result becomes the state from which the prefix and the own tokens go on (Appendix C.3/C.4): weight S times
 // its LogSumExp, values normalised.
 template <typename T, int DW>
 __device__ __forceinline__ void scale_contexts(Rows<T, DW>& st, float scale) {
     const float lt = sum_halves(st.l);
-    const bool any = lt > 0.f;                               // (else the state is empty and stays so)
+    const bool any = seen(lt);                               // (else the state is empty and stays so)
     const float inv = any ? 1.f / lt : 0.f, w = scale * ScoreScale<T>::lse(st.m, lt);
     st.m = any ? (sizeof(T) == 4 ? w : w * LOG2E) : kUnset;
     st.l = any && (threadIdx.x & 32) == 0 ? 1.f : 0.f;
@@ -535,18 +539,18 @@ __global__ __launch_bounds__(64 * WR * WK * WD, (Tile<T, DP, WR, WK, WD>::WAVES)
         const float lt = sum_halves(st.l);
         if (!valid) return;
         const long slot = (long)split * a.units_total + unit;
-        store_row<T, DP, WD>(st, lt > 0.f ? 1.f / lt : 0.f, d, wd, a.part_o + slot * d);
-        if (hi == 0 && wd == 0) a.part_lse[slot] = lt > 0.f ? ScoreScale<T>::lse(st.m, lt) : -INFINITY;
+        store_row<T, DP, WD>(st, seen(lt) ? 1.f / lt : 0.f, d, wd, a.part_o + slot * d);
+        if (hi == 0 && wd == 0) a.part_lse[slot] = seen(lt) ? ScoreScale<T>::lse(st.m, lt) : -INFINITY;
     }
 }
 
 // ------------------------------------------------------------------------------------------
 // Block-diagonal causal encode: team = (context, KV head), members = its row tiles, the heaviest first.
-template <typename T, int DP, int WR>
-__global__ __launch_bounds__(64 * WR, (Tile<T, DP, WR, 1, 1>::WAVES)) void tile_encode_kernel(const EncodeArgs a, int n_qtiles) {
-    using X = Tile<T, DP, WR, 1, 1>;
+template <typename T, int DP, int WR, int WK, int WD>
+__global__ __launch_bounds__(64 * WR * WK * WD, (Tile<T, DP, WR, WK, WD>::WAVES)) void tile_encode_kernel(const EncodeArgs a, int n_qtiles) {
+    using X = Tile<T, DP, WR, WK, WD>;
     extern __shared__ __attribute__((aligned(16))) char lds[];
-    const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), l32 = lane & 31, hi = lane >> 5;
+    const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), l32 = lane & 31, hi = lane >> 5, wd = wave % WD;
     const int d = a.head_dim, hq = a.n_q_heads, hkv = a.n_kv_heads, G = hq / hkv;
     int team, member;
     team_of_block(blockIdx.x, n_qtiles, team, member);
@@ -557,7 +561,7 @@ __global__ __launch_bounds__(64 * WR, (Tile<T, DP, WR, 1, 1>::WAVES)) void tile_
     const long rows = (long)len * G;
     if ((long)qtile * X::ROWS >= rows) return;
     const long stride = (long)hkv * d * sizeof(T), head = (long)hk * d * sizeof(T);
-    const long R0 = (long)qtile * X::ROWS + wave * 32, R = R0 + l32, Rc = R < rows ? R : rows - 1;
+    const long R0 = (long)qtile * X::ROWS + wave / (WK * WD) * 32, R = R0 + l32, Rc = R < rows ? R : rows - 1;
     const int tok = (int)(Rc / G), h = hk * G + (int)(Rc % G);
     const bool valid = R < rows;
     const long tile_last = (long)qtile * X::ROWS + X::ROWS - 1, wave_last = R0 + 31;
@@ -565,15 +569,15 @@ __global__ __launch_bounds__(64 * WR, (Tile<T, DP, WR, 1, 1>::WAVES)) void tile_
     src.init_seq(a.k_prefix, a.v_prefix, a.prefix_len, (const T*)a.k + (long)c0 * hkv * d, (const T*)a.v + (long)c0 * hkv * d, len, stride, head);
     const int t_end = a.prefix_len + (int)((tile_last < rows ? tile_last : rows - 1) / G) + 1;
     const int lim = a.prefix_len + tok, lim_hi = a.prefix_len + (int)((wave_last < rows ? wave_last : rows - 1) / G);
-    Rows<T, DP> st;
-    init_rows<T, DP, 1>(st, (const T*)a.q + ((long)(c0 + tok) * hq + h) * d, d, 0);
-    stream<T, DP, WR, 1, 1>(src, 0, t_end, d, ScoreScale<T>(d, 1.f), lim, lim_hi, R0 < rows, lds, st);
+    Rows<T, DP / WD> st;
+    init_rows<T, DP, WD>(st, (const T*)a.q + ((long)(c0 + tok) * hq + h) * d, d, wd);
+    stream<T, DP, WR, WK, WD>(src, 0, t_end, d, ScoreScale<T>(d, 1.f), lim, lim_hi, R0 < rows, lds, st);
+    if (!combine<T, DP / WD, WR, WK>(lds, st)) return;
 
     const float lt = sum_halves(st.l);
     if (!valid) return;
-    const float inv = 1.f / lt;                              // a row always sees itself
-    store_row<T, DP, 1>(st, inv, d, 0, (T*)a.out + ((long)(c0 + tok) * hq + h) * d);
-    if (a.lse && hi == 0) a.lse[(long)h * a.total_rows + c0 + tok] = ScoreScale<T>::lse(st.m, lt);
+    store_row<T, DP, WD>(st, 1.f / lt, d, wd, (T*)a.out + ((long)(c0 + tok) * hq + h) * d);   // (a row always sees itself)
+    if (a.lse && hi == 0 && wd == 0) a.lse[(long)h * a.total_rows + c0 + tok] = ScoreScale<T>::lse(st.m, lt);
 }
 
 template <typename T, int DP, int WR, int WK, int WD, bool WHOLE>
@@ -600,16 +604,23 @@ hipError_t query_with(const QueryArgs& a, int block_rows, bool whole, hipStream_
     return whole ? query_as<T, DP, 1, K4, D4, true>(a, s) : query_as<T, DP, 1, K4, D4, false>(a, s);
 }
 
-template <typename T, int DP>
-hipError_t encode_with(const EncodeArgs& a, hipStream_t s) {
-    using X = Tile<T, DP, 4, 1, 1>;
-    auto kernel = tile_encode_kernel<T, DP, 4>;
+template <typename T, int DP, int WR, int WK, int WD>
+hipError_t encode_as(const EncodeArgs& a, hipStream_t s) {
+    using X = Tile<T, DP, WR, WK, WD>;
+    auto kernel = tile_encode_kernel<T, DP, WR, WK, WD>;
     const long rows = (long)a.max_chunk_len * (a.n_q_heads / a.n_kv_heads);
     const int n_qtiles = (int)((rows + X::ROWS - 1) / X::ROWS);
     hipError_t e = hipFuncSetAttribute((const void*)kernel, hipFuncAttributeMaxDynamicSharedMemorySize, X::LDS);
     if (e != hipSuccess) return e;
     kernel<<<(unsigned)((a.n_chunks * a.n_kv_heads + 7) / 8 * 8 * n_qtiles), X::NT, X::LDS, s>>>(a, n_qtiles);
     return hipGetLastError();
+}
+template <typename T, int DP>
+hipError_t encode_with(const EncodeArgs& a, int block_rows, hipStream_t s) {
+    constexpr bool WIDE = DP * (int)sizeof(T) > 256;
+    constexpr int K2 = WIDE ? 1 : 2, D2 = WIDE ? 2 : 1, K4 = WIDE ? 1 : 4, D4 = WIDE ? 4 : 1;
+    if (block_rows == 128) return encode_as<T, DP, 4, 1, 1>(a, s);
+    return block_rows == 64 ? encode_as<T, DP, 2, K2, D2>(a, s) : encode_as<T, DP, 1, K4, D4>(a, s);
 }
 
 }  // namespace
@@ -632,11 +643,30 @@ hipError_t launch_tile_query(const QueryArgs& a, int dtype, int block_rows, bool
     return d <= 64 ? query_with<__bf16, 64>(a, block_rows, whole, s) : d <= 128 ? query_with<__bf16, 128>(a, block_rows, whole, s) : query_with<__bf16, 256>(a, block_rows, whole, s);
 }
 
+// Rows per workgroup of an encode.  The last tile of the longest context is one serial stream: the fewer tiles there are
+// to fill the chip with, the fewer rows each takes and the more wavefronts share them (ragged contexts, 128 / 64 / 32 rows, us: fp32
+// 32/8 heads of 128, 4 x 64 tokens 23.9 / 17.4 / 13.8, 16 x 256 tokens 150 / 140 / 156; 16/8 of 256, 4 x 256 tokens 52.3 / 33.0 / 23.8,
+// 16 x 256 207 / 160 / 189; bf16 16/8 of 256, 16 x 256 tokens 51.0 / 45.6 / 59.4; 32/8 of 64, 1024 tokens 27.9 / 19.0 / 20.2,
+// 64 x 64 21.9 / 30.7 / 49.5; 8/8 of 96, 4 x 1024 53.3 / 34.9 / 48.2, 64 x 64 14.2 / 20.1 / 53.5).
+static int encode_block_rows(const EncodeArgs& a, int dtype) {
+    const long group = a.n_q_heads / a.n_kv_heads;
+    const long tiles = ((long)a.total_rows * group + 63) / 64 * a.n_kv_heads;   // of 64 rows
+    const bool f32 = dtype == APE_F32;
+    int rows;
+    if (a.head_dim > 128) rows = tiles < 384 ? 32 : 64;
+    else if (f32) rows = tiles < 192 ? 32 : 64;
+    else if (a.head_dim <= 64) rows = tiles < 1024 ? 64 : 128;
+    else rows = tiles < 256 || (tiles <= 512 && a.max_chunk_len > 512) ? 64 : 128;
+    // (the grid is contexts x KV heads x tiles of the longest context: uneven lengths may not fit it with small tiles)
+    while (rows < 128 && ((long)a.n_chunks * a.n_kv_heads + 7) / 8 * 8 * (((long)a.max_chunk_len * group + rows - 1) / rows) >= 1L << 24) rows *= 2;
+    return rows;
+}
+
 hipError_t launch_tile_encode(const EncodeArgs& a, int dtype, hipStream_t s) {
     if (a.total_rows == 0) return hipSuccess;
-    const int d = a.head_dim;
-    if (dtype == APE_F32) return d <= 64 ? encode_with<float, 64>(a, s) : d <= 128 ? encode_with<float, 128>(a, s) : encode_with<float, 256>(a, s);
-    return d <= 64 ? encode_with<__bf16, 64>(a, s) : d <= 128 ? encode_with<__bf16, 128>(a, s) : encode_with<__bf16, 256>(a, s);
+    const int d = a.head_dim, br = encode_block_rows(a, dtype);
+    if (dtype == APE_F32) return d <= 64 ? encode_with<float, 64>(a, br, s) : d <= 128 ? encode_with<float, 128>(a, br, s) : encode_with<float, 256>(a, br, s);
+    return d <= 64 ? encode_with<__bf16, 64>(a, br, s) : d <= 128 ? encode_with<__bf16, 128>(a, br, s) : encode_with<__bf16, 256>(a, br, s);
 }
 
 }  // namespace ape
