@@ -211,6 +211,15 @@ QueryPlan decode_plan(const ShapeInfo& si, int batch, long max_ctx) {
     return plan_query(base, max_ctx, 256, (want < 8 ? 8 : want) * base);
 }
 
+// Workgroups of a query whose row tiles do not divide the target: rather a few CUs with nothing than a few with two long
+// streams, which the whole call then waits for (ceil / floor of target / base, us: 150 query tokens, 5 row tiles x 8 KV heads, over
+// 10240 tokens 51.0 / 43.2, over 65536 277 / 180; 3 requests of 64 rows over 10240 tokens 58.9 / 50.4).  Only a narrow tile's single
+// split is cut in two all the same (192 row tiles over 10240 tokens 149 / 171: two of its workgroups share a CU).
+int whole_rounds(int base, int target, int bm) {
+    if (base >= target || (bm == 128 && 2 * base > target)) return target;
+    return target / base * base;
+}
+
 // Split plan of the query prefill.  Matrix-core path: about one workgroup per CU (two of the narrow
 // tile for contexts of middle length), the query tile chosen by flash_prefill_block_rows.
 QueryPlan prefill_plan(const ShapeInfo& si, int batch, int q_len, long max_ctx) {
@@ -224,8 +233,8 @@ QueryPlan prefill_plan(const ShapeInfo& si, int batch, int q_len, long max_ctx) 
     // the same target cuts the context into splits of a few hundred tokens, whose fixed cost per
     // workgroup outweighs the second workgroup (64 rows over 16K: 0.049 ms with 32 splits of 512 tokens,
     // 0.036 ms with 16 of 1024).
-    if (si.mfma && target > 256 && max_ctx / ceil_div(target, base) < 2048) target = 256;
-    QueryPlan p = plan_query(base, max_ctx, 256, target);
+    if (si.mfma && target > 256 && max_ctx / ceil_div(whole_rounds(base, target, bm), base) < 2048) target = 256;
+    QueryPlan p = plan_query(base, max_ctx, 256, si.mfma ? whole_rounds(base, target, bm) : target);
     p.block_rows = bm;
     return p;
 }
@@ -589,7 +598,15 @@ int ape_attention_tree(const ape_shape* shape, const ape_request* req,
     if (rc) return rc;
     if (!nodes_dev) return fail(APE_ERR_INVALID_ARG, "the device copy of the tree nodes is NULL");
 
-    const TreePlan plan = plan_tree(si, req->total_ctx_len, n_nodes, q_len);
+    TreePlan plan = plan_tree(si, req->total_ctx_len, n_nodes, q_len);
+    // Nodes of a few thousand tokens are streams as short as a short context's: the narrow tile, whose two workgroups per CU
+    // cover for each other's start and output, wins (256 / 128 rows, us: a node per context, 256 query tokens, 64 x 2048 tokens
+    // 632 / 604; 20 x 4096 tokens 346 / 333, 16 x 8192 482 / 498; 100 query tokens, 256 x 512 tokens 526 / 484).
+    if (plan.block_rows == 256) {
+        long groups = 0;
+        for (int n = 0; n < n_nodes; ++n) groups += nodes_host[n].leaf_children != 0;
+        if (req->total_ctx_len <= 4096 * groups) plan.block_rows = 128;
+    }
     if (plan.max_splits > kMaxTreeSplits)
         return fail(APE_ERR_UNSUPPORTED, "%d splits would be needed, at most %d are supported", plan.max_splits, kMaxTreeSplits);
     const long units = (long)q_len * si.hq;

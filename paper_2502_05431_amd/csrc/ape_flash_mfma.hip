@@ -963,11 +963,11 @@ __global__ __launch_bounds__(NT) void flash_prefill_kernel(const QueryArgs a, in
     const int ctx_teams = a.n_ctx_splits * a.n_kv_heads;
     const int ctx_blocks = (ctx_teams + 7) / 8 * 8 * n_qtiles;
     int bx = blockIdx.x, rq = blockIdx.y;                // position in the request's part of the grid; request
-    if (NTL && a.n_req > 1) {
-        // A batch on one tile per KV head (a decode step): the context workgroups of ALL requests
-        // first, then every request's short prefix+self ones, in the order workgroups are dispatched
-        // (x fastest, then y).  Dealt request by request, the short ones sit between the long ones
-        // and leave their slots early, which spoils the balance when the long ones are few.
+    if (a.n_req > 1) {
+        // A batch: the context workgroups of ALL requests first, then every request's short prefix+self ones, in the
+        // order workgroups are dispatched (x fastest, then y).  Dealt request by request, the short ones sit between the
+        // long ones and leave their slots early, which spoils the balance when the long ones are few (three requests of 64
+        // query rows over 10240 tokens in 240 long workgroups 63.0 us, 50.4 in this order).
         const int short_blocks = (int)gridDim.x - ctx_blocks;
         const int lin = (int)blockIdx.y * (int)gridDim.x + (int)blockIdx.x;
         const int ctx_all = a.n_req * ctx_blocks;
