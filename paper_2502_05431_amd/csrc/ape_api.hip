@@ -154,10 +154,14 @@ QueryPlan plan_query(int base_workgroups, long max_ctx, int min_len, int target_
 QueryPlan tile_plan(const ShapeInfo& si, int batch, int q_len, long max_ctx, long max_splits = kMaxSplits) {
     const int rows = q_len * si.group, bm = tile_query_block_rows(si, batch, rows, max_ctx);
     const bool f32 = si.dtype == APE_F32;
-    const int target = (f32 ? si.d > 128 : si.d > 64 && si.d <= 128 && bm < 128) ? 256 : 512;
+    const bool half = !f32 && si.d > 64 && si.d <= 128 && bm < 128;     // one of the two workgroups that a CU has room for
+    const long base = (long)batch * si.hkv * ceil_div(rows, bm), full = half || (f32 && si.d > 128) ? 256 : 512;
+    // A plan that fills every slot leaves one per row tile to the prefix + own workgroups, which would otherwise start when
+    // the first others have ended (64 rows, splits filling all / all but those slots, us: 16/8 bf16 heads of 256 over 10240 tokens
+    // 52.5 / 47.3, 32/8 of 64 28.8 / 25.3, 16/8 fp32 heads of 256 over 4096 78 / 68).
+    const long n = full / base, target = n >= 3 && !half ? (n - 1) * base : n == 2 ? 2 * base : full;
     // (16 rows over 2048 tokens, 2/2 fp32 heads of 256: splits of 64 / 128 / 256 tokens 18.9 / 25.8 / 40.2 us; 40 bf16 rows, 6/2
     // heads of 40: 14.5 / 14.7 / 17.2)
-    const long base = (long)batch * si.hkv * ceil_div(rows, bm);
     QueryPlan p = plan_query((int)base, max_ctx, f32 && si.d > 128 ? 64 : 128, (int)(target < base * max_splits ? target : base * max_splits));
     p.block_rows = bm;
     return p;
