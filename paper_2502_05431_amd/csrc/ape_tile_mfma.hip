@@ -261,6 +261,13 @@ __device__ __forceinline__ f32x16 sum_scores(const char* sums) {
     return s;
 }
 
+// (the compiler is told that there are no NaNs: it is not shown where these bits come from)
+__device__ __forceinline__ bool finite(float x) {
+    uint32_t bits = __float_as_uint(x);
+    asm("" : "+v"(bits));
+    return (bits & 0x7fffffffu) < 0x7f800000u;
+}
+
 // The softmax of the run's scores and O^T += V^T P^T.  `nvis`: how many of the tokens this lane's row sees.
 template <typename T, int DP, int WD>
 __device__ __forceinline__ void update(f32x16 s, const char* vpart, int wd, const ScoreScale<T>& sc, int nvis, Rows<T, DP / WD>& st) {
@@ -286,15 +293,25 @@ __device__ __forceinline__ void update(f32x16 s, const char* vpart, int wd, cons
 #pragma unroll
             for (int r = 0; r < 16; ++r) st.o[db][r] *= alpha;
     }
-    float p[16], sum0 = 0.f, sum1 = 0.f;
+    float p[16], sum0, sum1;
 #pragma unroll
     for (int r = 0; r < 16; ++r) p[r] = sc.prob(s[r], st.m);
-    if (sizeof(T) == 4 && masked) {                          // (-inf times the scale's remainder, which may be 0 or negative)
+    // fp32: a score of -inf times the scale's remainder, which may be 0 or negative, is not -inf.  The hidden tokens of a run
+    // have such scores, and so have tokens that the caller masks with the lowest keys, in any run: their sum tells.
+    auto drop = [&]() {
 #pragma unroll
-        for (int r = 0; r < 16; ++r) p[r] = s[r] > -INFINITY ? p[r] : 0.f;
+        for (int r = 0; r < 16; ++r) p[r] = __float_as_uint(s[r]) == 0xff800000u ? 0.f : p[r];
+    };
+    auto add_up = [&]() {
+        sum0 = sum1 = 0.f;
+#pragma unroll
+        for (int r = 0; r < 16; r += 2) { sum0 += p[r]; sum1 += p[r + 1]; }
+    };
+    if (sizeof(T) == 4 && masked) drop();
+    add_up();
+    if constexpr (sizeof(T) == 4) {
+        if (__builtin_expect(__builtin_amdgcn_ballot_w64(!finite(sum0 + sum1)) != 0, 0)) { drop(); add_up(); }
     }
-#pragma unroll
-    for (int r = 0; r < 16; r += 2) { sum0 += p[r]; sum1 += p[r + 1]; }
     st.l += sum0 + sum1;
     if constexpr (sizeof(T) == 2) {
         // k-slot e of slab sl is token 16 sl + (e < 4 ? 4 hi + e : 8 + 4 hi + e - 4): the registers 8 sl .. 8 sl + 7

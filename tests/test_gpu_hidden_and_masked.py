@@ -1,0 +1,68 @@
+"""Keys and values at the ends of the number range, on the matrix-core kernels: keys that mask their token (a score of minus
+infinity), scores of a magnitude at which fp32 resolves no single unit any more, infinite keys in heads whose width is padded, and
+tokens that a row does not see and that hold no number."""
+import numpy as np
+import pytest
+import torch
+
+from paper_2502_05431_amd import workloads as W
+
+import helpers as H
+
+pytestmark = pytest.mark.gpu
+DEV = "cuda:0"
+
+
+def _request(dtype, hq, hkv, d, lens, prefix=9, own=20, rows=21, T=0.8):
+    spec = W.WorkloadSpec(name="ends", cfg=6, dtype=dtype, n_q_heads=hq, n_kv_heads=hkv, head_dim=d, prefix_len=prefix,
+                          chunk_lens=tuple(lens), q_len=rows, decode_steps=own, temperature=T, scale=0.9)
+    return spec, W.make_request(spec, DEV)
+
+
+def _lse_close(got, ref, dtype):
+    assert np.all(np.abs(got - ref) <= H.lse_tol(dtype) + 1e-6 * np.abs(ref))
+
+
+def _check_query(spec, r, rows=(1, 21), nodes=None):
+    """Prefill, decode and tree against the oracle."""
+    h, n, d = H.HostArrays(r), spec.self_len_max, spec.head_dim
+    for q_len in rows:
+        out, lse = H.run_decode(spec, [r], [n]) if q_len == 1 else H.run_prefill(spec, r, q_len, n)
+        ref, ref_lse, _ = H.oracle_prefill(h, q_len, n, r.temperature, r.scale)
+        H.check_close(H.f64(out).reshape(-1, d), ref, spec.dtype, "%s rows %d" % (spec, q_len))
+        _lse_close(H.f64(lse).reshape(-1) if q_len == 1 else H.f64(lse).T.reshape(-1), ref_lse, spec.dtype)
+        if nodes:
+            out, lse = H.run_tree(spec, r, nodes, q_len, n)
+            ref, ref_lse = H.oracle_tree(h, q_len, n, r.temperature, nodes)
+            H.check_close(H.f64(out).reshape(-1, d), ref, spec.dtype, "%s tree rows %d" % (spec, q_len))
+            _lse_close(H.f64(lse).T.reshape(-1), ref_lse, spec.dtype)
+
+
+def _check_encode(spec, r, keep=None):
+    """`keep`: the context rows that are compared (the others may hold anything)."""
+    h, d, hq = H.HostArrays(r), spec.head_dim, spec.n_q_heads
+    keep = np.ones(sum(r.chunk_lens), bool) if keep is None else keep
+    o, lse, _, _ = H.run_encode(spec, r, with_prefix_rows=False)
+    ref, ref_lse = H.oracle_encode(h)
+    H.check_close(H.f64(o)[keep].reshape(-1, d), ref.reshape(-1, hq, d)[keep].reshape(-1, d), spec.dtype, "%s encode" % (spec,))
+    _lse_close(H.f64(lse).T[keep], ref_lse.reshape(-1, hq)[keep], spec.dtype)
+
+
+CH = 5                                                    # the channel that masks
+
+
+@pytest.mark.parametrize("T", [1.0, 0.8])
+@pytest.mark.parametrize("dtype, hq, hkv, d", [("f32", 3, 1, 40), ("f32", 4, 2, 64), ("f32", 4, 2, 128), ("f32", 2, 2, 256), ("bf16", 4, 2, 64), ("bf16", 2, 2, 256)])
+@pytest.mark.parametrize("lens", [(40, 24), (300, 257, 65)])
+def test_masked_tokens_on_the_tile_kernels(dtype, hq, hkv, d, lens, T):
+    """A token whose key has the type's lowest value in one channel has the weight zero, wherever its run of 32 tokens ends."""
+    spec, r = _request(dtype, hq, hkv, d, lens, T=T)
+    for t in (r.q_self, r.q_ctx):
+        t[..., CH] = 3.0
+    low = torch.finfo(spec.torch_dtype).min
+    r.k_ctx[:33, :, CH] = low                             # a whole run and a token of the next
+    r.k_ctx[36::7, :, CH] = low
+    r.k_self[3:6, :, CH] = low
+    r.k_prefix[1:8, :, CH] = low
+    _check_query(spec, r, nodes=W.tree_per_context(len(lens), 0.85))
+    _check_encode(spec, r)
