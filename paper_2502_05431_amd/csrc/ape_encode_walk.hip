@@ -197,7 +197,9 @@ __global__ __launch_bounds__(256, 2) void encode_walk_kernel(const EncodeArgs a,
                     x0 = fmaxf(fmaxf(x0, sc[10]), sc[11]); x1 = fmaxf(fmaxf(x1, sc[12]), sc[13]);
                     return max_halves(fmaxf(fmaxf(x0, x1), fmaxf(sc[14], sc[15]))) * sc2;
                 };
-                if (j == 0) m = row_max();                    // (every row sees index 0)
+                // every row sees index 0, but a first block may be masked by its keys: scores of -inf, or below kUnset, are no reference
+                // (a later block exceeds the unset one and moves it)
+                if (j == 0) m = fmaxf(row_max(), kUnset);
                 float p[16], s0 = 0.f, s1 = 0.f;
                 auto probs = [&]() {
                     s0 = s1 = 0.f;

@@ -66,3 +66,21 @@ def test_masked_tokens_on_the_tile_kernels(dtype, hq, hkv, d, lens, T):
     r.k_prefix[1:8, :, CH] = low
     _check_query(spec, r, nodes=W.tree_per_context(len(lens), 0.85))
     _check_encode(spec, r)
+
+
+@pytest.mark.parametrize("low", [torch.finfo(torch.bfloat16).min, -2.0 ** 110])
+@pytest.mark.parametrize("hq, hkv", [(2, 2), (8, 2), (16, 2)])
+@pytest.mark.parametrize("prefix", [0, 40, 64])
+def test_masked_tokens_at_the_start_of_the_encode_walk(hq, hkv, prefix, low):
+    """The first block of every tile is masked (padding at the front, a masked prefix): the rows take their weights from what follows."""
+    spec, r = _request("bf16", hq, hkv, 128, (12, 200, 300, 65), prefix=prefix)
+    r.q_ctx[..., CH] = 3.0
+    keep = np.ones(sum(r.chunk_lens), bool)
+    r.k_prefix[:, :, CH] = low
+    if prefix == 0:                                       # (rows that see masked tokens only have no result)
+        c0 = 0
+        for n in r.chunk_lens:
+            r.k_ctx[c0:c0 + min(n, 32), :, CH] = low
+            keep[c0:c0 + min(n, 32)] = False
+            c0 += n
+    _check_encode(spec, r, keep)
