@@ -79,7 +79,6 @@ int check_request(const ape_request* r, int q_len, int idx) {
 // kernels index with fits an int.  Calls beyond that are refused here, before any size is narrowed.
 constexpr long kMaxUnits = 1L << 24;            // a query call writes FEWER (row, head) outputs than this: one 256-thread workgroup each in the merge
 constexpr long kMaxTreeBlocks = 1L << 24;       // workgroups of the attention launch of a tree call (256 threads each)
-constexpr long kMaxEncodeBlocks = 1L << 24;     // workgroups of the matrix-core encode (256 threads each)
 constexpr long kMaxEncodeUnits = 1L << 26;      // (row, head) outputs of the generic encode: one wavefront each
 }  // namespace
 

@@ -29,6 +29,7 @@ struct KvView {
 constexpr int kMaxReqPerLaunch = 32;     // requests whose descriptors travel in one kernel-argument block
 constexpr int kMaxSplits = 64;           // upper bound of context splits per (request, head)
 constexpr int kWsAlign = 256;
+constexpr long kMaxEncodeBlocks = 1L << 24;     // workgroups of a matrix-core encode launch (256 threads each)
 
 // Kernel-argument block of the query-time kernels (prefill and decode).
 struct QueryArgs {

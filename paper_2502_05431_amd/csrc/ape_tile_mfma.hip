@@ -30,6 +30,8 @@
 
 #include <math.h>
 
+#include <algorithm>
+
 namespace ape {
 namespace {
 
@@ -636,7 +638,9 @@ template <typename T, int DP>
 hipError_t encode_with(const EncodeArgs& a, int block_rows, hipStream_t s) {
     constexpr bool WIDE = DP * (int)sizeof(T) > 256;
     constexpr int K2 = WIDE ? 1 : 2, D2 = WIDE ? 2 : 1, K4 = WIDE ? 1 : 4, D4 = WIDE ? 4 : 1;
-    if (block_rows == 128) return encode_as<T, DP, 4, 1, 1>(a, s);
+    if constexpr (DP <= 128) {
+        if (block_rows == 128) return encode_as<T, DP, 4, 1, 1>(a, s);
+    }
     return block_rows == 64 ? encode_as<T, DP, 2, K2, D2>(a, s) : encode_as<T, DP, 1, K4, D4>(a, s);
 }
 
@@ -674,16 +678,26 @@ static int encode_block_rows(const EncodeArgs& a, int dtype) {
     else if (f32) rows = tiles < 192 ? 32 : 64;
     else if (a.head_dim <= 64) rows = tiles < 1024 ? 64 : 128;
     else rows = tiles < 256 || (tiles <= 512 && a.max_chunk_len > 512) ? 64 : 128;
-    // (the grid is contexts x KV heads x tiles of the longest context: uneven lengths may not fit it with small tiles)
-    while (rows < 128 && ((long)a.n_chunks * a.n_kv_heads + 7) / 8 * 8 * (((long)a.max_chunk_len * group + rows - 1) / rows) >= 1L << 24) rows *= 2;
     return rows;
 }
 
 hipError_t launch_tile_encode(const EncodeArgs& a, int dtype, hipStream_t s) {
     if (a.total_rows == 0) return hipSuccess;
     const int d = a.head_dim, br = encode_block_rows(a, dtype);
-    if (dtype == APE_F32) return d <= 64 ? encode_with<float, 64>(a, br, s) : d <= 128 ? encode_with<float, 128>(a, br, s) : encode_with<float, 256>(a, br, s);
-    return d <= 64 ? encode_with<__bf16, 64>(a, br, s) : d <= 128 ? encode_with<__bf16, 128>(a, br, s) : encode_with<__bf16, 256>(a, br, s);
+    // The grid is contexts x KV heads x tiles of the longest context: where uneven lengths make it too large, it goes out a run of
+    // contexts at a time (one context always fits: the outputs of a call are fewer than 2^26).
+    const long per_context = (long)a.n_kv_heads * (((long)a.max_chunk_len * (a.n_q_heads / a.n_kv_heads) + br - 1) / br);
+    const int most = (int)std::min<long>(kMaxEncodeBlocks / 2 / per_context, a.n_chunks);
+    EncodeArgs e = a;
+    for (int c = 0; c < a.n_chunks; c += most) {
+        e.n_chunks = std::min(most, a.n_chunks - c);
+        if (a.cu) e.cu = a.cu + c;
+        hipError_t he;
+        if (dtype == APE_F32) he = d <= 64 ? encode_with<float, 64>(e, br, s) : d <= 128 ? encode_with<float, 128>(e, br, s) : encode_with<float, 256>(e, br, s);
+        else he = d <= 64 ? encode_with<__bf16, 64>(e, br, s) : d <= 128 ? encode_with<__bf16, 128>(e, br, s) : encode_with<__bf16, 256>(e, br, s);
+        if (he != hipSuccess) return he;
+    }
+    return hipSuccess;
 }
 
 }  // namespace ape

@@ -107,3 +107,14 @@ def test_batch_of_mixed_requests():
         ref, ref_lse, _ = H.oracle_prefill(H.HostArrays(r), 1, lens[b], r.temperature, r.scale)
         H.check_close(H.f64(out[b]), ref, "bf16", "request %d" % b)
         assert np.abs(H.f64(lse[b]) - ref_lse).max() <= H.lse_tol("bf16")
+
+
+@pytest.mark.parametrize("dtype", ["f32", "bf16"])
+def test_uneven_contexts_of_wide_heads(dtype):
+    """One long context among thousands of one token: the grid has room for tiles of 128 rows only.  Against the vector-ALU kernels."""
+    spec = _spec(dtype, 16, 2, 136, (3,) + (1,) * 16400 + (4090,), 1, prefix=5)
+    r = W.make_request(spec, DEV)
+    o, lse, _, _ = H.run_encode(spec, r, with_prefix_rows=False)
+    ref, ref_lse, _, _ = H.run_encode(spec, r, generic=True, with_prefix_rows=False)
+    H.check_close(H.f64(o), H.f64(ref), dtype, "uneven contexts")
+    assert (lse - ref_lse).abs().max().item() <= H.lse_tol(dtype)
