@@ -35,6 +35,8 @@
 namespace ape {
 namespace {
 
+constexpr float kNone = -3.402823466e+38f;   // softmax reference of a row that has not seen a score yet: the lowest, so that every score can be one
+constexpr float kFar = 0x1p27f;              // beyond this (either sign) the rounding of a reference alone is more than exp can take
 constexpr float kSlack = 10.f;               // a reference moves only when exceeded by this (fp32 sums lose nothing by that)
 
 // 1/(T sqrt d), rounded once.  Scores of |x| = 40 (T = 0.1) turn one rounding of the scale into 2.4e-6 of a probability, so
@@ -78,6 +80,9 @@ struct Tile {
     static constexpr int LPT = PART / (16 * NT);            // loads per thread and part
     // wavefronts per SIMD, which set the register budget: what LDS has room for
     static constexpr int WAVES = DP / WD == 256 || 160 * 1024 / LDS * NW < 8 ? 1 : 2;
+    // ... and how many there can be at most (or two), which the scheduler is to know where registers are left: for more it saves
+    // them, with one fragment in flight at a time (bf16 encode, 8/8 heads of 96, 4 x 1024 tokens: 35.9 us, 33.8 told)
+    static constexpr int MOST = DP / WD == 256 ? 8 : 160 * 1024 / LDS * NW < 8 ? 2 : 160 * 1024 / LDS * NW / 4;
     static_assert(PART % (16 * NT) == 0 && LDS <= 160 * 1024, "stage size");
     static_assert(WK == 1 || WD == 1, "one way to share the rows");
 };
@@ -186,7 +191,7 @@ struct Rows {
 
 template <typename T, int DW>
 __device__ __forceinline__ void clear_rows(Rows<T, DW>& st) {
-    st.m = kUnset; st.l = 0.f;
+    st.m = kNone; st.l = 0.f;
 #pragma unroll
     for (int db = 0; db < Rows<T, DW>::NB; ++db)
 #pragma unroll
@@ -286,7 +291,7 @@ __device__ __forceinline__ void update(f32x16 s, const char* vpart, int wd, cons
     for (int r = 1; r < 16; ++r) mx = fmaxf(mx, s[r]);
     mx = max_halves(mx) * sc.hi;                             // -inf: the row sees nothing here
     if (__builtin_amdgcn_ballot_w64(mx > st.m + kSlack) != 0) {
-        const float m_new = mx > st.m + kSlack ? mx : st.m;  // (kUnset + kSlack == kUnset)
+        const float m_new = mx > st.m + kSlack ? mx : st.m;  // (kNone + kSlack == kNone)
         const float alpha = ScoreScale<T>::exp_of(st.m - m_new);
         st.m = m_new;
         st.l *= alpha;
@@ -452,7 +457,7 @@ __device__ __forceinline__ void scale_contexts(Rows<T, DW>& st, float scale) {
     const float lt = sum_halves(st.l);
     const bool any = seen(lt);                               // (else the state is empty and stays so)
     const float inv = any ? 1.f / lt : 0.f, w = scale * ScoreScale<T>::lse(st.m, lt);
-    st.m = any ? (sizeof(T) == 4 ? w : w * LOG2E) : kUnset;
+    st.m = any ? (sizeof(T) == 4 ? w : w * LOG2E) : kNone;
     st.l = any && (threadIdx.x & 32) == 0 ? 1.f : 0.f;
 #pragma unroll
     for (int db = 0; db < Rows<T, DW>::NB; ++db)
@@ -477,13 +482,166 @@ __device__ __forceinline__ void store_row(const Rows<T, DP / WD>& st, float inv,
         }
 }
 
+// Rows that the products above cannot give are computed again, one at a time on the vector ALUs, where every score is rounded
+// once and a token counts only if the row sees it.  Which rows, the results tell: a reference so large that its own
+// rounding is more than exp takes (scores of 1e8 and more, of either sign), or a sum that is no number.  Nothing of
+// this runs for ordinary inputs.  A wavefront does its own rows (a bit of the mask each).
+template <typename T, int DW>
+__device__ __forceinline__ uint32_t rows_to_redo(const Rows<T, DW>& st, float sum, bool valid) {
+    const bool odd = (fabsf(st.m) > kFar && st.m > kNone) || !finite(sum);
+    const uint64_t lanes = __builtin_amdgcn_ballot_w64(valid && odd);
+    return (uint32_t)lanes | (uint32_t)(lanes >> 32);        // (a row lives in lanes l and l ^ 32)
+}
+
+__device__ __forceinline__ float lane_value(float x, int lane) { return __uint_as_float(__builtin_amdgcn_readlane(__float_as_uint(x), lane)); }
+
+// One row by a whole wavefront: scores with a token per lane, values with dims lane + 64 r per lane.  Natural-log units.
+template <typename T>
+struct ExactRow {
+    const T* q;
+    float acc[4], m, l;
+    int d;
+    __device__ __forceinline__ ExactRow(const T* row, int d_) : q(row), m(-INFINITY), l(0.f), d(d_) {
+#pragma unroll
+        for (int r = 0; r < 4; ++r) acc[r] = 0.f;
+    }
+    // n tokens, `stride` elements apart
+    __device__ __forceinline__ void attend(const T* k, const T* v, long stride, int n, float scale) {
+#pragma clang fp contract(off)
+        const int lane = threadIdx.x & 63;
+        for (int j0 = 0; j0 < n; j0 += 64) {
+            const int cnt = min(64, n - j0);
+            const T* kr = k + (long)(j0 + min(lane, cnt - 1)) * stride;
+            float dot = 0.f;
+#pragma unroll 1
+            for (int c = 0; c < d; ++c) dot = fmaf((float)q[c], (float)kr[c], dot);
+            const float s = lane < cnt ? dot * scale : -INFINITY;
+            float m_new = s;
+#pragma unroll
+            for (int o = 32; o > 0; o >>= 1) m_new = fmaxf(m_new, __shfl_xor(m_new, o));
+            m_new = fmaxf(m, m_new);
+            if (m_new == -INFINITY) continue;                // masked tokens only
+            const float p = lane < cnt ? expf(s - m_new) : 0.f, alpha = m == -INFINITY ? 0.f : expf(m - m_new);
+            float sum = p;
+#pragma unroll
+            for (int o = 32; o > 0; o >>= 1) sum += __shfl_xor(sum, o);
+            m = m_new; l = l * alpha + sum;
+            if (!finite(l)) return;                          // a seen score is no number: no more of it
+#pragma unroll
+            for (int r = 0; r < 4; ++r) acc[r] *= alpha;
+#pragma unroll 1
+            for (int jj = 0; jj < cnt; ++jj) {
+                const float pj = lane_value(p, jj);
+                const T* vr = v + (long)(j0 + jj) * stride;
+#pragma unroll
+                for (int r = 0; r < 4; ++r)
+                    if (lane + 64 * r < d) acc[r] = fmaf(pj, (float)vr[lane + 64 * r], acc[r]);
+            }
+        }
+    }
+    __device__ __forceinline__ float lse() const { return seen(l) ? m + logf(l) : -INFINITY; }
+    // as scale_contexts
+    __device__ __forceinline__ void scale_contexts(float scale) {
+        if (!seen(l)) return;
+        const float inv = 1.f / l;
+        m = scale * lse(); l = 1.f;
+#pragma unroll
+        for (int r = 0; r < 4; ++r) acc[r] *= inv;
+    }
+    // dims [c0, c1) of the normalised values
+    template <typename OUT>
+    __device__ __forceinline__ void store(OUT* o, int c0, int c1, float empty) const {
+        const float inv = seen(l) ? 1.f / l : empty;
+#pragma unroll
+        for (int r = 0; r < 4; ++r) {
+            const int c = (threadIdx.x & 63) + 64 * r;
+            if (c >= c0 && c < min(c1, d)) o[c] = (OUT)(acc[r] * inv);
+        }
+    }
+};
+
+// `redo`: rows R0 + bit; dims [c0, c1) are this wavefront's.  The kernel's arguments are read again where they lie (through a pointer
+// that the compiler cannot see through), so that nothing is kept for this over the streams.
+template <typename Args>
+__device__ __forceinline__ __attribute__((address_space(4))) const Args* kernarg_again() {
+    auto a = kernarg<Args>();
+    asm volatile("" : "+s"(a));
+    return a;
+}
+
+// Query rows past context tokens [t0, t1) and, if `own`, then past the prefix and the own tokens; `whole`: this is the output.
+template <typename T>
+__device__ __forceinline__ void redo_query_rows(__attribute__((address_space(4))) const QueryArgs* a, int rq, int hk, int split, int t0, int t1,
+                                                bool own, bool whole, int R0, uint32_t redo, int c0, int c1) {
+    const int d = a->head_dim, hq = a->n_q_heads, hkv = a->n_kv_heads, G = hq / hkv, q_len = a->q_len;
+    const int n_chunks = a->req[rq].n_chunks;
+    const int32_t* cu = a->req[rq].cu;
+    const long stride = (long)hkv * d, head = (long)hk * d;
+    const bool first_dims = c0 == 0 && (threadIdx.x & 63) == 0;
+    for (; redo; redo &= redo - 1) {
+        const int R = R0 + __builtin_ctz(redo), tok = R / G, h = hk * G + R % G;
+        const long row = ((long)rq * q_len + tok) * hq + h, unit = (long)a->req_base * q_len * hq + row;
+        ExactRow<T> x((const T*)a->q + row * d, d);
+        const int last = own ? n_chunks + 2 : n_chunks;
+        int t = t0;
+        for (int c = t0 < t1 ? find_chunk(cu, n_chunks, t0) : n_chunks; c < last; ++c) {   // the contexts, the prefix, the own tokens
+            const T *k, *v;
+            int n;
+            float scale = rsqrtf((float)d);
+            if (c < n_chunks) {
+                const int from = cu[c], to = min(cu[c + 1], t1);
+                n = to - t;
+                k = (const T*)a->req[rq].k_chunks[c] + (long)(t - from) * stride; v = (const T*)a->req[rq].v_chunks[c] + (long)(t - from) * stride;
+                scale /= a->req[rq].temperature;
+                t = max(t, to);
+            } else if (c == n_chunks) {
+                x.scale_contexts(a->req[rq].scale);
+                n = a->req[rq].prefix_len;
+                k = (const T*)a->req[rq].k_prefix; v = (const T*)a->req[rq].v_prefix;
+            } else {
+                n = a->req[rq].self_len - q_len + tok + 1;
+                k = (const T*)a->req[rq].k_self; v = (const T*)a->req[rq].v_self;
+            }
+            x.attend(k + head, v + head, stride, n, scale);
+        }
+        if (whole) {
+            x.store((T*)a->out + unit * d, c0, c1, INFINITY);
+            if (a->lse_out && first_dims) a->lse_out[a->lse_head_major ? ((long)(a->req_base + rq) * hq + h) * q_len + tok : unit] = x.lse();
+        } else {
+            const long slot = (long)split * a->units_total + unit;
+            x.store(a->part_o + slot * d, c0, c1, 0.f);
+            if (first_dims) a->part_lse[slot] = x.lse();
+        }
+    }
+}
+
+// Rows of one (context, KV head) of an encode; first: the context's first packed row.
+template <typename T>
+__device__ __forceinline__ void redo_encode_rows(__attribute__((address_space(4))) const EncodeArgs* a, int first, int hk, int R0, uint32_t redo, int c0, int c1) {
+    const int d = a->head_dim, hq = a->n_q_heads, hkv = a->n_kv_heads, G = hq / hkv;
+    const long stride = (long)hkv * d, head = (long)hk * d;
+    for (; redo; redo &= redo - 1) {
+        const int R = R0 + __builtin_ctz(redo), row = first + R / G;
+        const int h = hk * G + R % G;
+        ExactRow<T> x((const T*)a->q + ((long)row * hq + h) * d, d);
+#pragma unroll 1
+        for (int part = 0; part < 2; ++part) {                // the prefix, the context
+            const long at = (part ? first * stride : 0) + head;
+            x.attend((const T*)(part ? a->k : a->k_prefix) + at, (const T*)(part ? a->v : a->v_prefix) + at, stride, part ? R / G + 1 : a->prefix_len, rsqrtf((float)d));
+        }
+        x.store((T*)a->out + ((long)row * hq + h) * d, c0, c1, INFINITY);
+        if (a->lse && c0 == 0 && (threadIdx.x & 63) == 0) a->lse[(long)h * a->total_rows + row] = x.lse();
+    }
+}
+
 // ------------------------------------------------------------------------------------------
 // Query prefill and decode: team = (split, KV head), members = tiles of the query rows; the context
 // teams come first, the prefix + own ones follow.  grid: x as in the flash prefill, y = request.
 // WHOLE: over short contexts one workgroup takes its rows past the contexts and then past the prefix and the own tokens and
 // writes their output: team = KV head, no partial results, no merge.
 template <typename T, int DP, int WR, int WK, int WD, bool WHOLE>
-__global__ __launch_bounds__(64 * WR * WK * WD, (Tile<T, DP, WR, WK, WD>::WAVES)) void tile_query_kernel(const QueryArgs a, int n_qtiles) {
+__global__ __launch_bounds__(64 * WR * WK * WD) __attribute__((amdgpu_waves_per_eu(Tile<T, DP, WR, WK, WD>::WAVES, Tile<T, DP, WR, WK, WD>::MOST)))
+void tile_query_kernel(const QueryArgs a, int n_qtiles) {
     using X = Tile<T, DP, WR, WK, WD>;
     extern __shared__ __attribute__((aligned(16))) char lds[];
     const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), l32 = lane & 31, hi = lane >> 5;
@@ -537,13 +695,18 @@ __global__ __launch_bounds__(64 * WR * WK * WD, (Tile<T, DP, WR, WK, WD>::WAVES)
         sequence();
         if (!combine<T, DP / WD, WR, WK>(lds, st)) return;
         const float lt = sum_halves(st.l);                   // (a row always sees itself)
-        if (!valid) return;
-        store_row<T, DP, WD>(st, 1.f / lt, d, wd, (T*)a.out + unit * d);
-        if (a.lse_out && hi == 0 && wd == 0)
-            a.lse_out[a.lse_head_major ? ((long)(a.req_base + rq) * hq + h) * q_len + tok : unit] = ScoreScale<T>::lse(st.m, lt);
+        const uint32_t redo = rows_to_redo(st, lt, valid);
+        if (valid && !(redo >> l32 & 1)) {
+            store_row<T, DP, WD>(st, 1.f / lt, d, wd, (T*)a.out + unit * d);
+            if (a.lse_out && hi == 0 && wd == 0)
+                a.lse_out[a.lse_head_major ? ((long)(a.req_base + rq) * hq + h) * q_len + tok : unit] = ScoreScale<T>::lse(st.m, lt);
+        }
+        if (__builtin_expect(redo != 0, 0))
+            redo_query_rows<T>(kernarg_again<QueryArgs>(), rq, hk, 0, 0, t1, true, true, R0, redo, DP / WD * wd, DP / WD * (wd + 1));
     } else {
-        if (split < a.n_ctx_splits) {
-            long t0, t1;
+        long t0 = 0, t1 = 0;
+        const bool own = split >= a.n_ctx_splits;
+        if (!own) {
             ctx_split_range(a, kv, split, t0, t1);
             if (t0 >= t1) return;                            // an empty split: the merge never looks at it (a request without contexts has no table)
             t1 = min(t1, (long)scalar_load_i32(kv.cu + kv.n_chunks));   // (stay inside the table whatever total_ctx says)
@@ -556,17 +719,22 @@ __global__ __launch_bounds__(64 * WR * WK * WD, (Tile<T, DP, WR, WK, WD>::WAVES)
         }
         if (!combine<T, DP / WD, WR, WK>(lds, st)) return;
         const float lt = sum_halves(st.l);
-        if (!valid) return;
-        const long slot = (long)split * a.units_total + unit;
-        store_row<T, DP, WD>(st, seen(lt) ? 1.f / lt : 0.f, d, wd, a.part_o + slot * d);
-        if (hi == 0 && wd == 0) a.part_lse[slot] = seen(lt) ? ScoreScale<T>::lse(st.m, lt) : -INFINITY;
+        const uint32_t redo = rows_to_redo(st, lt, valid);
+        if (valid && !(redo >> l32 & 1)) {
+            const long slot = (long)split * a.units_total + unit;
+            store_row<T, DP, WD>(st, seen(lt) ? 1.f / lt : 0.f, d, wd, a.part_o + slot * d);
+            if (hi == 0 && wd == 0) a.part_lse[slot] = seen(lt) ? ScoreScale<T>::lse(st.m, lt) : -INFINITY;
+        }
+        if (__builtin_expect(redo != 0, 0))
+            redo_query_rows<T>(kernarg_again<QueryArgs>(), rq, hk, split, (int)t0, (int)t1, own, false, R0, redo, DP / WD * wd, DP / WD * (wd + 1));
     }
 }
 
 // ------------------------------------------------------------------------------------------
 // Block-diagonal causal encode: team = (context, KV head), members = its row tiles, the heaviest first.
 template <typename T, int DP, int WR, int WK, int WD>
-__global__ __launch_bounds__(64 * WR * WK * WD, (Tile<T, DP, WR, WK, WD>::WAVES)) void tile_encode_kernel(const EncodeArgs a, int n_qtiles) {
+__global__ __launch_bounds__(64 * WR * WK * WD) __attribute__((amdgpu_waves_per_eu(Tile<T, DP, WR, WK, WD>::WAVES, Tile<T, DP, WR, WK, WD>::MOST)))
+void tile_encode_kernel(const EncodeArgs a, int n_qtiles) {
     using X = Tile<T, DP, WR, WK, WD>;
     extern __shared__ __attribute__((aligned(16))) char lds[];
     const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), l32 = lane & 31, hi = lane >> 5, wd = wave % WD;
@@ -594,9 +762,12 @@ __global__ __launch_bounds__(64 * WR * WK * WD, (Tile<T, DP, WR, WK, WD>::WAVES)
     if (!combine<T, DP / WD, WR, WK>(lds, st)) return;
 
     const float lt = sum_halves(st.l);
-    if (!valid) return;
-    store_row<T, DP, WD>(st, 1.f / lt, d, wd, (T*)a.out + ((long)(c0 + tok) * hq + h) * d);   // (a row always sees itself)
-    if (a.lse && hi == 0 && wd == 0) a.lse[(long)h * a.total_rows + c0 + tok] = ScoreScale<T>::lse(st.m, lt);
+    const uint32_t redo = rows_to_redo(st, lt, valid);
+    if (valid && !(redo >> l32 & 1)) {
+        store_row<T, DP, WD>(st, 1.f / lt, d, wd, (T*)a.out + ((long)(c0 + tok) * hq + h) * d);   // (a row always sees itself)
+        if (a.lse && hi == 0 && wd == 0) a.lse[(long)h * a.total_rows + c0 + tok] = ScoreScale<T>::lse(st.m, lt);
+    }
+    if (__builtin_expect(redo != 0, 0)) redo_encode_rows<T>(kernarg_again<EncodeArgs>(), c0, hk, (int)R0, redo, DP / WD * wd, DP / WD * (wd + 1));
 }
 
 template <typename T, int DP, int WR, int WK, int WD, bool WHOLE>

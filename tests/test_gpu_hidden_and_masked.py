@@ -84,3 +84,20 @@ def test_masked_tokens_at_the_start_of_the_encode_walk(hq, hkv, prefix, low):
             keep[c0:c0 + min(n, 32)] = False
             c0 += n
     _check_encode(spec, r, keep)
+
+
+@pytest.mark.parametrize("q_ch, k_ch", [(1.0, -2.0 ** 105), (2.0 ** 20, 2.0 ** 20), (2.0 ** 20, -2.0 ** 20)])
+@pytest.mark.parametrize("dtype, hq, hkv, d", [("f32", 3, 1, 40), ("f32", 4, 2, 64), ("f32", 2, 2, 256), ("bf16", 4, 2, 64), ("bf16", 2, 2, 256)])
+@pytest.mark.parametrize("lens", [(40, 24), (300, 257, 65)])
+def test_scores_of_any_magnitude_on_the_tile_kernels(dtype, hq, hkv, d, lens, q_ch, k_ch):
+    """All of a row's scores far from zero and from each other, as products that fp32 holds exactly up to the scale (q has one
+    channel): one token takes all of the weight.  (Not under a tree, whose merge works with differences of log-weights.)"""
+    spec, r = _request(dtype, hq, hkv, d, lens)
+    for t in (r.q_self, r.q_ctx):
+        t[:] = 0.0
+        t[..., CH] = q_ch
+    for i, t in enumerate((r.k_prefix, r.k_ctx, r.k_self)):
+        at = torch.arange(t.shape[0], device=DEV)         # 8 bits of mantissa: no two alike
+        t[..., CH] = (k_ch * (1.0 + at * 37 % 128 / 128.0) * 2.0 ** (at // 128 - (1, 0, 2)[i])).to(t.dtype)[:, None]
+    _check_query(spec, r)
+    _check_encode(spec, r)
