@@ -30,9 +30,11 @@
  *   - Tensors are row-major [tokens, heads, head_dim]; K/V have n_kv_heads heads,
  *     Q/O have n_q_heads heads; query head h reads KV head h / (n_q_heads/n_kv_heads).
  *     Q and K arrive already position-rotated.
- *   - The matrix-core kernels take K and V in runs of 32 tokens and give a token that a row does not see the
- *     weight zero: a value that is not finite in such a token (later in the row's own context or
- *     among the own tokens) can make the row NaN when both are in one run.  Only APE_DTYPE_FLAG_GENERIC never reads it.
+ *   - Tokens that a row does not see (later in its own context or among the own tokens) have no part in it, whatever
+ *     they hold, with one exception: the flash kernels (see ape_shape) take K and V in runs of 32 tokens and give a hidden token
+ *     the weight zero, so that a value that is not finite in it can make the row NaN when both are in one run.
+ *     Elsewhere rows that values which are not finite, or scores beyond 1e8, have reached are computed one by one, as the
+ *     portable kernels do, and a call with many of them takes several times as long.
  *   - dtype APE_F32: fp32 in/out, fp32 arithmetic.  APE_BF16: bf16 in/out, bf16
  *     matrix-core products with fp32 accumulation and fp32 softmax.
  *   - Kernels are enqueued on `stream` (a hipStream_t passed as void*, NULL = the

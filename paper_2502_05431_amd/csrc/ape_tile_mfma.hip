@@ -17,7 +17,7 @@
 // of 32 WK tokens filled by direct global->LDS loads.  A stage is a run of consecutive indices of the
 // pooled contexts (or of prefix + own tokens), whatever context they belong to: a stage that crosses the
 // end of a context picks its source row by row, so short and ragged contexts waste no MFMA on padding.
-// head_dim is padded to 64, 128 or 256 inside LDS; the padding of K repeats finite data that meets zeros in Q.
+// head_dim is padded to 64, 128 or 256 inside LDS; the padding of K repeats the row's first dims, which meet zeros in Q.
 //
 // What bounds it: the MFMAs once the streams are long (fp32: 64 cycles for 4096 multiply-adds; 1.5 times the
 // attention's own count for bf16), the fixed chain of a launch, first loads and merge for a short query.  Against the
@@ -31,6 +31,7 @@
 #include <math.h>
 
 #include <algorithm>
+#include <type_traits>
 
 namespace ape {
 namespace {
@@ -448,7 +449,11 @@ __device__ __forceinline__ bool combine(char* lds, Rows<T, DP>& st) {
 
 // Whether a row saw any token: a sum of probabilities that is not zero, be it not a number (the compiler is told that there are
 // none, so the bits are asked).
-__device__ __forceinline__ bool seen(float sum) { return __float_as_uint(sum) != 0; }
+__device__ __forceinline__ bool seen(float sum) {
+    uint32_t bits = __float_as_uint(sum);
+    asm("" : "+v"(bits));
+    return bits != 0;
+}
 
 // The contexts' result becomes the state from which the prefix and the own tokens go on (Appendix C.3/C.4): weight S times
 // its LogSumExp, values normalised.
@@ -484,11 +489,28 @@ __device__ __forceinline__ void store_row(const Rows<T, DP / WD>& st, float inv,
 
 // Rows that the products above cannot give are computed again, one at a time on the vector ALUs, where every score is rounded
 // once and a token counts only if the row sees it.  Which rows, the results tell: a reference so large that its own
-// rounding is more than exp takes (scores of 1e8 and more, of either sign), or a sum that is no number.  Nothing of
-// this runs for ordinary inputs.  A wavefront does its own rows (a bit of the mask each).
+// rounding is more than exp takes (scores of 1e8 and more, of either sign); a sum that is no number (infinite keys, which meet
+// the zeros of Q where the padding of a row repeats them); and, past streams in which some tokens are `hidden` from a row, values
+// that are none (the products give a hidden token the weight zero, and zero times infinity is no number).
+// Nothing of this runs for ordinary inputs.  A wavefront does its own rows (a bit of the mask each): the fp32 encode of eight
+// contexts of about 512 tokens takes 7.4 ms, and not 0.22, with a value that is none in the eleventh token of each (the vector-ALU
+// kernels 2.6 whatever the values); 64 bf16 rows over 20 x 512 tokens, 16/8 heads of 256, 1.7 ms with one such token (14).
 template <typename T, int DW>
-__device__ __forceinline__ uint32_t rows_to_redo(const Rows<T, DW>& st, float sum, bool valid) {
-    const bool odd = (fabsf(st.m) > kFar && st.m > kNone) || !finite(sum);
+__device__ __forceinline__ uint32_t rows_to_redo(const Rows<T, DW>& st, float sum, bool valid, bool hidden) {
+    bool odd = (fabsf(st.m) > kFar && st.m > kNone) || !finite(sum);
+    if (hidden) {
+        int32_t pos = 0;                                     // as whole numbers, an infinity or a NaN is above every number of its sign
+        uint32_t neg = 0;
+#pragma unroll
+        for (int db = 0; db < Rows<T, DW>::NB; ++db)
+#pragma unroll
+            for (int r = 0; r < 16; ++r) {
+                const uint32_t bits = __float_as_uint(st.o[db][r]);
+                pos = max(pos, (int32_t)bits);
+                neg = max(neg, bits);
+            }
+        odd |= pos >= 0x7f800000 || neg >= 0xff800000u;
+    }
     const uint64_t lanes = __builtin_amdgcn_ballot_w64(valid && odd);
     return (uint32_t)lanes | (uint32_t)(lanes >> 32);        // (a row lives in lanes l and l ^ 32)
 }
@@ -498,12 +520,16 @@ __device__ __forceinline__ float lane_value(float x, int lane) { return __uint_a
 // One row by a whole wavefront: scores with a token per lane, values with dims lane + 64 r per lane.  Natural-log units.
 template <typename T>
 struct ExactRow {
-    const T* q;
-    float acc[4], m, l;
+    static constexpr int E = 16 / (int)sizeof(T);
+    float q[4], acc[4], m, l;
     int d;
-    __device__ __forceinline__ ExactRow(const T* row, int d_) : q(row), m(-INFINITY), l(0.f), d(d_) {
+    __device__ __forceinline__ ExactRow(const T* row, int d_) : m(-INFINITY), l(0.f), d(d_) {
 #pragma unroll
-        for (int r = 0; r < 4; ++r) acc[r] = 0.f;
+        for (int r = 0; r < 4; ++r) {
+            const int c = (threadIdx.x & 63) + 64 * r;
+            q[r] = c < d ? (float)row[c] : 0.f;
+            acc[r] = 0.f;
+        }
     }
     // n tokens, `stride` elements apart
     __device__ __forceinline__ void attend(const T* k, const T* v, long stride, int n, float scale) {
@@ -513,15 +539,23 @@ struct ExactRow {
             const int cnt = min(64, n - j0);
             const T* kr = k + (long)(j0 + min(lane, cnt - 1)) * stride;
             float dot = 0.f;
-#pragma unroll 1
-            for (int c = 0; c < d; ++c) dot = fmaf((float)q[c], (float)kr[c], dot);
+#pragma unroll
+            for (int r = 0; r < 4; ++r)
+#pragma unroll 4
+                for (int c = 64 * r; c < min(d, 64 * r + 64); c += E) {
+                    T x[E];
+                    *(u32x4*)x = *(const u32x4*)(kr + c);
+#pragma unroll
+                    for (int e = 0; e < E; ++e) dot = fmaf(lane_value(q[r], c - 64 * r + e), (float)x[e], dot);
+                }
             const float s = lane < cnt ? dot * scale : -INFINITY;
             float m_new = s;
 #pragma unroll
             for (int o = 32; o > 0; o >>= 1) m_new = fmaxf(m_new, __shfl_xor(m_new, o));
             m_new = fmaxf(m, m_new);
             if (m_new == -INFINITY) continue;                // masked tokens only
-            const float p = lane < cnt ? expf(s - m_new) : 0.f, alpha = m == -INFINITY ? 0.f : expf(m - m_new);
+            // (the instructions, which keep a score that is no number: the library's functions may be compiled not to)
+            const float p = lane < cnt ? __builtin_amdgcn_exp2f((s - m_new) * LOG2E) : 0.f, alpha = m == -INFINITY ? 0.f : __builtin_amdgcn_exp2f((m - m_new) * LOG2E);
             float sum = p;
 #pragma unroll
             for (int o = 32; o > 0; o >>= 1) sum += __shfl_xor(sum, o);
@@ -529,17 +563,24 @@ struct ExactRow {
             if (!finite(l)) return;                          // a seen score is no number: no more of it
 #pragma unroll
             for (int r = 0; r < 4; ++r) acc[r] *= alpha;
-#pragma unroll 1
-            for (int jj = 0; jj < cnt; ++jj) {
-                const float pj = lane_value(p, jj);
-                const T* vr = v + (long)(j0 + jj) * stride;
+            int jj = 0;
+            auto add_values = [&](auto few) {
+                float x[few()][4];
 #pragma unroll
-                for (int r = 0; r < 4; ++r)
-                    if (lane + 64 * r < d) acc[r] = fmaf(pj, (float)vr[lane + 64 * r], acc[r]);
-            }
+                for (int u = 0; u < few(); ++u)
+#pragma unroll
+                    for (int r = 0; r < 4; ++r) x[u][r] = lane + 64 * r < d ? (float)v[(long)(j0 + jj + u) * stride + lane + 64 * r] : 0.f;
+#pragma unroll
+                for (int u = 0; u < few(); ++u)
+#pragma unroll
+                    for (int r = 0; r < 4; ++r) acc[r] = fmaf(lane_value(p, jj + u), x[u][r], acc[r]);
+                jj += few();
+            };
+            while (jj + 8 <= cnt) add_values(std::integral_constant<int, 8>());
+            while (jj < cnt) add_values(std::integral_constant<int, 1>());
         }
     }
-    __device__ __forceinline__ float lse() const { return seen(l) ? m + logf(l) : -INFINITY; }
+    __device__ __forceinline__ float lse() const { return seen(l) ? m + __builtin_amdgcn_logf(l) * LN2 : -INFINITY; }
     // as scale_contexts
     __device__ __forceinline__ void scale_contexts(float scale) {
         if (!seen(l)) return;
@@ -695,7 +736,7 @@ void tile_query_kernel(const QueryArgs a, int n_qtiles) {
         sequence();
         if (!combine<T, DP / WD, WR, WK>(lds, st)) return;
         const float lt = sum_halves(st.l);                   // (a row always sees itself)
-        const uint32_t redo = rows_to_redo(st, lt, valid);
+        const uint32_t redo = rows_to_redo(st, lt, valid, true);
         if (valid && !(redo >> l32 & 1)) {
             store_row<T, DP, WD>(st, 1.f / lt, d, wd, (T*)a.out + unit * d);
             if (a.lse_out && hi == 0 && wd == 0)
@@ -719,7 +760,7 @@ void tile_query_kernel(const QueryArgs a, int n_qtiles) {
         }
         if (!combine<T, DP / WD, WR, WK>(lds, st)) return;
         const float lt = sum_halves(st.l);
-        const uint32_t redo = rows_to_redo(st, lt, valid);
+        const uint32_t redo = rows_to_redo(st, lt, valid, own);
         if (valid && !(redo >> l32 & 1)) {
             const long slot = (long)split * a.units_total + unit;
             store_row<T, DP, WD>(st, seen(lt) ? 1.f / lt : 0.f, d, wd, a.part_o + slot * d);
@@ -762,7 +803,7 @@ void tile_encode_kernel(const EncodeArgs a, int n_qtiles) {
     if (!combine<T, DP / WD, WR, WK>(lds, st)) return;
 
     const float lt = sum_halves(st.l);
-    const uint32_t redo = rows_to_redo(st, lt, valid);
+    const uint32_t redo = rows_to_redo(st, lt, valid, true);
     if (valid && !(redo >> l32 & 1)) {
         store_row<T, DP, WD>(st, 1.f / lt, d, wd, (T*)a.out + ((long)(c0 + tok) * hq + h) * d);   // (a row always sees itself)
         if (a.lse && hi == 0 && wd == 0) a.lse[(long)h * a.total_rows + c0 + tok] = ScoreScale<T>::lse(st.m, lt);

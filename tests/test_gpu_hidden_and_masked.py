@@ -101,3 +101,62 @@ def test_scores_of_any_magnitude_on_the_tile_kernels(dtype, hq, hkv, d, lens, q_
         t[..., CH] = (k_ch * (1.0 + at * 37 % 128 / 128.0) * 2.0 ** (at // 128 - (1, 0, 2)[i])).to(t.dtype)[:, None]
     _check_query(spec, r)
     _check_encode(spec, r)
+
+
+@pytest.mark.parametrize("dtype, hq, hkv, d", [("f32", 3, 1, 40), ("f32", 6, 2, 72), ("f32", 2, 2, 136), ("bf16", 6, 2, 40), ("bf16", 8, 8, 96), ("bf16", 2, 2, 200)])
+@pytest.mark.parametrize("lens", [(40, 24), (300, 257, 65)])
+def test_infinite_keys_in_padded_heads(dtype, hq, hkv, d, lens):
+    """A key of minus infinity in one of its first channels, which is what the padding repeated."""
+    spec, r = _request(dtype, hq, hkv, d, lens)
+    for t in (r.q_self, r.q_ctx):
+        t[..., 0] = 3.0
+    r.k_ctx[2::5, :, 0] = -float("inf")
+    r.k_self[2, :, 0] = -float("inf")
+    _check_query(spec, r, nodes=W.tree_per_context(len(lens), 0.85))
+    _check_encode(spec, r)
+
+
+@pytest.mark.parametrize("what", [float("nan"), float("inf"), -float("inf")])
+@pytest.mark.parametrize("dtype, hq, hkv, d", [("f32", 3, 1, 40), ("f32", 4, 2, 64), ("f32", 8, 4, 128), ("f32", 2, 2, 256), ("bf16", 4, 2, 64), ("bf16", 6, 2, 96), ("bf16", 4, 2, 256)])
+@pytest.mark.parametrize("lens", [(70, 40), (300, 90), (130,) * 40])
+def test_hidden_tokens_leave_no_trace_on_the_tile_kernels(dtype, hq, hkv, d, lens, what):
+    """Tokens that hold no numbers, from some place on in a context and in the own tokens: the rows in front of them are those of a
+    request without them."""
+    spec, r = _request(dtype, hq, hkv, d, lens, prefix=5, own=7, rows=80)
+    n = spec.self_len_max
+    h = H.HostArrays(r)
+    at = [17, 39, 5, 33][:len(lens)] + [50] * (len(lens) - 4)     # first row of each context that sees one
+    keep, c0 = np.ones(sum(lens), bool), 0
+    for a, ln in zip(at, lens):
+        keep[c0 + a:c0 + ln] = False
+        c0 += ln
+    refs = H.oracle_encode(h) if len(lens) < 10 else H.run_encode(spec, r, with_prefix_rows=False)[:2]
+    first = 7 + 45                                            # ... and first own token
+    dirty = [t.clone() for t in (r.k_ctx, r.v_ctx, r.k_self, r.v_self)]
+    for t in dirty[:2]:
+        t[torch.from_numpy(~keep).to(DEV)] = what
+    for t in dirty[2:]:
+        t[first:] = what
+    clean = r.k_self, r.v_self, r.k_ctx, r.v_ctx
+    r.k_ctx, r.v_ctx = dirty[:2]
+    o, lse, _, _ = H.run_encode(spec, r, with_prefix_rows=False)
+    r.k_ctx, r.v_ctx = clean[2:]
+    if len(lens) < 10:
+        ref, ref_lse = refs[0].reshape(-1, hq, d), refs[1].reshape(-1, hq)
+    else:
+        ref, ref_lse = H.f64(refs[0]), H.f64(refs[1]).T
+    H.check_close(H.f64(o)[keep].reshape(-1, d), ref[keep].reshape(-1, d), dtype, "encode")
+    _lse_close(H.f64(lse).T[keep], ref_lse[keep], dtype)
+    assert not torch.isfinite(o.float())[torch.from_numpy(~keep).to(DEV)].any()
+    nodes = W.tree_per_context(len(lens), 0.85)
+    for rows in (80, 60):
+        ref, ref_lse, _ = H.oracle_prefill(h, rows, n, r.temperature, r.scale)
+        tref, tref_lse = H.oracle_tree(h, rows, n, r.temperature, nodes)
+        r.k_self, r.v_self = dirty[2:]
+        got = H.run_prefill(spec, r, rows, n), H.run_tree(spec, r, nodes, rows, n)
+        r.k_self, r.v_self = clean[:2]
+        seen = first - (n - rows)                             # rows in front of the first such token
+        for (o, lse), want, want_lse in zip(got, (ref, tref), (ref_lse, tref_lse)):
+            H.check_close(H.f64(o)[:seen].reshape(-1, d), want.reshape(rows, hq, d)[:seen].reshape(-1, d), dtype, "%d rows" % rows)
+            _lse_close(H.f64(lse).T[:seen], want_lse.reshape(rows, hq)[:seen], dtype)
+            assert not torch.isfinite(o.float())[seen:].any()
