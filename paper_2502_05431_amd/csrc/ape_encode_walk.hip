@@ -275,21 +275,29 @@ __global__ __launch_bounds__(256, 2) void encode_walk_kernel(const EncodeArgs a,
 
 }  // namespace
 
-// The walk wins while a tile's stream is short; over long streams the software-pipelined body of the flash kernel does
-// (uniform contexts, 131072 tokens, 32/8 heads, per tile / walk, us: 256 tokens 742 / 639, 512 964 / 880, 700 1133 / 1079,
-// 1024 1392 / 1382, 2048 2272 / 2495).  With few tiles the longest stream is the whole time and the line lies lower (two
-// contexts of 700 tokens 20.9 / 23.0, four of 512 22.6 / 22.3).
+// The walk wins while the streams of the tiles are short, the prefix in front of a context counted; past long streams the
+// software-pipelined body of the flash kernel does.  Where the line lies (32/8 heads, flash / walk, us):
+//   many tiles, where the mean stream counts: contexts alone (131072 tokens) 256 tokens 742 / 639, 512 964 / 880, 1024 1392 / 1382,
+//   2048 2272 / 2495; behind a prefix of 256 / 384 / 1024 tokens 64 x 512 343 / 323, 396 / 389, 512 x 256 ragged at 1024 2714 / 2835,
+//   64 x 256 ragged 166 / 159, 192 / 194, 1024 x 64 at 1024 1131 / 1208;
+//   fewer than 2048, where the longest is the whole time: 4 x 512 tokens behind 0 / 128 / 256 / 512 21.9 / 21.0, 25.5 / 24.8, 28.7 / 28.7,
+//   35.1 / 35.9; 8 x 256 behind 384 / 1024 27.3 / 26.8, 44.0 / 45.4;
+//   a tile or less per CU, with no second workgroup to fill the gaps: 2 x 256 behind 0 / 128 10.4 / 10.0, 13.1 / 12.7; 1 x 300 behind 0 / 32
+//   10.9 / 11.1, 11.6 / 12.0; 2 x 400 12.8 / 13.7; 2 x 100 behind 512 16.1 / 18.3.
 // Workgroups per context: about four tiles each when that still leaves thousands of workgroups, fewer tiles otherwise
-// (tiles per workgroup 4 / 2 / 1, us: 512 x 256 tokens 641 / 653 / 687, 64 x 512 - / 222 / 238, 16 x 128 ragged - / 14.7 / 12.3).
+// (tiles per workgroup 4 / 2 / 1, us: 512 x 256 tokens 641 / 653 / 687, 64 x 512 - / 222 / 238, 16 x 128 ragged - / 14.7 / 12.3), but two
+// also where the chip then holds all workgroups at once and would not with one (8 x 512 39.2 / 27.4 / 33.6, 6 x 512 36.1 / 25.9 / 28.0; and not
+// 10 x 512 44.5 / 40.7 / 40.0).
 int encode_walk_parts(const EncodeArgs& a) {
     const int group = a.n_q_heads / a.n_kv_heads;
     const long tiles = ((long)a.total_rows * group + 127) / 128 * a.n_kv_heads, teams = (long)a.n_chunks * a.n_kv_heads;
+    const long prefix = a.prefix_len, context = a.max_chunk_len;
     if (a.n_kv_heads > 4096) return 0;                       // (32-bit offsets inside a block of 32 tokens)
-    if (a.max_chunk_len > 1024 || (a.max_chunk_len > 512 && tiles < 2048)) return 0;
+    if (tiles >= 2048 ? prefix + context / 2 > 512 : tiles > 256 ? context > 512 || prefix + context > 640 : context > 256 || prefix + context > 384) return 0;
     const int longest = (a.max_chunk_len * group + 127) / 128;
     for (int per : {4, 2}) {
         const int parts = (longest + per - 1) / per;
-        if (teams * parts >= (per == 4 ? 4096 : 900)) return parts;
+        if (teams * parts >= (per == 4 ? 4096 : 900) || (per == 2 && tiles > 640 && teams * parts <= 512)) return parts;
     }
     return longest;
 }

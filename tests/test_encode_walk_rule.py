@@ -1,0 +1,40 @@
+"""Host logic: which encodes take the walk of short contexts.  The rule is about the stream of a query tile, and that is the
+prefix and the context."""
+import ctypes
+
+import pytest
+
+from paper_2502_05431_amd import binding as B
+
+
+class EncodeArgs(ctypes.Structure):                       # csrc/ape_internal.h
+    _fields_ = [(n, ctypes.c_void_p) for n in ("q", "k", "v", "k_prefix", "v_prefix", "cu", "out", "lse")] + \
+               [(n, ctypes.c_int32) for n in ("n_chunks", "prefix_len", "total_rows", "max_chunk_len", "n_q_heads", "n_kv_heads", "head_dim", "uniform_chunks")]
+
+
+def _parts(n, context, prefix, hq=32, hkv=8, total=None):
+    rule = B.load()._ZN3ape17encode_walk_partsERKNS_10EncodeArgsE
+    return rule(ctypes.byref(EncodeArgs(n_chunks=n, prefix_len=prefix, total_rows=total or n * context, max_chunk_len=context, n_q_heads=hq, n_kv_heads=hkv, head_dim=128)))
+
+
+@pytest.mark.parametrize("n, context, last", [(512, 256, 384), (64, 512, 256), (1024, 64, 480), (128, 1024, 0), (4, 512, 128), (8, 256, 384), (2, 256, 128), (2, 100, 284)])
+def test_a_long_prefix_is_part_of_the_stream(n, context, last):
+    """`last`: the longest prefix behind which the walk is still the faster one."""
+    for prefix in (0, last // 2, last):
+        assert _parts(n, context, prefix) > 0
+    for prefix in (last + 32, 1024, 4096, 100000, 2 ** 31 - 1 - n * context):
+        assert _parts(n, context, prefix) == 0
+
+
+@pytest.mark.parametrize("n, context", [(512, 2048), (1, 300), (1, 500), (2, 400), (3, 700)])
+def test_long_streams_of_few_tiles_stay_with_the_flash_kernel(n, context):
+    assert _parts(n, context, 0) == 0
+
+
+@pytest.mark.parametrize("n, context, parts", [(512, 256, 2), (64, 512, 8), (16, 128, 4), (6, 512, 8), (8, 512, 8), (9, 512, 16), (4, 512, 16)])
+def test_workgroups_of_a_context(n, context, parts):
+    assert _parts(n, context, 0) == parts
+
+
+def test_tiles_that_uneven_contexts_do_not_have_are_not_counted():
+    assert _parts(16, 224, 0, total=2048) == 7

@@ -33,3 +33,8 @@ def test_work_splits(n, chunk_len):
 
 def test_many_ragged_contexts():
     _check(32, 8, [1 + (37 * i) % 300 for i in range(300)], 32)
+
+
+@pytest.mark.parametrize("hq, hkv, lens, prefix", [(32, 8, (512,) * 8, 5), (8, 2, (96,) * 40, 300), (8, 2, (96,) * 40, 600), (8, 2, (200, 300), 1100)])
+def test_prefixes_on_both_sides_of_the_switch(hq, hkv, lens, prefix):
+    _check(hq, hkv, lens, prefix)
