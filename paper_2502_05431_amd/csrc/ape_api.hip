@@ -175,22 +175,32 @@ QueryPlan tile_decode_plan(const ShapeInfo& si, int batch, long max_ctx) {
     return tile_plan(si, batch, 1, max_ctx, fit > other ? fit : other);
 }
 
+}  // namespace
+
 // Rows per workgroup of a call that runs without splits, one workgroup taking its rows past the contexts and then past the
-// prefix and the own tokens and writing the output (0: it is split and merged).  Worth it while the longer stream costs less
-// than the second launch, the partial results and their merge, about 4 us: up to 512 context tokens per request with bf16 heads
-// of up to 64, 256 up to 128 (the flash kernels' shapes too), 128 beyond; 128 with fp32 heads of up to 64, 64 up to 128
-// (16 rows, split / whole, us: bf16 heads of 64 over 512 tokens 13.7 / 12.0, 1024 14.1 / 16.9; of 128 over 256 15.4 / 14.5, 512
+// prefix and the own tokens (`own`: of all requests) and writing the output (0: it is split and merged).  Worth it while the longer
+// stream costs less than the second launch, the partial results and their merge, about 4 us: up to 512 context tokens per request
+// with bf16 heads of up to 64, 256 up to 128 (the flash kernels' shapes too), 128 beyond; 128 with fp32 heads of up to 64, 64 up to
+// 128 (16 rows, split / whole, us: bf16 heads of 64 over 512 tokens 13.7 / 12.0, 1024 14.1 / 16.9; of 128 over 256 15.4 / 14.5, 512
 // 15.6 / 18.1; of 256 over 128 16.7 / 13.0, 256 17.2 / 19.4; fp32 of 64 over 128 14.0 / 12.9, 256 14.7 / 16.5); and
 // where the requests and heads alone fill the chip and the tile kernels would not split anyway (32 decode steps over 4096 tokens, 16/8
 // bf16 heads of 256: 280 / 228; 32/8 fp32 heads of 128: 366 / 319).
-int whole_block_rows(const ShapeInfo& si, const QueryPlan& plan, int batch, int q_len, long max_ctx) {
+// The flash kernels' shapes give up their own kernels for it, which are the faster ones (32/8 heads over 200 tokens, flash / whole, us):
+// where tiles of 32 rows are more than a CU each (8 requests of 64 rows 26.4 / 29.3, 500 rows 29.5 / 34.7; 3 of 64 16.9 / 12.2, 256 rows
+// 20.7 / 15.6), counted within an XCD, since a KV head's tiles run on one (16/2 heads, 8 requests of 64 rows 24.6 / 56.3, 2 of them
+// 16.8 / 15.4), and where prefixes and own tokens are more than the caches hold (16 decode steps behind 1500 own tokens 32.6 / 31.7, 4000
+// 66.0 / 69.1; 64 behind 700 69.6 / 64.6, 1500 88.9 / 101; 8 behind 4000 61.8 / 59.2, 12000 161 / 192).
+int whole_block_rows(const ShapeInfo& si, int ctx_splits, int batch, int q_len, long max_ctx, long own) {
     if (si.force_generic) return 0;
-    const long workgroups = (long)batch * si.hkv * ceil_div((long)q_len * si.group, 32);
+    const long row_tiles = ceil_div((long)q_len * si.group, 32), workgroups = (long)batch * si.hkv * row_tiles;
     if (workgroups > 512) return 0;
+    if (si.mfma && ((row_tiles > 1 && batch * row_tiles * ceil_div(si.hkv, 8) > 32) || (batch > 1 && own * si.hkv > 400000))) return 0;
     const int width = si.d <= 64 ? 0 : si.d <= 128 ? 1 : 2;
     const long most = si.dtype == APE_F32 ? (width == 0 ? 128 : width == 1 ? 64 : 0) : 512 >> width;
-    return max_ctx <= most || (si.tile && plan.n_ctx_splits <= 1 && workgroups >= 128) ? 32 : 0;
+    return max_ctx <= most || (si.tile && ctx_splits <= 1 && workgroups >= 128) ? 32 : 0;
 }
+
+namespace {
 
 // Split plan of a decode step.  Matrix-core path: one workgroup per (request, KV head, split), two
 // of them resident per CU.  What decides the rate is how evenly the long (context) workgroups fill the
@@ -433,10 +443,11 @@ int ape_encode_chunks(const ape_shape* shape,
 static int run_query(const ShapeInfo& si, const ape_request* reqs, int batch, int q_len, bool decode,
                      const void* q, void* out, float* lse_out, void* workspace, size_t workspace_bytes, hipStream_t st,
                      bool static_limit = false) {
-    long max_ctx = 0;
+    long max_ctx = 0, own = 0;
     for (int b = 0; b < batch; ++b) {
         int rc = check_request(&reqs[b], q_len, b);
         if (rc) return rc;
+        own += (long)reqs[b].prefix_len + reqs[b].self_len;
         const long m = reqs[b].n_chunks > 0 ? reqs[b].total_ctx_len : 0;
         if (m > max_ctx) max_ctx = m;
     }
@@ -460,7 +471,7 @@ static int run_query(const ShapeInfo& si, const ape_request* reqs, int batch, in
     float* part_o = (float*)workspace;
     float* part_lse = (float*)((char*)workspace + align_up((size_t)units * plan.n_splits_total * si.d * sizeof(float), kWsAlign));
 
-    const int whole = whole_block_rows(si, plan, batch, q_len, max_ctx);
+    const int whole = whole_block_rows(si, plan.n_ctx_splits, batch, q_len, max_ctx, own);
     for (int b0 = 0; b0 < batch; b0 += kMaxReqPerLaunch) {
         const int nb = batch - b0 < kMaxReqPerLaunch ? batch - b0 : kMaxReqPerLaunch;
         QueryArgs a{};

@@ -285,6 +285,9 @@ struct QueryPlan {
     int block_rows;        // query tile this plan was made for (0: the vector-ALU kernels, which have none)
 };
 
+// rows per workgroup of a query that runs without splits, or 0 (see the definition)
+int whole_block_rows(const ShapeInfo& si, int ctx_splits, int batch, int q_len, long max_ctx, long own);
+
 // ---- launchers (each returns hipGetLastError() of its launch) ------------------------------
 hipError_t launch_generic_query(const QueryArgs& a, int dtype, hipStream_t s);
 hipError_t launch_generic_encode(const EncodeArgs& a, int dtype, hipStream_t s);
