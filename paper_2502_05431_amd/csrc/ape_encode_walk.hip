@@ -279,7 +279,10 @@ __global__ __launch_bounds__(256, 2) void encode_walk_kernel(const EncodeArgs a,
 // software-pipelined body of the flash kernel does.  Where the line lies (32/8 heads, flash / walk, us):
 //   many tiles, where the mean stream counts: contexts alone (131072 tokens) 256 tokens 742 / 639, 512 964 / 880, 1024 1392 / 1382,
 //   2048 2272 / 2495; behind a prefix of 256 / 384 / 1024 tokens 64 x 512 343 / 323, 396 / 389, 512 x 256 ragged at 1024 2714 / 2835,
-//   64 x 256 ragged 166 / 159, 192 / 194, 1024 x 64 at 1024 1131 / 1208;
+//   64 x 256 ragged 166 / 159, 192 / 194, 1024 x 64 at 1024 1131 / 1208.  With one query head per KV head tiles are as long as 128 tokens
+//   and the last one of a context is half empty, which costs the walk less, since a wavefront without rows leaves its time to the
+//   others: 8/8 heads, 64 x 512 behind 512 / 1024 128 / 117, 186 / 186, 256 x 200 209 / 196, 312 / 326, 256 x 256 ragged 341 / 270, 484 / 429 and
+//   behind 2048 789 / 737, but 100 x 700 ragged behind 256 273 / 280;
 //   fewer than 2048, where the longest is the whole time: 4 x 512 tokens behind 0 / 128 / 256 / 512 21.9 / 21.0, 25.5 / 24.8, 28.7 / 28.7,
 //   35.1 / 35.9; 8 x 256 behind 384 / 1024 27.3 / 26.8, 44.0 / 45.4;
 //   a tile or less per CU, with no second workgroup to fill the gaps: 2 x 256 behind 0 / 128 10.4 / 10.0, 13.1 / 12.7; 1 x 300 behind 0 / 32
@@ -293,7 +296,8 @@ int encode_walk_parts(const EncodeArgs& a) {
     const long tiles = ((long)a.total_rows * group + 127) / 128 * a.n_kv_heads, teams = (long)a.n_chunks * a.n_kv_heads;
     const long prefix = a.prefix_len, context = a.max_chunk_len;
     if (a.n_kv_heads > 4096) return 0;                       // (32-bit offsets inside a block of 32 tokens)
-    if (tiles >= 2048 ? prefix + context / 2 > 512 : tiles > 256 ? context > 512 || prefix + context > 640 : context > 256 || prefix + context > 384) return 0;
+    const long mean = group > 1 ? 512 : a.uniform_chunks || context > 512 ? 768 : 2304;
+    if (tiles >= 2048 ? prefix + context / 2 > mean : tiles > 256 ? context > 512 || prefix + context > 640 : context > 256 || prefix + context > 384) return 0;
     const int longest = (a.max_chunk_len * group + 127) / 128;
     for (int per : {4, 2}) {
         const int parts = (longest + per - 1) / per;

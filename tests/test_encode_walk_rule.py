@@ -12,9 +12,9 @@ class EncodeArgs(ctypes.Structure):                       # csrc/ape_internal.h
                [(n, ctypes.c_int32) for n in ("n_chunks", "prefix_len", "total_rows", "max_chunk_len", "n_q_heads", "n_kv_heads", "head_dim", "uniform_chunks")]
 
 
-def _parts(n, context, prefix, hq=32, hkv=8, total=None):
+def _parts(n, context, prefix, hq=32, hkv=8, total=None, uniform=1):
     rule = B.load()._ZN3ape17encode_walk_partsERKNS_10EncodeArgsE
-    return rule(ctypes.byref(EncodeArgs(n_chunks=n, prefix_len=prefix, total_rows=total or n * context, max_chunk_len=context, n_q_heads=hq, n_kv_heads=hkv, head_dim=128)))
+    return rule(ctypes.byref(EncodeArgs(n_chunks=n, prefix_len=prefix, total_rows=total or n * context, max_chunk_len=context, n_q_heads=hq, n_kv_heads=hkv, head_dim=128, uniform_chunks=uniform)))
 
 
 @pytest.mark.parametrize("n, context, last", [(512, 256, 384), (64, 512, 256), (1024, 64, 480), (128, 1024, 0), (4, 512, 128), (8, 256, 384), (2, 256, 128), (2, 100, 284)])
@@ -38,3 +38,9 @@ def test_workgroups_of_a_context(n, context, parts):
 
 def test_tiles_that_uneven_contexts_do_not_have_are_not_counted():
     assert _parts(16, 224, 0, total=2048) == 7
+
+
+@pytest.mark.parametrize("n, context, uniform, last", [(64, 512, 1, 512), (256, 200, 1, 640), (256, 448, 0, 2048), (100, 1225, 0, 128)])
+def test_one_query_head_per_kv_head(n, context, uniform, last):
+    assert _parts(n, context, last, hq=8, uniform=uniform) > 0
+    assert _parts(n, context, last + 256, hq=8, uniform=uniform) == 0
