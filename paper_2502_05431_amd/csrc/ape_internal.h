@@ -291,7 +291,7 @@ int whole_block_rows(const ShapeInfo& si, int ctx_splits, int batch, int q_len, 
 // ---- launchers (each returns hipGetLastError() of its launch) ------------------------------
 hipError_t launch_generic_query(const QueryArgs& a, int dtype, hipStream_t s);
 hipError_t launch_generic_encode(const EncodeArgs& a, int dtype, hipStream_t s);
-// any supported shape; block_rows from the plan; whole: one workgroup per row tile and KV head, writing the output (32 or 64 rows)
+// any supported shape; block_rows from the plan; whole: one workgroup per tile of 32 rows and KV head, writing the output
 hipError_t launch_tile_query(const QueryArgs& a, int dtype, int block_rows, bool whole, hipStream_t s);
 hipError_t launch_tile_encode(const EncodeArgs& a, int dtype, hipStream_t s);
 hipError_t launch_merge(const MergeArgs& a, hipStream_t s);

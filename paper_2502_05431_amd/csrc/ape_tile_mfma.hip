@@ -73,19 +73,19 @@ struct Tile {
     static constexpr int PART = KS * PITCH;                 // K part of a stage; V follows
     static constexpr int STAGE = 2 * PART;
     static constexpr int SUMS = WD > 1 ? NW * 4096 : 0;     // partial scores of the wavefronts that share rows, behind the ring
-    // Stages in the ring: as many as leave room for a second workgroup on the CU, where the registers allow one (Q and the
-    // accumulators of 256-wide rows alone are 192 of them), else as fit.
-    static constexpr int ROOM = (DP / WD == 256 ? 160 : 80) * 1024 - SUMS;
+    // Stages in the ring: as many as leave room for a second workgroup on the CU, else two.
+    static constexpr int ROOM = 80 * 1024 - SUMS;
     static constexpr int NSTG = STAGE * 4 <= ROOM ? 4 : STAGE * 3 <= ROOM ? 3 : 2;
     static constexpr int LDS = NSTG * STAGE + SUMS;
     static constexpr int LPT = PART / (16 * NT);            // loads per thread and part
     // wavefronts per SIMD, which set the register budget: what LDS has room for
-    static constexpr int WAVES = DP / WD == 256 || 160 * 1024 / LDS * NW < 8 ? 1 : 2;
-    // ... and how many there can be at most (or two), which the scheduler is to know where registers are left: for more it saves
-    // them, with one fragment in flight at a time (bf16 encode, 8/8 heads of 96, 4 x 1024 tokens: 35.9 us, 33.8 told)
-    static constexpr int MOST = DP / WD == 256 ? 8 : 160 * 1024 / LDS * NW < 8 ? 2 : 160 * 1024 / LDS * NW / 4;
+    static constexpr int WAVES = 160 * 1024 / LDS * NW < 8 ? 1 : 2;
+    // ... and how many there can be at most (or two), which the scheduler is to know: for more it saves registers,
+    // with one fragment in flight at a time (bf16 encode, 8/8 heads of 96, 4 x 1024 tokens: 35.9 us, 33.8 told)
+    static constexpr int MOST = 160 * 1024 / LDS * NW < 8 ? 2 : 160 * 1024 / LDS * NW / 4;
     static_assert(PART % (16 * NT) == 0 && LDS <= 160 * 1024, "stage size");
     static_assert(WK == 1 || WD == 1, "one way to share the rows");
+    static_assert(DP / WD <= 128, "a wavefront's registers: Q and the accumulators of 256 dims alone are 192 or more of them");
 };
 
 // XOR swizzles of the 16-byte chunk index inside a row (see the reads in `compute`).
@@ -199,13 +199,6 @@ __device__ __forceinline__ void clear_rows(Rows<T, DW>& st) {
         for (int r = 0; r < 16; ++r) st.o[db][r] = 0.f;
 }
 
-// With 256-wide rows the accumulators and Q take 192 of the 256 registers of a wavefront (two per SIMD): LDS
-// reads may run ahead of their MFMAs by a few fragments only, which the scheduler has to be told.
-template <int DP>
-__device__ __forceinline__ void group_barrier() {
-    if constexpr (DP == 256) __builtin_amdgcn_sched_barrier(0);
-}
-
 // One run of 32 tokens.  S^T = K Q^T over the dims of part `wd`.
 template <typename T, int DP, int WD>
 __device__ __forceinline__ f32x16 scores(const char* kpart, int wd, const Rows<T, DP / WD>& st) {
@@ -226,7 +219,6 @@ __device__ __forceinline__ f32x16 scores(const char* kpart, int wd, const Rows<T
     kpart += 256 * (wd * NQ / 8);
 #pragma unroll
     for (int i = 0; i < NQ; ++i) {
-        if (i % 4 == 0) group_barrier<DW>();
         const u32x4 a = *(const u32x4*)(kpart + (koff ^ (32 * (i % 8))) + 256 * (i / 8));
         if constexpr (sizeof(T) == 2) {
             sc_part[0] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(__builtin_bit_cast(bf16x8, a), __builtin_bit_cast(bf16x8, st.q[i]), sc_part[0], 0, 0, 0);
@@ -342,7 +334,6 @@ __device__ __forceinline__ void update(f32x16 s, const char* vpart, int wd, cons
         for (int sl = 0; sl < 2; ++sl)
 #pragma unroll
             for (int db = 0; db < NB; ++db) {
-                if (db % 2 == 0) group_barrier<DW>();
                 const char* at = vpart + (voff ^ (64 * (db % 4))) + 256 * (db / 4) + 16 * sl * PITCH;
                 const bf16x4 lo4 = lds_read_tr(at), hi4 = lds_read_tr(at + 8 * PITCH);
                 const bf16x8 a = __builtin_shufflevector(lo4, hi4, 0, 1, 2, 3, 4, 5, 6, 7);
@@ -830,9 +821,11 @@ template <typename T, int DP>
 hipError_t query_with(const QueryArgs& a, int block_rows, bool whole, hipStream_t s) {
     constexpr bool WIDE = DP * (int)sizeof(T) > 256;
     constexpr int K2 = WIDE ? 1 : 2, D2 = WIDE ? 2 : 1, K4 = WIDE ? 1 : 4, D4 = WIDE ? 4 : 1;
-    if (block_rows == 128) return query_as<T, DP, 4, 1, 1, false>(a, s);
-    if (block_rows == 64) return whole ? query_as<T, DP, 2, K2, D2, true>(a, s) : query_as<T, DP, 2, K2, D2, false>(a, s);
-    return whole ? query_as<T, DP, 1, K4, D4, true>(a, s) : query_as<T, DP, 1, K4, D4, false>(a, s);
+    if (whole) return query_as<T, DP, 1, K4, D4, true>(a, s);
+    if constexpr (DP <= 128) {
+        if (block_rows == 128) return query_as<T, DP, 4, 1, 1, false>(a, s);
+    }
+    return block_rows == 64 ? query_as<T, DP, 2, K2, D2, false>(a, s) : query_as<T, DP, 1, K4, D4, false>(a, s);
 }
 
 template <typename T, int DP, int WR, int WK, int WD>

@@ -46,6 +46,23 @@ def test_flash_kernels_keep_their_register_budget():
 
 def test_merge_kernels_occupancy():
     rep = _report()
+    seen = 0
     for name, r in rep["ape_generic.hip"].items():
-        if "merge_kernel" in name:
+        m = re.search(r"merge_units_kernelI\w+?Li(\d)ELi(\d)E", name)
+        if m:
+            # a row of up to 256 dims (NV == 2) holds twice the rows in flight
+            seen += 1
+            assert r["Occupancy"] >= (4 if m.group(1) == "1" else 3), (name, r)
+        elif "merge" in name:
             assert r["Occupancy"] >= 4, (name, r)
+    assert seen == 16
+
+
+def test_tile_and_walk_kernels_keep_their_register_budget():
+    rep = _report()
+    assert len(rep["ape_tile_mfma.hip"]) == 38 and len(rep["ape_encode_walk.hip"]) == 1
+    for name, r in [*rep["ape_tile_mfma.hip"].items(), *rep["ape_encode_walk.hip"].items()]:
+        # two wavefronts per SIMD, everything in the 256 architectural registers
+        assert r["Occupancy"] >= 2 and r["AGPRs"] == 0, (name, r)
+        if re.search(r"tile_\w+_kernelIDF16bLi64ELi4ELi1ELi1E", name):
+            assert r["Occupancy"] >= 4, (name, r)         # 32 KB of LDS: five workgroups fit a CU
