@@ -101,8 +101,8 @@ hipError_t launch_encode(const ShapeInfo& si, const EncodeArgs& e, hipStream_t s
         const int parts = encode_walk_parts(e);
         return parts > 0 ? launch_encode_walk(e, parts, s) : launch_flash_encode(e, s);
     }
-    // The tile kernel's grid is contexts x KV heads x row tiles of the longest context; a call whose lengths are so
-    // uneven that this passes the launch limit takes the vector-ALU kernel, whose grid is the rows themselves.
+    // The tile kernel's grid is contexts x KV heads x row tiles of the longest context, most of them empty where lengths are uneven; a
+    // call that passes the limit of a launch even with the largest tile takes the vector-ALU kernel, whose grid is the rows themselves.
     const long n_qtiles = ((long)e.max_chunk_len * si.group + 127) / 128;
     if (si.tile && ((long)e.n_chunks * si.hkv + 7) / 8 * 8 * n_qtiles < kMaxEncodeBlocks) return launch_tile_encode(e, si.dtype, s);
     return launch_generic_encode(e, si.dtype, s);
@@ -614,8 +614,8 @@ int ape_attention_tree(const ape_shape* shape, const ape_request* req,
 
     TreePlan plan = plan_tree(si, req->total_ctx_len, n_nodes, q_len);
     // Nodes of a few thousand tokens are streams as short as a short context's: the narrow tile, whose two workgroups per CU
-    // cover for each other's start and output, wins (256 / 128 rows, us: a node per context, 256 query tokens, 64 x 2048 tokens
-    // 632 / 604; 20 x 4096 tokens 346 / 333, 16 x 8192 482 / 498; 100 query tokens, 256 x 512 tokens 526 / 484).
+    // cover for each other's start and output, wins, by little at the line (256 / 128 rows, us, fastest of eight: a node per context, 200 query tokens, 64 x 1024 tokens
+    // 374 / 296; 100 over 256 x 512 561 / 478; 256 over 128 x 1024 807 / 737, 64 x 2048 630 / 620, 20 x 4096 367 / 361, 32 x 4096 553 / 562, 16 x 8192 522 / 543).
     if (plan.block_rows == 256) {
         long groups = 0;
         for (int n = 0; n < n_nodes; ++n) groups += nodes_host[n].leaf_children != 0;

@@ -11,10 +11,10 @@
 // that every read is conflict-free) and 8 KB per wavefront for its query rows, which also turns the output around.
 // Scores are computed transposed, S^T = K Q^T, then O^T += V^T P^T (MFMA 32x32x16), as in the flash kernels; bf16
 // probabilities, fp32 sums of the unrounded ones.  The other workgroup of the CU is what overlaps with a softmax: starting
-// the next block's S^T in its shadow took more scalar and register work than it hid (815 against 738 us below).
+// the next block's S^T in its shadow took more scalar and register work than it hid (815 against 738 us for the call below).
 //
-// 512 contexts of 64 .. 448 tokens (mean 256), 32/8 heads: 903 -> 749 us, 3.6 TB/s of the 5.1 that a large copy reaches
-// here; 2048 of 16 .. 112 tokens 954 -> 532 us.  What is left is the blocks: 2048-token contexts, which the memory does not
+// 512 contexts of 64 .. 448 tokens (mean 256), 32/8 heads: 888 -> 740 us (731 .. 751 over several cards), 3.6 TB/s of
+// the 5.1 that a large copy reaches here; 2048 of 16 .. 112 tokens 954 -> 532 us.  What is left is the blocks: 2048-token contexts, which the memory does not
 // bound, run at 0.9 of the flash kernel's rate.
 #include "ape_mfma.h"
 
