@@ -189,12 +189,16 @@ QueryPlan tile_decode_plan(const ShapeInfo& si, int batch, long max_ctx) {
 // where tiles of 32 rows are more than a CU each (8 requests of 64 rows 26.4 / 29.3, 500 rows 29.5 / 34.7; 3 of 64 16.9 / 12.2, 256 rows
 // 20.7 / 15.6), counted within an XCD, since a KV head's tiles run on one (16/2 heads, 8 requests of 64 rows 24.6 / 56.3, 2 of them
 // 16.8 / 15.4), and where prefixes and own tokens are more than the caches hold (16 decode steps behind 1500 own tokens 32.6 / 31.7, 4000
-// 66.0 / 69.1; 64 behind 700 69.6 / 64.6, 1500 88.9 / 101; 8 behind 4000 61.8 / 59.2, 12000 161 / 192).
+// 66.0 / 69.1; 64 behind 700 69.6 / 64.6, 1500 88.9 / 101; 8 behind 4000 61.8 / 59.2, 12000 161 / 192), and where a few workgroups have more than
+// a stage of 128 tokens on both sides, until the own stream is all that counts (one decode step over 128 / 160 tokens behind 128 12.3 / 11.4, 12.8 / 13.1,
+// behind 160 12.6 / 12.8, 12.9 / 14.4, 400 16.2 / 16.0, 16.3 / 17.6, 1000 23.8 / 21.8, 24.0 / 23.2; 16 rows over 160 behind 160 12.8 / 15.1; 12 steps 17.9 / 15.8, 64 rows
+// 14.7 / 15.2 and over 256 16.0 / 15.1).
 int whole_block_rows(const ShapeInfo& si, int ctx_splits, int batch, int q_len, long max_ctx, long own) {
     if (si.force_generic) return 0;
     const long row_tiles = ceil_div((long)q_len * si.group, 32), workgroups = (long)batch * si.hkv * row_tiles;
     if (workgroups > 512) return 0;
     if (si.mfma && ((row_tiles > 1 && batch * row_tiles * ceil_div(si.hkv, 8) > 32) || (batch > 1 && own * si.hkv > 400000))) return 0;
+    if (si.mfma && batch < 8 && workgroups < 64 && max_ctx > 128 && own > 128L * batch && own <= 640L * batch) return 0;
     const int width = si.d <= 64 ? 0 : si.d <= 128 ? 1 : 2;
     const long most = si.dtype == APE_F32 ? (width == 0 ? 128 : width == 1 ? 64 : 0) : 512 >> width;
     return max_ctx <= most || (si.tile && ctx_splits <= 1 && workgroups >= 128) ? 32 : 0;

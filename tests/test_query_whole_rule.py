@@ -38,3 +38,11 @@ def test_a_kv_head_has_one_xcd(batch, q_len, whole):
 @pytest.mark.parametrize("batch, q_len, own", [(32, 1, 4000), (4, 64, 64), (1, 250, 250)])
 def test_other_shapes_have_no_other_kernel(batch, q_len, own):
     assert _whole(batch, q_len, own, ctx=100, hq=16, hkv=8, d=256)
+
+
+@pytest.mark.parametrize("batch, q_len, ctx, own, whole", [
+    (1, 1, 128, 160, True), (1, 1, 129, 129, False), (3, 1, 256, 400, False), (1, 16, 160, 200, False), (1, 1, 256, 128, True), (1, 1, 256, 1000, True),
+    (12, 1, 256, 400, True), (1, 64, 200, 200, True),
+])
+def test_two_stages_on_both_sides(batch, q_len, ctx, own, whole):
+    assert _whole(batch, q_len, own, ctx=ctx) == whole
