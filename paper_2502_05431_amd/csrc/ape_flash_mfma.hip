@@ -950,9 +950,9 @@ __device__ __forceinline__ void init_state(WaveState<RB>& st) {
 // Query prefill: team = (split, KV head); grid = the context teams (padded to a multiple of 8) times
 // n_qtiles, then the prefix+self teams likewise.
 // Rows: R = qtile*BM + wave*32*RB + rb*32 + (lane & 31); query token = R / G, head = hk*G + R % G.
-template <int RB, int G, bool NTL>
-__global__ __launch_bounds__(NT) void flash_prefill_kernel(const QueryArgs a, int n_qtiles) {
-    extern __shared__ __attribute__((aligned(16))) char lds[];
+// UNEVEN: the requests of a batch have splits of their own (QueryArgs::n_own_splits), and the whole batch lies in x.
+template <int RB, int G, bool NTL, bool UNEVEN>
+__device__ __forceinline__ void query_tile(const QueryArgs& a, const int n_qtiles, char* const lds) {
     constexpr int BM = NW * 32 * RB;
     const int tid = threadIdx.x;
     const int lane = tid & 63, wave = tid >> 6;
@@ -960,10 +960,10 @@ __global__ __launch_bounds__(NT) void flash_prefill_kernel(const QueryArgs a, in
     // Blocks of the context splits come first: they are the long ones, and the grid is planned so
     // that they fill the chip exactly once; the short prefix+self workgroups follow.
     int team, qtile, split, hk;
-    const int ctx_teams = a.n_ctx_splits * a.n_kv_heads;
+    const int ctx_teams = (UNEVEN ? a.n_own_splits : a.n_ctx_splits) * a.n_kv_heads;
     const int ctx_blocks = (ctx_teams + 7) / 8 * 8 * n_qtiles;
     int bx = blockIdx.x, rq = blockIdx.y;                // position in the request's part of the grid; request
-    if (a.n_req > 1) {
+    if (!UNEVEN && a.n_req > 1) {
         // A batch: the context workgroups of ALL requests first, then every request's short prefix+self ones, in the
         // order workgroups are dispatched (x fastest, then y).  Dealt request by request, the short ones sit between the
         // long ones and leave their slots early, which spoils the balance when the long ones are few (three requests of 64
@@ -985,12 +985,16 @@ __global__ __launch_bounds__(NT) void flash_prefill_kernel(const QueryArgs a, in
         // once) reads faster in that order too, 87.4 against 89.8 us over 128K tokens -- the eight
         // heads of a token's 2 KB row are then fetched at about the same time; a batch does not
         // (config 5: 0.346 against 0.339 ms), its workgroups run in several rounds.
-        if (a.split_ranges != nullptr || (n_qtiles == 1 && a.n_req == 1)) { hk = team % a.n_kv_heads; split = team / a.n_kv_heads; }
+        // An uneven batch has it there too, so that every XCD gets the same share of every request (with the split fastest, the last
+        // splits, which only long requests have, meet on few XCDs: 32 requests of 1 to 15 x 1024 tokens, four splits, 220 against 176 us).
+        if constexpr (UNEVEN) { hk = team % a.n_kv_heads; own_split(a.n_req, team / a.n_kv_heads, rq, split); }
+        else if (a.split_ranges != nullptr || (n_qtiles == 1 && a.n_req == 1)) { hk = team % a.n_kv_heads; split = team / a.n_kv_heads; }
         else { split = team % a.n_ctx_splits; hk = team / a.n_ctx_splits; }
     } else {
         team_of_block(bx - ctx_blocks, n_qtiles, team, qtile);
-        if (team >= a.n_kv_heads) return;
+        if (team >= (UNEVEN ? a.n_req : 1) * a.n_kv_heads) return;
         split = a.n_ctx_splits; hk = team;
+        if constexpr (UNEVEN) { hk = team % a.n_kv_heads; rq = team / a.n_kv_heads; }
     }
     const KvView kv = load_view<QueryArgs>(rq);
     const int hq = a.n_q_heads, q_len = a.q_len;
@@ -1006,7 +1010,8 @@ __global__ __launch_bounds__(NT) void flash_prefill_kernel(const QueryArgs a, in
     int vis_lo = 0;
     if (split < a.n_ctx_splits) {
         long t0, t1;
-        ctx_split_range(a, kv, split, t0, t1);
+        if constexpr (UNEVEN) own_split_range(kv, rq, split, t0, t1);
+        else ctx_split_range(a, kv, split, t0, t1);
         // An empty split (a slot past the splits a tree plan uses; in a batch, a split past the end
         // of a request's context) is one the merge never looks at: the whole workgroup leaves
         // here, before any barrier or load.
@@ -1058,7 +1063,7 @@ __global__ __launch_bounds__(NT) void flash_prefill_kernel(const QueryArgs a, in
         if (tok >= q_len) continue;
         const float inv = lt > 0.f ? 1.f / lt : 0.f;
         const long unit = ((long)(a.req_base + rq) * q_len + tok) * hq + hk * G + g;
-        const long slot = (long)split * a.units_total + unit;
+        const long slot = UNEVEN ? own_partial_rows(a, rq, split) + (long)tok * hq + hk * G + g : (long)split * a.units_total + unit;
         float* o = a.part_o + slot * D;
 #pragma unroll
         for (int db = 0; db < 4; ++db)
@@ -1071,6 +1076,18 @@ __global__ __launch_bounds__(NT) void flash_prefill_kernel(const QueryArgs a, in
             }
         if (hi == 0) a.part_lse[slot] = lt > 0.f ? (st.m[rb] + __builtin_amdgcn_logf(lt)) * LN2 : -INFINITY;
     }
+}
+
+template <int RB, int G, bool NTL>
+__global__ __launch_bounds__(NT) void flash_prefill_kernel(const QueryArgs a, int n_qtiles) {
+    extern __shared__ __attribute__((aligned(16))) char lds[];
+    query_tile<RB, G, NTL, false>(a, n_qtiles, lds);
+}
+// (kernels of their own: what they look up would cost the others 0.3 us a call)
+template <int RB, int G, bool NTL>
+__global__ __launch_bounds__(NT) void flash_uneven_kernel(const QueryArgs a, int n_qtiles) {
+    extern __shared__ __attribute__((aligned(16))) char lds[];
+    query_tile<RB, G, NTL, true>(a, n_qtiles, lds);
 }
 
 // ------------------------------------------------------------------------------------------
@@ -1206,9 +1223,10 @@ __global__ __launch_bounds__(NT) void flash_encode_kernel(const EncodeArgs a, in
 
 template <int RB, int G, bool NTL>
 hipError_t launch_prefill_t(const QueryArgs& a, dim3 grid, int n_qtiles, hipStream_t s) {
-    hipError_t e = hipFuncSetAttribute((const void*)flash_prefill_kernel<RB, G, NTL>, hipFuncAttributeMaxDynamicSharedMemorySize, Ring<RB>::slots * SLOTB);
+    auto kernel = a.n_own_splits > 0 ? flash_uneven_kernel<RB, G, NTL> : flash_prefill_kernel<RB, G, NTL>;
+    hipError_t e = hipFuncSetAttribute((const void*)kernel, hipFuncAttributeMaxDynamicSharedMemorySize, Ring<RB>::slots * SLOTB);
     if (e != hipSuccess) return e;
-    flash_prefill_kernel<RB, G, NTL><<<grid, NT, Ring<RB>::slots * SLOTB, s>>>(a, n_qtiles);
+    kernel<<<grid, NT, Ring<RB>::slots * SLOTB, s>>>(a, n_qtiles);
     return hipGetLastError();
 }
 
@@ -1273,7 +1291,8 @@ hipError_t launch_flash_prefill(const QueryArgs& a, int block_rows, hipStream_t 
     const int n_qtiles = (rows + bm - 1) / bm;
     const int ctx_teams = a.n_ctx_splits * a.n_kv_heads;
     // x is a multiple of 8, so the workgroups of every request start on the same XCD phase
-    const dim3 grid((unsigned)(((ctx_teams + 7) / 8 * 8 + (a.n_kv_heads + 7) / 8 * 8) * n_qtiles), (unsigned)a.n_req);
+    dim3 grid((unsigned)(((ctx_teams + 7) / 8 * 8 + (a.n_kv_heads + 7) / 8 * 8) * n_qtiles), (unsigned)a.n_req);
+    if (a.n_own_splits > 0) grid = uneven_grid(a, n_qtiles);
     if (bm == 256) return launch_prefill_g<2, false>(group, a, grid, n_qtiles, s);
     // one row tile: every K/V block is fetched by one workgroup and never again -> non-temporal loads
     return n_qtiles == 1 ? launch_prefill_g<1, true>(group, a, grid, n_qtiles, s) : launch_prefill_g<1, false>(group, a, grid, n_qtiles, s);

@@ -207,8 +207,8 @@ __global__ __launch_bounds__(kWave) void generic_encode_kernel(const EncodeArgs 
 // Whole calls, against a workgroup per unit that read the LogSumExps and then the rows of one group after the other (us): a decode
 // step over 20 x 512 tokens, 32 units of 33 splits, 17.8 -> 15.3; 80 units of 33 splits of a 20-row query 25.9 -> 23.6; 64 rows,
 // 32/8 bf16 heads of 64, 30.7 -> 27.4; 256 rows over 128K tokens, 8192 units of 9 splits, 481 -> 480.
-template <typename T, int NV, int H>
-__global__ __launch_bounds__(256) void merge_units_kernel(const MergeArgs a) {
+template <typename T, int NV, int H, bool UNEVEN>
+__device__ __forceinline__ void merge_units(const MergeArgs& a) {
     constexpr int UN = 8;
     __shared__ float4 part[H > 1 ? 8 : 1][32 * NV];
     const int lane = threadIdx.x & (kWave - 1), wave = threadIdx.x / kWave;
@@ -223,19 +223,24 @@ __global__ __launch_bounds__(256) void merge_units_kernel(const MergeArgs a) {
     auto ka = kernarg<MergeArgs>();
     const float S = ka->scale[rq];                                   // (per lane: the two halves may belong to different requests)
     const int tc = ka->total_ctx[rq];
-    const int n_split = a.n_ctx_splits;                              // slots of the context group; slot n_split is prefix + self
-    const int n_ctx = min(n_split, (tc + a.ctx_split_len - 1) / a.ctx_split_len);   // those this request wrote
-    const int n_slots = n_split + 1;                                 // wavefront-uniform loop bound
+    // slots of the context group that this request wrote; the slot of prefix + self
+    const int first = UNEVEN ? ka->first_split[rq] : 0;
+    const int n_ctx = UNEVEN ? ka->first_split[rq + 1] - first : min(a.n_ctx_splits, (tc + a.ctx_split_len - 1) / a.ctx_split_len);
+    const int n_split = UNEVEN ? n_ctx : a.n_ctx_splits;
+    const int n_slots = a.n_ctx_splits + 1;                          // wavefront-uniform loop bound
+    // slot sl of this unit is row row0 + sl * row_step (uneven: one slot per request in front is prefix + self; `unit` counts its rows)
+    const int row_step = UNEVEN ? a.q_len * hq : a.units_total;
+    const long row0 = UNEVEN ? unit + (long)first * row_step : gunit;
     // LogSumExps: slot s lives in lane s % 32 of this half, register s / 32 (at most 65 slots)
     float l[3];
 #pragma unroll
     for (int r = 0; r < 3; ++r) {
         const int sl = j + 32 * r;
         const bool used = sl < n_ctx || sl == n_split;
-        l[r] = used ? a.part_lse[(long)sl * a.units_total + gunit] : -INFINITY;
+        l[r] = used ? a.part_lse[(long)sl * row_step + row0] : -INFINITY;
     }
-    const long slot_stride = (long)a.units_total * d;
-    const float* base = a.part_o + gunit * d;
+    const long slot_stride = (long)row_step * d;
+    const float* base = a.part_o + row0 * d;
     float4 v[UN][NV], acc[NV];
     auto load_rows = [&](int s0) {
 #pragma unroll
@@ -267,7 +272,7 @@ __global__ __launch_bounds__(256) void merge_units_kernel(const MergeArgs a) {
 #pragma unroll
     for (int r = 0; r < 3; ++r) e[r] = any ? expf(lc[r] - mc) : 0.f;               // 0 for empty and unused slots
     const float zc = half_sum(e[0] + e[1] + e[2]);
-    const float lse_o = __shfl(l[n_split >> 5], (n_split & 31) + 32 * half);       // prefix + self: never empty
+    const float lse_o = __shfl(UNEVEN ? (n_split < 32 ? l[0] : n_split < 64 ? l[1] : l[2]) : l[n_split >> 5], (n_split & 31) + 32 * half);       // prefix + self: never empty
     // the context splits are pooled first; only then is their LogSumExp multiplied by S
     const float ac = any ? S * (mc + logf(zc)) : -INFINITY;
     const float mx = fmaxf(ac, lse_o);
@@ -328,6 +333,12 @@ __global__ __launch_bounds__(256) void merge_units_kernel(const MergeArgs a) {
         }
     }
 }
+
+template <typename T, int NV, int H>
+__global__ __launch_bounds__(256) void merge_units_kernel(const MergeArgs a) { merge_units<T, NV, H, false>(a); }
+// requests with splits of their own (a kernel of its own: the look-ups would cost the others 0.5 us)
+template <typename T, int NV, int H>
+__global__ __launch_bounds__(256) void pool_uneven_kernel(const MergeArgs a) { merge_units<T, NV, H, true>(a); }
 
 // ------------------------------------------------------------------------------------------
 // Tree of contexts (Appendix C.2 applied at every node, Appendix C.5).
@@ -753,10 +764,12 @@ hipError_t launch_merge_t(const MergeArgs& a, hipStream_t s) {
     const int slots = a.n_splits_total;
     const int h = units >= 4096 || slots <= 8 ? 1 : slots <= 16 ? 2 : slots <= 32 ? 4 : 8;
     const unsigned blocks = (unsigned)((units * h + 7) / 8);
-    if (h == 1) merge_units_kernel<T, NV, 1><<<blocks, 256, 0, s>>>(a);
-    else if (h == 2) merge_units_kernel<T, NV, 2><<<blocks, 256, 0, s>>>(a);
-    else if (h == 4) merge_units_kernel<T, NV, 4><<<blocks, 256, 0, s>>>(a);
-    else merge_units_kernel<T, NV, 8><<<blocks, 256, 0, s>>>(a);
+    const bool un = a.n_own_splits > 0;
+    auto kernel = h == 1 ? (un ? pool_uneven_kernel<T, NV, 1> : merge_units_kernel<T, NV, 1>)
+                : h == 2 ? (un ? pool_uneven_kernel<T, NV, 2> : merge_units_kernel<T, NV, 2>)
+                : h == 4 ? (un ? pool_uneven_kernel<T, NV, 4> : merge_units_kernel<T, NV, 4>)
+                         : (un ? pool_uneven_kernel<T, NV, 8> : merge_units_kernel<T, NV, 8>);
+    kernel<<<blocks, 256, 0, s>>>(a);
     return hipGetLastError();
 }
 }  // namespace

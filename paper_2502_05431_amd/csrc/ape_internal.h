@@ -34,6 +34,12 @@ constexpr long kMaxEncodeBlocks = 1L << 24;     // workgroups of a matrix-core e
 // Kernel-argument block of the query-time kernels (prefill and decode).
 struct QueryArgs {
     KvView req[kMaxReqPerLaunch];
+    // Uneven batches: every request has splits of its own number and length, n_own_splits in the launch; request r has splits
+    // first_split[r] .. first_split[r + 1] - 1 of split_len[r] tokens.  Partial results are then dense,
+    // [first_split[r] + r + split][rows of a request], a request's prefix + self behind its last split.
+    // (In front of the scalars, which a kernel reads first: those stay together.)
+    int32_t split_len[kMaxReqPerLaunch];
+    uint16_t first_split[kMaxReqPerLaunch + 2];
     const void* q;              // [batch*q_len, Hq, d]
     float* part_o;              // [n_splits_total][units][d], unit = (request*q_len + row)*Hq + head
     float* part_lse;            // [n_splits_total][units]
@@ -49,6 +55,7 @@ struct QueryArgs {
                                 // [split_ranges[2s], split_ranges[2s+1]) of the pooled contexts; empty if equal
     int32_t units_total;        // n_req * q_len * Hq (stride of the split dimension)
     int32_t req_base;           // index of req[0] in the whole batch
+    int32_t n_own_splits;       // see first_split; 0: not so
     // a call that takes no merge writes its output itself
     void* out;                  // [units][d]
     float* lse_out;             // NULL or fp32
@@ -62,6 +69,7 @@ struct MergeArgs {
     float* lse_out;             // NULL or fp32
     float scale[kMaxReqPerLaunch];
     int32_t total_ctx[kMaxReqPerLaunch];   // context tokens of each request: splits past them were never written
+    uint16_t first_split[kMaxReqPerLaunch + 2];   // as in QueryArgs
     int32_t ctx_split_len;
     int32_t n_req;
     int32_t q_len;
@@ -73,6 +81,7 @@ struct MergeArgs {
     int32_t req_base;
     int32_t lse_head_major;     // 1: lse_out[h*q_len + r] (prefill); 0: lse_out[unit] (decode)
     int32_t dtype;
+    int32_t n_own_splits;       // as in QueryArgs (n_ctx_splits: the most splits of a request)
 };
 
 // Device-side plan of a tree call, written into the workspace by the plan kernel and read by the
@@ -250,6 +259,27 @@ __device__ __forceinline__ KvView load_view(int rq) {
     return v;
 }
 
+// Uneven batches (QueryArgs::n_own_splits): the request that the launch's split `i` belongs to, and which of its splits it is.
+__device__ __forceinline__ void own_split(int n_req, int i, int& rq, int& split) {
+    auto first = kernarg<QueryArgs>()->first_split;
+    const int lane = threadIdx.x & 63;
+    static_assert(kMaxReqPerLaunch < 64, "a lane per request");
+    rq = __builtin_popcountll(__builtin_amdgcn_ballot_w64(lane < n_req && first[min(lane + 1, n_req)] <= i));
+    split = i - first[rq];
+}
+// ... the context tokens that it covers,
+__device__ __forceinline__ void own_split_range(const KvView& kv, int rq, int split, long& t0, long& t1) {
+    const int len = kernarg<QueryArgs>()->split_len[rq];
+    t0 = (long)split * len;
+    t1 = min((long)kv.total_ctx, t0 + len);
+}
+// ... and where its partial results begin, in rows of d values; split a.n_ctx_splits: prefix + self.
+__device__ __forceinline__ long own_partial_rows(const QueryArgs& a, int rq, int split) {
+    auto ap = kernarg<QueryArgs>();
+    const int at = split < a.n_ctx_splits ? ap->first_split[rq] + split : ap->first_split[rq + 1];
+    return (long)(at + rq) * a.q_len * a.n_q_heads;
+}
+
 // XCD-aware work mapping.  Workgroups are dealt round-robin to the 8 XCDs (each with its own
 // L2); a "team" = the workgroups that read the same K/V (all query tiles of one KV range).
 // Teams are dealt to XCDs so that the members of a team run on one XCD back to back.
@@ -284,6 +314,11 @@ struct QueryPlan {
     int n_bound;           // >= n_ctx_splits of this plan and of the plan for any shorter context with the same base and target
     int block_rows;        // query tile this plan was made for (0: the vector-ALU kernels, which have none)
 };
+
+// grid of a matrix-core query launch with splits of every request's own (the whole batch in x)
+inline dim3 uneven_grid(const QueryArgs& a, int n_qtiles) {
+    return dim3((unsigned)((((long)a.n_own_splits * a.n_kv_heads + 7) / 8 * 8 + ((long)a.n_req * a.n_kv_heads + 7) / 8 * 8) * n_qtiles));
+}
 
 // rows per workgroup of a query that runs without splits, or 0 (see the definition)
 int whole_block_rows(const ShapeInfo& si, int ctx_splits, int batch, int q_len, long max_ctx, long own);

@@ -603,9 +603,10 @@ __device__ __forceinline__ __attribute__((address_space(4))) const Args* kernarg
     return a;
 }
 
-// Query rows past context tokens [t0, t1) and, if `own`, then past the prefix and the own tokens; `whole`: this is the output.
+// Query rows past context tokens [t0, t1) and, if `own`, then past the prefix and the own tokens; `whole`: this is the output (else
+// the partial result whose rows begin at part0).
 template <typename T>
-__device__ __forceinline__ void redo_query_rows(__attribute__((address_space(4))) const QueryArgs* a, int rq, int hk, int split, int t0, int t1,
+__device__ __forceinline__ void redo_query_rows(__attribute__((address_space(4))) const QueryArgs* a, int rq, int hk, long part0, int t0, int t1,
                                                 bool own, bool whole, int R0, uint32_t redo, int c0, int c1) {
     const int d = a->head_dim, hq = a->n_q_heads, hkv = a->n_kv_heads, G = hq / hkv, q_len = a->q_len;
     const int n_chunks = a->req[rq].n_chunks;
@@ -642,7 +643,7 @@ __device__ __forceinline__ void redo_query_rows(__attribute__((address_space(4))
             x.store((T*)a->out + unit * d, c0, c1, INFINITY);
             if (a->lse_out && first_dims) a->lse_out[a->lse_head_major ? ((long)(a->req_base + rq) * hq + h) * q_len + tok : unit] = x.lse();
         } else {
-            const long slot = (long)split * a->units_total + unit;
+            const long slot = part0 + (long)tok * hq + h;
             x.store(a->part_o + slot * d, c0, c1, 0.f);
             if (first_dims) a->part_lse[slot] = x.lse();
         }
@@ -679,17 +680,20 @@ void tile_query_kernel(const QueryArgs a, int n_qtiles) {
     using X = Tile<T, DP, WR, WK, WD>;
     extern __shared__ __attribute__((aligned(16))) char lds[];
     const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), l32 = lane & 31, hi = lane >> 5;
-    const int d = a.head_dim, hq = a.n_q_heads, hkv = a.n_kv_heads, G = hq / hkv, q_len = a.q_len, rq = blockIdx.y;
-    const int ctx_teams = WHOLE ? 0 : a.n_ctx_splits * hkv, ctx_blocks = (ctx_teams + 7) / 8 * 8 * n_qtiles;
-    int team, qtile, split;
+    const int d = a.head_dim, hq = a.n_q_heads, hkv = a.n_kv_heads, G = hq / hkv, q_len = a.q_len;
+    const bool uneven = !WHOLE && a.n_own_splits > 0;        // (then the whole batch lies in x)
+    const int ctx_teams = WHOLE ? 0 : (uneven ? a.n_own_splits : a.n_ctx_splits) * hkv, ctx_blocks = (ctx_teams + 7) / 8 * 8 * n_qtiles;
+    int team, qtile, split, rq = blockIdx.y;
     if ((int)blockIdx.x < ctx_blocks) {
         team_of_block(blockIdx.x, n_qtiles, team, qtile);
         if (team >= ctx_teams) return;
-        split = team / hkv;
+        if (uneven) own_split(a.n_req, team / hkv, rq, split);
+        else split = team / hkv;
     } else {
         team_of_block(blockIdx.x - ctx_blocks, n_qtiles, team, qtile);
-        if (team >= hkv) return;
+        if (team >= (uneven ? a.n_req : 1) * hkv) return;
         split = a.n_ctx_splits;
+        if (uneven) rq = team / hkv;
     }
     const int hk = team % hkv;
     const KvView kv = load_view<QueryArgs>(rq);
@@ -741,7 +745,7 @@ void tile_query_kernel(const QueryArgs a, int n_qtiles) {
         long t0 = 0, t1 = 0;
         const bool own = split >= a.n_ctx_splits;
         if (!own) {
-            ctx_split_range(a, kv, split, t0, t1);
+            if (uneven) own_split_range(kv, rq, split, t0, t1); else ctx_split_range(a, kv, split, t0, t1);
             if (t0 >= t1) return;                            // an empty split: the merge never looks at it (a request without contexts has no table)
             t1 = min(t1, (long)scalar_load_i32(kv.cu + kv.n_chunks));   // (stay inside the table whatever total_ctx says)
             if (t0 >= t1) return;
@@ -754,13 +758,14 @@ void tile_query_kernel(const QueryArgs a, int n_qtiles) {
         if (!combine<T, DP / WD, WR, WK>(lds, st)) return;
         const float lt = sum_halves(st.l);
         const uint32_t redo = rows_to_redo(st, lt, valid, own);
+        const long part0 = uneven ? own_partial_rows(a, rq, split) : (long)split * a.units_total + (long)(a.req_base + rq) * q_len * hq;
         if (valid && !(redo >> l32 & 1)) {
-            const long slot = (long)split * a.units_total + unit;
+            const long slot = part0 + (long)tok * hq + h;
             store_row<T, DP, WD>(st, seen(lt) ? 1.f / lt : 0.f, d, wd, a.part_o + slot * d);
             if (hi == 0 && wd == 0) a.part_lse[slot] = seen(lt) ? ScoreScale<T>::lse(st.m, lt) : -INFINITY;
         }
         if (__builtin_expect(redo != 0, 0))
-            redo_query_rows<T>(kernarg_again<QueryArgs>(), rq, hk, split, (int)t0, (int)t1, own, false, R0, redo, DP / WD * wd, DP / WD * (wd + 1));
+            redo_query_rows<T>(kernarg_again<QueryArgs>(), rq, hk, part0, (int)t0, (int)t1, own, false, R0, redo, DP / WD * wd, DP / WD * (wd + 1));
     }
 }
 
@@ -810,7 +815,8 @@ hipError_t query_as(const QueryArgs& a, hipStream_t s) {
     auto kernel = tile_query_kernel<T, DP, WR, WK, WD, WHOLE>;
     const int rows = a.q_len * (a.n_q_heads / a.n_kv_heads), n_qtiles = (rows + X::ROWS - 1) / X::ROWS;
     const int ctx_teams = WHOLE ? 0 : a.n_ctx_splits * a.n_kv_heads;
-    const dim3 grid((unsigned)(((ctx_teams + 7) / 8 * 8 + (a.n_kv_heads + 7) / 8 * 8) * n_qtiles), (unsigned)a.n_req);
+    dim3 grid((unsigned)(((ctx_teams + 7) / 8 * 8 + (a.n_kv_heads + 7) / 8 * 8) * n_qtiles), (unsigned)a.n_req);
+    if (!WHOLE && a.n_own_splits > 0) grid = uneven_grid(a, n_qtiles);
     hipError_t e = hipFuncSetAttribute((const void*)kernel, hipFuncAttributeMaxDynamicSharedMemorySize, X::LDS);
     if (e != hipSuccess) return e;
     kernel<<<grid, X::NT, X::LDS, s>>>(a, n_qtiles);
