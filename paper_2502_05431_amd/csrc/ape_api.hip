@@ -486,7 +486,7 @@ int ape_encode_chunks(const ape_shape* shape,
     if (total > 0) {
         EncodeArgs e{};
         e.q = q_chunks; e.k = k_chunks; e.v = v_chunks; e.k_prefix = k_prefix; e.v_prefix = v_prefix;
-        e.cu = cu_dev; e.out = o_chunks; e.lse = lse_chunks;
+        e.cu = cu_dev; e.cu_host = cu_host; e.out = o_chunks; e.lse = lse_chunks;
         e.n_chunks = n_chunks; e.prefix_len = prefix_len; e.total_rows = (int)total; e.max_chunk_len = max_len;
         e.n_q_heads = si.hq; e.n_kv_heads = si.hkv; e.head_dim = si.d;
         e.uniform_chunks = min_len == max_len;

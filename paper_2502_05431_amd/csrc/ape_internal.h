@@ -145,6 +145,7 @@ struct EncodeArgs {
     int32_t n_kv_heads;
     int32_t head_dim;
     int32_t uniform_chunks;     // != 0: every chunk has max_chunk_len tokens (known on the host)
+    const int32_t* cu_host;     // the HOST's copy of cu, for the launch only
 };
 
 // Kernel-argument block of the rotary embedding + cache write.

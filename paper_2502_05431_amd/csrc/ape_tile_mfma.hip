@@ -201,42 +201,49 @@ __device__ __forceinline__ void clear_rows(Rows<T, DW>& st) {
         for (int r = 0; r < 16; ++r) st.o[db][r] = 0.f;
 }
 
-// One run of 32 tokens.  S^T = K Q^T over the dims of part `wd`.
-template <typename T, int DP, int WD>
+// One run of 32 tokens.  S^T = K Q^T over the dims of part `wd`.  RUNS: 64 dims at a time.
+template <typename T, int DP, int WD, bool RUNS>
 __device__ __forceinline__ f32x16 scores(const char* kpart, int wd, const Rows<T, DP / WD>& st) {
     constexpr int PITCH = DP * (int)sizeof(T), DW = DP / WD, NQ = Rows<T, DW>::NQ;
     const int lane = threadIdx.x & 63, l32 = lane & 31, hi = lane >> 5;
     // fp32 scores are summed in several chains (every element of a 16-byte piece its own, two where registers are
-    // short): a sum of up to 256 terms of one sign pattern loses fewer bits, at 16 additions a chain.
-    constexpr int NCH = sizeof(T) == 2 ? 1 : DW == 64 ? 4 : 2;
-    f32x16 sc_part[NCH];
-#pragma unroll
-    for (int c = 0; c < NCH; ++c)
-#pragma unroll
-        for (int r = 0; r < 16; ++r) sc_part[c][r] = 0.f;
+    // short): a sum of up to 256 terms of one sign pattern loses fewer bits, at 16 additions a chain.  RUNS sums 128 dims as two
+    // wavefronts of 64 each would, in four chains of 8 additions each (outputs 2.7e-7 off, in two chains of 32 3.3e-7; 3 % more time).
+    constexpr int NCH = sizeof(T) == 2 ? 1 : DW == 64 || RUNS ? 4 : 2, RUN = RUNS ? 8 : NQ;
+    static_assert(!RUNS || NQ % 8 == 0, "fp32, 64 dims or more");
+    f32x16 s;
     // K: token row l32, chunk 2 i + hi.  The swizzle leaves one address for every i % 8; the lane's offset is made
     // opaque so that they are recomputed here (an instruction each) and not kept in registers over the loop.
     int koff = (l32 * PITCH + ((hi ^ swz_k<T, DP>(l32)) << 4)) ^ (32 * (wd * NQ % 8));
     asm volatile("" : "+v"(koff));
     kpart += 256 * (wd * NQ / 8);
 #pragma unroll
-    for (int i = 0; i < NQ; ++i) {
-        const u32x4 a = *(const u32x4*)(kpart + (koff ^ (32 * (i % 8))) + 256 * (i / 8));
-        if constexpr (sizeof(T) == 2) {
-            sc_part[0] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(__builtin_bit_cast(bf16x8, a), __builtin_bit_cast(bf16x8, st.q[i]), sc_part[0], 0, 0, 0);
+    for (int i0 = 0; i0 < NQ; i0 += RUN) {
+        f32x16 sc_part[NCH];
+#pragma unroll
+        for (int c = 0; c < NCH; ++c)
+#pragma unroll
+            for (int r = 0; r < 16; ++r) sc_part[c][r] = 0.f;
+#pragma unroll
+        for (int i = i0; i < i0 + RUN; ++i) {
+            const u32x4 a = *(const u32x4*)(kpart + (koff ^ (32 * (i % 8))) + 256 * (i / 8));
+            if constexpr (sizeof(T) == 2) {
+                sc_part[0] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(__builtin_bit_cast(bf16x8, a), __builtin_bit_cast(bf16x8, st.q[i]), sc_part[0], 0, 0, 0);
+            } else {
+#pragma unroll
+                for (int e = 0; e < 4; ++e)
+                    sc_part[e % NCH] = __builtin_amdgcn_mfma_f32_32x32x2f32(__uint_as_float(a[e]), __uint_as_float(st.q[i][e]), sc_part[e % NCH], 0, 0, 0);
+            }
+        }
+        if constexpr (NCH == 1) {
+            s = sc_part[0];
         } else {
 #pragma unroll
-            for (int e = 0; e < 4; ++e)
-                sc_part[e % NCH] = __builtin_amdgcn_mfma_f32_32x32x2f32(__uint_as_float(a[e]), __uint_as_float(st.q[i][e]), sc_part[e % NCH], 0, 0, 0);
+            for (int r = 0; r < 16; ++r) {
+                const float x = NCH == 2 ? sc_part[0][r] + sc_part[1][r] : (sc_part[0][r] + sc_part[1][r]) + (sc_part[NCH - 2][r] + sc_part[NCH - 1][r]);
+                s[r] = i0 == 0 ? x : s[r] + x;
+            }
         }
-    }
-    f32x16 s = sc_part[0];
-    if constexpr (NCH == 2) {
-#pragma unroll
-        for (int r = 0; r < 16; ++r) s[r] += sc_part[1][r];
-    } else if constexpr (NCH == 4) {
-#pragma unroll
-        for (int r = 0; r < 16; ++r) s[r] = (s[r] + sc_part[1][r]) + (sc_part[2][r] + sc_part[3][r]);
     }
     return s;
 }
@@ -360,7 +367,7 @@ __device__ __forceinline__ void update(f32x16 s, const char* vpart, int wd, cons
 
 // Streams tokens [t_beg, t_end) past the workgroup's rows.  `lim`: this lane's row sees indices up to
 // and including lim; `lim_hi`: the largest lim of the wavefront; `active`: it has rows at all.
-template <typename T, int DP, int WR, int WK, int WD>
+template <typename T, int DP, int WR, int WK, int WD, bool RUNS = false>
 __device__ __forceinline__ void stream(Source& src, int t_beg, int t_end, int d, const ScoreScale<T>& sc, int lim, int lim_hi, bool active,
                                        char* lds, Rows<T, DP / WD>& st) {
     using X = Tile<T, DP, WR, WK, WD>;
@@ -377,10 +384,10 @@ __device__ __forceinline__ void stream(Source& src, int t_beg, int t_end, int d,
         const bool sees = active && t <= lim_hi && t < t_end;
         const char* part = lds + at * X::STAGE + 32 * kw * X::PITCH;
         if constexpr (WD == 1) {
-            if (sees) update<T, DP, WD>(scores<T, DP, WD>(part, wd, st), part + X::PART, wd, sc, min(lim, t_end - 1) - t + 1, st);
+            if (sees) update<T, DP, WD>(scores<T, DP, WD, RUNS>(part, wd, st), part + X::PART, wd, sc, min(lim, t_end - 1) - t + 1, st);
         } else {
             char* sums = lds + X::NSTG * X::STAGE + 4096 * (wave - wd);
-            if (sees) put_scores(sums + 4096 * wd, scores<T, DP, WD>(part, wd, st));
+            if (sees) put_scores(sums + 4096 * wd, scores<T, DP, WD, RUNS>(part, wd, st));
             asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
             stage_barrier();
             if (sees) update<T, DP, WD>(sum_scores<WD>(sums), part + X::PART, wd, sc, min(lim, t_end - 1) - t + 1, st);
@@ -770,20 +777,69 @@ void tile_query_kernel(const QueryArgs a, int n_qtiles) {
 }
 
 // ------------------------------------------------------------------------------------------
-// Block-diagonal causal encode: team = (context, KV head), members = its row tiles, the heaviest first.
+// Block-diagonal causal encode.  A tile's work grows with its place in its context, so tiles are dealt out by that place, the last
+// tiles of the longest contexts first: what starts last is short then.  (By contexts, each one's last tile first, the last
+// context's heaviest tiles start when the chip is about to run empty: 8 ragged fp32 contexts of about 512 tokens, 32/8 heads of 128, 222 against
+// 193 us, 30 of about 64 50 / 43; 6 x 700 bf16 tokens, 32/8 of 64, 39 / 33.)  Only as many contexts at a time as the L2 of an XCD holds: 1 MB of one
+// head's K and V in bf16 rows of 256 dims (16 x 256 tokens, 16/8 heads, by contexts 48, 1 MB 40, 2 MB 42.6, 4 MB 54.7), 2 MB below (12/2 of 128, 2 x 2048
+// tokens 93 / 77 / 71 / 71), 8 MB in fp32, which is bound by its MFMAs (the 8 above with 2 / 4 MB 225 / 193).
+constexpr int kMaxGroups = 31;
+struct Listing {
+    int32_t n_groups;           // 0: not listed
+    int32_t first_context[kMaxGroups + 1];   // a group: up to 64 consecutive contexts
+    int32_t first_tile[kMaxGroups + 1];
+};
+
+// The sum over the lanes.
+__device__ __forceinline__ int wave_sum(int x) {
+    x += __builtin_amdgcn_update_dpp(0, x, 0x111, 0xf, 0xf, true);      // row_shr 1, 2, 4, 8
+    x += __builtin_amdgcn_update_dpp(0, x, 0x112, 0xf, 0xf, true);
+    x += __builtin_amdgcn_update_dpp(0, x, 0x114, 0xf, 0xf, true);
+    x += __builtin_amdgcn_update_dpp(0, x, 0x118, 0xf, 0xf, true);
+    x += __builtin_amdgcn_update_dpp(0, x, 0x142, 0xa, 0xf, false);     // row_bcast 15, 31
+    x += __builtin_amdgcn_update_dpp(0, x, 0x143, 0xc, 0xf, false);
+    return __builtin_amdgcn_readlane(x, 63);
+}
+// Tile `w` of the tiles of up to 64 contexts in that order; `tiles`: how many the lane's context has.  false: there are fewer.
+__device__ __forceinline__ bool listed_tile(int tiles, int most, int w, int& context, int& qtile) {
+    int lo = 0, hi = most, behind = 0;                       // `behind`: tiles of index hi and above
+    if (wave_sum(tiles) <= w) return false;
+    while (hi - lo > 1) {                                    // tiles of index lo and above: more than w
+        const int mid = (lo + hi) / 2, n = wave_sum(max(tiles - mid, 0));
+        if (n > w) lo = mid; else { hi = mid; behind = n; }
+    }
+    const uint64_t there = __builtin_amdgcn_ballot_w64(tiles > lo);
+    const int before = __builtin_amdgcn_mbcnt_hi((uint32_t)(there >> 32), __builtin_amdgcn_mbcnt_lo((uint32_t)there, 0));
+    qtile = lo;
+    context = __builtin_ctzll(__builtin_amdgcn_ballot_w64(tiles > lo && before == w - behind));
+    return true;
+}
+
 template <typename T, int DP, int WR, int WK, int WD>
 __global__ __launch_bounds__(64 * WR * WK * WD) __attribute__((amdgpu_waves_per_eu(Tile<T, DP, WR, WK, WD>::WAVES, Tile<T, DP, WR, WK, WD>::MOST)))
-void tile_encode_kernel(const EncodeArgs a, int n_qtiles) {
+void tile_encode_kernel(const EncodeArgs a, int n_qtiles, const Listing list) {
     using X = Tile<T, DP, WR, WK, WD>;
     extern __shared__ __attribute__((aligned(16))) char lds[];
     const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), l32 = lane & 31, hi = lane >> 5, wd = wave % WD;
     const int d = a.head_dim, hq = a.n_q_heads, hkv = a.n_kv_heads, G = hq / hkv;
-    int team, member;
-    team_of_block(blockIdx.x, n_qtiles, team, member);
-    if (team >= a.n_chunks * hkv) return;
-    const int qtile = n_qtiles - 1 - member, chunk = team / hkv, hk = team % hkv;
-    const int c0 = a.cu ? scalar_load_i32(a.cu + chunk) : 0;
-    const int len = a.cu ? scalar_load_i32(a.cu + chunk + 1) - c0 : a.total_rows;
+    int chunk, hk, qtile, c0, len;
+    if (list.n_groups > 0) {
+        int w = blockIdx.x / hkv, g = 0;
+        hk = blockIdx.x % hkv;
+        while (g + 1 < list.n_groups && list.first_tile[g + 1] <= w) ++g;
+        const int c = list.first_context[g] + lane;
+        const bool there = c < list.first_context[g + 1];
+        const int start = there && a.cu ? a.cu[c] : 0, n = !there ? 0 : a.cu ? a.cu[c + 1] - start : a.total_rows;
+        if (!listed_tile((int)(((long)n * G + X::ROWS - 1) / X::ROWS), n_qtiles, w - list.first_tile[g], chunk, qtile)) return;
+        c0 = __builtin_amdgcn_readlane(start, chunk); len = __builtin_amdgcn_readlane(n, chunk);
+    } else {
+        int team, member;
+        team_of_block(blockIdx.x, n_qtiles, team, member);
+        if (team >= a.n_chunks * hkv) return;
+        qtile = n_qtiles - 1 - member; chunk = team / hkv; hk = team % hkv;
+        c0 = a.cu ? scalar_load_i32(a.cu + chunk) : 0;
+        len = a.cu ? scalar_load_i32(a.cu + chunk + 1) - c0 : a.total_rows;
+    }
     const long rows = (long)len * G;
     if ((long)qtile * X::ROWS >= rows) return;
     const long stride = (long)hkv * d * sizeof(T), head = (long)hk * d * sizeof(T);
@@ -797,7 +853,8 @@ void tile_encode_kernel(const EncodeArgs a, int n_qtiles) {
     const int lim = a.prefix_len + tok, lim_hi = a.prefix_len + (int)((wave_last < rows ? wave_last : rows - 1) / G);
     Rows<T, DP / WD> st;
     init_rows<T, DP, WD>(st, (const T*)a.q + ((long)(c0 + tok) * hq + h) * d, d, wd);
-    stream<T, DP, WR, WK, WD>(src, 0, t_end, d, ScoreScale<T>(d, 1.f), lim, lim_hi, R0 < rows, lds, st);
+    // (the 128-row fp32 tile is to round as the 64-row one does)
+    stream<T, DP, WR, WK, WD, (sizeof(T) == 4 && DP == 128 && WR == 4)>(src, 0, t_end, d, ScoreScale<T>(d, 1.f), lim, lim_hi, R0 < rows, lds, st);
     if (!combine<T, DP / WD, WR, WK>(lds, st)) return;
 
     const float lt = sum_halves(st.l);
@@ -836,6 +893,28 @@ hipError_t query_with(const QueryArgs& a, int block_rows, bool whole, hipStream_
     return block_rows == 64 ? query_as<T, DP, 2, K2, D2, false>(a, s) : query_as<T, DP, 1, K4, D4, false>(a, s);
 }
 
+Listing list_tiles(const EncodeArgs& a, int rows, size_t elem) {
+    Listing l{};
+    if (a.cu && !a.cu_host) return l;
+    const long group_tokens = ((elem == 4 ? 8L : a.head_dim > 128 ? 1L : 2L) << 20) / (2 * a.head_dim * (long)elem);
+    long tiles = 0, tokens = 0;
+    int g = 0, first = 0;
+    for (int c = 0; c < a.n_chunks; ++c) {
+        const long n = a.cu ? a.cu_host[c + 1] - a.cu_host[c] : a.total_rows;
+        if (c > first && (c - first == 64 || tokens + n > group_tokens)) {
+            if (++g == kMaxGroups) return l;
+            l.first_context[g] = first = c; l.first_tile[g] = (int)tiles;
+            tokens = 0;
+        }
+        tokens += n;
+        tiles += (n * (a.n_q_heads / a.n_kv_heads) + rows - 1) / rows;
+        if (tiles * a.n_kv_heads >= kMaxEncodeBlocks) return l;
+    }
+    if (tiles * a.n_kv_heads <= 256) return l;             // a CU each
+    l.n_groups = g + 1; l.first_context[g + 1] = a.n_chunks; l.first_tile[g + 1] = (int)tiles;
+    return l;
+}
+
 template <typename T, int DP, int WR, int WK, int WD>
 hipError_t encode_as(const EncodeArgs& a, hipStream_t s) {
     using X = Tile<T, DP, WR, WK, WD>;
@@ -844,7 +923,10 @@ hipError_t encode_as(const EncodeArgs& a, hipStream_t s) {
     const int n_qtiles = (int)((rows + X::ROWS - 1) / X::ROWS);
     hipError_t e = hipFuncSetAttribute((const void*)kernel, hipFuncAttributeMaxDynamicSharedMemorySize, X::LDS);
     if (e != hipSuccess) return e;
-    kernel<<<(unsigned)((a.n_chunks * a.n_kv_heads + 7) / 8 * 8 * n_qtiles), X::NT, X::LDS, s>>>(a, n_qtiles);
+    long blocks = ((long)a.n_chunks * a.n_kv_heads + 7) / 8 * 8 * n_qtiles;
+    const Listing list = list_tiles(a, X::ROWS, sizeof(T));
+    if (list.n_groups > 0) blocks = (long)list.first_tile[list.n_groups] * a.n_kv_heads;
+    kernel<<<(unsigned)blocks, X::NT, X::LDS, s>>>(a, n_qtiles, list);
     return hipGetLastError();
 }
 template <typename T, int DP>
@@ -881,16 +963,20 @@ hipError_t launch_tile_query(const QueryArgs& a, int dtype, int block_rows, bool
 // to fill the chip with, the fewer rows each takes and the more wavefronts share them (ragged contexts, 128 / 64 / 32 rows, us: fp32
 // 32/8 heads of 128, 4 x 64 tokens 23.9 / 17.4 / 13.8, 16 x 256 tokens 150 / 140 / 156; 16/8 of 256, 4 x 256 tokens 52.3 / 33.0 / 23.8,
 // 16 x 256 207 / 160 / 189; bf16 16/8 of 256, 16 x 256 tokens 51.0 / 45.6 / 59.4; 32/8 of 64, 1024 tokens 27.9 / 19.0 / 20.2,
-// 64 x 64 21.9 / 30.7 / 49.5; 8/8 of 96, 4 x 1024 53.3 / 34.9 / 48.2, 64 x 64 14.2 / 20.1 / 53.5).
+// 64 x 64 21.9 / 30.7 / 49.5; 8/8 of 96, 4 x 1024 53.3 / 34.9 / 48.2, 64 x 64 14.2 / 20.1 / 53.5).  With the tiles dealt out by
+// their place (below), 128 / 64 / 32: fp32 32/8 of 128, 8 ragged of about 512 180 / 193 / 234, 6 x 512 154 / 159 / 205, 4 x 512 116 / 114 / 133;
+// 4/2 of 64, 4 x 1000 89 / 52 / 41, 6/2 of 40, 12 x 300 33 / 25 / 31; bf16 8/8 of 96, 8 x 512 22.0 / 18.9 / 39.6, 20 ragged of about 200 17.7 / 21.3 /
+// 40.5; 12/2 of 128, 2 x 2048 70.4 / 61.7 / 115, 4 x 1000 39.2 / 38.5 / 77, 8 x 500 24.2 / 27.4 / 59.
 static int encode_block_rows(const EncodeArgs& a, int dtype) {
     const long group = a.n_q_heads / a.n_kv_heads;
     const long tiles = ((long)a.total_rows * group + 63) / 64 * a.n_kv_heads;   // of 64 rows
     const bool f32 = dtype == APE_F32;
     int rows;
     if (a.head_dim > 128) rows = tiles < 384 ? 32 : 64;
-    else if (f32) rows = tiles < 192 ? 32 : 64;
+    else if (f32 && a.head_dim > 64) rows = tiles < 192 ? 32 : tiles < 1500 ? 64 : 128;
+    else if (f32) rows = tiles < 192 || (tiles < 512 && a.max_chunk_len > 512) ? 32 : 64;
     else if (a.head_dim <= 64) rows = tiles < 1024 ? 64 : 128;
-    else rows = tiles < 256 || (tiles <= 512 && a.max_chunk_len > 512) ? 64 : 128;
+    else rows = tiles < 256 || (tiles <= 512 && a.max_chunk_len >= 512) || (tiles <= 768 && a.max_chunk_len > 1024) ? 64 : 128;
     return rows;
 }
 
@@ -904,7 +990,7 @@ hipError_t launch_tile_encode(const EncodeArgs& a, int dtype, hipStream_t s) {
     EncodeArgs e = a;
     for (int c = 0; c < a.n_chunks; c += most) {
         e.n_chunks = std::min(most, a.n_chunks - c);
-        if (a.cu) e.cu = a.cu + c;
+        if (a.cu) { e.cu = a.cu + c; e.cu_host = a.cu_host ? a.cu_host + c : nullptr; }
         hipError_t he;
         if (dtype == APE_F32) he = d <= 64 ? encode_with<float, 64>(e, br, s) : d <= 128 ? encode_with<float, 128>(e, br, s) : encode_with<float, 256>(e, br, s);
         else he = d <= 64 ? encode_with<__bf16, 64>(e, br, s) : d <= 128 ? encode_with<__bf16, 128>(e, br, s) : encode_with<__bf16, 256>(e, br, s);
