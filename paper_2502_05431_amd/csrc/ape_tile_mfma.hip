@@ -154,13 +154,30 @@ struct Source {
 
 // Starts the loads of tokens [t, t + KS) into `stage`; rows past t_end - 1 repeat that token (finite
 // data whose probabilities are zero).
-template <typename T, int DP, int WR, int WK, int WD>
+// NEAR: a stage that lies within one segment has a base that is the wavefront's and 32-bit offsets per lane, 8 vector instructions
+// per pair of loads; the general form takes 35, with a 64-bit product and four selects, and the vector ALUs are what bounds the bf16 kernels (64 rows over
+// 20 x 512 tokens, 16/8 heads of 256: VALU 43 % and MFMA 20 % of the SIMDs' time; 42.6 -> 40.2 us, 200 rows 96.3 -> 86.4).
+constexpr long kNearStride = 1 << 24;                       // 128 tokens at this stride: offsets of 32 bits
+template <typename T, int DP, int WR, int WK, int WD, bool NEAR>
 __device__ __forceinline__ void start_stage(Source& src, int t, int t_end, int d, char* stage) {
     using X = Tile<T, DP, WR, WK, WD>;
     if (src.cu) while (t >= src.b && src.e > src.b) src.next_context();
     const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
     int lane = threadIdx.x & 63;
     asm volatile("" : "+v"(lane));                          // the lane's offsets are recomputed here, not kept over the loop
+    if (NEAR && __builtin_expect(t + X::KS <= t_end && (t + X::KS <= src.b || t >= src.b) && t + X::KS <= src.e && src.stride <= kNearStride, 1)) {
+        const bool in_a = t + X::KS <= src.b;
+        const char *k = (in_a ? src.ka : src.kb) + (long)t * src.stride, *v = (in_a ? src.va : src.vb) + (long)t * src.stride;
+        const uint32_t width = d * (uint32_t)sizeof(T), row0 = (wave * 64 + lane) / X::CPR, from0 = row0 * (uint32_t)src.stride;
+#pragma unroll
+        for (int i = 0; i < X::LPT; ++i) {
+            const int at = (i * X::NW + wave) * 64, down = i * X::NW * 64 / X::CPR;
+            const uint32_t ck = 16 * (lane % X::CPR ^ swz_k<T, DP>(row0 + down)), cv = 16 * (lane % X::CPR ^ swz_v<T, DP>(row0 + down));
+            load_lds16(k + down * src.stride, from0 + (ck < width ? ck : 0), stage + at * 16);
+            load_lds16(v + down * src.stride, from0 + (cv < width ? cv : 0), stage + X::PART + at * 16);
+        }
+        return;
+    }
     const bool beyond = min(t + X::KS, t_end) > src.e;      // a third context begins inside the stage
 #pragma unroll
     for (int i = 0; i < X::LPT; ++i) {
@@ -367,19 +384,19 @@ __device__ __forceinline__ void update(f32x16 s, const char* vpart, int wd, cons
 
 // Streams tokens [t_beg, t_end) past the workgroup's rows.  `lim`: this lane's row sees indices up to
 // and including lim; `lim_hi`: the largest lim of the wavefront; `active`: it has rows at all.
-template <typename T, int DP, int WR, int WK, int WD, bool RUNS = false>
+template <typename T, int DP, int WR, int WK, int WD, bool NEAR, bool RUNS = false>
 __device__ __forceinline__ void stream(Source& src, int t_beg, int t_end, int d, const ScoreScale<T>& sc, int lim, int lim_hi, bool active,
                                        char* lds, Rows<T, DP / WD>& st) {
     using X = Tile<T, DP, WR, WK, WD>;
     const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), kw = wave / WD % WK, wd = wave % WD;
     const int n = (t_end - t_beg + X::KS - 1) / X::KS;
     for (int j = 0; j < X::NSTG - 1 && j < n; ++j)
-        start_stage<T, DP, WR, WK, WD>(src, t_beg + j * X::KS, t_end, d, lds + j * X::STAGE);
+        start_stage<T, DP, WR, WK, WD, NEAR>(src, t_beg + j * X::KS, t_end, d, lds + j * X::STAGE);
     int at = 0, to = X::NSTG - 1;                           // ring positions of stage j and of the one whose loads start
     for (int j = 0; j < n; ++j) {
         if (j + X::NSTG - 2 < n) wait_loads<(X::NSTG - 2) * 2 * X::LPT>(); else wait_loads<0>();
         stage_barrier();                                     // stage j has landed for every wavefront, all of which are done with stage j - 1
-        if (j + X::NSTG - 1 < n) start_stage<T, DP, WR, WK, WD>(src, t_beg + (j + X::NSTG - 1) * X::KS, t_end, d, lds + to * X::STAGE);
+        if (j + X::NSTG - 1 < n) start_stage<T, DP, WR, WK, WD, NEAR>(src, t_beg + (j + X::NSTG - 1) * X::KS, t_end, d, lds + to * X::STAGE);
         const int t = t_beg + j * X::KS + 32 * kw;
         const bool sees = active && t <= lim_hi && t < t_end;
         const char* part = lds + at * X::STAGE + 32 * kw * X::PITCH;
@@ -685,6 +702,9 @@ template <typename T, int DP, int WR, int WK, int WD, bool WHOLE>
 __global__ __launch_bounds__(64 * WR * WK * WD) __attribute__((amdgpu_waves_per_eu(Tile<T, DP, WR, WK, WD>::WAVES, Tile<T, DP, WR, WK, WD>::MOST)))
 void tile_query_kernel(const QueryArgs a, int n_qtiles) {
     using X = Tile<T, DP, WR, WK, WD>;
+    // Where streams are short and nothing but the code is between them and the first result it costs more than it saves (general / near, us: 16 rows over
+    // 3 x 100 tokens, 32/8 bf16 heads of 64, 10.6 / 10.9; 4 x 32, 4/2 fp32 heads of 64, 14.9 / 15.2; a decode step over 20 x 512, bf16 heads of 64, 12.4 / 12.7).
+    constexpr bool NEAR = !WHOLE && (X::PITCH > 128 || WR > 1);
     extern __shared__ __attribute__((aligned(16))) char lds[];
     const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), l32 = lane & 31, hi = lane >> 5;
     const int d = a.head_dim, hq = a.n_q_heads, hkv = a.n_kv_heads, G = hq / hkv, q_len = a.q_len;
@@ -716,14 +736,14 @@ void tile_query_kernel(const QueryArgs a, int n_qtiles) {
     auto contexts = [&](long t0, long t1) {
         Source src;
         src.init_ctx(kv, (int)t0, stride, head);
-        stream<T, DP, WR, WK, WD>(src, (int)t0, (int)t1, d, ScoreScale<T>(d, kv.temperature), (int)t1 - 1, (int)t1 - 1, R0 < rows, lds, st);
+        stream<T, DP, WR, WK, WD, NEAR>(src, (int)t0, (int)t1, d, ScoreScale<T>(d, kv.temperature), (int)t1 - 1, (int)t1 - 1, R0 < rows, lds, st);
     };
     auto sequence = [&]() {
         const int off = kv.prefix_len + kv.self_len - q_len; // index of query token 0
         const int tile_hi = min(qtile * X::ROWS + X::ROWS - 1, rows - 1) / G;
         Source src;
         src.init_seq(kv.k_prefix, kv.v_prefix, kv.prefix_len, kv.k_self, kv.v_self, kv.self_len, stride, head);
-        stream<T, DP, WR, WK, WD>(src, 0, off + tile_hi + 1, d, ScoreScale<T>(d, 1.f), off + tok, off + min(R0 + 31, rows - 1) / G, R0 < rows, lds, st);
+        stream<T, DP, WR, WK, WD, NEAR>(src, 0, off + tile_hi + 1, d, ScoreScale<T>(d, 1.f), off + tok, off + min(R0 + 31, rows - 1) / G, R0 < rows, lds, st);
     };
 
     if constexpr (WHOLE) {
@@ -853,8 +873,10 @@ void tile_encode_kernel(const EncodeArgs a, int n_qtiles, const Listing list) {
     const int lim = a.prefix_len + tok, lim_hi = a.prefix_len + (int)((wave_last < rows ? wave_last : rows - 1) / G);
     Rows<T, DP / WD> st;
     init_rows<T, DP, WD>(st, (const T*)a.q + ((long)(c0 + tok) * hq + h) * d, d, wd);
+    // (general / near, us, ragged bf16: 20 contexts of about 200 tokens, 32/8 heads of 64, 21.5 / 22.1, 4 of 256, 16/8 of 256 in tiles of 32 rows, 17.7 / 18.4)
+    constexpr bool NEAR = X::PITCH > 128 && (sizeof(T) == 4 || WR > 1);
     // (the 128-row fp32 tile is to round as the 64-row one does)
-    stream<T, DP, WR, WK, WD, (sizeof(T) == 4 && DP == 128 && WR == 4)>(src, 0, t_end, d, ScoreScale<T>(d, 1.f), lim, lim_hi, R0 < rows, lds, st);
+    stream<T, DP, WR, WK, WD, NEAR, (sizeof(T) == 4 && DP == 128 && WR == 4)>(src, 0, t_end, d, ScoreScale<T>(d, 1.f), lim, lim_hi, R0 < rows, lds, st);
     if (!combine<T, DP / WD, WR, WK>(lds, st)) return;
 
     const float lt = sum_halves(st.l);
