@@ -146,6 +146,11 @@ QueryPlan plan_query(int base_workgroups, long max_ctx, int min_len, int target_
     return p;
 }
 
+// The shortest split of the tile kernels.
+// (16 rows over 2048 tokens, 2/2 fp32 heads of 256: splits of 64 / 128 / 256 tokens 18.9 / 25.8 / 40.2 us; 40 bf16 rows, 6/2
+// heads of 40: 14.5 / 14.7 / 17.2)
+int tile_shortest_split(const ShapeInfo& si) { return si.dtype == APE_F32 && si.d > 128 ? 64 : 128; }
+
 // Split plan of the tile kernels, queries and decode alike: as many workgroups as fit the chip at once, of splits that are
 // long against a workgroup's fixed cost.  Measured with 64 / 32 rows per tile: 64 bf16 rows over 10240 tokens, 16/8 heads of
 // 256, 512 workgroups 49.9 us, 256 51.4; 12/2 heads of 128, 29.0 / 25.9 (its partial results weigh more than the second
@@ -159,9 +164,7 @@ QueryPlan tile_plan(const ShapeInfo& si, int batch, int q_len, long max_ctx, lon
     // the first others have ended (64 rows, splits filling all / all but those slots, us: 16/8 bf16 heads of 256 over 10240 tokens
     // 52.5 / 47.3, 32/8 of 64 28.8 / 25.3, 16/8 fp32 heads of 256 over 4096 78 / 68).
     const long n = full / base, target = n >= 3 && !half ? (n - 1) * base : n == 2 ? 2 * base : full;
-    // (16 rows over 2048 tokens, 2/2 fp32 heads of 256: splits of 64 / 128 / 256 tokens 18.9 / 25.8 / 40.2 us; 40 bf16 rows, 6/2
-    // heads of 40: 14.5 / 14.7 / 17.2)
-    QueryPlan p = plan_query((int)base, max_ctx, f32 && si.d > 128 ? 64 : 128, (int)(target < base * max_splits ? target : base * max_splits));
+    QueryPlan p = plan_query((int)base, max_ctx, tile_shortest_split(si), (int)(target < base * max_splits ? target : base * max_splits));
     p.block_rows = bm;
     return p;
 }
@@ -279,8 +282,9 @@ bool uneven_batch(const ape_request* reqs, int nb, double ratio) {
     return nb > 1 && (double)longest * nb > ratio * (double)total;
 }
 
-// The splits of a launch of nb requests; false: there are none to deal out.
-bool plan_uneven(const ape_request* reqs, int nb, long splits, UnevenPlan& p) {
+// The splits of a launch of nb requests; false: there are none to deal out.  `shortest`: what a split has at least, as in the even plan
+// (10 fp32 decode steps of 1 to 19 x 203 tokens, 16/8 heads of 256, with the flash kernels' 256 for all 36.4 us, 5 of 1 to 5 x 397, 2/2 heads, 35.6).
+bool plan_uneven(const ape_request* reqs, int nb, long splits, int shortest, UnevenPlan& p) {
     auto ctx = [&](int i) { return reqs[i].n_chunks > 0 ? (long)reqs[i].total_ctx_len : 0L; };
     long longest = 0;
     for (int i = 0; i < nb; ++i)
@@ -290,9 +294,9 @@ bool plan_uneven(const ape_request* reqs, int nb, long splits, UnevenPlan& p) {
         for (int i = 0; i < nb; ++i) n += (ctx(i) + len - 1) / len;
         return n;
     };
-    // the shortest length, in units of 64 tokens: 256 tokens at least, and kMaxSplits of it hold the longest
+    // the shortest length, in units of 64 tokens: kMaxSplits of it hold the longest
     long lo = (longest + 64 * kMaxSplits - 1) / (64 * kMaxSplits), hi = (longest + 63) / 64;
-    if (lo < 4) lo = 4;
+    if (lo < shortest / 64) lo = shortest / 64;
     while (lo < hi) {
         const long mid = (lo + hi) / 2;
         if (count(64 * mid) <= splits) hi = mid; else lo = mid + 1;
@@ -559,7 +563,7 @@ static int run_query(const ShapeInfo& si, const ape_request* reqs, int batch, in
         a.n_req = nb; a.q_len = q_len; a.n_q_heads = si.hq; a.n_kv_heads = si.hkv; a.head_dim = si.d;
         a.n_ctx_splits = plan.n_ctx_splits; a.ctx_split_len = plan.ctx_split_len;
         a.units_total = (int)units; a.req_base = b0;
-        if (uneven && plan_uneven(reqs + b0, nb, splits, up)) {
+        if (uneven && plan_uneven(reqs + b0, nb, splits, si.tile ? tile_shortest_split(si) : 256, up)) {
             a.n_own_splits = m.n_own_splits = up.n_splits;
             a.n_ctx_splits = up.most;
             a.part_lse = (float*)((char*)workspace + align_up((size_t)(up.n_splits + nb) * q_len * si.hq * si.d * sizeof(float), kWsAlign));
