@@ -129,8 +129,8 @@ KvView to_view(const ape_request* r) {
 }
 
 // Number of context splits: enough workgroups to fill 256 CUs a few times over, never more than
-// kMaxSplits, never splits shorter than `min_len` tokens.  Depends on sizes only.
-QueryPlan plan_query(int base_workgroups, long max_ctx, int min_len, int target_workgroups) {
+// kMaxSplits, never splits shorter than `min_len` tokens, all of whole units of `unit` tokens.  Depends on sizes only.
+QueryPlan plan_query(int base_workgroups, long max_ctx, int min_len, int target_workgroups, int unit = 64) {
     QueryPlan p{};
     if (max_ctx <= 0) { p.n_ctx_splits = 0; p.ctx_split_len = 64; p.n_splits_total = 1; return p; }
     int want = ceil_div(target_workgroups, base_workgroups > 0 ? base_workgroups : 1);
@@ -140,7 +140,7 @@ QueryPlan plan_query(int base_workgroups, long max_ctx, int min_len, int target_
     if (n > kMaxSplits) n = kMaxSplits;
     p.n_bound = n;                                     // rounding the length up to whole tiles can only lower the count
     long len = (max_ctx + n - 1) / n;
-    len = (len + 63) / 64 * 64;                        // tiles never straddle a split
+    len = (len + unit - 1) / unit * unit;              // tiles never straddle a split
     n = ceil_div(max_ctx, len);
     p.n_ctx_splits = n; p.ctx_split_len = (int)len; p.n_splits_total = n + 1;
     return p;
@@ -164,7 +164,12 @@ QueryPlan tile_plan(const ShapeInfo& si, int batch, int q_len, long max_ctx, lon
     // the first others have ended (64 rows, splits filling all / all but those slots, us: 16/8 bf16 heads of 256 over 10240 tokens
     // 52.5 / 47.3, 32/8 of 64 28.8 / 25.3, 16/8 fp32 heads of 256 over 4096 78 / 68).
     const long n = full / base, target = n >= 3 && !half ? (n - 1) * base : n == 2 ? 2 * base : full;
-    QueryPlan p = plan_query((int)base, max_ctx, tile_shortest_split(si), (int)(target < base * max_splits ? target : base * max_splits));
+    // Splits are whole stages of the form that runs (rounded to 64 / to the stage, us: 64 rows over 20 x 512, 16/8 bf16 heads of 256, stages of 32 tokens,
+    // 41.2 / 39.3; 64 fp32 rows over 4096, 32/8 heads of 128 61.3 / 56.9, 16/8 of 256 64.7 / 59.9; 5 bf16 rows over 20 x 512, 8/8 heads of 96, stages of
+    // 128, 22.7 / 16.6, 12/2 of 128 14.3 / 13.5).
+    const bool wide = (si.d <= 64 ? 64 : si.d <= 128 ? 128 : 256) * (f32 ? 4 : 2) > 256;
+    const int stage = wide || bm == 128 ? 32 : 4096 / bm;
+    QueryPlan p = plan_query((int)base, max_ctx, tile_shortest_split(si), (int)(target < base * max_splits ? target : base * max_splits), stage);
     p.block_rows = bm;
     return p;
 }
