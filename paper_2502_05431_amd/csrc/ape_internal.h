@@ -49,7 +49,7 @@ struct QueryArgs {
     int32_t n_kv_heads;
     int32_t head_dim;
     int32_t n_ctx_splits;       // splits of the context group; split index n_ctx_splits is prefix + self
-    int32_t ctx_split_len;      // context tokens per split (multiple of 64)
+    int32_t ctx_split_len;      // context tokens per split (whole stages or blocks of the kernel)
     const int32_t* split_ranges; // NULL: split s covers tokens [s*ctx_split_len, ...) of the pooled contexts.
                                 // Else (one request only) DEVICE [2*n_ctx_splits]: split s covers tokens
                                 // [split_ranges[2s], split_ranges[2s+1]) of the pooled contexts; empty if equal

@@ -25,9 +25,9 @@
 // What bounds it: the MFMAs once the streams are long (fp32: 64 cycles for 4096 multiply-adds; 1.5 times the
 // attention's own count for bf16), the fixed chain of a launch, first loads and merge for a short query.  Against the
 // vector-ALU kernels, which give a wavefront one row and read every K/V byte once per row (same card, same inputs):
-// fp32 encode of eight contexts of about 512 tokens, 32/8 heads of 128: 2754 -> 225 us (75 TFLOP/s; the vendor's fp32 GEMM
-// reaches 154); 64 bf16 rows over 20 x 512 tokens, 16/8 heads of 256: 14200 -> 46 us (1.9 TB/s); a fp32 decode step over 4096
-// tokens, 16/8 heads of 256: 38 us, 88 by one wavefront per workgroup; 16 fp32 rows over 4 x 32 tokens, 4/2 heads of 64: 47.8 -> 14.8 us.
+// fp32 encode of eight contexts of about 512 tokens, 32/8 heads of 128: 2754 -> 180 us (94 TFLOP/s; the vendor's fp32 GEMM
+// reaches 154); 64 bf16 rows over 20 x 512 tokens, 16/8 heads of 256: 14200 -> 39 us (2.1 TB/s); a fp32 decode step over 4096
+// tokens, 16/8 heads of 256: 28 us, 88 by one wavefront per workgroup; 16 fp32 rows over 4 x 32 tokens, 4/2 heads of 64: 47.8 -> 14.8 us.
 #include "ape_mfma.h"
 
 #include <math.h>
