@@ -90,8 +90,10 @@ __global__ __launch_bounds__(256, 2) void encode_walk_kernel(const EncodeArgs a,
     Keys x;
     x.P = a.prefix_len;
     x.stride = (uint32_t)a.n_kv_heads * ROW;
-    x.kp = (const char*)a.k_prefix + hk * ROW; x.vp = (const char*)a.v_prefix + hk * ROW;
-    x.kc = (const char*)a.k + (long)c0 * x.stride + hk * ROW; x.vc = (const char*)a.v + (long)c0 * x.stride + hk * ROW;
+    // (scalar registers: the blocks' addresses are then scalar work; 512 ragged contexts of about 256 tokens 743 / 731 us)
+    auto uniform = [&](const void* p, long at) { return (const char*)uniform_address((const char*)p + at); };
+    x.kp = uniform(a.k_prefix, hk * ROW); x.vp = uniform(a.v_prefix, hk * ROW);
+    x.kc = uniform(a.k, (long)c0 * x.stride + hk * ROW); x.vc = uniform(a.v, (long)c0 * x.stride + hk * ROW);
     auto t_end_of = [&](int q) { return x.P + min((q + 1) * toks, len); };
     char* const qbuf = lds + NSLOT * SLOT + wave * QBUF;
 

@@ -27,10 +27,13 @@ __device__ __forceinline__ void load_lds16(const char* src, const char* lds) {
     const uint32_t m0v = (uint32_t)(uintptr_t)(const __attribute__((address_space(3))) char*)lds;
     asm volatile("s_mov_b32 m0, %1\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %0, off" :: "v"(src), "s"(m0v) : "m0");
 }
-// The same from a wavefront-uniform base and a 32-bit offset per lane.
+// The same from a wavefront-uniform base and a 32-bit offset per lane.  Where the base comes from vector registers, the v_readfirstlane that
+// writes its scalar registers must be five wait states ahead of the load that reads them.  The compiler keeps that distance for
+// its own loads and does not look inside the statement, so they are in here: one for s_mov, four for s_nop 3 (and one of
+// them is what M0 needs).
 __device__ __forceinline__ void load_lds16(const char* base, uint32_t off, const char* lds) {
     const uint32_t m0v = (uint32_t)(uintptr_t)(const __attribute__((address_space(3))) char*)lds;
-    asm volatile("s_mov_b32 m0, %2\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %0, %1" :: "v"(off), "s"(uniform_address(base)), "s"(m0v) : "m0");
+    asm volatile("s_mov_b32 m0, %2\n\ts_nop 3\n\tglobal_load_lds_dwordx4 %0, %1" :: "v"(off), "s"(uniform_address(base)), "s"(m0v) : "m0");
 }
 
 // All but the youngest N vector-memory operations of this wavefront are complete (they complete in order).

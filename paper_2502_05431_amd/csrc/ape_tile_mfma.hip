@@ -154,8 +154,8 @@ struct Source {
 
 // Starts the loads of tokens [t, t + KS) into `stage`; rows past t_end - 1 repeat that token (finite
 // data whose probabilities are zero).
-// NEAR: a stage that lies within one segment has a base that is the wavefront's and 32-bit offsets per lane, 8 vector instructions
-// per pair of loads; the general form takes 35, with a 64-bit product and four selects, and the vector ALUs are what bounds the bf16 kernels (64 rows over
+// NEAR: a stage that lies within one segment has a base that is the wavefront's, in scalar registers, and 32-bit offsets per lane: behind the
+// first, 7 vector instructions per pair of loads in rows of 512 bytes, 10 of 1024, 1 below; the general form takes 35, with a 64-bit product and four selects, and the vector ALUs are what bounds the bf16 kernels (64 rows over
 // 20 x 512 tokens, 16/8 heads of 256: VALU 43 % and MFMA 20 % of the SIMDs' time; 42.6 -> 40.2 us, 200 rows 96.3 -> 86.4).
 constexpr long kNearStride = 1 << 24;                       // 128 tokens at this stride: offsets of 32 bits
 template <typename T, int DP, int WR, int WK, int WD, bool NEAR>
@@ -869,6 +869,10 @@ void tile_encode_kernel(const EncodeArgs a, int n_qtiles, const Listing list) {
     const long tile_last = (long)qtile * X::ROWS + X::ROWS - 1, wave_last = R0 + 31;
     Source src;
     src.init_seq(a.k_prefix, a.v_prefix, a.prefix_len, (const T*)a.k + (long)c0 * hkv * d, (const T*)a.v + (long)c0 * hkv * d, len, stride, head);
+    // (in scalar registers: left in vector registers, as c0 would have them, every near load costs a 64-bit addition there and two moves: 18
+    // vector instructions per pair; ragged bf16 encodes of 4 x 1000 tokens, 16/8 heads of 256, 111.0 / 108.0 us, 12/2 of 128 58.6 / 57.0; fp32 within 1 %)
+    src.ka = (const char*)uniform_address(src.ka); src.va = (const char*)uniform_address(src.va);
+    src.kb = (const char*)uniform_address(src.kb); src.vb = (const char*)uniform_address(src.vb);
     const int t_end = a.prefix_len + (int)((tile_last < rows ? tile_last : rows - 1) / G) + 1;
     const int lim = a.prefix_len + tok, lim_hi = a.prefix_len + (int)((wave_last < rows ? wave_last : rows - 1) / G);
     Rows<T, DP / WD> st;
