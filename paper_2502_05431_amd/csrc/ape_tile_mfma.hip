@@ -695,7 +695,7 @@ __device__ __forceinline__ void redo_encode_rows(__attribute__((address_space(4)
 
 // ------------------------------------------------------------------------------------------
 // Query prefill and decode: team = (split, KV head), members = tiles of the query rows; the context
-// teams come first, the prefix + own ones follow.  grid: x as in the flash prefill, y = request.
+// teams come first, the prefix + own ones follow.  grid: x = teams x row tiles, y = request.
 // WHOLE: over short contexts one workgroup takes its rows past the contexts and then past the prefix and the own tokens and
 // writes their output: team = KV head, no partial results, no merge.
 template <typename T, int DP, int WR, int WK, int WD, bool WHOLE>
@@ -709,15 +709,18 @@ void tile_query_kernel(const QueryArgs a, int n_qtiles) {
     const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), l32 = lane & 31, hi = lane >> 5;
     const int d = a.head_dim, hq = a.n_q_heads, hkv = a.n_kv_heads, G = hq / hkv, q_len = a.q_len;
     const bool uneven = !WHOLE && a.n_own_splits > 0;        // (then the whole batch lies in x)
-    const int ctx_teams = WHOLE ? 0 : (uneven ? a.n_own_splits : a.n_ctx_splits) * hkv, ctx_blocks = (ctx_teams + 7) / 8 * 8 * n_qtiles;
+    const int ctx_teams = WHOLE ? 0 : (uneven ? a.n_own_splits : a.n_ctx_splits) * hkv;
     int team, qtile, split, rq = blockIdx.y;
-    if ((int)blockIdx.x < ctx_blocks) {
-        team_of_block(blockIdx.x, n_qtiles, team, qtile);
-        if (team >= ctx_teams) return;
+    // Teams are numbered on from the splits' to the prefix + own tokens', which so start on the XCDs where the splits' end: a plan that fills
+    // the chip leaves its slots there (dealt out anew from the first XCD on, those are full and the call takes a second round: fp32, 2/2
+    // heads of 256, 64 rows over 10000 tokens, 126 + 2 teams of two row tiles, 42.0 / 29.9 us, 256 rows over 3200, 30 + 2 of eight, 67.3 / 40.3;
+    // 64 bf16 rows over 600, 12/2 of 128, 17.1 / 11.5).
+    team_of_block(blockIdx.x, n_qtiles, team, qtile);
+    if (team < ctx_teams) {
         if (uneven) own_split(a.n_req, team / hkv, rq, split);
         else split = team / hkv;
     } else {
-        team_of_block(blockIdx.x - ctx_blocks, n_qtiles, team, qtile);
+        team -= ctx_teams;
         if (team >= (uneven ? a.n_req : 1) * hkv) return;
         split = a.n_ctx_splits;
         if (uneven) rq = team / hkv;
@@ -897,9 +900,9 @@ hipError_t query_as(const QueryArgs& a, hipStream_t s) {
     using X = Tile<T, DP, WR, WK, WD>;
     auto kernel = tile_query_kernel<T, DP, WR, WK, WD, WHOLE>;
     const int rows = a.q_len * (a.n_q_heads / a.n_kv_heads), n_qtiles = (rows + X::ROWS - 1) / X::ROWS;
-    const int ctx_teams = WHOLE ? 0 : a.n_ctx_splits * a.n_kv_heads;
-    dim3 grid((unsigned)(((ctx_teams + 7) / 8 * 8 + (a.n_kv_heads + 7) / 8 * 8) * n_qtiles), (unsigned)a.n_req);
-    if (!WHOLE && a.n_own_splits > 0) grid = uneven_grid(a, n_qtiles);
+    const bool uneven = !WHOLE && a.n_own_splits > 0;
+    const long teams = (long)(WHOLE ? 1 : uneven ? a.n_own_splits + a.n_req : a.n_ctx_splits + 1) * a.n_kv_heads;
+    const dim3 grid((unsigned)((teams + 7) / 8 * 8 * n_qtiles), uneven ? 1u : (unsigned)a.n_req);
     hipError_t e = hipFuncSetAttribute((const void*)kernel, hipFuncAttributeMaxDynamicSharedMemorySize, X::LDS);
     if (e != hipSuccess) return e;
     kernel<<<grid, X::NT, X::LDS, s>>>(a, n_qtiles);
