@@ -264,61 +264,6 @@ QueryPlan prefill_plan(const ShapeInfo& si, int batch, int q_len, long max_ctx) 
     return p;
 }
 
-// Split plan of an uneven batch: the even plan cuts every request into the splits of the longest, whose workgroups then are
-// what the call ends with (one CU alone reads 40 GB/s, whatever it has in flight).  Here every request has as many splits as its
-// length asks for, of about one length.  A decode step wants 512 workgroups, all of them resident (32/8 heads, even plan | 256 / 512 /
-// 1024, us: 8 requests of about 4096 tokens 43.5 | 34.9 / 33.4 / 36.9; 4 of 32K 85.6 | 69.0 / 69.4 / 71.2; 20 of 1 to 5 x 4096
-// 226 | 201 / 186 / 180; 24 of 1 to 7 x 1024 113 | 91.5 / 82.1 / 88.7), a prefill as many as the even plan has (4 x 64 rows over about 4096 tokens 46.1 |
-// 41.8, with 512 42.5).  Its partial results take no more room than the even plan's.  Where that leaves a decode step with less than
-// two splits a request (one per CU is what the even plan has for 32 requests) and the longest is far from the mean, the batch goes
-// out in two launches, each with all of the room: 32 of 2 to 14 x 1024 220 / 183, of 1 to 7 116 / 113; 32 of 10K to 15K tokens stay 280 / 288.
-struct UnevenPlan {
-    int n_splits, most, first[kMaxReqPerLaunch + 1], len[kMaxReqPerLaunch];
-};
-
-// Whether the longest request is more than `ratio` times the mean.
-bool uneven_batch(const ape_request* reqs, int nb, double ratio) {
-    long total = 0, longest = 0;
-    for (int i = 0; i < nb; ++i) {
-        const long m = reqs[i].n_chunks > 0 ? reqs[i].total_ctx_len : 0;
-        total += m;
-        if (m > longest) longest = m;
-    }
-    return nb > 1 && (double)longest * nb > ratio * (double)total;
-}
-
-// The splits of a launch of nb requests; false: there are none to deal out.  `shortest`: what a split has at least, as in the even plan
-// (10 fp32 decode steps of 1 to 19 x 203 tokens, 16/8 heads of 256, with the flash kernels' 256 for all 36.4 us, 5 of 1 to 5 x 397, 2/2 heads, 35.6).
-bool plan_uneven(const ape_request* reqs, int nb, long splits, int shortest, UnevenPlan& p) {
-    auto ctx = [&](int i) { return reqs[i].n_chunks > 0 ? (long)reqs[i].total_ctx_len : 0L; };
-    long longest = 0;
-    for (int i = 0; i < nb; ++i)
-        if (ctx(i) > longest) longest = ctx(i);
-    auto count = [&](long len) {
-        long n = 0;
-        for (int i = 0; i < nb; ++i) n += (ctx(i) + len - 1) / len;
-        return n;
-    };
-    // the shortest length, in units of 64 tokens: kMaxSplits of it hold the longest
-    long lo = (longest + 64 * kMaxSplits - 1) / (64 * kMaxSplits), hi = (longest + 63) / 64;
-    if (lo < shortest / 64) lo = shortest / 64;
-    while (lo < hi) {
-        const long mid = (lo + hi) / 2;
-        if (count(64 * mid) <= splits) hi = mid; else lo = mid + 1;
-    }
-    p.first[0] = 0; p.most = 0;
-    for (int i = 0; i < nb; ++i) {
-        int n = ceil_div(ctx(i), 64 * lo);
-        p.len[i] = n > 0 ? ceil_div(ctx(i), 64L * n) * 64 : 64;    // its splits are of one length
-        n = ceil_div(ctx(i), p.len[i]);                            // (no more than before)
-        p.first[i + 1] = p.first[i] + n;
-        if (n > p.most) p.most = n;
-    }
-    p.n_splits = p.first[nb];
-    static_assert(kMaxReqPerLaunch * kMaxSplits < 1 << 16, "first_split");
-    return p.most > 1 && p.n_splits <= splits;
-}
-
 // Splits of the tree entry point: the contexts of every node that holds contexts are cut into
 // runs of `len` tokens; `len` is what the flat entry points would use for the same sizes, so a
 // one-node tree runs exactly like them.  max_splits bounds the splits in use from sizes only:
@@ -539,20 +484,20 @@ static int run_query(const ShapeInfo& si, const ape_request* reqs, int batch, in
     float* part_lse = (float*)((char*)workspace + align_up((size_t)units * plan.n_splits_total * si.d * sizeof(float), kWsAlign));
 
     const int whole = whole_block_rows(si, plan.n_ctx_splits, batch, q_len, max_ctx, own);
-    const bool uneven = !whole && (si.mfma || si.tile) && plan.n_ctx_splits > 0 && uneven_batch(reqs, batch, 1.125);
-    int per_launch = kMaxReqPerLaunch;
-    long splits = (long)plan.n_ctx_splits * batch;
+    // An uneven batch is dealt out.  A decode step on the flash kernels asks for what suits it, any other call for as many splits as the even
+    // plan has (4 prefills of 64 rows over about 4096 tokens, 32/8 heads, even / so / 512 workgroups 46.1 / 41.8 / 42.5 us).
+    auto ctx = [&](int i) { return reqs[i].n_chunks > 0 ? (long)reqs[i].total_ctx_len : 0L; };
+    const bool uneven = !whole && (si.mfma || si.tile) && plan.n_ctx_splits > 0 && uneven_batch(ctx, batch);
+    DealRule rule{};
+    UnevenCall call{kMaxReqPerLaunch, 0};
     UnevenPlan up;
-    if (uneven && decode && si.mfma) {
-        const long slots = (long)plan.n_splits_total * batch;      // of one request each
-        if (per_launch > batch) per_launch = batch;
-        auto room = [&](long target) { const long n = target / si.hkv; return n < slots - per_launch ? n : slots - per_launch; };
-        splits = room(512);
-        if (splits < 2 * per_launch && uneven_batch(reqs, batch, 1.6)) {
-            per_launch = (per_launch + 1) / 2;
-            splits = room(256);
-        }
+    if (uneven) {
+        rule = {si.tile ? tile_shortest_split(si) : 256, 64, plan.n_ctx_splits, plan.ctx_split_len,
+                (long)si.hkv * ceil_div((long)q_len * si.group, plan.block_rows > 0 ? plan.block_rows : 128)};
+        call.splits = (long)plan.n_ctx_splits * batch;
+        if (decode && si.mfma) call = uneven_decode_call(ctx, batch, si.hkv, rule);
     }
+    const int per_launch = call.per_launch;
     for (int b0 = 0; b0 < batch; b0 += per_launch) {
         const int nb = batch - b0 < per_launch ? batch - b0 : per_launch;
         QueryArgs a{};
@@ -568,7 +513,7 @@ static int run_query(const ShapeInfo& si, const ape_request* reqs, int batch, in
         a.n_req = nb; a.q_len = q_len; a.n_q_heads = si.hq; a.n_kv_heads = si.hkv; a.head_dim = si.d;
         a.n_ctx_splits = plan.n_ctx_splits; a.ctx_split_len = plan.ctx_split_len;
         a.units_total = (int)units; a.req_base = b0;
-        if (uneven && plan_uneven(reqs + b0, nb, splits, si.tile ? tile_shortest_split(si) : 256, up)) {
+        if (uneven && plan_uneven([&](int i) { return ctx(b0 + i); }, nb, call.splits, rule, up)) {
             a.n_own_splits = m.n_own_splits = up.n_splits;
             a.n_ctx_splits = up.most;
             a.part_lse = (float*)((char*)workspace + align_up((size_t)(up.n_splits + nb) * q_len * si.hq * si.d * sizeof(float), kWsAlign));

@@ -6,6 +6,7 @@
 #include <stdint.h>
 
 #include "ape.h"
+#include "ape_plan.h"
 
 namespace ape {
 
@@ -26,8 +27,6 @@ struct KvView {
     float scale;
 };
 
-constexpr int kMaxReqPerLaunch = 32;     // requests whose descriptors travel in one kernel-argument block
-constexpr int kMaxSplits = 64;           // upper bound of context splits per (request, head)
 constexpr int kWsAlign = 256;
 constexpr long kMaxEncodeBlocks = 1L << 24;     // workgroups of a matrix-core encode launch (256 threads each)
 
