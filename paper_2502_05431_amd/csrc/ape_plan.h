@@ -57,9 +57,12 @@ bool deal_splits(const Ctx& ctx, int nb, long splits, const DealRule& r, UnevenP
     return p.most > 1 && p.n_splits <= splits;
 }
 
+// ... within what a launch holds.
 template <class Ctx>
 bool plan_uneven(const Ctx& ctx, int nb, long splits, const DealRule& r, UnevenPlan& p) {
-    return deal_splits(ctx, nb, splits, r, p);
+    if (!deal_splits(ctx, nb, splits, r, p)) return false;
+    if ((p.n_splits + nb) * r.tiles >= 1L << 24) return false;       // (a launch holds 2^32 work items in x, and the whole batch lies there)
+    return true;
 }
 
 // Requests per launch of an uneven batch, and the splits that a launch deals out.

@@ -43,6 +43,7 @@ static int check_call(const std::vector<long>& lens, const DealRule& r, const Un
         }
         CHECK(most == p.most && most > 1);
         CHECK(p.n_splits + nb <= (long)(r.even_splits + 1) * batch);            // the workspace
+        CHECK((p.n_splits + nb) * r.tiles < 1L << 24);
     }
     return dealt;
 }
@@ -95,6 +96,19 @@ int main() {
         DealRule r{256, 64, 0, 0, 16};
         even_plan(2100, 1, r);
         CHECK(uneven_decode_call([&](int i) { return lens[i]; }, 32, 16, r).per_launch == 32);
+    }
+    // a million KV heads: the batch passes what a launch holds in x (a request at a time it does not)
+    {
+        g_case = 250000;
+        std::vector<long> lens(32);
+        lens[0] = 5000; lens[1] = 700;
+        DealRule r{256, 64, 0, 0, 1L << 20};
+        even_plan(5000, 1, r);
+        UnevenPlan p;
+        const auto ctx = [&](int i) { return lens[i]; };
+        CHECK(deal_splits(ctx, 32, 32, r, p) && !plan_uneven(ctx, 32, 32, r, p));
+        r.tiles = 4;
+        CHECK(plan_uneven(ctx, 32, 32, r, p));
     }
     printf("ok\n");
     return 0;
