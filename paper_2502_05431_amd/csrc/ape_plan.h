@@ -57,12 +57,22 @@ bool deal_splits(const Ctx& ctx, int nb, long splits, const DealRule& r, UnevenP
     return p.most > 1 && p.n_splits <= splits;
 }
 
-// ... within what a launch holds.
+// ... where dealing them out gives something: shorter splits, fewer rounds of 256 workgroups (the even plan's grid holds those of splits that
+// shorter requests do not have), or, with more than one workgroup to a CU, at least others.  Otherwise what the kernel looks up is all that is
+// left of it (even / dealt, us: 16 steps of 3 x ~2048 tokens, 32/8 heads, the same 248 splits 77.9 / 80.9; 4 of 1 to 7 x 1000, 8/8 bf16 heads
+// of 96, 25.0 / 25.9; 2 prefills of 16 rows, 6/2 of 40, 9.2 / 9.9; but the same splits in fewer rounds: 2 of 16 rows, 32/8 fp32 heads of 128,
+// 31.3 / 24.2, 24 steps of ~2770 tokens, 16/2 heads, 30.6 / 20.6, and others of the same length 4 of 1 to 7 x 1000, 32/32 fp32 heads, 238 / 215).
 template <class Ctx>
 bool plan_uneven(const Ctx& ctx, int nb, long splits, const DealRule& r, UnevenPlan& p) {
     if (!deal_splits(ctx, nb, splits, r, p)) return false;
     if ((p.n_splits + nb) * r.tiles >= 1L << 24) return false;       // (a launch holds 2^32 work items in x, and the whole batch lies there)
-    return true;
+    if (16L * p.longest <= 15L * r.even_len) return true;
+    const long dealt = p.n_splits * r.tiles, even = (long)r.even_splits * nb * r.tiles;
+    if (plan_ceil(dealt, 256) < plan_ceil(even, 256)) return true;
+    if (dealt <= 256) return false;
+    for (int i = 0; i < nb; ++i)
+        if (plan_ceil(ctx(i), r.even_len) != p.first[i + 1] - p.first[i] || (p.first[i + 1] - p.first[i] > 1 && p.len[i] != r.even_len)) return true;
+    return false;
 }
 
 // Requests per launch of an uneven batch, and the splits that a launch deals out.

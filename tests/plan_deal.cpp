@@ -110,6 +110,18 @@ int main() {
         r.tiles = 4;
         CHECK(plan_uneven(ctx, 32, 32, r, p));
     }
+    // the even plan's own splits, one per CU: nothing is dealt out; one request of twice the length: it is
+    {
+        g_case = 300000;
+        std::vector<long> lens = {1024, 4096, 2048, 512};
+        DealRule r{256, 64, 0, 0, 2};
+        even_plan(4096, 16, r);
+        UnevenPlan p;
+        const auto ctx = [&](int i) { return lens[i]; };
+        CHECK(deal_splits(ctx, 4, 64, r, p) && !plan_uneven(ctx, 4, 30, r, p));
+        even_plan(4096, 4, r);
+        CHECK(plan_uneven(ctx, 4, 16, r, p) && p.longest < r.even_len);
+    }
     printf("ok\n");
     return 0;
 }
