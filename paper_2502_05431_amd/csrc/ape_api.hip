@@ -142,7 +142,7 @@ QueryPlan plan_query(int base_workgroups, long max_ctx, int min_len, int target_
     long len = (max_ctx + n - 1) / n;
     len = (len + unit - 1) / unit * unit;              // tiles never straddle a split
     n = ceil_div(max_ctx, len);
-    p.n_ctx_splits = n; p.ctx_split_len = (int)len; p.n_splits_total = n + 1;
+    p.n_ctx_splits = n; p.ctx_split_len = (int)len; p.n_splits_total = n + 1; p.unit = unit;
     return p;
 }
 
@@ -171,6 +171,7 @@ QueryPlan tile_plan(const ShapeInfo& si, int batch, int q_len, long max_ctx, lon
     const int stage = wide || bm == 128 ? 32 : 4096 / bm;
     QueryPlan p = plan_query((int)base, max_ctx, tile_shortest_split(si), (int)(target < base * max_splits ? target : base * max_splits), stage);
     p.block_rows = bm;
+    if (half) p.slots = (int)full;
     return p;
 }
 
@@ -485,16 +486,19 @@ static int run_query(const ShapeInfo& si, const ape_request* reqs, int batch, in
 
     const int whole = whole_block_rows(si, plan.n_ctx_splits, batch, q_len, max_ctx, own);
     // An uneven batch is dealt out.  A decode step on the flash kernels asks for what suits it, any other call for as many splits as the even
-    // plan has (4 prefills of 64 rows over about 4096 tokens, 32/8 heads, even / so / 512 workgroups 46.1 / 41.8 / 42.5 us).
+    // plan has (4 prefills of 64 rows over about 4096 tokens, 32/8 heads, even / so / 512 workgroups 46.1 / 41.8 / 42.5 us), those tile
+    // kernels that run one workgroup per CU for no more than that (10 steps of 1 to 19 x 203 tokens, 8/8 bf16 heads of 96, 320 workgroups of the even plan's /
+    // 256 at most: 35.4 / 27.1).
     auto ctx = [&](int i) { return reqs[i].n_chunks > 0 ? (long)reqs[i].total_ctx_len : 0L; };
     const bool uneven = !whole && (si.mfma || si.tile) && plan.n_ctx_splits > 0 && uneven_batch(ctx, batch);
     DealRule rule{};
     UnevenCall call{kMaxReqPerLaunch, 0};
     UnevenPlan up;
     if (uneven) {
-        rule = {si.tile ? tile_shortest_split(si) : 256, 64, plan.n_ctx_splits, plan.ctx_split_len,
+        rule = {si.tile ? tile_shortest_split(si) : 256, plan.unit, plan.n_ctx_splits, plan.ctx_split_len,
                 (long)si.hkv * ceil_div((long)q_len * si.group, plan.block_rows > 0 ? plan.block_rows : 128)};
         call.splits = (long)plan.n_ctx_splits * batch;
+        if (plan.slots > 0 && call.splits > plan.slots / rule.tiles) call.splits = plan.slots / rule.tiles;
         if (decode && si.mfma) call = uneven_decode_call(ctx, batch, si.hkv, rule);
     }
     const int per_launch = call.per_launch;

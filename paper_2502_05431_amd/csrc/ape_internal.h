@@ -312,6 +312,8 @@ struct QueryPlan {
     int ctx_split_len;
     int n_splits_total;
     int n_bound;           // >= n_ctx_splits of this plan and of the plan for any shorter context with the same base and target
+    int unit;              // splits are whole units of so many tokens
+    int slots;             // workgroups that the splits of an uneven batch are at most (0: as many as the even plan has)
     int block_rows;        // query tile this plan was made for (0: the vector-ALU kernels, which have none)
 };
 
