@@ -698,18 +698,22 @@ __device__ __forceinline__ void redo_encode_rows(__attribute__((address_space(4)
 // teams come first, the prefix + own ones follow.  grid: x = teams x row tiles, y = request.
 // WHOLE: over short contexts one workgroup takes its rows past the contexts and then past the prefix and the own tokens and
 // writes their output: team = KV head, no partial results, no merge.
-template <typename T, int DP, int WR, int WK, int WD, bool WHOLE>
+// UNEVEN: the requests of a batch have splits of their own (QueryArgs::n_own_splits), and the whole batch lies in x (kernels of their own: with the
+// request looked up behind a branch the others fetch its pointers a round trip later; decode steps over 600 tokens, one kernel for both / two, us: bf16 heads
+// of 64 8.75 / 8.51, of 128 10.50 / 10.33, fp32 of 64 10.93 / 10.63).
+enum class Form { split, uneven, whole };
+template <typename T, int DP, int WR, int WK, int WD, Form FORM>
 __global__ __launch_bounds__(64 * WR * WK * WD) __attribute__((amdgpu_waves_per_eu(Tile<T, DP, WR, WK, WD>::WAVES, Tile<T, DP, WR, WK, WD>::MOST)))
 void tile_query_kernel(const QueryArgs a, int n_qtiles) {
     using X = Tile<T, DP, WR, WK, WD>;
+    constexpr bool WHOLE = FORM == Form::whole, UNEVEN = FORM == Form::uneven;
     // Where streams are short and nothing but the code is between them and the first result it costs more than it saves (general / near, us: 16 rows over
     // 3 x 100 tokens, 32/8 bf16 heads of 64, 10.6 / 10.9; 4 x 32, 4/2 fp32 heads of 64, 14.9 / 15.2; a decode step over 20 x 512, bf16 heads of 64, 12.4 / 12.7).
     constexpr bool NEAR = !WHOLE && (X::PITCH > 128 || WR > 1);
     extern __shared__ __attribute__((aligned(16))) char lds[];
     const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), l32 = lane & 31, hi = lane >> 5;
     const int d = a.head_dim, hq = a.n_q_heads, hkv = a.n_kv_heads, G = hq / hkv, q_len = a.q_len;
-    const bool uneven = !WHOLE && a.n_own_splits > 0;        // (then the whole batch lies in x)
-    const int ctx_teams = WHOLE ? 0 : (uneven ? a.n_own_splits : a.n_ctx_splits) * hkv;
+    const int ctx_teams = WHOLE ? 0 : (UNEVEN ? a.n_own_splits : a.n_ctx_splits) * hkv;
     int team, qtile, split, rq = blockIdx.y;
     // Teams are numbered on from the splits' to the prefix + own tokens', which so start on the XCDs where the splits' end: a plan that fills
     // the chip leaves its slots there (dealt out anew from the first XCD on, those are full and the call takes a second round: fp32, 2/2
@@ -717,13 +721,13 @@ void tile_query_kernel(const QueryArgs a, int n_qtiles) {
     // 64 bf16 rows over 600, 12/2 of 128, 17.1 / 11.5).
     team_of_block(blockIdx.x, n_qtiles, team, qtile);
     if (team < ctx_teams) {
-        if (uneven) own_split(a.n_req, team / hkv, rq, split);
+        if constexpr (UNEVEN) own_split(a.n_req, team / hkv, rq, split);
         else split = team / hkv;
     } else {
         team -= ctx_teams;
-        if (team >= (uneven ? a.n_req : 1) * hkv) return;
+        if (team >= (UNEVEN ? a.n_req : 1) * hkv) return;
         split = a.n_ctx_splits;
-        if (uneven) rq = team / hkv;
+        if constexpr (UNEVEN) rq = team / hkv;
     }
     const int hk = team % hkv;
     const KvView kv = load_view<QueryArgs>(rq);
@@ -775,7 +779,7 @@ void tile_query_kernel(const QueryArgs a, int n_qtiles) {
         long t0 = 0, t1 = 0;
         const bool own = split >= a.n_ctx_splits;
         if (!own) {
-            if (uneven) own_split_range(kv, rq, split, t0, t1); else ctx_split_range(a, kv, split, t0, t1);
+            if constexpr (UNEVEN) own_split_range(kv, rq, split, t0, t1); else ctx_split_range(a, kv, split, t0, t1);
             if (t0 >= t1) return;                            // an empty split: the merge never looks at it (a request without contexts has no table)
             t1 = min(t1, (long)scalar_load_i32(kv.cu + kv.n_chunks));   // (stay inside the table whatever total_ctx says)
             if (t0 >= t1) return;
@@ -788,7 +792,7 @@ void tile_query_kernel(const QueryArgs a, int n_qtiles) {
         if (!combine<T, DP / WD, WR, WK>(lds, st)) return;
         const float lt = sum_halves(st.l);
         const uint32_t redo = rows_to_redo(st, lt, valid, own);
-        const long part0 = uneven ? own_partial_rows(a, rq, split) : (long)split * a.units_total + (long)(a.req_base + rq) * q_len * hq;
+        const long part0 = UNEVEN ? own_partial_rows(a, rq, split) : (long)split * a.units_total + (long)(a.req_base + rq) * q_len * hq;
         if (valid && !(redo >> l32 & 1)) {
             const long slot = part0 + (long)tok * hq + h;
             store_row<T, DP, WD>(st, seen(lt) ? 1.f / lt : 0.f, d, wd, a.part_o + slot * d);
@@ -898,9 +902,10 @@ void tile_encode_kernel(const EncodeArgs a, int n_qtiles, const Listing list) {
 template <typename T, int DP, int WR, int WK, int WD, bool WHOLE>
 hipError_t query_as(const QueryArgs& a, hipStream_t s) {
     using X = Tile<T, DP, WR, WK, WD>;
-    auto kernel = tile_query_kernel<T, DP, WR, WK, WD, WHOLE>;
-    const int rows = a.q_len * (a.n_q_heads / a.n_kv_heads), n_qtiles = (rows + X::ROWS - 1) / X::ROWS;
     const bool uneven = !WHOLE && a.n_own_splits > 0;
+    auto kernel = tile_query_kernel<T, DP, WR, WK, WD, WHOLE ? Form::whole : Form::split>;
+    if constexpr (!WHOLE) kernel = uneven ? tile_query_kernel<T, DP, WR, WK, WD, Form::uneven> : kernel;
+    const int rows = a.q_len * (a.n_q_heads / a.n_kv_heads), n_qtiles = (rows + X::ROWS - 1) / X::ROWS;
     const long teams = (long)(WHOLE ? 1 : uneven ? a.n_own_splits + a.n_req : a.n_ctx_splits + 1) * a.n_kv_heads;
     const dim3 grid((unsigned)((teams + 7) / 8 * 8 * n_qtiles), uneven ? 1u : (unsigned)a.n_req);
     hipError_t e = hipFuncSetAttribute((const void*)kernel, hipFuncAttributeMaxDynamicSharedMemorySize, X::LDS);
