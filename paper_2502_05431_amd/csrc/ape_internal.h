@@ -331,6 +331,9 @@ hipError_t launch_generic_encode(const EncodeArgs& a, int dtype, hipStream_t s);
 // any supported shape; block_rows from the plan; whole: one workgroup per tile of 32 rows and KV head, writing the output
 hipError_t launch_tile_query(const QueryArgs& a, int dtype, int block_rows, bool whole, hipStream_t s);
 hipError_t launch_tile_encode(const EncodeArgs& a, int dtype, hipStream_t s);
+// its rows per workgroup, and how its tiles are dealt out (see the definitions)
+int tile_encode_block_rows(const EncodeArgs& a, int dtype);
+int tile_encode_groups(const EncodeArgs& a, int dtype, int32_t* first_context);
 hipError_t launch_merge(const MergeArgs& a, hipStream_t s);
 hipError_t launch_rope_write(const RopeArgs& a, int dtype, hipStream_t s);
 hipError_t launch_tree_plan(const TreePlanArgs& a, hipStream_t s);

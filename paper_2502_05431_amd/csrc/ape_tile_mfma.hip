@@ -930,6 +930,9 @@ hipError_t query_with(const QueryArgs& a, int block_rows, bool whole, hipStream_
 Listing list_tiles(const EncodeArgs& a, int rows, size_t elem) {
     Listing l{};
     if (a.cu && !a.cu_host) return l;
+    // (contexts of one tile each have all their tiles in the first place: 400 of about 40 tokens, listed / by contexts, 8/8 bf16 heads of 96 52.7 / 49.8 us,
+    // 16/16 of 64 51.0 / 47.3)
+    if ((long)a.max_chunk_len * (a.n_q_heads / a.n_kv_heads) <= rows) return l;
     const long group_tokens = ((elem == 4 ? 8L : a.head_dim > 128 ? 1L : 2L) << 20) / (2 * a.head_dim * (long)elem);
     long tiles = 0, tokens = 0;
     int g = 0, first = 0;
@@ -1001,7 +1004,7 @@ hipError_t launch_tile_query(const QueryArgs& a, int dtype, int block_rows, bool
 // their place (below), 128 / 64 / 32: fp32 32/8 of 128, 8 ragged of about 512 180 / 193 / 234, 6 x 512 154 / 159 / 205, 4 x 512 116 / 114 / 133;
 // 4/2 of 64, 4 x 1000 89 / 52 / 41, 6/2 of 40, 12 x 300 33 / 25 / 31; bf16 8/8 of 96, 8 x 512 22.0 / 18.9 / 39.6, 20 ragged of about 200 17.7 / 21.3 /
 // 40.5; 12/2 of 128, 2 x 2048 70.4 / 61.7 / 115, 4 x 1000 39.2 / 38.5 / 77, 8 x 500 24.2 / 27.4 / 59.
-static int encode_block_rows(const EncodeArgs& a, int dtype) {
+int tile_encode_block_rows(const EncodeArgs& a, int dtype) {
     const long group = a.n_q_heads / a.n_kv_heads;
     const long tiles = ((long)a.total_rows * group + 63) / 64 * a.n_kv_heads;   // of 64 rows
     const bool f32 = dtype == APE_F32;
@@ -1013,10 +1016,16 @@ static int encode_block_rows(const EncodeArgs& a, int dtype) {
     else rows = tiles < 256 || (tiles <= 512 && a.max_chunk_len >= 512) || (tiles <= 768 && a.max_chunk_len > 1024) ? 64 : 128;
     return rows;
 }
+// The groups of contexts whose tiles are dealt out by their place, 0: they go by contexts.
+int tile_encode_groups(const EncodeArgs& a, int dtype, int32_t* first_context) {
+    const Listing l = list_tiles(a, tile_encode_block_rows(a, dtype), dtype == APE_F32 ? 4 : 2);
+    for (int g = 0; g < l.n_groups; ++g) first_context[g] = l.first_context[g];
+    return l.n_groups;
+}
 
 hipError_t launch_tile_encode(const EncodeArgs& a, int dtype, hipStream_t s) {
     if (a.total_rows == 0) return hipSuccess;
-    const int d = a.head_dim, br = encode_block_rows(a, dtype);
+    const int d = a.head_dim, br = tile_encode_block_rows(a, dtype);
     // The grid is contexts x KV heads x tiles of the longest context: where uneven lengths make it too large, it goes out a run of
     // contexts at a time (one context always fits: the outputs of a call are fewer than 2^26).
     const long per_context = (long)a.n_kv_heads * (((long)a.max_chunk_len * (a.n_q_heads / a.n_kv_heads) + br - 1) / br);

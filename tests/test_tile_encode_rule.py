@@ -1,0 +1,47 @@
+"""Host logic of the tile kernels' encode: rows per workgroup, and whether the tiles of a call are dealt out by their place, in which groups of
+contexts."""
+import ctypes
+
+import pytest
+
+from paper_2502_05431_amd import binding as B
+
+
+class EncodeArgs(ctypes.Structure):                       # csrc/ape_internal.h
+    _fields_ = [(n, ctypes.c_void_p) for n in ("q", "k", "v", "k_prefix", "v_prefix", "cu", "out", "lse")] + \
+               [(n, ctypes.c_int32) for n in ("n_chunks", "prefix_len", "total_rows", "max_chunk_len", "n_q_heads", "n_kv_heads", "head_dim", "uniform_chunks")] + \
+               [("cu_host", ctypes.c_void_p)]
+
+
+def _args(heads, lens):
+    cu = (ctypes.c_int32 * (len(lens) + 1))()
+    for i, n in enumerate(lens):
+        cu[i + 1] = cu[i] + n
+    a = EncodeArgs(cu=0x1000, n_chunks=len(lens), total_rows=sum(lens), max_chunk_len=max(lens), n_q_heads=heads[0], n_kv_heads=heads[1], head_dim=heads[2],
+                   uniform_chunks=min(lens) == max(lens), cu_host=ctypes.addressof(cu))
+    return a, cu
+
+
+def rows(dtype, heads, lens):
+    a, _ = _args(heads, lens)
+    return B.load()._ZN3ape22tile_encode_block_rowsERKNS_10EncodeArgsEi(ctypes.byref(a), B.APE_F32 if dtype == "f32" else B.APE_BF16)
+
+
+def groups(dtype, heads, lens):
+    """First contexts of the groups; empty: by contexts."""
+    a, cu = _args(heads, lens)
+    first = (ctypes.c_int32 * 64)()
+    n = B.load()._ZN3ape18tile_encode_groupsERKNS_10EncodeArgsEiPi(ctypes.byref(a), B.APE_F32 if dtype == "f32" else B.APE_BF16, first)
+    return list(first[:n])
+
+
+@pytest.mark.parametrize("dtype, heads, lens, first", [
+    ("bf16", (8, 8, 96), [10 + 10 * (i % 7) for i in range(400)], []),            # a tile each: nothing to order
+    ("bf16", (16, 16, 64), [128] * 100, []),
+    ("bf16", (8, 8, 96), [129] + [70] * 70, [0, 64]),                             # ... but one
+    ("f32", (4, 2, 64), [300, 200], []),                                          # a CU each
+    ("f32", (32, 8, 128), [512] * 8, [0]),
+    ("bf16", (16, 8, 256), [600, 424, 1000, 24, 1, 2000], [0, 2, 4, 5]),          # 1024 tokens of 256 dims: 1 MB
+    ("f32", (4, 2, 64), [0] * 130 + [5000], [0, 64, 128])])
+def test_order(dtype, heads, lens, first):
+    assert groups(dtype, heads, lens) == first
