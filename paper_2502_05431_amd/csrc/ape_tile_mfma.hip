@@ -1004,16 +1004,25 @@ hipError_t launch_tile_query(const QueryArgs& a, int dtype, int block_rows, bool
 // their place (below), 128 / 64 / 32: fp32 32/8 of 128, 8 ragged of about 512 180 / 193 / 234, 6 x 512 154 / 159 / 205, 4 x 512 116 / 114 / 133;
 // 4/2 of 64, 4 x 1000 89 / 52 / 41, 6/2 of 40, 12 x 300 33 / 25 / 31; bf16 8/8 of 96, 8 x 512 22.0 / 18.9 / 39.6, 20 ragged of about 200 17.7 / 21.3 /
 // 40.5; 12/2 of 128, 2 x 2048 70.4 / 61.7 / 115, 4 x 1000 39.2 / 38.5 / 77, 8 x 500 24.2 / 27.4 / 59.
+// Which of 64 and 128 rows also hangs on how long the contexts are (64 / 128 rows, us, ragged): bf16 heads of 96, 3 x 2000 tokens, 8/8, 80.5 / 131, 6 x 1000 48.4 / 74,
+// 12/2 of 128, 6 x 1000 64 / 71, 12 x 700 64.7 / 58.5; of 64, 32/8, 12 x 100 14.6 / 12.6, 40 x 30 15.0 / 11.3, 3 x 400 19.4 / 23.1, 16/16, 30 x 64 15.3 / 12.2;
+// fp32 heads of 128, 8/8, 60 x 256 187 / 203, 100 x 300 346 / 381, 400 x 40 134 / 183, 10 x 2000 1217 / 1129, 16/8, 60 x 256 308 / 299, 400 x 40 195 / 209.
 int tile_encode_block_rows(const EncodeArgs& a, int dtype) {
     const long group = a.n_q_heads / a.n_kv_heads;
     const long tiles = ((long)a.total_rows * group + 63) / 64 * a.n_kv_heads;   // of 64 rows
+    const long longest = a.max_chunk_len, longest_rows = longest * group;
     const bool f32 = dtype == APE_F32;
     int rows;
     if (a.head_dim > 128) rows = tiles < 384 ? 32 : 64;
-    else if (f32 && a.head_dim > 64) rows = tiles < 192 ? 32 : tiles < 1500 ? 64 : 128;
+    else if (f32 && a.head_dim > 64) {
+        // (a tile of one query head per KV head is as long as 128 tokens: its diagonal and the context's last tile are half empty)
+        const bool empty = group > 1 ? !a.uniform_chunks && longest_rows <= 256 : longest <= 1024 && (a.n_chunks <= 64 * kMaxGroups || longest > 128);
+        rows = tiles < 192 ? 32 : tiles < 1500 || empty ? 64 : 128;
+    }
     else if (f32) rows = tiles < 192 || (tiles < 512 && a.max_chunk_len > 512) ? 32 : 64;
-    else if (a.head_dim <= 64) rows = tiles < 1024 ? 64 : 128;
-    else rows = tiles < 256 || (tiles <= 512 && a.max_chunk_len >= 512) || (tiles <= 768 && a.max_chunk_len > 1024) ? 64 : 128;
+    else if (longest_rows <= 128 && tiles >= (a.head_dim <= 64 ? 224 : 128)) rows = 128;      // a tile for each context
+    else if (a.head_dim <= 64) rows = tiles < 512 || (tiles < 1024 && longest > 256) ? 64 : 128;
+    else rows = tiles < 256 || (tiles <= 512 && longest >= 512) || (tiles <= 768 && longest > 640) || (tiles <= 1408 && longest > 1024) ? 64 : 128;
     return rows;
 }
 // The groups of contexts whose tiles are dealt out by their place, 0: they go by contexts.

@@ -45,3 +45,22 @@ def groups(dtype, heads, lens):
     ("f32", (4, 2, 64), [0] * 130 + [5000], [0, 64, 128])])
 def test_order(dtype, heads, lens, first):
     assert groups(dtype, heads, lens) == first
+
+
+def _ragged(n, mean):
+    return [max(1, mean * (2 + 3 * (i % 5)) // 8) for i in range(n)]
+
+
+@pytest.mark.parametrize("dtype, heads, lens, expect", [
+    # long contexts on few tiles: 64 rows up to where the chip is full of 128-row tiles
+    ("bf16", (8, 8, 96), _ragged(3, 2000), 64), ("bf16", (8, 8, 96), _ragged(6, 1000), 64), ("bf16", (12, 2, 128), _ragged(8, 512), 64),
+    ("bf16", (8, 8, 96), _ragged(20, 200), 128), ("bf16", (12, 2, 128), _ragged(12, 700), 128), ("bf16", (8, 8, 96), _ragged(30, 1000), 128),
+    # short ones: 128 rows on fewer
+    ("bf16", (32, 8, 64), _ragged(12, 100), 128), ("bf16", (32, 8, 64), _ragged(3, 400), 64), ("bf16", (16, 16, 64), _ragged(30, 64), 128),
+    ("bf16", (8, 8, 96), [64] * 20, 128), ("bf16", (8, 8, 96), [64] * 4, 64),
+    # fp32, one query head per KV head: tiles of 128 tokens only where contexts are long
+    ("f32", (8, 8, 128), _ragged(60, 256), 64), ("f32", (8, 8, 72), _ragged(400, 40), 64), ("f32", (8, 8, 128), _ragged(10, 2000), 128),
+    ("f32", (16, 8, 128), _ragged(400, 40), 64), ("f32", (16, 8, 128), _ragged(60, 256), 128), ("f32", (16, 8, 128), [128] * 200, 128),
+    ("f32", (32, 8, 128), _ragged(8, 512), 128), ("f32", (32, 8, 128), _ragged(4, 512), 64)])
+def test_rows(dtype, heads, lens, expect):
+    assert rows(dtype, heads, lens) == expect
