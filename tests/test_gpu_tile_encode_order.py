@@ -1,5 +1,6 @@
-"""GPU parity of the tile kernels' encode over the ways its tiles are dealt out: one group of contexts, a group that ends by its number
-of contexts (64) or by its bytes, contexts without tokens at the ends of groups, more groups than one call lists, one context."""
+"""GPU parity of the tile kernels' encode over the ways its tiles are dealt out: by contexts (few tiles, or more groups than one call lists), one
+group of contexts, groups that end by their number of contexts (64) or by their bytes, contexts without tokens at the ends of groups, a whole group
+of them, one context, as many groups as one call lists.  Which way a case goes is checked on the host."""
 import numpy as np
 import pytest
 import torch
@@ -7,20 +8,33 @@ import torch
 from paper_2502_05431_amd import workloads as W
 
 import helpers as H
+from test_tile_encode_rule import groups
 
 pytestmark = pytest.mark.gpu
 DEV = "cuda:0"
 
 
-@pytest.mark.parametrize("dtype, hq, hkv, d, lens, prefix", [
-    ("f32", 6, 2, 40, [1], 0), ("f32", 4, 2, 64, [33, 1, 64, 0, 65], 7),
-    ("f32", 3, 1, 40, [(7 * i) % 40 for i in range(131)], 5),                        # groups of 64, 64 and 3 contexts
-    ("bf16", 2, 1, 256, [600, 424, 0, 1, 300, 723, 1, 0], 9),                        # 1024 tokens of 256 dims: 1 MB
-    ("bf16", 2, 1, 256, [1024, 1, 1023, 0, 1100], 3),
-    ("bf16", 8, 8, 96, [0, 0, 130, 5, 0, 128], 32),
-    ("bf16", 6, 2, 40, [(5 * i) % 4 for i in range(64 * 31 + 7)], 3),                # 32 groups: by contexts, as larger calls
-    ("f32", 4, 1, 128, [(i * 37) % 400 for i in range(60)], 16)])
-def test_order(dtype, hq, hkv, d, lens, prefix):
+CASES = [
+    ("f32", 6, 2, 40, [1], 0, []), ("f32", 4, 2, 64, [33, 1, 64, 0, 65], 7, []),
+    ("f32", 3, 1, 40, [(7 * i) % 40 for i in range(131)], 5, [0, 64, 128]),
+    ("bf16", 2, 1, 256, [600, 424, 0, 1, 300, 723, 1, 0], 9, []),
+    ("bf16", 2, 1, 256, [1024, 1, 1023, 0, 1100], 3, []),
+    ("bf16", 8, 8, 96, [0, 0, 130, 5, 0, 128], 32, []),
+    ("bf16", 6, 2, 40, [(5 * i) % 4 for i in range(64 * 31 + 7)], 3, []),
+    ("f32", 4, 1, 128, [(i * 37) % 400 for i in range(60)], 16, [0, 42]),         # 8192 tokens of 128 dims: 8 MB
+    ("f32", 64, 16, 64, [33, 1, 64, 0, 65, 90], 7, [0]),
+    ("bf16", 16, 8, 256, [600, 424, 0, 1, 300, 723, 1, 0], 9, [0, 3, 6]),             # 1024 tokens of 256 dims: 1 MB
+    ("bf16", 16, 8, 256, [1024, 1, 1023, 0, 1100], 3, [0, 1, 4]),
+    ("bf16", 32, 8, 96, [0, 0, 130, 5, 0, 128, 700, 0], 32, [0]),
+    ("bf16", 32, 8, 64, [1100], 5, [0]),
+    ("f32", 4, 2, 64, [20, 70] * 32 + [0] * 64 + [50, 100] * 10, 4, [0, 64, 128]),
+    ("bf16", 6, 2, 40, [(5 * i) % 4 for i in range(64 * 31 - 1)] + [60], 3, list(range(0, 64 * 31, 64))),
+    ("bf16", 6, 2, 40, [(5 * i) % 4 for i in range(64 * 31)] + [60], 3, [])]
+
+
+@pytest.mark.parametrize("dtype, hq, hkv, d, lens, prefix, listed", CASES)
+def test_order(dtype, hq, hkv, d, lens, prefix, listed):
+    assert groups(dtype, (hq, hkv, d), lens) == listed
     spec = W.WorkloadSpec(name="order", cfg=8, dtype=dtype, n_q_heads=hq, n_kv_heads=hkv, head_dim=d, prefix_len=prefix, chunk_lens=tuple(lens),
                           q_len=1, decode_steps=0)
     r = W.make_request(spec, DEV)

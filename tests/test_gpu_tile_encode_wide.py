@@ -1,0 +1,69 @@
+"""GPU parity of the fp32 encode in tiles of 128 rows (heads of 65 to 128 dims, many tiles): ragged and empty contexts, remainder rows, a prefix, a
+padded width, tokens that a row does not see and that hold no number, and the same bits as in tiles of 64 rows."""
+import numpy as np
+import pytest
+import torch
+
+from paper_2502_05431_amd import workloads as W
+
+import helpers as H
+from test_tile_encode_rule import rows
+
+pytestmark = pytest.mark.gpu
+DEV = "cuda:0"
+
+LENS = (150, 0, 301, 33, 1, 128, 129, 260, 95, 200, 64, 173)              # 1534 tokens: 1534 tiles of 64 rows on 32 KV heads
+
+
+def _request(hq, hkv, d, prefix, lens=LENS):
+    spec = W.WorkloadSpec(name="wide", cfg=6, dtype="f32", n_q_heads=hq, n_kv_heads=hkv, head_dim=d, prefix_len=prefix, chunk_lens=tuple(lens),
+                          q_len=1, decode_steps=0)
+    assert rows("f32", (hq, hkv, d), lens) == 128
+    return spec, W.make_request(spec, DEV)
+
+
+def _check(spec, r, keep=slice(None)):
+    hq, d = spec.n_q_heads, spec.head_dim
+    o, lse, _, _ = H.run_encode(spec, r, with_prefix_rows=False)
+    ref, ref_lse = H.oracle_encode(H.HostArrays(r))
+    H.check_close(H.f64(o)[keep].reshape(-1, d), ref.reshape(-1, hq, d)[keep].reshape(-1, d), "f32", str(spec))
+    assert np.abs(H.f64(lse).T[keep] - ref_lse.reshape(-1, hq)[keep]).max() <= H.lse_tol("f32")
+    return o, lse
+
+
+@pytest.mark.parametrize("hq, hkv, d, prefix", [(64, 32, 128, 9), (64, 32, 72, 0), (96, 32, 96, 40)])
+def test_parity(hq, hkv, d, prefix):
+    _check(*_request(hq, hkv, d, prefix))
+
+
+def test_hidden_tokens_that_hold_no_number():
+    """The last tokens of contexts, which only their own rows see."""
+    spec, r = _request(64, 32, 128, 9)
+    keep, end = np.ones(sum(LENS), bool), 0
+    for i, n in enumerate(LENS):
+        end += n
+        if n > 40:
+            for t, x in ((r.k_ctx, float("nan")), (r.v_ctx, float("inf"))):
+                t[end - 1 - i % 3:end] = x
+            keep[end - 1 - i % 3:end] = False
+    _check(spec, r, keep)
+
+
+@pytest.mark.parametrize("d", [72, 128])
+def test_bits_of_the_64_row_tiles(d):
+    """A context's rows do not depend on how many contexts are encoded with it."""
+    spec, r = _request(64, 32, d, 9)
+    o, lse, _, _ = H.run_encode(spec, r, with_prefix_rows=False)
+    at = 0
+    for lens in (LENS[:4], LENS[4:8], LENS[8:]):
+        assert rows("f32", (64, 32, d), lens) == 64
+        n = sum(lens)
+        part = spec.replace(chunk_lens=lens)
+        s = W.make_request(part, DEV)
+        for name in ("q_ctx", "k_ctx", "v_ctx"):
+            getattr(s, name).copy_(getattr(r, name)[at:at + n])
+        for name in ("k_prefix", "v_prefix"):
+            getattr(s, name).copy_(getattr(r, name))
+        po, pl, _, _ = H.run_encode(part, s, with_prefix_rows=False)
+        assert torch.equal(po, o[at:at + n]) and torch.equal(pl, lse[:, at:at + n])
+        at += n
