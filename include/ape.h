@@ -166,6 +166,9 @@ int ape_attention_prefill(const ape_shape *shape, const ape_request *req,
  * Query prefill of a batch of independent requests with the same number of query rows (the
  * serving setting of Section 5.4 runs several queries at once): ape_attention_prefill for every
  * request, in one launch.  Each request has its own prefix, contexts, self KV, T and S.
+ * (How a request's contexts are split follows from the lengths of all requests of the call, and with the
+ * splits the last bits of its result: they may differ from those of another batch, within the rounding of the
+ * data type.  The same holds for ape_attention_decode.)
  *
  *   reqs      HOST array [batch]
  *   q, out    DEVICE [batch, q_len, n_q_heads, d]

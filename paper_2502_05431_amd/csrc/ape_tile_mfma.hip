@@ -26,7 +26,7 @@
 // attention's own count for bf16), the fixed chain of a launch, first loads and merge for a short query.  Against the
 // vector-ALU kernels, which give a wavefront one row and read every K/V byte once per row (same card, same inputs):
 // fp32 encode of eight contexts of about 512 tokens, 32/8 heads of 128: 2754 -> 180 us (94 TFLOP/s; the vendor's fp32 GEMM
-// reaches 154); 64 bf16 rows over 20 x 512 tokens, 16/8 heads of 256: 14200 -> 39 us (2.1 TB/s); a fp32 decode step over 4096
+// reaches 154); 64 bf16 rows over 20 x 512 tokens, 16/8 heads of 256: 14200 -> 43 us (2.0 TB/s, on inputs that change); a fp32 decode step over 4096
 // tokens, 16/8 heads of 256: 28 us, 88 by one wavefront per workgroup; 16 fp32 rows over 4 x 32 tokens, 4/2 heads of 64: 47.8 -> 14.8 us.
 #include "ape_mfma.h"
 
@@ -155,8 +155,9 @@ struct Source {
 // Starts the loads of tokens [t, t + KS) into `stage`; rows past t_end - 1 repeat that token (finite
 // data whose probabilities are zero).
 // NEAR: a stage that lies within one segment has a base that is the wavefront's, in scalar registers, and 32-bit offsets per lane: behind the
-// first, 7 vector instructions per pair of loads in rows of 512 bytes, 10 of 1024, 1 below; the general form takes 35, with a 64-bit product and four selects, and the vector ALUs are what bounds the bf16 kernels (64 rows over
-// 20 x 512 tokens, 16/8 heads of 256: VALU 43 % and MFMA 20 % of the SIMDs' time; 42.6 -> 40.2 us, 200 rows 96.3 -> 86.4).
+// first, 7 vector instructions per pair of loads in rows of 512 bytes, 10 of 1024, 1 below; the general form takes 35, with a 64-bit product and
+// four selects, and the vector ALUs are what bounds the bf16 kernels (20 x 512 tokens, 16/8 heads of 256: VALU 43 % and MFMA 20 % of the SIMDs' time;
+// looped on one input 64 rows 42.6 -> 40.2 us, 200 rows 96.3 -> 86.4).
 constexpr long kNearStride = 1 << 24;                       // 128 tokens at this stride: offsets of 32 bits
 template <typename T, int DP, int WR, int WK, int WD, bool NEAR>
 __device__ __forceinline__ void start_stage(Source& src, int t, int t_end, int d, char* stage) {
