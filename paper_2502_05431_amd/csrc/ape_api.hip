@@ -186,6 +186,23 @@ QueryPlan tile_decode_plan(const ShapeInfo& si, int batch, long max_ctx) {
 
 }  // namespace
 
+// Where the few-row kernels are the faster ones (decode steps, 32/8 bf16 heads of 128 where not stated, the kernels of before / these, us of GPU time).
+// A single request: 128 tokens 11.2 / 5.9, 1024 12.6 / 10.4, 20 x 512 15.6 / 14.0, heads of 64 13.2 / 10.9, 8/8 of 96 16.8 / 13.6, 100 ragged of about 100
+// 21.1 / 15.0; 32K 29.4 / 28.0, 64K 48.5 / 47.9, but 128K 86.0 / 89.4: what streams from HBM for long keeps the kernels whose wavefronts read one
+// block at a time together.  For the same reason a batch: 4 x 4096 19.4 / 18.6, 8 x 2048 19.4 / 19.2, 8 x 4096 28.2 / 29.4, 4 x 10240, heads of 64, 21.4 / 24.3; and with requests
+// of different lengths, whose splits those deal out (8 of 1 to 15 x 256 23.9 / 24.4).  Whole: split / whole, 384 tokens 8.5 / 7.5, 512 8.7 / 9.6; heads
+// of 64 over 512 8.2 / 7.1, 1024 8.4 / 9.1; of 256 over 128 10.0 / 9.7, 256 10.1 / 12.1; and where the requests give every CU one: 32 x 1024 32.7 / 26.2, 32 x 4096 94 / 86.9,
+// 16/8 heads of 256, 32 x 1024, 57 / 47.7 (before: 29.9, 86.9, 72.3), but 16 x 2048 29.8 / 33.1.
+FewForm few_form(const ShapeInfo& si, int batch, int q_len, long max_ctx, bool uneven) {
+    if (si.force_generic || si.dtype != APE_BF16 || (long)q_len * si.group > kFewRows || (long)si.hkv * si.d * 2 > kFewStride) return FewForm::no;
+    const long base = (long)batch * si.hkv, bytes = base * max_ctx * si.d * 4;
+    if (base > 1024) return FewForm::no;
+    if (max_ctx <= (si.d <= 64 ? 512 : si.d <= 128 ? 384 : 128)) return FewForm::whole;
+    if (base > 128 && base <= 256 && max_ctx <= 4096 && !uneven) return FewForm::whole;
+    if (batch == 1 ? bytes > 200L << 20 : uneven || bytes > 64L << 20) return FewForm::no;
+    return base <= 32 ? FewForm::full : FewForm::half;
+}
+
 // Rows per workgroup of a call that runs without splits, one workgroup taking its rows past the contexts and then past the
 // prefix and the own tokens (`own`: of all requests) and writing the output (0: it is split and merged).  Worth it while the longer
 // stream costs less than the second launch, the partial results and their merge, about 4 us: up to 512 context tokens per request
@@ -481,16 +498,23 @@ static int run_query(const ShapeInfo& si, const ape_request* reqs, int batch, in
     if (!workspace || workspace_bytes < need)
         return fail(APE_ERR_WORKSPACE, "workspace of %zu bytes given, %zu needed (ape_workspace_bytes gives the bound)", workspace_bytes, need);
     if ((uintptr_t)workspace % kWsAlign) return fail(APE_ERR_WORKSPACE, "workspace must be %d-byte aligned", kWsAlign);
+    auto ctx = [&](int i) { return reqs[i].n_chunks > 0 ? (long)reqs[i].total_ctx_len : 0L; };
+    const bool uneven_ctx = uneven_batch(ctx, batch);
+    const FewForm few = few_form(si, batch, q_len, max_ctx, uneven_ctx);
+    if (few == FewForm::full || few == FewForm::half) {
+        // as many splits as leave every workgroup, the prefix and own tokens' too, a CU of its own (`full`; half of one otherwise), and no more than in
+        // the other kernels' plan, which the workspace is made for
+        const int base = batch * si.hkv, n = (few == FewForm::full ? 256 : 512) / base - 1;
+        plan = plan_query(base, max_ctx, 64, base * (n < 1 ? 1 : n < plan.n_ctx_splits ? n : plan.n_ctx_splits), 32);
+    }
     float* part_o = (float*)workspace;
     float* part_lse = (float*)((char*)workspace + align_up((size_t)units * plan.n_splits_total * si.d * sizeof(float), kWsAlign));
-
-    const int whole = whole_block_rows(si, plan.n_ctx_splits, batch, q_len, max_ctx, own);
+    const int whole = few == FewForm::whole ? kFewRows : few != FewForm::no ? 0 : whole_block_rows(si, plan.n_ctx_splits, batch, q_len, max_ctx, own);
     // An uneven batch is dealt out.  A decode step on the flash kernels asks for what suits it, any other call for as many splits as the even
     // plan has (4 prefills of 64 rows over about 4096 tokens, 32/8 heads, even / so / 512 workgroups 46.1 / 41.8 / 42.5 us), those tile
     // kernels that run one workgroup per CU for no more than that (10 steps of 1 to 19 x 203 tokens, 8/8 bf16 heads of 96, 320 workgroups of the even plan's /
     // 256 at most: 35.4 / 27.1).
-    auto ctx = [&](int i) { return reqs[i].n_chunks > 0 ? (long)reqs[i].total_ctx_len : 0L; };
-    const bool uneven = !whole && (si.mfma || si.tile) && plan.n_ctx_splits > 0 && uneven_batch(ctx, batch);
+    const bool uneven = !whole && few == FewForm::no && (si.mfma || si.tile) && plan.n_ctx_splits > 0 && uneven_ctx;
     DealRule rule{};
     UnevenCall call{kMaxReqPerLaunch, 0};
     UnevenPlan up;
@@ -525,11 +549,11 @@ static int run_query(const ShapeInfo& si, const ape_request* reqs, int batch, in
         }
         if (whole) {
             a.out = out; a.lse_out = lse_out; a.lse_head_major = decode ? 0 : 1;
-            const hipError_t we = launch_tile_query(a, si.dtype, whole, true, st);
+            const hipError_t we = few == FewForm::whole ? launch_few_rows(a, few, st) : launch_tile_query(a, si.dtype, whole, true, st);
             if (we != hipSuccess) return fail(APE_ERR_DEVICE, "attention kernel: %s", hipGetErrorString(we));
             continue;
         }
-        hipError_t he = launch_query(si, a, plan.block_rows, st);
+        hipError_t he = few != FewForm::no ? launch_few_rows(a, few, st) : launch_query(si, a, plan.block_rows, st);
         if (he != hipSuccess) return fail(APE_ERR_DEVICE, "attention kernel: %s", hipGetErrorString(he));
 
         m.part_o = part_o; m.part_lse = a.part_lse; m.out = out; m.lse_out = lse_out;
@@ -700,7 +724,8 @@ int ape_attention_tree(const ape_shape* shape, const ape_request* req,
     a.n_ctx_splits = plan.max_splits; a.ctx_split_len = plan.len;
     a.split_ranges = plan_dev + TreePlanLayout{n_nodes, plan.max_splits}.ranges_at();
     a.units_total = (int)units; a.req_base = 0;
-    he = launch_query(si, a, plan.block_rows, st);
+    const FewForm few = few_form(si, 1, q_len, req->total_ctx_len, false);
+    he = few != FewForm::no ? launch_few_rows(a, FewForm::half, st) : launch_query(si, a, plan.block_rows, st);
     if (he != hipSuccess) return fail(APE_ERR_DEVICE, "attention kernel: %s", hipGetErrorString(he));
 
     m.part_o = part_o; m.part_lse = part_lse; m.out = out; m.lse_out = lse_out; m.nodes = nodes_dev; m.plan = plan_dev;

@@ -32,6 +32,7 @@ constexpr long kMaxEncodeBlocks = 1L << 24;     // workgroups of a matrix-core e
 
 // Kernel-argument block of the query-time kernels (prefill and decode).
 struct QueryArgs {
+    static constexpr int kRequests = kMaxReqPerLaunch;
     KvView req[kMaxReqPerLaunch];
     // Uneven batches: every request has splits of its own number and length, n_own_splits in the launch; request r has splits
     // first_split[r] .. first_split[r + 1] - 1 of split_len[r] tokens.  Partial results are then dense,
@@ -225,7 +226,8 @@ __device__ __forceinline__ int find_chunk(const int32_t* cu, int n_chunks, int t
 
 // Context tokens [t0, t1) (indices into the pooled contexts) that split `split` of request view
 // `kv` covers; t0 >= t1 for an empty split.  `split` must be wavefront-uniform.
-__device__ __forceinline__ void ctx_split_range(const QueryArgs& a, const KvView& kv, int split, long& t0, long& t1) {
+template <typename Args>
+__device__ __forceinline__ void ctx_split_range(const Args& a, const KvView& kv, int split, long& t0, long& t1) {
     if (a.split_ranges == nullptr) {
         t0 = (long)split * a.ctx_split_len;
         t1 = min((long)kv.total_ctx, t0 + a.ctx_split_len);
@@ -322,6 +324,13 @@ inline dim3 uneven_grid(const QueryArgs& a, int n_qtiles) {
     return dim3((unsigned)((((long)a.n_own_splits * a.n_kv_heads + 7) / 8 * 8 + ((long)a.n_req * a.n_kv_heads + 7) / 8 * 8) * n_qtiles));
 }
 
+// The few-row kernels (up to 16 rows per KV head, bf16, up to 16 MB between a KV head's tokens): whether they serve a call, and how: a workgroup for
+// all of a (request, KV head), or for a split of it with a CU's LDS or half of it.
+constexpr long kFewStride = 1 << 24;
+constexpr int kFewRows = 16;
+enum class FewForm { no, whole, full, half };
+FewForm few_form(const ShapeInfo& si, int batch, int q_len, long max_ctx, bool uneven);
+
 // rows per workgroup of a query that runs without splits, or 0 (see the definition)
 int whole_block_rows(const ShapeInfo& si, int ctx_splits, int batch, int q_len, long max_ctx, long own);
 
@@ -330,6 +339,7 @@ hipError_t launch_generic_query(const QueryArgs& a, int dtype, hipStream_t s);
 hipError_t launch_generic_encode(const EncodeArgs& a, int dtype, hipStream_t s);
 // any supported shape; block_rows from the plan; whole: one workgroup per tile of 32 rows and KV head, writing the output
 hipError_t launch_tile_query(const QueryArgs& a, int dtype, int block_rows, bool whole, hipStream_t s);
+hipError_t launch_few_rows(const QueryArgs& a, FewForm form, hipStream_t s);
 hipError_t launch_tile_encode(const EncodeArgs& a, int dtype, hipStream_t s);
 // its rows per workgroup, and how its tiles are dealt out (see the definitions)
 int tile_encode_block_rows(const EncodeArgs& a, int dtype);

@@ -1,0 +1,82 @@
+"""GPU parity of the few-row kernels (up to 16 (token, head) rows per KV head, bf16) against the oracle: head_dims that fill LDS rows and that do not,
+blocks of 32 tokens that end with a context and that hold several, more contexts than the lanes hold at once, both sides of the lengths up to which a
+call runs without splits, batches, the tree, tokens that a row does not see."""
+import numpy as np
+import pytest
+import torch
+
+from paper_2502_05431_amd import binding as B
+from paper_2502_05431_amd import workloads as W
+
+import helpers as H
+
+pytestmark = pytest.mark.gpu
+DEV = "cuda:0"
+SHAPES = [(8, 2, 128), (16, 1, 128), (3, 3, 128), (16, 8, 256), (5, 1, 200), (8, 2, 64), (6, 2, 40), (8, 8, 96), (7, 1, 8)]
+
+
+def _spec(hq, hkv, d, lens, q_len, prefix, own):
+    return W.WorkloadSpec(name="few", cfg=6, dtype="bf16", n_q_heads=hq, n_kv_heads=hkv, head_dim=d, prefix_len=prefix,
+                          chunk_lens=tuple(lens), q_len=q_len, decode_steps=own, temperature=0.6, scale=0.8)
+
+
+def _check(spec, r, q_len, self_len, out, lse, h=None):
+    ref, ref_lse, _ = H.oracle_prefill(h or H.HostArrays(r), q_len, self_len, r.temperature, r.scale)
+    H.check_close(H.f64(out).reshape(-1, spec.head_dim), ref, "bf16", "%s rows %d" % (spec, q_len))
+    got = H.f64(lse).reshape(-1) if lse.shape[0] != spec.n_q_heads or lse.dim() == 1 else H.f64(lse).T.reshape(-1)
+    assert np.abs(got - ref_lse).max() <= H.lse_tol("bf16")
+
+
+@pytest.mark.parametrize("hq, hkv, d", SHAPES)
+@pytest.mark.parametrize("lens, prefix, own", [
+    ((31,), 0, 0), ((32,), 32, 31), ((33, 95), 7, 33), ([2] * 70 + [0] * 3 + [1, 61], 1, 5), ([0, 40, 0, 25, 64] * 26 + [3], 40, 300),
+    ((384,), 0, 1), ((385,), 0, 1), ((300, 213), 5, 60), ((1000, 1, 1047), 64, 100), ([128] * 3, 600, 900)])
+def test_streams(hq, hkv, d, lens, prefix, own):
+    rows = max(1, 16 // (hq // hkv))
+    spec = _spec(hq, hkv, d, lens, rows, prefix, own)
+    r = W.make_request(spec, DEV)
+    h = H.HostArrays(r)
+    req = H.make_binding_request(r, own + rows, separate_buffers=True)
+    for q_len in {1, rows}:
+        out, lse = H.run_decode(spec, [r], [own + rows], reqs=[req]) if q_len == 1 else H.run_prefill(spec, r, q_len, own + rows, req=req)
+        _check(spec, r, q_len, own + rows, out, lse[0] if q_len == 1 else lse, h)
+
+
+@pytest.mark.parametrize("hq, hkv, d, n, ctx", [(8, 2, 128, 35, 300), (32, 8, 128, 17, 900), (8, 2, 128, 9, 900), (16, 8, 256, 3, 500), (8, 8, 96, 5, 700), (8, 2, 64, 20, 1500)])
+def test_batches(hq, hkv, d, n, ctx):
+    specs = [_spec(hq, hkv, d, (ctx - 3 * b - 40, 40 + 2 * b), 1, 11, 40) for b in range(n)]
+    rs = [W.make_request(s, DEV, request=b) for b, s in enumerate(specs)]
+    lens = [1 + (7 * b) % 40 for b in range(n)]
+    out, lse = H.run_decode(specs[0], rs, lens)
+    for b in range(n):
+        _check(specs[b], rs[b], 1, lens[b], out[b], lse[b])
+
+
+@pytest.mark.parametrize("hq, hkv, d", [(8, 2, 128), (4, 2, 256), (6, 2, 40)])
+@pytest.mark.parametrize("nodes", ["per_context", "grouped"])
+def test_tree(hq, hkv, d, nodes):
+    lens = [50, 1, 128, 33, 300, 64, 2, 95]
+    tree = W.tree_per_context(len(lens), 0.85) if nodes == "per_context" else W.tree_grouped(len(lens), 3, 0.9, 0.85)
+    spec = _spec(hq, hkv, d, lens, 2, 20, 30)
+    r = W.make_request(spec, DEV)
+    h = H.HostArrays(r)
+    for q_len in (1, 2):
+        out, lse = H.run_tree(spec, r, tree, q_len, 32)
+        ref, ref_lse = H.oracle_tree(h, q_len, 32, r.temperature, tree)
+        H.check_close(H.f64(out).reshape(-1, d), ref, "bf16", "tree")
+        assert np.abs(H.f64(lse).T.reshape(-1) - ref_lse).max() <= H.lse_tol("bf16")
+
+
+@pytest.mark.parametrize("hq, hkv, d", [(8, 2, 128), (4, 2, 256), (6, 2, 40)])
+@pytest.mark.parametrize("value", [float("inf"), float("nan")])
+@pytest.mark.parametrize("ctx", [100, 900])
+def test_a_token_that_a_row_does_not_see(hq, hkv, d, value, ctx):
+    """Rows in front of a token that holds no number keep their results; the last row sees it."""
+    spec = _spec(hq, hkv, d, (ctx,), 3, 5, 20)
+    r = W.make_request(spec, DEV)
+    h = H.HostArrays(r)
+    ref, _, _ = H.oracle_prefill(h, 3, 23, r.temperature, r.scale)
+    r.v_self[22] = value
+    out, _ = H.run_prefill(spec, r, 3, 23)
+    H.check_close(H.f64(out[:2]).reshape(-1, d), ref[:2 * hq], "bf16", "rows in front of it")
+    assert not torch.isfinite(out[2].float()).any()

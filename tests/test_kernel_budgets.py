@@ -66,3 +66,12 @@ def test_tile_and_walk_kernels_keep_their_register_budget():
         assert r["Occupancy"] >= 2 and r["AGPRs"] == 0, (name, r)
         if re.search(r"tile_\w+_kernelIDF16bLi64ELi4ELi1ELi1E", name):
             assert r["Occupancy"] >= 4, (name, r)         # 32 KB of LDS: five workgroups fit a CU
+
+
+def test_few_row_kernels_keep_their_register_budget():
+    rep = _report()["ape_few_rows.hip"]
+    assert len(rep) == 18
+    for name, r in rep.items():
+        dp, waves = map(int, re.search(r"few_rows_kernelI\w+?Li(\d+)ELi(\d+)E", name).groups())
+        # LDS has room for 16, 8 or 4 wavefronts on a CU
+        assert r["Occupancy"] >= {64: 3, 128: 2, 256: 1}[dp] and (dp == 256 or r["AGPRs"] == 0), (name, r)
