@@ -192,13 +192,23 @@ QueryPlan tile_decode_plan(const ShapeInfo& si, int batch, long max_ctx) {
 // block at a time together.  For the same reason a batch: 4 x 4096 19.4 / 18.6, 8 x 2048 19.4 / 19.2, 8 x 4096 28.2 / 29.4, 4 x 10240, heads of 64, 21.4 / 24.3; and with requests
 // of different lengths, whose splits those deal out (8 of 1 to 15 x 256 23.9 / 24.4).  Whole: split / whole, 384 tokens 8.5 / 7.5, 512 8.7 / 9.6; heads
 // of 64 over 512 8.2 / 7.1, 1024 8.4 / 9.1; of 256 over 128 10.0 / 9.7, 256 10.1 / 12.1; and where the requests give every CU one: 32 x 1024 32.7 / 26.2, 32 x 4096 94 / 86.9,
-// 16/8 heads of 256, 32 x 1024, 57 / 47.7 (before: 29.9, 86.9, 72.3), but 16 x 2048 29.8 / 33.1.
+// 16/8 heads of 256, 32 x 1024, 57 / 47.7 (before: 29.9, 86.9, 72.3), but 16 x 2048 29.8 / 33.1.  fp32, before / split / whole: 4096 tokens 23.4 / 16.9 / -, 256
+// 17.0 / 13.6 / 17.0, 128 17.0 / 13.6 / 13.8, 4/2 heads of 64 over 256 13.4 / 9.9 / 10.6, 16 requests of 2048 of them 25.0 / 15.1 / -.
+// More than 16 rows run whole, in tiles of 16 that read the same tokens, as long as every one has a CU: before / whole, 16 query tokens over 256
+// 13.5 / 7.5, 768 14.4 / 12.3, 1024 14.1 / 15.5, 64 over 768 16.8 / 12.3, 128 over 256 15.3 / 8.8, but 3 x 64 over 256 (384 workgroups) 13.9 / 14.6; heads of 64,
+// 64 over 1024 11.8 / 10.5, 16 over 1536 9.8 / 12.4; of 256, 16 over 256 13.8 / 11.9, 384 13.8 / 14.7; fp32, 16 over 256 16.1 / 13.9, 384 16.3 / 16.8, 4/2 heads of 64, 16 over
+// 256 11.7 / 9.4, 512 11.2 / 12.1.  Split, they read every token once per tile (8 query tokens over 20 x 512 17.4 / 24.0).
 FewForm few_form(const ShapeInfo& si, int batch, int q_len, long max_ctx, bool uneven) {
-    if (si.force_generic || si.dtype != APE_BF16 || (long)q_len * si.group > kFewRows || (long)si.hkv * si.d * 2 > kFewStride) return FewForm::no;
-    const long base = (long)batch * si.hkv, bytes = base * max_ctx * si.d * 4;
-    if (base > 1024) return FewForm::no;
-    if (max_ctx <= (si.d <= 64 ? 512 : si.d <= 128 ? 384 : 128)) return FewForm::whole;
+    const bool f32 = si.dtype == APE_F32;
+    const int elem = f32 ? 4 : 2, width = si.d <= 64 ? 0 : si.d <= 128 ? 1 : 2;
+    const long rows = (long)q_len * si.group, tiles = (rows + kFewRows - 1) / kFewRows, base = (long)batch * si.hkv, stride = (long)si.hkv * si.d * elem;
+    if (si.force_generic || (f32 && width == 2) || rows > 512 || stride > kFewStride || q_len * si.group * stride > 1L << 30) return FewForm::no;
+    if (tiles == 1 ? base > 1024 : base * tiles > 256) return FewForm::no;
+    const long few_rows[2][3] = {{512, 384, 128}, {192, 128, 0}}, more_rows[2][3] = {{1024, 768, 256}, {256, 256, 0}};
+    if (max_ctx <= (tiles == 1 ? few_rows : more_rows)[f32][width]) return FewForm::whole;
+    if (tiles > 1) return FewForm::no;
     if (base > 128 && base <= 256 && max_ctx <= 4096 && !uneven) return FewForm::whole;
+    const long bytes = 2 * (long)batch * max_ctx * stride;
     if (batch == 1 ? bytes > 200L << 20 : uneven || bytes > 64L << 20) return FewForm::no;
     return base <= 32 ? FewForm::full : FewForm::half;
 }
@@ -549,11 +559,11 @@ static int run_query(const ShapeInfo& si, const ape_request* reqs, int batch, in
         }
         if (whole) {
             a.out = out; a.lse_out = lse_out; a.lse_head_major = decode ? 0 : 1;
-            const hipError_t we = few == FewForm::whole ? launch_few_rows(a, few, st) : launch_tile_query(a, si.dtype, whole, true, st);
+            const hipError_t we = few == FewForm::whole ? launch_few_rows(a, si.dtype, few, st) : launch_tile_query(a, si.dtype, whole, true, st);
             if (we != hipSuccess) return fail(APE_ERR_DEVICE, "attention kernel: %s", hipGetErrorString(we));
             continue;
         }
-        hipError_t he = few != FewForm::no ? launch_few_rows(a, few, st) : launch_query(si, a, plan.block_rows, st);
+        hipError_t he = few != FewForm::no ? launch_few_rows(a, si.dtype, few, st) : launch_query(si, a, plan.block_rows, st);
         if (he != hipSuccess) return fail(APE_ERR_DEVICE, "attention kernel: %s", hipGetErrorString(he));
 
         m.part_o = part_o; m.part_lse = a.part_lse; m.out = out; m.lse_out = lse_out;
@@ -725,7 +735,7 @@ int ape_attention_tree(const ape_shape* shape, const ape_request* req,
     a.split_ranges = plan_dev + TreePlanLayout{n_nodes, plan.max_splits}.ranges_at();
     a.units_total = (int)units; a.req_base = 0;
     const FewForm few = few_form(si, 1, q_len, req->total_ctx_len, false);
-    he = few != FewForm::no ? launch_few_rows(a, FewForm::half, st) : launch_query(si, a, plan.block_rows, st);
+    he = few != FewForm::no ? launch_few_rows(a, si.dtype, FewForm::half, st) : launch_query(si, a, plan.block_rows, st);
     if (he != hipSuccess) return fail(APE_ERR_DEVICE, "attention kernel: %s", hipGetErrorString(he));
 
     m.part_o = part_o; m.part_lse = part_lse; m.out = out; m.lse_out = lse_out; m.nodes = nodes_dev; m.plan = plan_dev;

@@ -324,8 +324,8 @@ inline dim3 uneven_grid(const QueryArgs& a, int n_qtiles) {
     return dim3((unsigned)((((long)a.n_own_splits * a.n_kv_heads + 7) / 8 * 8 + ((long)a.n_req * a.n_kv_heads + 7) / 8 * 8) * n_qtiles));
 }
 
-// The few-row kernels (up to 16 rows per KV head, bf16, up to 16 MB between a KV head's tokens): whether they serve a call, and how: a workgroup for
-// all of a (request, KV head), or for a split of it with a CU's LDS or half of it.
+// The few-row kernels (tiles of 16 rows, up to 16 MB between a KV head's tokens): whether they serve a call, and how: a workgroup for all
+// of a (request, KV head, tile), or for a split of it with a CU's LDS or half of it.
 constexpr long kFewStride = 1 << 24;
 constexpr int kFewRows = 16;
 enum class FewForm { no, whole, full, half };
@@ -339,7 +339,7 @@ hipError_t launch_generic_query(const QueryArgs& a, int dtype, hipStream_t s);
 hipError_t launch_generic_encode(const EncodeArgs& a, int dtype, hipStream_t s);
 // any supported shape; block_rows from the plan; whole: one workgroup per tile of 32 rows and KV head, writing the output
 hipError_t launch_tile_query(const QueryArgs& a, int dtype, int block_rows, bool whole, hipStream_t s);
-hipError_t launch_few_rows(const QueryArgs& a, FewForm form, hipStream_t s);
+hipError_t launch_few_rows(const QueryArgs& a, int dtype, FewForm form, hipStream_t s);
 hipError_t launch_tile_encode(const EncodeArgs& a, int dtype, hipStream_t s);
 // its rows per workgroup, and how its tiles are dealt out (see the definitions)
 int tile_encode_block_rows(const EncodeArgs& a, int dtype);
