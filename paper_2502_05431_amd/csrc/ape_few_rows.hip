@@ -90,9 +90,6 @@ struct FewWalk {
         c0 = cu[c]; c1 = cu[c + 1];
         kp = (uint64_t)kt[c]; vp = (uint64_t)vt[c];
     }
-    static __device__ __forceinline__ uint64_t lane64(uint64_t x, int lane) {
-        return (uint64_t)(uint32_t)__builtin_amdgcn_readlane((int)(uint32_t)(x >> 32), lane) << 32 | (uint32_t)__builtin_amdgcn_readlane((int)(uint32_t)x, lane);
-    }
     // The lane of the context that holds index i (i < cu[n_chunks]): the first one that ends behind it (empty ones never do).
     __device__ __forceinline__ int context_of(int i) {
         uint64_t there;
@@ -130,7 +127,7 @@ __device__ __forceinline__ FewBlock take(FewWalk& w) {
     if (w.cu) {
         int l = w.context_of(b.t);
         int from = __builtin_amdgcn_readlane(w.c0, l), to = __builtin_amdgcn_readlane(w.c1, l);
-        uint64_t k = w.lane64(w.kp, l) + w.head, v = w.lane64(w.vp, l) + w.head;
+        uint64_t k = lane_u64(w.kp, l) + w.head, v = lane_u64(w.vp, l) + w.head;
         if (__builtin_expect(last < to, 1)) {
             b.k = (const char*)k + (long)(b.t - from) * w.stride; b.v = (const char*)v + (long)(b.t - from) * w.stride;
             return b;
@@ -140,7 +137,7 @@ __device__ __forceinline__ FewBlock take(FewWalk& w) {
             if (last < to) return b;
             l = w.context_of(to);
             from = __builtin_amdgcn_readlane(w.c0, l); to = __builtin_amdgcn_readlane(w.c1, l);
-            k = w.lane64(w.kp, l) + w.head; v = w.lane64(w.vp, l) + w.head;
+            k = lane_u64(w.kp, l) + w.head; v = lane_u64(w.vp, l) + w.head;
         }
     }
     if (last < w.np || b.t >= w.np) {
@@ -352,25 +349,6 @@ __device__ __forceinline__ void few_stream(FewWalk& walk, const FewOffsets<T, DP
         o[4] = o[3]; o[3] = o[2]; o[2] = o[1]; o[1] = o[0]; o[0] = o4;
     }
 }
-
-// The arguments of a call with a single request: in 200 bytes rather than 2800, which the host writes and the kernel reads in 0.4 us less.
-struct OneQuery {
-    static constexpr int kRequests = 1;
-    KvView req[1];
-    const void* q;
-    float* part_o;
-    float* part_lse;
-    int32_t n_req, q_len, n_q_heads, n_kv_heads, head_dim, n_ctx_splits, ctx_split_len, units_total;
-    const int32_t* split_ranges;
-    int32_t req_base;
-    int32_t lse_head_major;
-    void* out;
-    float* lse_out;
-    explicit OneQuery(const QueryArgs& a)
-        : req{a.req[0]}, q(a.q), part_o(a.part_o), part_lse(a.part_lse), n_req(1), q_len(a.q_len), n_q_heads(a.n_q_heads), n_kv_heads(a.n_kv_heads),
-          head_dim(a.head_dim), n_ctx_splits(a.n_ctx_splits), ctx_split_len(a.ctx_split_len), units_total(a.units_total), split_ranges(a.split_ranges),
-          req_base(a.req_base), lse_head_major(a.lse_head_major), out(a.out), lse_out(a.lse_out) {}
-};
 
 // A split's workgroup writes a partial result.  WHOLE: one workgroup per (request, KV head), with wavefronts of their own for the contexts and for the
 // prefix and own tokens, whose results make the output.

@@ -39,6 +39,7 @@
 #define ape_ring_load_ptr ::ape::scalar_load_ptr
 #define ape_ring_load_chunk ::ape::scalar_load_chunk
 #define ape_ring_find_chunk ::ape::find_chunk
+#define ape_ring_first_chunk ::ape::first_chunk
 #include "ape_ring.h"
 
 #include <math.h>
@@ -951,8 +952,8 @@ __device__ __forceinline__ void init_state(WaveState<RB>& st) {
 // n_qtiles, then the prefix+self teams likewise.
 // Rows: R = qtile*BM + wave*32*RB + rb*32 + (lane & 31); query token = R / G, head = hk*G + R % G.
 // UNEVEN: the requests of a batch have splits of their own (QueryArgs::n_own_splits), and the whole batch lies in x.
-template <int RB, int G, bool NTL, bool UNEVEN>
-__device__ __forceinline__ void query_tile(const QueryArgs& a, const int n_qtiles, char* const lds) {
+template <int RB, int G, bool NTL, bool UNEVEN, typename Args>
+__device__ __forceinline__ void query_tile(const Args& a, const int n_qtiles, char* const lds) {
     constexpr int BM = NW * 32 * RB;
     const int tid = threadIdx.x;
     const int lane = tid & 63, wave = tid >> 6;
@@ -960,10 +961,12 @@ __device__ __forceinline__ void query_tile(const QueryArgs& a, const int n_qtile
     // Blocks of the context splits come first: they are the long ones, and the grid is planned so
     // that they fill the chip exactly once; the short prefix+self workgroups follow.
     int team, qtile, split, hk;
-    const int ctx_teams = (UNEVEN ? a.n_own_splits : a.n_ctx_splits) * a.n_kv_heads;
+    constexpr bool ONE = Args::kRequests == 1;
+    int ctx_teams = a.n_ctx_splits * a.n_kv_heads;
+    if constexpr (UNEVEN) ctx_teams = a.n_own_splits * a.n_kv_heads;
     const int ctx_blocks = (ctx_teams + 7) / 8 * 8 * n_qtiles;
-    int bx = blockIdx.x, rq = blockIdx.y;                // position in the request's part of the grid; request
-    if (!UNEVEN && a.n_req > 1) {
+    int bx = blockIdx.x, rq = ONE ? 0 : blockIdx.y;      // position in the request's part of the grid; request
+    if (!UNEVEN && !ONE && a.n_req > 1) {
         // A batch: the context workgroups of ALL requests first, then every request's short prefix+self ones, in the
         // order workgroups are dispatched (x fastest, then y).  Dealt request by request, the short ones sit between the
         // long ones and leave their slots early, which spoils the balance when the long ones are few (three requests of 64
@@ -988,7 +991,7 @@ __device__ __forceinline__ void query_tile(const QueryArgs& a, const int n_qtile
         // An uneven batch has it there too, so that every XCD gets the same share of every request (with the split fastest, the last
         // splits, which only long requests have, meet on few XCDs: 32 requests of 1 to 15 x 1024 tokens, four splits, 220 against 176 us).
         if constexpr (UNEVEN) { hk = team % a.n_kv_heads; own_split(a.n_req, team / a.n_kv_heads, rq, split); }
-        else if (a.split_ranges != nullptr || (n_qtiles == 1 && a.n_req == 1)) { hk = team % a.n_kv_heads; split = team / a.n_kv_heads; }
+        else if (a.split_ranges != nullptr || (n_qtiles == 1 && (ONE || a.n_req == 1))) { hk = team % a.n_kv_heads; split = team / a.n_kv_heads; }
         else { split = team % a.n_ctx_splits; hk = team / a.n_ctx_splits; }
     } else {
         team_of_block(bx - ctx_blocks, n_qtiles, team, qtile);
@@ -996,7 +999,7 @@ __device__ __forceinline__ void query_tile(const QueryArgs& a, const int n_qtile
         split = a.n_ctx_splits; hk = team;
         if constexpr (UNEVEN) { hk = team % a.n_kv_heads; rq = team / a.n_kv_heads; }
     }
-    const KvView kv = load_view<QueryArgs>(rq);
+    const KvView kv = load_view<Args>(rq);
     const int hq = a.n_q_heads, q_len = a.q_len;
     const long stride_b = (long)a.n_kv_heads * ROWB, head_b = (long)hk * ROWB;
 
@@ -1063,7 +1066,8 @@ __device__ __forceinline__ void query_tile(const QueryArgs& a, const int n_qtile
         if (tok >= q_len) continue;
         const float inv = lt > 0.f ? 1.f / lt : 0.f;
         const long unit = ((long)(a.req_base + rq) * q_len + tok) * hq + hk * G + g;
-        const long slot = UNEVEN ? own_partial_rows(a, rq, split) + (long)tok * hq + hk * G + g : (long)split * a.units_total + unit;
+        long slot = (long)split * a.units_total + unit;
+        if constexpr (UNEVEN) slot = own_partial_rows(a, rq, split) + (long)tok * hq + hk * G + g;
         float* o = a.part_o + slot * D;
 #pragma unroll
         for (int db = 0; db < 4; ++db)
@@ -1080,6 +1084,11 @@ __device__ __forceinline__ void query_tile(const QueryArgs& a, const int n_qtile
 
 template <int RB, int G, bool NTL>
 __global__ __launch_bounds__(NT) void flash_prefill_kernel(const QueryArgs a, int n_qtiles) {
+    extern __shared__ __attribute__((aligned(16))) char lds[];
+    query_tile<RB, G, NTL, false>(a, n_qtiles, lds);
+}
+template <int RB, int G, bool NTL>
+__global__ __launch_bounds__(NT) void flash_single_kernel(const OneQuery a, int n_qtiles) {
     extern __shared__ __attribute__((aligned(16))) char lds[];
     query_tile<RB, G, NTL, false>(a, n_qtiles, lds);
 }
@@ -1223,6 +1232,12 @@ __global__ __launch_bounds__(NT) void flash_encode_kernel(const EncodeArgs a, in
 
 template <int RB, int G, bool NTL>
 hipError_t launch_prefill_t(const QueryArgs& a, dim3 grid, int n_qtiles, hipStream_t s) {
+    if (a.n_req == 1) {
+        hipError_t e = hipFuncSetAttribute((const void*)flash_single_kernel<RB, G, NTL>, hipFuncAttributeMaxDynamicSharedMemorySize, Ring<RB>::slots * SLOTB);
+        if (e != hipSuccess) return e;
+        flash_single_kernel<RB, G, NTL><<<grid, NT, Ring<RB>::slots * SLOTB, s>>>(OneQuery(a), n_qtiles);
+        return hipGetLastError();
+    }
     auto kernel = a.n_own_splits > 0 ? flash_uneven_kernel<RB, G, NTL> : flash_prefill_kernel<RB, G, NTL>;
     hipError_t e = hipFuncSetAttribute((const void*)kernel, hipFuncAttributeMaxDynamicSharedMemorySize, Ring<RB>::slots * SLOTB);
     if (e != hipSuccess) return e;

@@ -62,6 +62,25 @@ struct QueryArgs {
     int32_t lse_head_major;     // as in MergeArgs
 };
 
+// The arguments of a call with a single request: 200 bytes rather than 2800 (0.3 us less for the host to write, 0.2 for the kernel to read).
+struct OneQuery {
+    static constexpr int kRequests = 1;
+    KvView req[1];
+    const void* q;
+    float* part_o;
+    float* part_lse;
+    int32_t n_req, q_len, n_q_heads, n_kv_heads, head_dim, n_ctx_splits, ctx_split_len, units_total;
+    const int32_t* split_ranges;
+    int32_t req_base;
+    int32_t lse_head_major;
+    void* out;
+    float* lse_out;
+    explicit OneQuery(const QueryArgs& a)
+        : req{a.req[0]}, q(a.q), part_o(a.part_o), part_lse(a.part_lse), n_req(1), q_len(a.q_len), n_q_heads(a.n_q_heads), n_kv_heads(a.n_kv_heads),
+          head_dim(a.head_dim), n_ctx_splits(a.n_ctx_splits), ctx_split_len(a.ctx_split_len), units_total(a.units_total), split_ranges(a.split_ranges),
+          req_base(a.req_base), lse_head_major(a.lse_head_major), out(a.out), lse_out(a.lse_out) {}
+};
+
 struct MergeArgs {
     const float* part_o;
     const float* part_lse;
@@ -246,6 +265,29 @@ __device__ __forceinline__ void scalar_load_chunk(const int32_t* cu_next, const 
                  : "=&s"(c1), "=&s"(kk), "=&s"(vv)
                  : "s"(uniform_address(cu_next)), "s"(uniform_address(kp)), "s"(uniform_address(vp)) : "memory");
     k = (const void*)kk; v = (const void*)vv;
+}
+
+// The chunk that holds pooled context index t, and its entry: up to 64 chunks are read at once, one per lane, and the chunk is the first that ends
+// behind t (a search and four reads one after the other are 0.6 us more in front of a workgroup's first K/V load).
+__device__ __forceinline__ uint64_t lane_u64(uint64_t x, int lane) {
+    return (uint64_t)(uint32_t)__builtin_amdgcn_readlane((int)(uint32_t)(x >> 32), lane) << 32 | (uint32_t)__builtin_amdgcn_readlane((int)(uint32_t)x, lane);
+}
+__device__ __forceinline__ int first_chunk(const int32_t* cu, const void* const* kp, const void* const* vp, int n_chunks, int t, int32_t& c0, int32_t& c1,
+                                           const void*& k, const void*& v) {
+    if (n_chunks > 64) {
+        const int c = find_chunk(cu, n_chunks, t);
+        c0 = scalar_load_i32(cu + c);
+        scalar_load_chunk(cu + c + 1, kp + c, vp + c, c1, k, v);
+        return c;
+    }
+    const int l = min((int)(threadIdx.x & 63), n_chunks - 1);
+    const int from = cu[l], to = cu[l + 1];
+    const uint64_t kl = (uint64_t)kp[l], vl = (uint64_t)vp[l];
+    const uint64_t there = __builtin_amdgcn_ballot_w64(to > t);
+    const int c = there != 0 ? __builtin_ctzll(there) : n_chunks - 1;   // (none: the table is shorter than the caller says)
+    c0 = __builtin_amdgcn_readlane(from, c); c1 = __builtin_amdgcn_readlane(to, c);
+    k = (const void*)lane_u64(kl, c); v = (const void*)lane_u64(vl, c);
+    return c;
 }
 
 template <typename Args>

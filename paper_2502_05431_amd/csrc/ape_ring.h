@@ -9,11 +9,21 @@
 // The includer defines APE_RING_FN (function qualifiers), the table readers ape_ring_load_i32 /
 // ape_ring_load_ptr / ape_ring_load_chunk (scalar loads on the GPU, plain reads on the host) and
 // ape_ring_find_chunk(cu, n_chunks, t) = the largest c with cu[c] <= t (a search across the lanes
-// on the GPU, a plain one on the host).
+// on the GPU, a plain one on the host).  It may define ape_ring_first_chunk, which finds that chunk and reads its entry in one.
 #pragma once
 #include <stdint.h>
 
 namespace ape {
+
+#ifndef ape_ring_first_chunk
+APE_RING_FN int ape_ring_first_chunk(const int32_t* cu, const void* const* kp, const void* const* vp, int n_chunks, int t, int32_t& c0, int32_t& c1,
+                                     const void*& k, const void*& v) {
+    const int c = ape_ring_find_chunk(cu, n_chunks, t);
+    c0 = ape_ring_load_i32(cu + c);
+    ape_ring_load_chunk(cu + c + 1, kp + c, vp + c, c1, k, v);
+    return c;
+}
+#endif
 
 constexpr int BLK = 32;                      // KV tokens per block
 constexpr int ROWB = 128 * 2;                // bytes of one head's K or V row (head_dim 128, bf16)
@@ -48,17 +58,13 @@ struct Stream {
     const char *kc, *vc;
     int nc;
 
-    // Opens the segment that starts at pooled index t (t < t1).
-    APE_RING_FN void open_ctx() {
-        const void *kb = nullptr, *vb = nullptr;
-        bool have = false;
+    // Opens the segment that starts at pooled index t (t < t1); kb, vb: the rows of chunk c, if t lies in it.
+    APE_RING_FN void open_ctx(const void* kb, const void* vb) {
         while (t >= c1) {                                          // the next chunk, skipping empty ones
             if (c + 1 >= n_chunks) return;                         // table shorter than total_ctx: stop, stay in bounds
             ++c; c0 = c1;
             ape_ring_load_chunk(cu + c + 1, k_chunks + c, v_chunks + c, c1, kb, vb);   // one round trip per chunk
-            have = true;
         }
-        if (!have) { kb = ape_ring_load_ptr(k_chunks + c); vb = ape_ring_load_ptr(v_chunks + c); }
         const long off = (long)(t - c0) * stride_b + head_b;
         k = (const char*)kb + off;
         v = (const char*)vb + off;
@@ -72,9 +78,9 @@ struct Stream {
         k = v = kc = vc = nullptr; nc = 0; rem = 0; run = 0; j0 = -1; jstep = 0;
         t = t0_; t1 = t1_; c = 0; c0 = c1 = 0;
         if (t < t1 && cu != nullptr && n_chunks > 0) {
-            c = ape_ring_find_chunk(cu, n_chunks, t);              // the largest c with cu[c] <= t
-            c0 = ape_ring_load_i32(cu + c); c1 = ape_ring_load_i32(cu + c + 1);
-            open_ctx();
+            const void *kb, *vb;
+            c = ape_ring_first_chunk(cu, k_chunks, v_chunks, n_chunks, t, c0, c1, kb, vb);   // the largest c with cu[c] <= t
+            open_ctx(kb, vb);
         }
     }
     APE_RING_FN void init_seq(const char* kp, const char* vp, int np, const char* kc_, const char* vc_, int nc_, long stride_b_) {
@@ -94,7 +100,7 @@ struct Stream {
                 // the blocks on either side of the boundary are indistinguishable to the compute side.
                 // (After a partial block run_before is 0 already.)
                 const char *k_end = k, *v_end = v;
-                open_ctx();
+                open_ctx(nullptr, nullptr);                        // (t is where chunk c ends)
                 if (rem > 0 && k == k_end && v == v_end) run = run_before;
             }
         } else if (nc > 0) {
