@@ -9,6 +9,8 @@
 // use scores q.k/(T sqrt d); the merge multiplies the pooled context LogSumExp by S (C.3/C.4).
 #include "ape_internal.h"
 
+#include <type_traits>
+
 #include <math.h>
 
 namespace ape {
@@ -207,7 +209,7 @@ __global__ __launch_bounds__(kWave) void generic_encode_kernel(const EncodeArgs 
 // Whole calls, against a workgroup per unit that read the LogSumExps and then the rows of one group after the other (us): a decode
 // step over 20 x 512 tokens, 32 units of 33 splits, 17.8 -> 15.3; 80 units of 33 splits of a 20-row query 25.9 -> 23.6; 64 rows,
 // 32/8 bf16 heads of 64, 30.7 -> 27.4; 256 rows over 128K tokens, 8192 units of 9 splits, 481 -> 480.
-template <typename T, int NV, int H, bool UNEVEN>
+template <typename T, int NV, int H, bool UNEVEN, bool ONE>
 __device__ __forceinline__ void merge_units(const MergeArgs& a) {
     constexpr int UN = 8;
     __shared__ float4 part[H > 1 ? 8 : 1][32 * NV];
@@ -218,7 +220,7 @@ __device__ __forceinline__ void merge_units(const MergeArgs& a) {
     const bool valid = unit_raw < n_units;
     const long unit = valid ? unit_raw : n_units - 1;                // (a spare half-wavefront recomputes the last unit and stores nothing)
     const int hq = a.n_q_heads, d = a.head_dim;
-    const int rq = (int)(unit / ((long)hq * a.q_len));
+    const int rq = ONE ? 0 : (int)((uint32_t)unit / (uint32_t)(hq * a.q_len));     // (fewer than 2^24 units)
     const long gunit = (long)a.req_base * a.q_len * hq + unit;
     auto ka = kernarg<MergeArgs>();
     const float S = ka->scale[rq];                                   // (per lane: the two halves may belong to different requests)
@@ -326,7 +328,7 @@ __device__ __forceinline__ void merge_units(const MergeArgs& a) {
     if (a.lse_out && j == 0) {
         const float lse = mx + logf(ec + eo);
         if (a.lse_head_major) {                                     // [request, head, row]
-            const int h = (int)(unit % hq), row = (int)((unit / hq) % a.q_len);
+            const int in_rq = (int)unit - rq * a.q_len * hq, row = in_rq / hq, h = in_rq - row * hq;
             a.lse_out[((long)(a.req_base + rq) * hq + h) * a.q_len + row] = lse;
         } else {
             a.lse_out[gunit] = lse;
@@ -335,10 +337,13 @@ __device__ __forceinline__ void merge_units(const MergeArgs& a) {
 }
 
 template <typename T, int NV, int H>
-__global__ __launch_bounds__(256) void merge_units_kernel(const MergeArgs a) { merge_units<T, NV, H, false>(a); }
+__global__ __launch_bounds__(256) void merge_units_kernel(const MergeArgs a) { merge_units<T, NV, H, false, false>(a); }
+// one request: nothing is looked up per lane, so that the LogSumExps and rows are asked for as soon as the arguments are there
+template <typename T, int NV, int H>
+__global__ __launch_bounds__(256) void pool_single_kernel(const MergeArgs a) { merge_units<T, NV, H, false, true>(a); }
 // requests with splits of their own (a kernel of its own: the look-ups would cost the others 0.5 us)
 template <typename T, int NV, int H>
-__global__ __launch_bounds__(256) void pool_uneven_kernel(const MergeArgs a) { merge_units<T, NV, H, true>(a); }
+__global__ __launch_bounds__(256) void pool_uneven_kernel(const MergeArgs a) { merge_units<T, NV, H, true, false>(a); }
 
 // ------------------------------------------------------------------------------------------
 // Tree of contexts (Appendix C.2 applied at every node, Appendix C.5).
@@ -370,9 +375,9 @@ __global__ __launch_bounds__(kPlanThreads) void tree_plan_kernel(const TreePlanA
     __syncthreads();
     if (tid < kWave) {
         // lane owns a run of consecutive nodes; wavefront scan of the run sums, then the runs
-        constexpr int RUN = APE_TREE_MAX_NODES / kWave;
+        const int run_len = (a.n_nodes + kWave - 1) / kWave;         // (no counts behind the last node)
         int sum = 0;
-        for (int j = 0; j < RUN; ++j) sum += cnt[lane * RUN + j];
+        for (int j = 0; j < run_len; ++j) sum += cnt[lane * run_len + j];
         int incl = sum;
 #pragma unroll
         for (int o = 1; o < kWave; o <<= 1) {
@@ -380,7 +385,7 @@ __global__ __launch_bounds__(kPlanThreads) void tree_plan_kernel(const TreePlanA
             if (lane >= o) incl += v;
         }
         int run = incl - sum;
-        for (int j = 0; j < RUN; ++j) { off[lane * RUN + j] = run; run += cnt[lane * RUN + j]; }
+        for (int j = 0; j < run_len; ++j) { off[lane * run_len + j] = run; run += cnt[lane * run_len + j]; }
         if (lane == kWave - 1) a.plan[0] = min(incl, a.max_splits);
     }
     __syncthreads();
@@ -764,11 +769,13 @@ hipError_t launch_merge_t(const MergeArgs& a, hipStream_t s) {
     const int slots = a.n_splits_total;
     const int h = units >= 4096 || slots <= 8 ? 1 : slots <= 16 ? 2 : slots <= 32 ? 4 : 8;
     const unsigned blocks = (unsigned)((units * h + 7) / 8);
-    const bool un = a.n_own_splits > 0;
-    auto kernel = h == 1 ? (un ? pool_uneven_kernel<T, NV, 1> : merge_units_kernel<T, NV, 1>)
-                : h == 2 ? (un ? pool_uneven_kernel<T, NV, 2> : merge_units_kernel<T, NV, 2>)
-                : h == 4 ? (un ? pool_uneven_kernel<T, NV, 4> : merge_units_kernel<T, NV, 4>)
-                         : (un ? pool_uneven_kernel<T, NV, 8> : merge_units_kernel<T, NV, 8>);
+    const bool un = a.n_own_splits > 0, one = a.n_req == 1 && !un;
+    auto pick = [&](auto n) {
+        constexpr int H = n();
+        return un ? pool_uneven_kernel<T, NV, H> : one ? pool_single_kernel<T, NV, H> : merge_units_kernel<T, NV, H>;
+    };
+    auto kernel = h == 1 ? pick(std::integral_constant<int, 1>()) : h == 2 ? pick(std::integral_constant<int, 2>())
+                : h == 4 ? pick(std::integral_constant<int, 4>()) : pick(std::integral_constant<int, 8>());
     kernel<<<blocks, 256, 0, s>>>(a);
     return hipGetLastError();
 }

@@ -252,8 +252,9 @@ __device__ __forceinline__ void ctx_split_range(const Args& a, const KvView& kv,
         t1 = min((long)kv.total_ctx, t0 + a.ctx_split_len);
         return;
     }
-    t0 = scalar_load_i32(a.split_ranges + 2 * split);
-    t1 = scalar_load_i32(a.split_ranges + 2 * split + 1);
+    uint64_t r;                                             // both in one round trip (the pairs are 8-byte aligned: see TreePlanLayout)
+    asm volatile("s_load_dwordx2 %0, %1, 0x0\n\ts_waitcnt lgkmcnt(0)" : "=s"(r) : "s"(uniform_address(a.split_ranges + 2 * split)) : "memory");
+    t0 = (int32_t)(uint32_t)r; t1 = (int32_t)(uint32_t)(r >> 32);
 }
 
 // One chunk-table entry in a single round trip: cu[c + 1] and the K and V base pointers of chunk c
