@@ -350,6 +350,9 @@ __device__ __forceinline__ void few_stream(FewWalk& walk, const FewOffsets<T, DP
     }
 }
 
+// r / group as (r * inverse) >> kFewShift, the inverse rounded up: exact as long as r * group < 2^kFewShift, and both are 512 or less.
+constexpr int kFewShift = 20;
+
 // A split's workgroup writes a partial result.  WHOLE: one workgroup per (request, KV head), with wavefronts of their own for the contexts and for the
 // prefix and own tokens, whose results make the output.
 template <typename T, typename Args, int DP, int W, bool WHOLE>
@@ -372,7 +375,7 @@ __global__ __launch_bounds__(64 * W) void few_rows_kernel(const Args a, const in
     const long stride = (long)hkv * d * sizeof(T), head = (long)hk * d * sizeof(T);
     const uint32_t width = (uint32_t)sizeof(T) * d;
     const int rows = q_len * G, R0 = 16 * blockIdx.z, R = min(R0 + row, rows - 1);
-    auto token_of = [&](int r) { return (int)(r * group_inv >> 16); };   // r / G
+    auto token_of = [&](int r) { return (int)(r * group_inv >> kFewShift); };   // r / G
     const int tok = token_of(R);
 
     // the wavefront's stream, which it shares with `waves` others: tokens [t0, t1) of the contexts (from_ctx), or the prefix and the own tokens
@@ -507,7 +510,7 @@ hipError_t few_as(const QueryArgs& q, hipStream_t s) {
     hipError_t e = hipFuncSetAttribute((const void*)kernel, hipFuncAttributeMaxDynamicSharedMemorySize, lds);
     if (e != hipSuccess) return e;
     kernel<<<dim3((unsigned)q.n_kv_heads, (unsigned)(splits + q.n_req), (unsigned)((q.q_len * group + 15) / 16)), 64 * W, lds, s>>>
-        (a, group, (uint32_t)((65536 + group - 1) / group));
+        (a, group, (uint32_t)(((1 << kFewShift) + group - 1) / group));
     return hipGetLastError();
 }
 template <typename T, int DP>
