@@ -77,8 +77,8 @@ typedef enum { APE_OP_ENCODE = 0, APE_OP_PREFILL = 1, APE_OP_DECODE = 2 } ape_op
 
 /* Attention head geometry.  Supported: head_dim multiple of 8 and <= 256 for APE_F32 and
  * APE_BF16; n_q_heads a multiple of n_kv_heads.  bf16 with head_dim == 128 and
- * n_q_heads/n_kv_heads in {1,2,4,8} runs on the flash kernels, everything else on matrix-core kernels of
- * its own (fp32 products in fp32). */
+ * n_q_heads/n_kv_heads in {1,2,4,8} runs on the flash kernels (decode steps and queries that are short, or of a few rows over
+ * contexts of middle length, on the few-row kernels), everything else on matrix-core kernels of its own (fp32 products in fp32). */
 typedef struct {
     int32_t n_q_heads;
     int32_t n_kv_heads;

@@ -214,7 +214,8 @@ FewForm few_form(const ShapeInfo& si, int batch, int q_len, long max_ctx, bool u
 }
 
 // Rows per workgroup of a call that runs without splits, one workgroup taking its rows past the contexts and then past the
-// prefix and the own tokens (`own`: of all requests) and writing the output (0: it is split and merged).  Worth it while the longer
+// prefix and the own tokens (`own`: of all requests) and writing the output (0: it is split and merged); asked for calls that the few-row kernels leave, i.e.
+// more tiles of 16 rows than CUs, and fp32 heads beyond 128.  Worth it while the longer
 // stream costs less than the second launch, the partial results and their merge, about 4 us: up to 512 context tokens per request
 // with bf16 heads of up to 64, 256 up to 128 (the flash kernels' shapes too), 128 beyond; 128 with fp32 heads of up to 64, 64 up to
 // 128 (16 rows, split / whole, us: bf16 heads of 64 over 512 tokens 13.7 / 12.0, 1024 14.1 / 16.9; of 128 over 256 15.4 / 14.5, 512
@@ -251,6 +252,7 @@ namespace {
 // that makes requests x KV heads x splits a multiple of 256, if the splits stay at 256 tokens or more
 // and the count at 2048 or less; otherwise many workgroups (at least 8 splits per request, about
 // 2048 workgroups), where the remainder of the last round matters less.
+// (What the few-row kernels serve takes no more splits than this plan has, see run_query.)
 QueryPlan decode_plan(const ShapeInfo& si, int batch, long max_ctx) {
     if (si.tile) return tile_decode_plan(si, batch, max_ctx);
     if (!si.mfma) return plan_query(batch * si.hq, max_ctx, 256, 1024);

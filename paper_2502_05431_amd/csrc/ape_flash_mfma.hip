@@ -1,5 +1,5 @@
 // Matrix-core flash attention for gfx950 (bf16, head_dim 128): query prefill over the cached
-// contexts (split over the keys), the decode step (the same kernel on a tile of which one wavefront has
+// contexts (split over the keys), long decode steps and batches of them (the same kernel on a tile of which one wavefront has
 // query rows and the other three only fetch: it is bound by HBM) and the block-diagonal causal encoding
 // of the contexts.
 //

@@ -27,7 +27,7 @@
 // vector-ALU kernels, which give a wavefront one row and read every K/V byte once per row (same card, same inputs):
 // fp32 encode of eight contexts of about 512 tokens, 32/8 heads of 128: 2754 -> 180 us (94 TFLOP/s; the vendor's fp32 GEMM
 // reaches 154); 64 bf16 rows over 20 x 512 tokens, 16/8 heads of 256: 14200 -> 43 us (2.0 TB/s, on inputs that change); a fp32 decode step over 4096
-// tokens, 16/8 heads of 256: 28 us, 88 by one wavefront per workgroup; 16 fp32 rows over 4 x 32 tokens, 4/2 heads of 64: 47.8 -> 14.8 us.
+// tokens, 16/8 heads of 256: 28 us, 88 by one wavefront per workgroup; 16 fp32 rows over 4 x 32 tokens, 4/2 heads of 64: 47.8 -> 14.8 us (on the few-row kernels 7.3).
 #include "ape_exact_row.h"
 
 #include <algorithm>
