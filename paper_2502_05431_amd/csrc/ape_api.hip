@@ -197,7 +197,10 @@ QueryPlan tile_decode_plan(const ShapeInfo& si, int batch, long max_ctx) {
 // More than 16 rows run whole, in tiles of 16 that read the same tokens, as long as every one has a CU: before / whole, 16 query tokens over 256
 // 13.5 / 7.5, 768 14.4 / 12.3, 1024 14.1 / 15.5, 64 over 768 16.8 / 12.3, 128 over 256 15.3 / 8.8, but 3 x 64 over 256 (384 workgroups) 13.9 / 14.6; heads of 64,
 // 64 over 1024 11.8 / 10.5, 16 over 1536 9.8 / 12.4; of 256, 16 over 256 13.8 / 11.9, 384 13.8 / 14.7; fp32, 16 over 256 16.1 / 13.9, 384 16.3 / 16.8, 4/2 heads of 64, 16 over
-// 256 11.7 / 9.4, 512 11.2 / 12.1.  Split, they read every token once per tile (8 query tokens over 20 x 512 17.4 / 24.0).
+// 256 11.7 / 9.4, 512 11.2 / 12.1.  Split, they read every token once per
+// tile (8 query tokens over 20 x 512 17.4 / 24.0) and are ahead while that stays little, before / split: 5 query tokens over 1024 11.6 / 9.0, 16 over 1024 13.7 / 10.5, 3072 14.0 / 12.4,
+// 32 over 2048 15.6 / 13.0, 3072 16.0 / 16.0; heads of 64, 16 over 3072 11.9 / 10.9; of 256, 20 over 1024 14.9 / 11.8, 2048 16.1 / 15.6; fp32, 8 over 1024 15.9 / 11.1, 16 over 2048
+// 19.7 / 19.7, 4/2 heads of 64, 32 over 1024 11.4 / 9.6.
 FewForm few_form(const ShapeInfo& si, int batch, int q_len, long max_ctx, bool uneven) {
     const bool f32 = si.dtype == APE_F32;
     const int elem = f32 ? 4 : 2, width = si.d <= 64 ? 0 : si.d <= 128 ? 1 : 2;
@@ -206,9 +209,9 @@ FewForm few_form(const ShapeInfo& si, int batch, int q_len, long max_ctx, bool u
     if (tiles == 1 ? base > 1024 : base * tiles > 256) return FewForm::no;
     const long few_rows[2][3] = {{512, 384, 128}, {192, 128, 0}}, more_rows[2][3] = {{1024, 768, 256}, {256, 256, 0}};
     if (max_ctx <= (tiles == 1 ? few_rows : more_rows)[f32][width]) return FewForm::whole;
-    if (tiles > 1) return FewForm::no;
-    if (base > 128 && base <= 256 && max_ctx <= 4096 && !uneven) return FewForm::whole;
+    if (tiles == 1 && base > 128 && base <= 256 && max_ctx <= 4096 && !uneven) return FewForm::whole;
     const long bytes = 2 * (long)batch * max_ctx * stride;
+    if (tiles > 1) return batch == 1 && base * tiles <= 64 && max_ctx <= 3072 && bytes * tiles <= 64L << 20 ? FewForm::full : FewForm::no;
     if (batch == 1 ? bytes > 200L << 20 : uneven || bytes > 64L << 20) return FewForm::no;
     return base <= 32 ? FewForm::full : FewForm::half;
 }
@@ -516,7 +519,7 @@ static int run_query(const ShapeInfo& si, const ape_request* reqs, int batch, in
     if (few == FewForm::full || few == FewForm::half) {
         // as many splits as leave every workgroup, the prefix and own tokens' too, a CU of its own (`full`; half of one otherwise), and no more than in
         // the other kernels' plan, which the workspace is made for
-        const int base = batch * si.hkv, n = (few == FewForm::full ? 256 : 512) / base - 1;
+        const int base = batch * si.hkv * ceil_div((long)q_len * si.group, kFewRows), n = (few == FewForm::full ? 256 : 512) / base - 1;
         plan = plan_query(base, max_ctx, 64, base * (n < 1 ? 1 : n < plan.n_ctx_splits ? n : plan.n_ctx_splits), 32);
     }
     float* part_o = (float*)workspace;

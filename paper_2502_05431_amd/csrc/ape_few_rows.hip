@@ -1,5 +1,5 @@
 // Matrix-core attention for a few query rows (a row is a (query token, head of the group) pair): a decode step, a query of a few tokens, and any
-// query of up to 512 rows per KV head over short contexts.  bf16 of head_dims up to 256 and fp32 up to 128, any number of query heads per KV head.
+// query of up to 512 rows per KV head over short contexts (whole) or 128 over up to 3072 tokens (split).  bf16 of head_dims up to 256 and fp32 up to 128, any number of query heads per KV head.
 //
 // Math, precision and what happens to values that are not finite: as in the tile kernels (ape_tile_mfma.hip).  Errors against 64 bits likewise:
 // outputs 1.6e-3 (bf16), 2e-7 to 4e-7 (fp32; relative 2-norm).

@@ -88,6 +88,7 @@ def test_a_token_that_a_row_does_not_see(dtype, hq, hkv, d, value, ctx):
 @pytest.mark.parametrize("dtype, hq, hkv, d, rows, lens", [
     ("bf16", 8, 2, 128, 5, (300, 468)), ("bf16", 32, 8, 128, 128, (33, 70)), ("bf16", 3, 1, 128, 170, (400,)), ("bf16", 4, 2, 256, 40, (250, 6)), ("bf16", 8, 2, 64, 33, (1000, 24)),
     ("f32", 4, 2, 64, 16, (32,) * 4), ("f32", 8, 2, 128, 21, (200, 56)), ("f32", 3, 3, 40, 100, (100,)), ("bf16", 6, 2, 40, 7, ()),
+    ("bf16", 8, 2, 128, 21, (900, 1, 800)), ("bf16", 32, 8, 128, 32, (2048,)), ("bf16", 3, 1, 200, 100, (310, 500)), ("f32", 8, 2, 128, 9, (700, 1400)), ("f32", 6, 2, 40, 33, (1500,)),
     ("bf16", 255, 1, 8, 2, (40,)), ("bf16", 171, 1, 8, 2, (33, 9)), ("f32", 127, 1, 8, 4, (40,)), ("bf16", 512, 1, 8, 1, (70,))])
 def test_tiles_of_rows(dtype, hq, hkv, d, rows, lens):
     spec = _spec(dtype, hq, hkv, d, lens, rows, 9, 40)
