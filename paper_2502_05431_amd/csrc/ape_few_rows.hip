@@ -516,7 +516,7 @@ hipError_t few_as(const QueryArgs& q, hipStream_t s) {
 template <typename T, int DP>
 hipError_t few_with(const QueryArgs& a, FewForm form, hipStream_t s) {
     constexpr int W = 160 * 1024 / Few<T, DP>::WAVE;
-    const bool one = a.n_req == 1;
+    const bool one = OneQuery::holds(a);
     if (form == FewForm::whole) return one ? few_as<T, OneQuery, DP, W, true>(a, s) : few_as<T, QueryArgs, DP, W, true>(a, s);
     if (form == FewForm::full) return one ? few_as<T, OneQuery, DP, W, false>(a, s) : few_as<T, QueryArgs, DP, W, false>(a, s);
     return one ? few_as<T, OneQuery, DP, W / 2, false>(a, s) : few_as<T, QueryArgs, DP, W / 2, false>(a, s);

@@ -1232,7 +1232,7 @@ __global__ __launch_bounds__(NT) void flash_encode_kernel(const EncodeArgs a, in
 
 template <int RB, int G, bool NTL>
 hipError_t launch_prefill_t(const QueryArgs& a, dim3 grid, int n_qtiles, hipStream_t s) {
-    if (a.n_req == 1) {
+    if (OneQuery::holds(a)) {
         hipError_t e = hipFuncSetAttribute((const void*)flash_single_kernel<RB, G, NTL>, hipFuncAttributeMaxDynamicSharedMemorySize, Ring<RB>::slots * SLOTB);
         if (e != hipSuccess) return e;
         flash_single_kernel<RB, G, NTL><<<grid, NT, Ring<RB>::slots * SLOTB, s>>>(OneQuery(a), n_qtiles);

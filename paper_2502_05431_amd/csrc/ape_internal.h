@@ -62,9 +62,11 @@ struct QueryArgs {
     int32_t lse_head_major;     // as in MergeArgs
 };
 
-// The arguments of a call with a single request: 200 bytes rather than 2800 (0.3 us less for the host to write, 0.2 for the kernel to read).
+// The arguments of a launch with a single request: 200 bytes rather than 2800 (0.3 us less for the host to write, 0.2 for the kernel to read).  Not of
+// one that is dealt out, as the last request of an uneven batch may be: it has no room for splits of the request's own.
 struct OneQuery {
     static constexpr int kRequests = 1;
+    static bool holds(const QueryArgs& a) { return a.n_req == 1 && a.n_own_splits == 0; }
     KvView req[1];
     const void* q;
     float* part_o;
@@ -75,7 +77,7 @@ struct OneQuery {
     int32_t lse_head_major;
     void* out;
     float* lse_out;
-    explicit OneQuery(const QueryArgs& a)
+    explicit OneQuery(const QueryArgs& a)                    // (holds(a))
         : req{a.req[0]}, q(a.q), part_o(a.part_o), part_lse(a.part_lse), n_req(1), q_len(a.q_len), n_q_heads(a.n_q_heads), n_kv_heads(a.n_kv_heads),
           head_dim(a.head_dim), n_ctx_splits(a.n_ctx_splits), ctx_split_len(a.ctx_split_len), units_total(a.units_total), split_ranges(a.split_ranges),
           req_base(a.req_base), lse_head_major(a.lse_head_major), out(a.out), lse_out(a.lse_out) {}

@@ -1,0 +1,189 @@
+// Host check of the query entry points' launches: where the kernels of a call put their partial results, and where its merge looks for them.  The functions of
+// the HIP runtime that libape_hip.so imports are defined here, so that a launch is a record of its kernel's name, grid and arguments and nothing runs.
+//   launch_layout                                                      random batches; exit status 0: every launch is in order
+//   launch_layout bf16|f32 HQ HKV D decode|prefill ROWS OWN CONTEXT..  the kernels of one call: request i has CONTEXT i tokens of contexts, OWN own tokens in front
+#include "ape_internal.h"
+
+#include <cstdio>
+#include <cstdlib>
+#include <cstring>
+#include <map>
+#include <random>
+#include <set>
+#include <string>
+#include <tuple>
+#include <vector>
+
+using namespace ape;
+
+namespace {
+struct Launch {
+    std::string kernel;
+    dim3 grid;
+    QueryArgs query;            // a query kernel's arguments, or a merge's
+    MergeArgs merge;
+};
+std::map<const void*, std::string>& names() { static std::map<const void*, std::string> m; return m; }   // (the library registers before this file's objects are made)
+std::vector<Launch> g_launches;
+dim3 g_grid, g_block;
+size_t g_lds;
+hipStream_t g_stream;
+
+bool has(const std::string& s, const char* part) { return s.find(part) != std::string::npos; }
+bool is_merge(const std::string& k) { return has(k, "merge_units_kernel") || has(k, "pool_single_kernel") || has(k, "pool_uneven_kernel"); }
+bool is_small(const std::string& k) { return has(k, "OneQuery") || has(k, "flash_single_kernel"); }
+}  // namespace
+
+extern "C" {
+void** __hipRegisterFatBinary(const void*) { static void* handle; return &handle; }
+void __hipUnregisterFatBinary(void**) {}
+void __hipRegisterFunction(void**, const void* host, char*, const char* name, unsigned, void*, void*, void*, void*, int*) { names()[host] = name; }
+void __hipRegisterVar(void**, void*, char*, char*, int, size_t, int, int) {}
+hipError_t __hipPushCallConfiguration(dim3 grid, dim3 block, size_t lds, hipStream_t s) { g_grid = grid; g_block = block; g_lds = lds; g_stream = s; return hipSuccess; }
+hipError_t __hipPopCallConfiguration(dim3* grid, dim3* block, size_t* lds, hipStream_t* s) { *grid = g_grid; *block = g_block; *lds = g_lds; *s = g_stream; return hipSuccess; }
+hipError_t hipFuncSetAttribute(const void*, hipFuncAttribute, int) { return hipSuccess; }
+hipError_t hipGetLastError() { return hipSuccess; }
+hipError_t hipLaunchKernel(const void* f, dim3 grid, dim3, void** args, size_t, hipStream_t) {
+    Launch l{names()[f], grid, {}, {}};
+    if (is_merge(l.kernel)) {
+        memcpy((void*)&l.merge, args[0], sizeof(MergeArgs));
+    } else if (is_small(l.kernel)) {
+        OneQuery o = *(const OneQuery*)args[0];
+        QueryArgs& a = l.query;
+        a.req[0] = o.req[0]; a.part_o = o.part_o; a.part_lse = o.part_lse; a.n_req = o.n_req; a.q_len = o.q_len; a.n_q_heads = o.n_q_heads;
+        a.n_kv_heads = o.n_kv_heads; a.head_dim = o.head_dim; a.n_ctx_splits = o.n_ctx_splits; a.ctx_split_len = o.ctx_split_len; a.units_total = o.units_total;
+        a.req_base = o.req_base; a.out = o.out;
+    } else {
+        memcpy((void*)&l.query, args[0], sizeof(QueryArgs));
+    }
+    g_launches.push_back(l);
+    return hipSuccess;
+}
+}
+
+namespace {
+// A partial result that a call writes or reads: request, split (-1: prefix + own tokens), first row in part_o
+using Part = std::tuple<int, int, long>;
+
+std::set<Part> written(const Launch& l) {
+    const QueryArgs& a = l.query;
+    const bool dense = has(l.kernel, "flash_uneven_kernel") || (has(l.kernel, "tile_query_kernel") && has(l.kernel, "FormE1E"));
+    const long rows = (long)a.q_len * a.n_q_heads;
+    std::set<Part> p;
+    for (int r = 0; r < a.n_req; ++r) {
+        const int len = dense ? a.split_len[r] : a.ctx_split_len, n = dense ? a.first_split[r + 1] - a.first_split[r] : a.n_ctx_splits;
+        for (int s = 0; s < n; ++s)
+            if ((long)s * len < a.req[r].total_ctx) p.insert({r, s, dense ? (a.first_split[r] + r + s) * rows : (long)s * a.units_total + (a.req_base + r) * rows});
+        p.insert({r, -1, dense ? (a.first_split[r + 1] + r) * rows : (long)a.n_ctx_splits * a.units_total + (a.req_base + r) * rows});
+    }
+    return p;
+}
+
+std::set<Part> read(const Launch& l) {
+    const MergeArgs& a = l.merge;
+    const bool dense = has(l.kernel, "pool_uneven_kernel");
+    const long rows = (long)a.q_len * a.n_q_heads;
+    std::set<Part> p;
+    for (int r = 0; r < a.n_req; ++r) {
+        const int first = dense ? a.first_split[r] : 0;
+        const int n = dense ? a.first_split[r + 1] - first : std::min(a.n_ctx_splits, (a.total_ctx[r] + a.ctx_split_len - 1) / a.ctx_split_len);
+        const long row0 = dense ? (first + r) * rows : (a.req_base + r) * rows, step = dense ? rows : a.units_total;
+        for (int s = 0; s < n; ++s) p.insert({r, s, row0 + s * step});
+        p.insert({r, -1, row0 + (dense ? n : a.n_ctx_splits) * step});
+    }
+    return p;
+}
+
+struct Call {
+    int dtype, hq, hkv, d, rows, own;
+    bool decode;
+    std::vector<int> ctx;
+};
+
+std::string text(const Call& c) {
+    std::string s = std::string(c.dtype == APE_F32 ? "f32" : "bf16") + " " + std::to_string(c.hq) + "/" + std::to_string(c.hkv) + " heads of " + std::to_string(c.d) +
+                    (c.decode ? " decode" : " prefill of " + std::to_string(c.rows)) + ", contexts";
+    for (int n : c.ctx) s += " " + std::to_string(n);
+    return s;
+}
+
+// Makes the call with a workspace of exactly what it asks for.  Returns what is wrong with its launches.
+std::string check(const Call& c) {
+    static char fake[16];
+    char* const data = (char*)0x10000000, *const ws = (char*)0x20000000;
+    const ape_shape shape{c.hq, c.hkv, c.d, c.dtype};
+    std::vector<ape_request> reqs(c.ctx.size());
+    for (size_t i = 0; i < reqs.size(); ++i) {
+        ape_request& r = reqs[i];
+        memset(&r, 0, sizeof r);
+        r.k_prefix = r.v_prefix = r.k_self = r.v_self = data;
+        r.prefix_len = 9; r.n_chunks = c.ctx[i] > 0; r.total_ctx_len = c.ctx[i]; r.self_len = c.own + c.rows;
+        r.k_chunks = (const void* const*)data; r.v_chunks = (const void* const*)data; r.cu_chunk_lens = (const int32_t*)data;
+        r.temperature = r.scale = 0.9f;
+    }
+    size_t bytes = 0;
+    auto call = [&]() {
+        g_launches.clear();
+        return c.decode ? ape_attention_decode(&shape, reqs.data(), (int)reqs.size(), data, data, nullptr, bytes ? ws : nullptr, bytes, fake)
+                        : ape_attention_prefill_batch(&shape, reqs.data(), (int)reqs.size(), data, c.rows, data, nullptr, bytes ? ws : nullptr, bytes, fake);
+    };
+    if (call() != APE_ERR_WORKSPACE || sscanf(ape_last_error(), "workspace of 0 bytes given, %zu needed", &bytes) != 1) return std::string("asked for no workspace: ") + ape_last_error();
+    const size_t bound = ape_workspace_bytes(c.decode ? APE_OP_DECODE : APE_OP_PREFILL, &shape, (int)reqs.size(), c.rows, -1);
+    if (bytes > bound) return "asks for more than the bound";
+    if (call() != APE_OK) return ape_last_error();
+    int served = 0;
+    for (size_t i = 0; i < g_launches.size(); ++i) {
+        const Launch& q = g_launches[i];
+        const QueryArgs& a = q.query;
+        if (is_merge(q.kernel)) return "a merge behind no query: " + q.kernel;
+        if (a.req_base != served || a.n_req < 1 || a.n_req > (is_small(q.kernel) ? 1 : kMaxReqPerLaunch)) return "not its requests: " + q.kernel;
+        served += a.n_req;
+        if (a.out) continue;                                // (writes the output itself)
+        if (++i == g_launches.size() || !is_merge(g_launches[i].kernel)) return "no merge: " + q.kernel;
+        const Launch& m = g_launches[i];
+        if (m.merge.n_req != a.n_req || m.merge.req_base != a.req_base || m.merge.part_o != a.part_o || m.merge.part_lse != a.part_lse) return "not its merge: " + q.kernel;
+        const std::set<Part> w = written(q);
+        if (w != read(m)) return q.kernel + " writes other partial results than " + m.kernel + " reads";
+        std::set<long> rows;
+        for (const Part& p : w) {
+            const long first = std::get<2>(p), last = first + (long)a.q_len * a.n_q_heads;
+            if ((char*)(a.part_o + last * a.head_dim) > (char*)a.part_lse || (char*)(a.part_lse + last) > ws + bytes) return q.kernel + " writes past its workspace";
+            if (!rows.insert(first).second) return q.kernel + " writes a partial result twice";
+        }
+    }
+    return served == (int)reqs.size() ? "" : "requests without a launch";
+}
+}  // namespace
+
+int main(int argc, char** argv) {
+    if (argc > 1) {
+        Call c{strcmp(argv[1], "f32") ? APE_BF16 : APE_F32, atoi(argv[2]), atoi(argv[3]), atoi(argv[4]), atoi(argv[6]), atoi(argv[7]), !strcmp(argv[5], "decode"), {}};
+        for (int i = 8; i < argc; ++i) c.ctx.push_back(atoi(argv[i]));
+        const std::string wrong = check(c);
+        for (const Launch& l : g_launches) printf("%s grid %u %u %u\n", l.kernel.c_str(), l.grid.x, l.grid.y, l.grid.z);
+        if (!wrong.empty()) printf("%s\n", wrong.c_str());
+        return !wrong.empty();
+    }
+    std::mt19937 rng(11);
+    auto pick = [&](long lo, long hi) { return lo + (long)(rng() % (unsigned long)(hi - lo + 1)); };
+    const int shapes[][4] = {{APE_BF16, 32, 8, 128}, {APE_BF16, 16, 2, 128}, {APE_BF16, 8, 8, 128}, {APE_BF16, 256, 256, 128}, {APE_BF16, 16, 8, 256}, {APE_BF16, 32, 8, 64},
+                             {APE_BF16, 6, 2, 40}, {APE_F32, 4, 2, 64}, {APE_F32, 32, 8, 128}, {APE_F32, 16, 8, 256}, {APE_BF16 | APE_DTYPE_FLAG_GENERIC, 8, 2, 128}};
+    std::set<std::string> kernels;
+    long failed = 0, single_tails = 0;
+    for (int i = 0; i < 12000; ++i) {
+        const int* s = shapes[pick(0, 10)];
+        Call c{s[0], s[1], s[2], s[3], 1, (int)pick(0, 300), pick(0, 1) == 0, {}};
+        if (!c.decode) c.rows = 1 << pick(0, 8);
+        const int batches[] = {1, 2, 3, 33, 65, 97}, batch = pick(0, 1) ? batches[pick(0, 5)] : (int)pick(1, 70);
+        const long top = 1L << pick(5, 15);
+        for (int b = 0; b < batch; ++b) c.ctx.push_back(pick(0, 9) == 0 ? 0 : (int)(pick(0, 2) ? pick(1, top) : pick(top / 2, top)));
+        const std::string wrong = check(c);
+        if (!wrong.empty() && failed++ < 10) printf("%s\n    %s\n", text(c).c_str(), wrong.c_str());
+        for (size_t k = 0; k < g_launches.size(); ++k) {
+            kernels.insert(g_launches[k].kernel.substr(0, g_launches[k].kernel.find("kernelI")));
+            if (k >= 2 && has(g_launches[k].kernel, "pool_uneven") && g_launches[k].merge.n_req == 1) ++single_tails;
+        }
+    }
+    printf("%zu kinds of kernels, %ld dealt-out launches of one request, %ld failed\n", kernels.size(), single_tails, failed);
+    return failed != 0;
+}

@@ -1,6 +1,6 @@
 """GPU parity of batches whose requests have contexts of very different length (every request then has splits of its own number and
 length, and dense partial results): no context, one token, the edges of a 64-token unit and of a split, one long request among
-short ones, more requests than one launch describes, and the batch that goes out in two launches."""
+short ones, more requests than one launch describes (the last of them with a single request), and the batch that goes out in two launches."""
 import numpy as np
 import pytest
 import torch
@@ -55,3 +55,26 @@ def test_many(batch):
     lens = [1 + b % 4 for b in range(batch)]
     out, lse = H.run_decode(spec, rs, lens)
     _check("bf16", rs, out, lse, 1, lens)
+
+
+@pytest.mark.parametrize("hq, hkv, q_len", [(16, 8, 1), (16, 8, 16), (4, 4, 40), (16, 2, 40)])
+def test_the_last_launch_holds_one_request(hq, hkv, q_len):
+    """33 requests: a launch of 32 and one of a single long request, which is dealt out too.  Nothing is written behind the workspace."""
+    spec, rs = _requests("bf16", hq, hkv, 128, [(150 + 61 * (b * 7 % 32),) for b in range(32)] + [(3000, 1096)], q_len, 3)
+    n, op = len(rs), B.APE_OP_DECODE if q_len == 1 else B.APE_OP_PREFILL
+    shape = B.make_shape(hq, hkv, 128, spec.torch_dtype)
+    reqs = [H.make_binding_request(r, q_len + b % 4) for b, r in enumerate(rs)]
+    q = torch.stack([r.q_self[b % 4:q_len + b % 4] for b, r in enumerate(rs)]).contiguous()
+    size = B.workspace_bytes(op, shape, n, q_len, 4096) // 4
+    ws = H.poisoned_workspace(4 * size + (32 << 20), DEV)
+    ws[size:] = 7.0
+    for static in ([False, True] if q_len == 1 else [False]):
+        out = torch.full_like(q, float("nan"))
+        lse = torch.full((n, hq) if q_len == 1 else (n, hq, q_len), float("nan"), device=DEV)
+        if static:
+            B.attention_decode_static(shape, reqs, q[:, 0], out[:, 0], lse)
+        else:
+            (B.attention_decode if q_len == 1 else B.attention_prefill_batch)(shape, reqs, q[:, 0] if q_len == 1 else q, out[:, 0] if q_len == 1 else out, lse, ws[:size])
+        torch.cuda.synchronize()
+        _check("bf16", rs, out, lse, q_len, [q_len + b % 4 for b in range(n)])
+        assert bool((ws[size:] == 7.0).all())
