@@ -191,9 +191,15 @@ QueryPlan tile_decode_plan(const ShapeInfo& si, int batch, long max_ctx) {
 // 21.1 / 15.0; 32K 29.4 / 28.0, 64K 48.5 / 47.9, but 128K 86.0 / 89.4: what streams from HBM for long keeps the kernels whose wavefronts read one
 // block at a time together.  For the same reason a batch: 4 x 4096 19.4 / 18.6, 8 x 2048 19.4 / 19.2, 8 x 4096 28.2 / 29.4, 4 x 10240, heads of 64, 21.4 / 24.3; and with requests
 // of different lengths, whose splits those deal out (8 of 1 to 15 x 256 23.9 / 24.4).  Whole: split / whole, 384 tokens 8.5 / 7.5, 512 8.7 / 9.6; heads
-// of 64 over 512 8.2 / 7.1, 1024 8.4 / 9.1; of 256 over 128 10.0 / 9.7, 256 10.1 / 12.1; and where the requests give every CU one: 32 x 1024 32.7 / 26.2, 32 x 4096 94 / 86.9,
+// of 64 over 512 8.2 / 7.1, 1024 8.4 / 9.1; of 256 over 128 10.0 / 9.7, 256 10.1 / 12.1; and where the requests give most CUs one: 32 x 1024 32.7 / 26.2, 32 x 4096 94 / 86.9,
 // 16/8 heads of 256, 32 x 1024, 57 / 47.7 (before: 29.9, 86.9, 72.3), but 16 x 2048 29.8 / 33.1.  fp32, before / split / whole: 4096 tokens 23.4 / 16.9 / -, 256
 // 17.0 / 13.6 / 17.0, 128 17.0 / 13.6 / 13.8, 4/2 heads of 64 over 256 13.4 / 9.9 / 10.6, 16 requests of 2048 of them 25.0 / 15.1 / -.
+// Most CUs: of 136 workgroups on (before / whole, 17 x 1024 25.0 / 20.2, 2048 38.2 / 33.9, 4096 60.2 / 60.4, 20 x 4096 63.6 / 63.6, 28 x 4096 84.8 / 77.7), with heads beyond 128 more
+// of them, whose blocks are twice as long (129 to 160 workgroups of 29 sizes over more than 512 tokens 1.02 times as fast, 8 slower, up to 96 of 72 sizes 1.21 times).  A launch holds 32 requests: of
+// few KV heads it leaves CUs empty, and one launch follows the other.  Then long contexts are ahead split, in the flash kernels and where blocks are long, unless the launches are all but full or
+// the kernels of before would not split either (before / whole, 16/4 heads, 33 x 1024 37.2 / 37.2, 2048 49.1 / 61.3, 4096 70.5 / 109, 48 x 1024 40.2 / 39.0, 2048 53.9 / 64.6, 60 x 2048 72.8 / 66.7, 64 x
+// 4096 162 / 120; 8/4 of 256, 48 x 1024 73.3 / 76.1, 1536 99 / 105, 60 x 2048 139.9 / 139.7; 16/2 of 128, 65 x 2048 61.9 / 86.0, 96 x 4096 87.9 / 156), later where the tile kernels are the others
+// (12/2 heads of 128, 65 x 1536 69.4 / 66.3, 2048 79.2 / 83.9, 4096 133 / 145; 4/4 of 96, 33 x 4096 114 / 102, 16/4 of 64 65.1 / 59.2), in fp32 not at all (16/4 of 64, 33 x 4096 183 / 124).
 // More than 16 rows run whole, in tiles of 16 that read the same tokens, as long as every one has a CU: before / whole, 16 query tokens over 256
 // 13.5 / 7.5, 768 14.4 / 12.3, 1024 14.1 / 15.5, 64 over 768 16.8 / 12.3, 128 over 256 15.3 / 8.8, but 3 x 64 over 256 (384 workgroups) 13.9 / 14.6; heads of 64,
 // 64 over 1024 11.8 / 10.5, 16 over 1536 9.8 / 12.4; of 256, 16 over 256 13.8 / 11.9, 384 13.8 / 14.7; fp32, 16 over 256 16.1 / 13.9, 384 16.3 / 16.8, 4/2 heads of 64, 16 over
@@ -209,7 +215,12 @@ FewForm few_form(const ShapeInfo& si, int batch, int q_len, long max_ctx, bool u
     if (tiles == 1 ? base > 1024 : base * tiles > 256) return FewForm::no;
     const long few_rows[2][3] = {{512, 384, 128}, {192, 128, 0}}, more_rows[2][3] = {{1024, 768, 256}, {256, 256, 0}};
     if (max_ctx <= (tiles == 1 ? few_rows : more_rows)[f32][width]) return FewForm::whole;
-    if (tiles == 1 && base > 128 && base <= 256 && max_ctx <= 4096 && !uneven) return FewForm::whole;
+    if (tiles == 1 && base > (width == 2 ? 160 : 128) && base <= 256 && max_ctx <= 4096 && !uneven) {
+        const long launches = ceil_div(batch, kMaxReqPerLaunch);
+        if (launches == 1 || f32 || base == 256) return FewForm::whole;
+        const long most = si.mfma || width == 2 ? (base >= 112 * launches ? 2048 : 1024) : base > 64 * launches ? 4096 : 1536;
+        if (max_ctx <= most) return FewForm::whole;
+    }
     const long bytes = 2 * (long)batch * max_ctx * stride;
     if (tiles > 1) return batch == 1 && base * tiles <= 64 && max_ctx <= 3072 && bytes * tiles <= 64L << 20 ? FewForm::full : FewForm::no;
     if (batch == 1 ? bytes > 200L << 20 : uneven || bytes > 64L << 20) return FewForm::no;

@@ -1,6 +1,7 @@
 """What the query entry points launch, without a GPU: tests/launch_layout.cpp stands in for the HIP runtime and records the kernels, grids and arguments of
 random batches.  A merge reads exactly the partial results that the kernel in front of it writes, and they lie in the workspace that the call asks for."""
 import os
+import re
 import shutil
 import subprocess
 
@@ -27,3 +28,29 @@ def test_partial_results_of_random_batches(recorder):
     out = subprocess.run([recorder], capture_output=True, text=True)
     assert out.returncode == 0, out.stdout + out.stderr
     assert int(out.stdout.split(",")[1].split()[0]) > 100     # a call's last launch of one request that is dealt out: reached
+
+
+def _form(recorder, call):
+    """How the few-row kernels serve the call (whole, or split with a CU's LDS for a workgroup or half of it), or "other"."""
+    out = subprocess.run([recorder, *call.split()], capture_output=True, text=True)
+    assert out.returncode == 0, out.stdout + out.stderr
+    forms = set()
+    for line in out.stdout.splitlines():
+        m = re.search(r"few_rows_kernelI(f|DF16b)\w+?Li(\d+)ELi(\d+)ELb([01])E", line)
+        if m:
+            full = 160 * 1024 // (5 * 16 * int(m.group(2)) * (4 if m.group(1) == "f" else 2))
+            forms.add("whole" if m.group(4) == "1" else "full" if int(m.group(3)) == full else "half")
+        elif "query_kernel" in line or "flash_" in line:
+            forms.add("other")
+    assert len(forms) == 1, out.stdout
+    return forms.pop()
+
+
+@pytest.mark.parametrize("shape, batch, ctx, whole", [
+    ("bf16 32 8 128", 17, 4096, True), ("bf16 32 8 128", 32, 4096, True), ("bf16 32 8 128", 16, 4096, False), ("bf16 32 8 128", 32, 4097, False),
+    ("bf16 16 4 128", 33, 1024, True), ("bf16 16 4 128", 33, 1025, False), ("bf16 16 4 128", 48, 2048, False), ("bf16 16 4 128", 56, 2048, True), ("bf16 16 4 128", 63, 2049, False),
+    ("bf16 16 4 128", 64, 4096, True), ("bf16 16 2 128", 65, 2048, False), ("bf16 16 2 128", 127, 2048, False), ("bf16 16 2 128", 128, 4096, True),
+    ("bf16 16 8 256", 20, 1024, False), ("bf16 16 8 256", 21, 1024, True), ("bf16 8 4 256", 48, 1024, True), ("bf16 8 4 256", 48, 1025, False),
+    ("bf16 12 2 128", 65, 1536, True), ("bf16 12 2 128", 65, 2048, False), ("bf16 4 4 96", 33, 4096, True), ("f32 16 4 64", 33, 4096, True)])
+def test_whole_decode_steps_fill_their_launches(recorder, shape, batch, ctx, whole):
+    assert (_form(recorder, "%s decode 1 100 %s" % (shape, " ".join([str(ctx)] * batch))) == "whole") == whole
