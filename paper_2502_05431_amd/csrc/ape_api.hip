@@ -200,6 +200,13 @@ QueryPlan tile_decode_plan(const ShapeInfo& si, int batch, long max_ctx) {
 // the kernels of before would not split either (before / whole, 16/4 heads, 33 x 1024 37.2 / 37.2, 2048 49.1 / 61.3, 4096 70.5 / 109, 48 x 1024 40.2 / 39.0, 2048 53.9 / 64.6, 60 x 2048 72.8 / 66.7, 64 x
 // 4096 162 / 120; 8/4 of 256, 48 x 1024 73.3 / 76.1, 1536 99 / 105, 60 x 2048 139.9 / 139.7; 16/2 of 128, 65 x 2048 61.9 / 86.0, 96 x 4096 87.9 / 156), later where the tile kernels are the others
 // (12/2 heads of 128, 65 x 1536 69.4 / 66.3, 2048 79.2 / 83.9, 4096 133 / 145; 4/4 of 96, 33 x 4096 114 / 102, 16/4 of 64 65.1 / 59.2), in fp32 not at all (16/4 of 64, 33 x 4096 183 / 124).
+// Split, a workgroup has a CU of its own (`full`) where they are few, and half of one otherwise, but all of it for long prefixes and own tokens (`own`, of all requests; one workgroup of
+// a KV head takes them): before / half / full, 5 requests of 512 tokens behind 100 12.7 / 12.2 / 11.3, behind 4000 59.7 / 62.9 / 53.6, 8 of 1024 behind 100 15.3 / 14.6 / 14.3, behind 4000
+// 63.6 / 67.1 / 57.5, 12 of 1024 behind 100 17.7 / 17.0 / 21.0, behind 500 22.7 / 23.1 / 22.2, behind 1000 29.1 / 30.0 / 23.9, 16 of 512 behind 2000 41.6 / 43.5 / 38.4; over 33 to 64 (request, KV head) pairs
+// of any shape half / full are 1.04 / 1.23 times as fast as before in fp32 and 1.02 / 1.10 with heads beyond 128.  bf16 heads of up to 64 keep the tile kernels in batches (10 of 2176, 8
+// KV heads, 16.5 / 19.2 / 17.3, 11 of 1152 14.6 / 17.2 / 16.0; 69 sizes of 33 to 64 pairs 0.91 / 1.05, 37 of more 0.87 / 0.90; up to 8 pairs 1.00 full), but for 9 to 32 pairs (1.06) and behind long own streams (1.23).
+// (Whole, own tokens do not matter: before / whole, 4 steps over 256 tokens behind 1000 25.5 / 18.0, 12000 183 / 134, 16 over 384 behind 4000 66.9 / 63.1, 64 over 256 behind 1500 87.6 / 83.4, 32 over
+// 4096 behind 4000 170 / 166, 16/8 heads of 256, 32 over 128 behind 4000 204 / 162, fp32 301 / 169, 16 query tokens over 256 behind 4000 59.4 / 39.8.)
 // More than 16 rows run whole, in tiles of 16 that read the same tokens, as long as every one has a CU: before / whole, 16 query tokens over 256
 // 13.5 / 7.5, 768 14.4 / 12.3, 1024 14.1 / 15.5, 64 over 768 16.8 / 12.3, 128 over 256 15.3 / 8.8, but 3 x 64 over 256 (384 workgroups) 13.9 / 14.6; heads of 64,
 // 64 over 1024 11.8 / 10.5, 16 over 1536 9.8 / 12.4; of 256, 16 over 256 13.8 / 11.9, 384 13.8 / 14.7; fp32, 16 over 256 16.1 / 13.9, 384 16.3 / 16.8, 4/2 heads of 64, 16 over
@@ -207,7 +214,7 @@ QueryPlan tile_decode_plan(const ShapeInfo& si, int batch, long max_ctx) {
 // tile (8 query tokens over 20 x 512 17.4 / 24.0) and are ahead while that stays little, before / split: 5 query tokens over 1024 11.6 / 9.0, 16 over 1024 13.7 / 10.5, 3072 14.0 / 12.4,
 // 32 over 2048 15.6 / 13.0, 3072 16.0 / 16.0; heads of 64, 16 over 3072 11.9 / 10.9; of 256, 20 over 1024 14.9 / 11.8, 2048 16.1 / 15.6; fp32, 8 over 1024 15.9 / 11.1, 16 over 2048
 // 19.7 / 19.7, 4/2 heads of 64, 32 over 1024 11.4 / 9.6.
-FewForm few_form(const ShapeInfo& si, int batch, int q_len, long max_ctx, bool uneven) {
+FewForm few_form(const ShapeInfo& si, int batch, int q_len, long max_ctx, long own, bool uneven) {
     const bool f32 = si.dtype == APE_F32;
     const int elem = f32 ? 4 : 2, width = si.d <= 64 ? 0 : si.d <= 128 ? 1 : 2;
     const long rows = (long)q_len * si.group, tiles = (rows + kFewRows - 1) / kFewRows, base = (long)batch * si.hkv, stride = (long)si.hkv * si.d * elem;
@@ -224,7 +231,9 @@ FewForm few_form(const ShapeInfo& si, int batch, int q_len, long max_ctx, bool u
     const long bytes = 2 * (long)batch * max_ctx * stride;
     if (tiles > 1) return batch == 1 && base * tiles <= 64 && max_ctx <= 3072 && bytes * tiles <= 64L << 20 ? FewForm::full : FewForm::no;
     if (batch == 1 ? bytes > 200L << 20 : uneven || bytes > 64L << 20) return FewForm::no;
-    return base <= 32 ? FewForm::full : FewForm::half;
+    const bool long_own = own >= 500L * batch;
+    if (batch > 1 && !f32 && width == 0 && !long_own) return base > 8 && base <= 32 ? FewForm::full : FewForm::no;
+    return base <= 64 || (long_own && base <= 256) ? FewForm::full : FewForm::half;
 }
 
 // Rows per workgroup of a call that runs without splits, one workgroup taking its rows past the contexts and then past the
@@ -526,7 +535,7 @@ static int run_query(const ShapeInfo& si, const ape_request* reqs, int batch, in
     if ((uintptr_t)workspace % kWsAlign) return fail(APE_ERR_WORKSPACE, "workspace must be %d-byte aligned", kWsAlign);
     auto ctx = [&](int i) { return reqs[i].n_chunks > 0 ? (long)reqs[i].total_ctx_len : 0L; };
     const bool uneven_ctx = uneven_batch(ctx, batch);
-    const FewForm few = few_form(si, batch, q_len, max_ctx, uneven_ctx);
+    const FewForm few = few_form(si, batch, q_len, max_ctx, own, uneven_ctx);
     if (few == FewForm::full || few == FewForm::half) {
         // as many splits as leave every workgroup, the prefix and own tokens' too, a CU of its own (`full`; half of one otherwise), and no more than in
         // the other kernels' plan, which the workspace is made for
@@ -751,7 +760,7 @@ int ape_attention_tree(const ape_shape* shape, const ape_request* req,
     a.split_ranges = plan_dev + TreePlanLayout{n_nodes, plan.max_splits}.ranges_at();
     a.units_total = (int)units; a.req_base = 0;
     // (more than 16 rows would read every token once per 16: 64 rows over 8 x 64 tokens 21.3 / 25.9 us, fp32 over 4 x 60 24.1 / 30.5)
-    const bool few = (long)q_len * si.group <= kFewRows && few_form(si, 1, q_len, req->total_ctx_len, false) != FewForm::no;
+    const bool few = (long)q_len * si.group <= kFewRows && few_form(si, 1, q_len, req->total_ctx_len, (long)req->prefix_len + req->self_len, false) != FewForm::no;
     he = few ? launch_few_rows(a, si.dtype, FewForm::half, st) : launch_query(si, a, plan.block_rows, st);
     if (he != hipSuccess) return fail(APE_ERR_DEVICE, "attention kernel: %s", hipGetErrorString(he));
 

@@ -374,7 +374,7 @@ inline dim3 uneven_grid(const QueryArgs& a, int n_qtiles) {
 constexpr long kFewStride = 1 << 24;
 constexpr int kFewRows = 16;
 enum class FewForm { no, whole, full, half };
-FewForm few_form(const ShapeInfo& si, int batch, int q_len, long max_ctx, bool uneven);
+FewForm few_form(const ShapeInfo& si, int batch, int q_len, long max_ctx, long own, bool uneven);
 
 // rows per workgroup of a query that runs without splits, or 0 (see the definition)
 int whole_block_rows(const ShapeInfo& si, int ctx_splits, int batch, int q_len, long max_ctx, long own);

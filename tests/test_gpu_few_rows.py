@@ -106,3 +106,16 @@ def test_tiles_of_rows(dtype, hq, hkv, d, rows, lens):
         torch.cuda.synchronize()
         for b in range(batch):
             _check(spec, rs[b], rows, 40 + rows, out[b], lse[b])
+
+
+@pytest.mark.parametrize("dtype, hq, hkv, d, n, ctx, own", [
+    ("bf16", 32, 8, 128, 8, 900, 40), ("bf16", 32, 8, 128, 9, 901, 40), ("bf16", 32, 8, 128, 9, 900, 640), ("bf16", 16, 8, 256, 7, 400, 40), ("bf16", 16, 8, 256, 11, 300, 40),
+    ("f32", 16, 8, 128, 8, 300, 40), ("f32", 16, 8, 128, 12, 300, 700), ("bf16", 16, 4, 64, 7, 1100, 40), ("bf16", 16, 4, 64, 9, 1100, 40), ("bf16", 16, 4, 64, 17, 700, 600)])
+def test_split_batches(dtype, hq, hkv, d, n, ctx, own):
+    """Both sides of the lines between a CU's LDS for a workgroup, half of it, and the other kernels."""
+    specs = [_spec(dtype, hq, hkv, d, (ctx - 3 * b - 40, 40 + 2 * b), 1, 11, own) for b in range(n)]
+    rs = [W.make_request(s, DEV, request=b) for b, s in enumerate(specs)]
+    lens = [own - (7 * b) % 40 for b in range(n)]
+    out, lse = H.run_decode(specs[0], rs, lens)
+    for b in range(n):
+        _check(specs[b], rs[b], 1, lens[b], out[b], lse[b])

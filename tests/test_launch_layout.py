@@ -54,3 +54,14 @@ def _form(recorder, call):
     ("bf16 12 2 128", 65, 1536, True), ("bf16 12 2 128", 65, 2048, False), ("bf16 4 4 96", 33, 4096, True), ("f32 16 4 64", 33, 4096, True)])
 def test_whole_decode_steps_fill_their_launches(recorder, shape, batch, ctx, whole):
     assert (_form(recorder, "%s decode 1 100 %s" % (shape, " ".join([str(ctx)] * batch))) == "whole") == whole
+
+
+@pytest.mark.parametrize("shape, batch, ctx, own, form", [
+    ("bf16 32 8 128", 4, 1024, 100, "full"), ("bf16 32 8 128", 8, 1024, 100, "full"), ("bf16 32 8 128", 9, 1024, 100, "half"), ("bf16 32 8 128", 16, 512, 2000, "full"),
+    ("bf16 32 8 128", 12, 1024, 489, "half"), ("bf16 32 8 128", 12, 1024, 490, "full"), ("bf16 16 8 256", 8, 512, 100, "full"), ("f32 32 8 128", 8, 512, 100, "full"),
+    ("f32 32 8 128", 12, 256, 100, "half"), ("bf16 32 8 64", 1, 2048, 100, "full"), ("bf16 32 8 64", 4, 2048, 100, "full"), ("bf16 32 8 64", 5, 2048, 100, "other"),
+    ("bf16 32 8 64", 10, 2176, 100, "other"), ("bf16 32 8 64", 10, 2176, 600, "full"), ("bf16 4 2 64", 4, 2048, 100, "other"), ("bf16 4 2 64", 5, 2048, 100, "full"),
+    ("bf16 4 4 8", 100, 600, 600, "half")])
+def test_split_decode_steps(recorder, shape, batch, ctx, own, form):
+    """(a request of the recorder has a prefix of 9 tokens, and its own row)"""
+    assert _form(recorder, "%s decode 1 %d %s" % (shape, own, " ".join([str(ctx)] * batch))) == form
