@@ -194,6 +194,9 @@ QueryPlan tile_decode_plan(const ShapeInfo& si, int batch, long max_ctx) {
 // of 64 over 512 8.2 / 7.1, 1024 8.4 / 9.1; of 256 over 128 10.0 / 9.7, 256 10.1 / 12.1; and where the requests give most CUs one: 32 x 1024 32.7 / 26.2, 32 x 4096 94 / 86.9,
 // 16/8 heads of 256, 32 x 1024, 57 / 47.7 (before: 29.9, 86.9, 72.3), but 16 x 2048 29.8 / 33.1.  fp32, before / split / whole: 4096 tokens 23.4 / 16.9 / -, 256
 // 17.0 / 13.6 / 17.0, 128 17.0 / 13.6 / 13.8, 4/2 heads of 64 over 256 13.4 / 9.9 / 10.6, 16 requests of 2048 of them 25.0 / 15.1 / -.
+// Short contexts with more (request, KV head) pairs than CUs take a second round; the tile kernels, two or more of whose workgroups share a CU, are ahead there with bf16 heads of up to 64 and beyond
+// 128 (one launch, 257 to 512 pairs, 43 and 11 sizes, 0.86 times as fast whole; 513 to 1024 0.98 and 1.01; behind 400 and more own tokens 1.00 to 1.13), but not with others (up to 512 pairs 1.4, flash
+// kernels 1.2 to 1.5, fp32 1.76 and 1.08) or in several launches (1.2 to 1.4).
 // Most CUs: of 136 workgroups on (before / whole, 17 x 1024 25.0 / 20.2, 2048 38.2 / 33.9, 4096 60.2 / 60.4, 20 x 4096 63.6 / 63.6, 28 x 4096 84.8 / 77.7), with heads beyond 128 more
 // of them, whose blocks are twice as long (129 to 160 workgroups of 29 sizes over more than 512 tokens 1.02 times as fast, 8 slower, up to 96 of 72 sizes 1.21 times).  A launch holds 32 requests: of
 // few KV heads it leaves CUs empty, and one launch follows the other.  Then long contexts are ahead split, in the flash kernels and where blocks are long, unless the launches are all but full or
@@ -224,7 +227,9 @@ FewForm few_form(const ShapeInfo& si, int batch, int q_len, long max_ctx, long o
     if (tiles == 1 ? base > 1024 : base * tiles > 256) return FewForm::no;
     const long few_rows[2][3] = {{512, 384, 128}, {192, 128, 0}}, more_rows[2][3] = {{1024, 768, 256}, {256, 256, 0}};
     const bool few_tiles = tiles > 1 && base * tiles <= (width == 0 ? 16 : 32) && !uneven;
-    if (max_ctx <= (tiles == 1 || few_tiles ? few_rows : more_rows)[f32][width]) return FewForm::whole;
+    const bool long_own = own >= 500L * batch;
+    if (max_ctx <= (tiles == 1 || few_tiles ? few_rows : more_rows)[f32][width])
+        return base > 256 && batch <= kMaxReqPerLaunch && !f32 && width != 1 && !long_own ? FewForm::no : FewForm::whole;
     if (few_tiles && max_ctx <= more_rows[f32][width]) return FewForm::full;
     if (tiles == 1 && base > (width == 2 ? 160 : 128) && base <= 256 && max_ctx <= 4096 && !uneven) {
         const long launches = ceil_div(batch, kMaxReqPerLaunch);
@@ -235,7 +240,6 @@ FewForm few_form(const ShapeInfo& si, int batch, int q_len, long max_ctx, long o
     const long bytes = 2 * (long)batch * max_ctx * stride;
     if (tiles > 1) return batch == 1 && base * tiles <= 64 && max_ctx <= 3072 && bytes * tiles <= 64L << 20 ? FewForm::full : FewForm::no;
     if (batch == 1 ? bytes > 200L << 20 : uneven || bytes > 64L << 20) return FewForm::no;
-    const bool long_own = own >= 500L * batch;
     if (batch > 1 && !f32 && width == 0 && !long_own) return base > 8 && base <= 32 ? FewForm::full : FewForm::no;
     return base <= 64 || (long_own && base <= 256) ? FewForm::full : FewForm::half;
 }
