@@ -28,6 +28,21 @@ static inline int ape_ring_find_chunk(const int32_t* cu, int n_chunks, int t) {
     while (lo < hi) { const int mid = (lo + hi + 1) >> 1; if (cu[mid] <= t) lo = mid; else hi = mid - 1; }
     return lo;
 }
+// The chunk that holds index t, and its entry, as ape::first_chunk finds it on the GPU (csrc/ape_internal.h): up to 64 chunks, one per lane, the first that ends behind t; else by search.
+static int lanes_first_chunk(const int32_t* cu, const void* const* kp, const void* const* vp, int n_chunks, int t, int32_t& c0, int32_t& c1, const void*& k, const void*& v) {
+    int c = n_chunks - 1;
+    if (n_chunks > 64) {
+        c = ape_ring_find_chunk(cu, n_chunks, t);
+    } else {
+        for (int lane = 63; lane >= 0; --lane) {
+            const int l = std::min(lane, n_chunks - 1);
+            if (cu[l + 1] > t) c = lane;
+        }
+    }
+    c0 = cu[c]; c1 = cu[c + 1]; k = kp[c]; v = vp[c];
+    return c;
+}
+#define ape_ring_first_chunk lanes_first_chunk
 #include "../paper_2502_05431_amd/csrc/ape_ring.h"
 
 using namespace ape;
@@ -198,7 +213,8 @@ int main() {
         }
     // context streams: ranges of the pooled contexts through a chunk table
     const std::vector<std::vector<int>> tables = {{64, 64}, {100, 1, 65, 300, 31}, {2048, 2048, 2048, 2048}, {257, 255}, {512, 512, 512}, {130},
-                                                  {32, 0, 0, 64, 1, 0, 33}, {256, 256, 256, 256, 256, 256, 256, 256}, {1, 1, 1, 1, 1}};
+                                                  {32, 0, 0, 64, 1, 0, 33}, {256, 256, 256, 256, 256, 256, 256, 256}, {1, 1, 1, 1, 1}, {0, 0, 70, 0, 5, 0, 0},
+                                                  std::vector<int>(64, 9), std::vector<int>(65, 9)};
     // gap 0: the contexts lie back to back (a packed cache), where a run of full blocks continues
     // across context boundaries; otherwise they are apart
     for (long gap : {8192L, 0L})
@@ -211,6 +227,15 @@ int main() {
         long off = 0;
         for (int l : lens) { kc.push_back(base + off); vc.push_back(base + (1 << 25) + off); valid.push_back({base + off, base + off + (long)l * stride_b}); off += (long)l * stride_b + gap; }
         const int total = cu.back();
+        // the look-up at a stream's start: the last chunk that begins at or before t among those that are not empty; behind the table the stream is empty
+        for (int t0 = 0; t0 < total + 40; ++t0) {
+            int32_t c0, c1; const void *k, *vv;
+            const int c = lanes_first_chunk(cu.data(), kc.data(), vc.data(), (int)lens.size(), t0, c0, c1, k, vv), by_search = ape_ring_find_chunk(cu.data(), (int)lens.size(), t0);
+            Stream ld; ld.init_ctx(cu.data(), kc.data(), vc.data(), (int)lens.size(), t0, total + 64, stride_b, 0);
+            const bool ok = c == by_search && c0 == cu[c] && c1 == cu[c + 1] && k == kc[c] && vv == vc[c] && (t0 < total ? c0 <= t0 && t0 < c1 && ld.rem > 0 : ld.rem == 0);
+            ++t.cases;
+            if (!ok && t.failed++ < 20) std::printf("table=%zu t=%d: chunk %d, by search %d\n", v, t0, c, by_search);
+        }
         for (int split_len : {64, 128, 320, 1024, 8192})
             for (int t0 = 0; t0 < total; t0 += split_len) {
                 const int t1 = std::min(total, t0 + split_len);
