@@ -768,8 +768,12 @@ int ape_attention_tree(const ape_shape* shape, const ape_request* req,
     a.split_ranges = plan_dev + TreePlanLayout{n_nodes, plan.max_splits}.ranges_at();
     a.units_total = (int)units; a.req_base = 0;
     // (more than 16 rows would read every token once per 16: 64 rows over 8 x 64 tokens 21.3 / 25.9 us, fp32 over 4 x 60 24.1 / 30.5)
-    const bool few = (long)q_len * si.group <= kFewRows && few_form(si, 1, q_len, req->total_ctx_len, (long)req->prefix_len + req->self_len, false) != FewForm::no;
-    he = few ? launch_few_rows(a, si.dtype, FewForm::half, st) : launch_query(si, a, plan.block_rows, st);
+    const long own = (long)req->prefix_len + req->self_len;
+    const bool few = (long)q_len * si.group <= kFewRows && few_form(si, 1, q_len, req->total_ctx_len, own, false) != FewForm::no;
+    // The prefix and own tokens' workgroup has a CU of its own where they are many (half of one / this, 20 contexts of 43 tokens behind 3489 own ones, 32/8 heads of 128, 59.5 / 49.6 us, the flash
+    // kernel 57.9; 8 of 36 behind 1225, fp32, 76.8 / 46.9; over 93 sizes behind 500 and more 1.15 times as fast, none slower), as long as the splits leave it one.
+    const FewForm form = own >= 500 && (plan.max_splits + 1L) * si.hkv <= 256 ? FewForm::full : FewForm::half;
+    he = few ? launch_few_rows(a, si.dtype, form, st) : launch_query(si, a, plan.block_rows, st);
     if (he != hipSuccess) return fail(APE_ERR_DEVICE, "attention kernel: %s", hipGetErrorString(he));
 
     m.part_o = part_o; m.part_lse = part_lse; m.out = out; m.lse_out = lse_out; m.nodes = nodes_dev; m.plan = plan_dev;

@@ -1,7 +1,8 @@
 // Host check of the query entry points' launches: where the kernels of a call put their partial results, and where its merge looks for them.  The functions of
 // the HIP runtime that libape_hip.so imports are defined here, so that a launch is a record of its kernel's name, grid and arguments and nothing runs.
 //   launch_layout                                                      random batches; exit status 0: every launch is in order
-//   launch_layout bf16|f32 HQ HKV D decode|prefill ROWS OWN CONTEXT..  the kernels of one call: request i has CONTEXT i tokens of contexts, OWN own tokens in front
+//   launch_layout bf16|f32 HQ HKV D decode|prefill|tree ROWS OWN CONTEXT..  the kernels of one call: request i has CONTEXT i tokens of contexts, OWN own tokens in
+//                                                                      front (a tree: one request and one node)
 #include "ape_internal.h"
 
 #include <cstdio>
@@ -53,7 +54,7 @@ hipError_t hipLaunchKernel(const void* f, dim3 grid, dim3, void** args, size_t, 
         a.req[0] = o.req[0]; a.part_o = o.part_o; a.part_lse = o.part_lse; a.n_req = o.n_req; a.q_len = o.q_len; a.n_q_heads = o.n_q_heads;
         a.n_kv_heads = o.n_kv_heads; a.head_dim = o.head_dim; a.n_ctx_splits = o.n_ctx_splits; a.ctx_split_len = o.ctx_split_len; a.units_total = o.units_total;
         a.req_base = o.req_base; a.out = o.out;
-    } else {
+    } else if (!has(l.kernel, "tree_")) {
         memcpy((void*)&l.query, args[0], sizeof(QueryArgs));
     }
     g_launches.push_back(l);
@@ -96,7 +97,7 @@ std::set<Part> read(const Launch& l) {
 
 struct Call {
     int dtype, hq, hkv, d, rows, own;
-    bool decode;
+    bool decode, tree;
     std::vector<int> ctx;
 };
 
@@ -124,10 +125,13 @@ std::string check(const Call& c) {
     size_t bytes = 0;
     auto call = [&]() {
         g_launches.clear();
+        const ape_tree_node root{0.9f, 0, 1, 1};
+        if (c.tree) return ape_attention_tree(&shape, reqs.data(), &root, (const ape_tree_node*)data, 1, data, c.rows, data, nullptr, bytes ? ws : nullptr, bytes, fake);
         return c.decode ? ape_attention_decode(&shape, reqs.data(), (int)reqs.size(), data, data, nullptr, bytes ? ws : nullptr, bytes, fake)
                         : ape_attention_prefill_batch(&shape, reqs.data(), (int)reqs.size(), data, c.rows, data, nullptr, bytes ? ws : nullptr, bytes, fake);
     };
     if (call() != APE_ERR_WORKSPACE || sscanf(ape_last_error(), "workspace of 0 bytes given, %zu needed", &bytes) != 1) return std::string("asked for no workspace: ") + ape_last_error();
+    if (c.tree) return call() == APE_OK ? "" : ape_last_error();
     const size_t bound = ape_workspace_bytes(c.decode ? APE_OP_DECODE : APE_OP_PREFILL, &shape, (int)reqs.size(), c.rows, -1);
     if (bytes > bound) return "asks for more than the bound";
     if (call() != APE_OK) return ape_last_error();
@@ -157,7 +161,7 @@ std::string check(const Call& c) {
 
 int main(int argc, char** argv) {
     if (argc > 1) {
-        Call c{strcmp(argv[1], "f32") ? APE_BF16 : APE_F32, atoi(argv[2]), atoi(argv[3]), atoi(argv[4]), atoi(argv[6]), atoi(argv[7]), !strcmp(argv[5], "decode"), {}};
+        Call c{strcmp(argv[1], "f32") ? APE_BF16 : APE_F32, atoi(argv[2]), atoi(argv[3]), atoi(argv[4]), atoi(argv[6]), atoi(argv[7]), !strcmp(argv[5], "decode"), !strcmp(argv[5], "tree"), {}};
         for (int i = 8; i < argc; ++i) c.ctx.push_back(atoi(argv[i]));
         const std::string wrong = check(c);
         for (const Launch& l : g_launches) printf("%s grid %u %u %u\n", l.kernel.c_str(), l.grid.x, l.grid.y, l.grid.z);
@@ -172,7 +176,7 @@ int main(int argc, char** argv) {
     long failed = 0, single_tails = 0;
     for (int i = 0; i < 12000; ++i) {
         const int* s = shapes[pick(0, 10)];
-        Call c{s[0], s[1], s[2], s[3], 1, (int)pick(0, 300), pick(0, 1) == 0, {}};
+        Call c{s[0], s[1], s[2], s[3], 1, (int)pick(0, 300), pick(0, 1) == 0, false, {}};
         if (!c.decode) c.rows = 1 << pick(0, 8);
         const int batches[] = {1, 2, 3, 33, 65, 97}, batch = pick(0, 1) ? batches[pick(0, 5)] : (int)pick(1, 70);
         const long top = 1L << pick(5, 15);

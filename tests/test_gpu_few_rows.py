@@ -126,3 +126,17 @@ def test_split_batches(dtype, hq, hkv, d, n, ctx, own):
 def test_few_tiles_split(dtype, hq, hkv, d, rows, lens):
     """Several tiles of 16 rows on an idle chip, one request and two, over the lengths at which more tiles run whole."""
     test_tiles_of_rows(dtype, hq, hkv, d, rows, lens)
+
+
+@pytest.mark.parametrize("dtype, hq, hkv, d", [("bf16", 8, 2, 128), ("bf16", 4, 2, 256), ("bf16", 6, 2, 40), ("f32", 4, 2, 64), ("f32", 8, 2, 128)])
+def test_tree_behind_long_own_streams(dtype, hq, hkv, d):
+    lens = [50, 1, 128, 33, 300, 64, 2, 95]
+    tree = W.tree_per_context(len(lens), 0.85)
+    spec = _spec(dtype, hq, hkv, d, lens, 2, 20, 700)
+    r = W.make_request(spec, DEV)
+    h = H.HostArrays(r)
+    for q_len in (1, 2):
+        out, lse = H.run_tree(spec, r, tree, q_len, 702)
+        ref, ref_lse = H.oracle_tree(h, q_len, 702, r.temperature, tree)
+        H.check_close(H.f64(out).reshape(-1, d), ref, dtype, "tree")
+        assert np.abs(H.f64(lse).T.reshape(-1) - ref_lse).max() <= H.lse_tol(dtype)

@@ -80,3 +80,9 @@ def test_tiles_that_leave_the_chip_idle_are_split(recorder, shape, batch, rows, 
     ("bf16 32 16 256", 17, 0, "other"), ("bf16 64 16 128", 17, 0, "whole"), ("bf16 16 16 96", 17, 0, "whole"), ("f32 64 16 64", 17, 0, "whole")])
 def test_short_steps_with_more_workgroups_than_cus(recorder, shape, batch, own, form):
     assert _form(recorder, "%s decode 1 %d %s" % (shape, own, " ".join(["120"] * batch))) == form
+
+
+@pytest.mark.parametrize("shape, rows, ctx, own, form", [
+    ("bf16 32 8 128", 1, 900, 100, "half"), ("bf16 32 8 128", 1, 900, 600, "full"), ("bf16 128 32 128", 1, 2560, 600, "half"), ("f32 4 2 64", 8, 900, 600, "full"), ("bf16 32 8 128", 5, 900, 600, "other")])
+def test_tree(recorder, shape, rows, ctx, own, form):
+    assert _form(recorder, "%s tree %d %d %d" % (shape, rows, own, ctx)) == form
