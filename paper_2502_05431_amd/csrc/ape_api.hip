@@ -206,7 +206,7 @@ QueryPlan tile_decode_plan(const ShapeInfo& si, int batch, long max_ctx) {
 // Split, a workgroup has a CU of its own (`full`) where they are few, and half of one otherwise, but all of it for long prefixes and own tokens (`own`, of all requests; one workgroup of
 // a KV head takes them): before / half / full, 5 requests of 512 tokens behind 100 12.7 / 12.2 / 11.3, behind 4000 59.7 / 62.9 / 53.6, 8 of 1024 behind 100 15.3 / 14.6 / 14.3, behind 4000
 // 63.6 / 67.1 / 57.5, 12 of 1024 behind 100 17.7 / 17.0 / 21.0, behind 500 22.7 / 23.1 / 22.2, behind 1000 29.1 / 30.0 / 23.9, 16 of 512 behind 2000 41.6 / 43.5 / 38.4; over 33 to 64 (request, KV head) pairs
-// of any shape half / full are 1.04 / 1.23 times as fast as before in fp32 and 1.02 / 1.10 with heads beyond 128.  bf16 heads of up to 64 keep the tile kernels in batches (10 of 2176, 8
+// of any shape half / full are 1.04 / 1.23 times as fast as before with fp32 heads beyond 64 and 1.02 / 1.10 with bf16 heads beyond 128.  bf16 heads of up to 64 keep the tile kernels in batches (10 of 2176, 8
 // KV heads, 16.5 / 19.2 / 17.3, 11 of 1152 14.6 / 17.2 / 16.0; 69 sizes of 33 to 64 pairs 0.91 / 1.05, 37 of more 0.87 / 0.90; up to 8 pairs 1.00 full), but for 9 to 32 pairs (1.06) and behind long own streams (1.23).
 // (Whole, own tokens do not matter: before / whole, 4 steps over 256 tokens behind 1000 25.5 / 18.0, 12000 183 / 134, 16 over 384 behind 4000 66.9 / 63.1, 64 over 256 behind 1500 87.6 / 83.4, 32 over
 // 4096 behind 4000 170 / 166, 16/8 heads of 256, 32 over 128 behind 4000 204 / 162, fp32 301 / 169, 16 query tokens over 256 behind 4000 59.4 / 39.8.)
@@ -245,8 +245,9 @@ FewForm few_form(const ShapeInfo& si, int batch, int q_len, long max_ctx, long o
 }
 
 // Rows per workgroup of a call that runs without splits, one workgroup taking its rows past the contexts and then past the
-// prefix and the own tokens (`own`: of all requests) and writing the output (0: it is split and merged); asked for calls that the few-row kernels leave, i.e.
-// more tiles of 16 rows than CUs, and fp32 heads beyond 128.  Worth it while the longer
+// prefix and the own tokens (`own`: of all requests) and writing the output (0: it is split and merged); asked for calls that the few-row kernels leave:
+// more tiles of 16 rows than CUs, rows beyond 512 per KV head, fp32 heads beyond 128, and short steps of more (request, KV head) pairs than CUs with bf16 heads of up to 64 or beyond 128.  (The
+// flash shapes' decode steps below drew the lines before there were few-row kernels, which take them now; what the lines still decide there are queries.)  Worth it while the longer
 // stream costs less than the second launch, the partial results and their merge, about 4 us: up to 512 context tokens per request
 // with bf16 heads of up to 64, 256 up to 128 (the flash kernels' shapes too), 128 beyond; 128 with fp32 heads of up to 64, 64 up to
 // 128 (16 rows, split / whole, us: bf16 heads of 64 over 512 tokens 13.7 / 12.0, 1024 14.1 / 16.9; of 128 over 256 15.4 / 14.5, 512
@@ -266,6 +267,7 @@ int whole_block_rows(const ShapeInfo& si, int ctx_splits, int batch, int q_len, 
     const long row_tiles = ceil_div((long)q_len * si.group, 32), workgroups = (long)batch * si.hkv * row_tiles;
     if (workgroups > 512) return 0;
     if (si.mfma && ((row_tiles > 1 && batch * row_tiles * ceil_div(si.hkv, 8) > 32) || (batch > 1 && own * si.hkv > 400000))) return 0;
+    // (reached with more than 512 rows per KV head, up to three of those)
     if (si.mfma && batch < 8 && workgroups < 64 && max_ctx > 128 && own > 128L * batch && own <= 640L * batch) return 0;
     const int width = si.d <= 64 ? 0 : si.d <= 128 ? 1 : 2;
     const long most = si.dtype == APE_F32 ? (width == 0 ? 128 : width == 1 ? 64 : 0) : 512 >> width;

@@ -1,5 +1,6 @@
 // Matrix-core attention for a few query rows (a row is a (query token, head of the group) pair): a decode step, a query of a few tokens, and any
-// query of up to 512 rows per KV head over short contexts (whole) or 128 over up to 3072 tokens (split).  bf16 of head_dims up to 256 and fp32 up to 128, any number of query heads per KV head.
+// query of up to 512 rows per KV head over short contexts (whole: (request, KV head, 16 rows) triples up to 256) or, while its tiles leave CUs idle, over up to 3072 tokens (split: KV heads
+// times tiles of 16 rows up to 64).  bf16 of head_dims up to 256 and fp32 up to 128, any number of query heads per KV head.
 //
 // Math, precision and what happens to values that are not finite: as in the tile kernels (ape_tile_mfma.hip).  Errors against 64 bits likewise:
 // outputs 1.6e-3 (bf16), 2e-7 to 4e-7 (fp32; relative 2-norm).
@@ -33,7 +34,8 @@ struct Few {
     static_assert(BOX + 128 <= WAVE && 4 * LOADS < 64, "sizes");
 };
 
-// One direct load of 16 bytes per lane that is not to stay in the caches: every byte of K and V is read once (as load_lds16).
+// One direct load of 16 bytes per lane that is not to stay in the caches (as load_lds16): a tile of 16 rows reads every byte of K and V once.  Several tiles read the same tokens each for
+// itself, and carry the hint too.
 __device__ __forceinline__ void load_once(const char* base, uint32_t off, const char* lds) {
     const uint32_t m0v = (uint32_t)(uintptr_t)(const __attribute__((address_space(3))) char*)lds;
     asm volatile("s_mov_b32 m0, %2\n\ts_nop 3\n\tglobal_load_lds_dwordx4 %0, %1 nt" :: "v"(off), "s"(uniform_address(base)), "s"(m0v) : "m0");

@@ -1,5 +1,5 @@
 """Host logic: which queries over short contexts run without splits.  The flash kernels' shapes leave their own kernels for that,
-which has to pay for the rows and for the prefixes and own tokens as well."""
+which has to pay for the rows and for the prefixes and own tokens as well.  The rule by itself: what the few-row kernels serve does not come to it (test_launch_layout.py)."""
 import ctypes
 
 import pytest
