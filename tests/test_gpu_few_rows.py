@@ -122,7 +122,8 @@ def test_split_batches(dtype, hq, hkv, d, n, ctx, own):
 
 
 @pytest.mark.parametrize("dtype, hq, hkv, d, rows, lens", [
-    ("bf16", 8, 2, 128, 8, (300, 460)), ("bf16", 14, 2, 256, 5, (60, 150)), ("bf16", 8, 2, 64, 8, (1000, 24)), ("f32", 6, 2, 128, 12, (200, 32)), ("f32", 6, 1, 40, 9, (199, 1, 56))])
+    ("bf16", 8, 2, 128, 8, (300, 460)), ("bf16", 8, 2, 128, 8, (213, 300)), ("bf16", 14, 2, 256, 5, (60, 150)), ("bf16", 8, 2, 64, 8, (1000, 24)), ("f32", 6, 2, 128, 12, (200, 32)),
+    ("f32", 6, 1, 40, 9, (199, 1, 56))])
 def test_few_tiles_split(dtype, hq, hkv, d, rows, lens):
     """Several tiles of 16 rows on an idle chip, one request and two, over the lengths at which more tiles run whole."""
     test_tiles_of_rows(dtype, hq, hkv, d, rows, lens)
