@@ -198,7 +198,7 @@ QueryPlan tile_decode_plan(const ShapeInfo& si, int batch, long max_ctx) {
 // 128 (one launch, 257 to 512 pairs, 43 and 11 sizes, 0.86 times as fast whole; 513 to 1024 0.98 and 1.01; behind 400 and more own tokens 1.00 to 1.13), but not with others (up to 512 pairs 1.4, flash
 // kernels 1.2 to 1.5, fp32 1.76 and 1.08) or in several launches (1.2 to 1.4).
 // Most CUs: of 136 workgroups on (before / whole, 17 x 1024 25.0 / 20.2, 2048 38.2 / 33.9, 4096 60.2 / 60.4, 20 x 4096 63.6 / 63.6, 28 x 4096 84.8 / 77.7), with heads beyond 128 more
-// of them, whose blocks are twice as long (129 to 160 workgroups of 29 sizes over more than 512 tokens 1.02 times as fast, 8 slower, up to 96 of 72 sizes 1.21 times).  A launch holds 32 requests: of
+// of them over more than 1024 tokens (129 to 160 workgroups, 17 sizes of up to 1024 1.08 times as fast, 24 of more 0.99, 8 of them slower; 161 to 256, 57 of more 1.17).  A launch holds 32 requests: of
 // few KV heads it leaves CUs empty, and one launch follows the other.  Then long contexts are ahead split, in the flash kernels and where blocks are long, unless the launches are all but full or
 // the kernels of before would not split either (before / whole, 16/4 heads, 33 x 1024 37.2 / 37.2, 2048 49.1 / 61.3, 4096 70.5 / 109, 48 x 1024 40.2 / 39.0, 2048 53.9 / 64.6, 60 x 2048 72.8 / 66.7, 64 x
 // 4096 162 / 120; 8/4 of 256, 48 x 1024 73.3 / 76.1, 1536 99 / 105, 60 x 2048 139.9 / 139.7; 16/2 of 128, 65 x 2048 61.9 / 86.0, 96 x 4096 87.9 / 156), later where the tile kernels are the others
@@ -232,7 +232,7 @@ FewForm few_form(const ShapeInfo& si, int batch, int q_len, long max_ctx, long o
     if (max_ctx <= (tiles == 1 ? few_rows : idle ? few_tiles : more_rows)[f32][width])
         return base > 256 && batch <= kMaxReqPerLaunch && !f32 && width != 1 && !long_own ? FewForm::no : FewForm::whole;
     if (idle && max_ctx <= more_rows[f32][width]) return FewForm::full;
-    if (tiles == 1 && base > (width == 2 ? 160 : 128) && base <= 256 && max_ctx <= 4096 && !uneven) {
+    if (tiles == 1 && base > (width == 2 && max_ctx > 1024 ? 160 : 128) && base <= 256 && max_ctx <= 4096 && !uneven) {
         const long launches = ceil_div(batch, kMaxReqPerLaunch);
         if (launches == 1 || f32 || base == 256) return FewForm::whole;
         const long most = si.mfma || width == 2 ? (base >= 112 * launches ? 2048 : 1024) : base > 64 * launches ? 4096 : 1536;

@@ -50,7 +50,7 @@ def _form(recorder, call):
     ("bf16 32 8 128", 17, 4096, True), ("bf16 32 8 128", 32, 4096, True), ("bf16 32 8 128", 16, 4096, False), ("bf16 32 8 128", 32, 4097, False),
     ("bf16 16 4 128", 33, 1024, True), ("bf16 16 4 128", 33, 1025, False), ("bf16 16 4 128", 48, 2048, False), ("bf16 16 4 128", 56, 2048, True), ("bf16 16 4 128", 63, 2049, False),
     ("bf16 16 4 128", 64, 4096, True), ("bf16 16 2 128", 65, 2048, False), ("bf16 16 2 128", 127, 2048, False), ("bf16 16 2 128", 128, 4096, True),
-    ("bf16 16 8 256", 20, 1024, False), ("bf16 16 8 256", 21, 1024, True), ("bf16 8 4 256", 48, 1024, True), ("bf16 8 4 256", 48, 1025, False),
+    ("bf16 16 8 256", 20, 1024, True), ("bf16 16 8 256", 20, 1025, False), ("bf16 16 8 256", 21, 1025, True), ("bf16 8 4 256", 48, 1024, True), ("bf16 8 4 256", 48, 1025, False),
     ("bf16 12 2 128", 65, 1536, True), ("bf16 12 2 128", 65, 2048, False), ("bf16 4 4 96", 33, 4096, True), ("f32 16 4 64", 33, 4096, True)])
 def test_whole_decode_steps_fill_their_launches(recorder, shape, batch, ctx, whole):
     assert (_form(recorder, "%s decode 1 100 %s" % (shape, " ".join([str(ctx)] * batch))) == "whole") == whole
