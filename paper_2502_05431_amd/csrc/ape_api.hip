@@ -195,8 +195,8 @@ QueryPlan tile_decode_plan(const ShapeInfo& si, int batch, long max_ctx) {
 // 16/8 heads of 256, 32 x 1024, 57 / 47.7 (before: 29.9, 86.9, 72.3), but 16 x 2048 29.8 / 33.1.  fp32, before / split / whole: 4096 tokens 23.4 / 16.9 / -, 256
 // 17.0 / 13.6 / 17.0, 128 17.0 / 13.6 / 13.8, 4/2 heads of 64 over 256 13.4 / 9.9 / 10.6, 16 requests of 2048 of them 25.0 / 15.1 / -.
 // Short contexts with more (request, KV head) pairs than CUs take a second round; the tile kernels, two or more of whose workgroups share a CU, are ahead there with bf16 heads of up to 64 and beyond
-// 128 (one launch, 257 to 512 pairs, 43 and 11 sizes, 0.86 times as fast whole; 513 to 1024 0.98 and 1.01; behind 400 and more own tokens 1.00 to 1.13), but not with others (up to 512 pairs 1.4, flash
-// kernels 1.2 to 1.5, fp32 1.76 and 1.08) or in several launches (1.2 to 1.4).
+// 128 as long as they take one launch too (257 to 512 pairs in one launch, 43 and 11 sizes, 0.86 times as fast whole; behind 400 and more own tokens 1.00 and 1.03; 513 to 1024, which they split,
+// 0.98 and 1.01), but not with others (up to 512 pairs 1.4, flash kernels 1.2 to 1.5, fp32 1.76 and 1.08) or in several launches (1.2 to 1.4).
 // Most CUs: of 136 workgroups on (before / whole, 17 x 1024 25.0 / 20.2, 2048 38.2 / 33.9, 4096 60.2 / 60.4, 20 x 4096 63.6 / 63.6, 28 x 4096 84.8 / 77.7), with heads beyond 128 more
 // of them over more than 1024 tokens (129 to 160 workgroups, 17 sizes of up to 1024 1.08 times as fast, 24 of more 0.99, 8 of them slower; 161 to 256, 57 of more 1.17).  A launch holds 32 requests: of
 // few KV heads it leaves CUs empty, and one launch follows the other.  Then long contexts are ahead split, in the flash kernels and where blocks are long, unless the launches are all but full or
@@ -230,7 +230,7 @@ FewForm few_form(const ShapeInfo& si, int batch, int q_len, long max_ctx, long o
     const bool idle = tiles > 1 && base * tiles <= (width == 0 ? 16 : 32) && !uneven;
     const bool long_own = own >= 500L * batch;
     if (max_ctx <= (tiles == 1 ? few_rows : idle ? few_tiles : more_rows)[f32][width])
-        return base > 256 && batch <= kMaxReqPerLaunch && !f32 && width != 1 && !long_own ? FewForm::no : FewForm::whole;
+        return base > 256 && base <= 512 && batch <= kMaxReqPerLaunch && !f32 && width != 1 && !long_own ? FewForm::no : FewForm::whole;
     if (idle && max_ctx <= more_rows[f32][width]) return FewForm::full;
     if (tiles == 1 && base > (width == 2 && max_ctx > 1024 ? 160 : 128) && base <= 256 && max_ctx <= 4096 && !uneven) {
         const long launches = ceil_div(batch, kMaxReqPerLaunch);

@@ -78,7 +78,7 @@ def test_tiles_that_leave_the_chip_idle_are_split(recorder, shape, batch, rows, 
 
 @pytest.mark.parametrize("shape, batch, own, form", [
     ("bf16 32 8 64", 32, 0, "whole"), ("bf16 64 16 64", 16, 0, "whole"), ("bf16 64 16 64", 17, 0, "other"), ("bf16 64 16 64", 17, 500, "whole"), ("bf16 64 16 64", 33, 0, "whole"),
-    ("bf16 32 16 256", 17, 0, "other"), ("bf16 64 16 128", 17, 0, "whole"), ("bf16 16 16 96", 17, 0, "whole"), ("f32 64 16 64", 17, 0, "whole")])
+    ("bf16 32 16 256", 17, 0, "other"), ("bf16 128 32 64", 16, 0, "other"), ("bf16 128 32 64", 17, 0, "whole"), ("bf16 64 16 128", 17, 0, "whole"), ("bf16 16 16 96", 17, 0, "whole"), ("f32 64 16 64", 17, 0, "whole")])
 def test_short_steps_with_more_workgroups_than_cus(recorder, shape, batch, own, form):
     assert _form(recorder, "%s decode 1 %d %s" % (shape, own, " ".join(["120"] * batch))) == form
 
