@@ -215,8 +215,8 @@ QueryPlan tile_decode_plan(const ShapeInfo& si, int batch, long max_ctx) {
 // 64 over 1024 11.8 / 10.5, 16 over 1536 9.8 / 12.4; of 256, 16 over 256 13.8 / 11.9, 384 13.8 / 14.7; fp32, 16 over 256 16.1 / 13.9, 384 16.3 / 16.8, 4/2 heads of 64, 16 over
 // 256 11.7 / 9.4, 512 11.2 / 12.1.  Where they leave most of the chip idle they are split sooner (before / whole / split, 16 query tokens over 768 13.4 / 12.1 / 10.4, behind 1000 own tokens
 // 23.8 / 21.9 / 16.8; 16/2 heads of 104, 4 over 686, 11.8 / 14.2 / 9.9; 12/4 fp32 heads of 128, 12 over 232, 17.4 / 21.4 / 15.3; of 102 sizes 11 were slower whole
-// than before, none is split; heads of 64 up to 16 tiles: from 17 to 32 they are 1.16 times as fast whole and 1.13 split), though not where one launch takes less than the 10 us that
-// two take on the host (5 query tokens over 6 x 65, calls among others, whole 8.0, split 10.0).  Split, they read every token once per
+// than before, none is split), though not where one launch takes less than the 10 us that two take on the host (calls among others, whole / split, 5 query tokens over 6 x 65 8.0 / 10.0; 8/2 heads
+// of 64, 6 over 834 9.7 / 10.8: heads of 64 stay whole).  Split, they read every token once per
 // tile (8 query tokens over 20 x 512 17.4 / 24.0) and are ahead while that stays little, before / split: 5 query tokens over 1024 11.6 / 9.0, 16 over 1024 13.7 / 10.5, 3072 14.0 / 12.4,
 // 32 over 2048 15.6 / 13.0, 3072 16.0 / 16.0; heads of 64, 16 over 3072 11.9 / 10.9; of 256, 20 over 1024 14.9 / 11.8, 2048 16.1 / 15.6; fp32, 8 over 1024 15.9 / 11.1, 16 over 2048
 // 19.7 / 19.7, 4/2 heads of 64, 32 over 1024 11.4 / 9.6.
@@ -226,8 +226,8 @@ FewForm few_form(const ShapeInfo& si, int batch, int q_len, long max_ctx, long o
     const long rows = (long)q_len * si.group, tiles = (rows + kFewRows - 1) / kFewRows, base = (long)batch * si.hkv, stride = (long)si.hkv * si.d * elem;
     if (si.force_generic || (f32 && width == 2) || rows > 512 || stride > kFewStride || q_len * si.group * stride > 1L << 30) return FewForm::no;
     if (tiles == 1 ? base > 1024 : base * tiles > 256) return FewForm::no;
-    const long few_rows[2][3] = {{512, 384, 128}, {192, 128, 0}}, few_tiles[2][3] = {{768, 512, 192}, {224, 144, 0}}, more_rows[2][3] = {{1024, 768, 256}, {256, 256, 0}};
-    const bool idle = tiles > 1 && base * tiles <= (width == 0 ? 16 : 32) && !uneven;
+    const long few_rows[2][3] = {{512, 384, 128}, {192, 128, 0}}, few_tiles[2][3] = {{1024, 512, 192}, {256, 144, 0}}, more_rows[2][3] = {{1024, 768, 256}, {256, 256, 0}};
+    const bool idle = tiles > 1 && base * tiles <= 32 && !uneven;
     const bool long_own = own >= 500L * batch;
     if (max_ctx <= (tiles == 1 ? few_rows : idle ? few_tiles : more_rows)[f32][width])
         return base > 256 && base <= 512 && batch <= kMaxReqPerLaunch && !f32 && width != 1 && !long_own ? FewForm::no : FewForm::whole;

@@ -68,9 +68,9 @@ def test_split_decode_steps(recorder, shape, batch, ctx, own, form):
 
 
 @pytest.mark.parametrize("shape, batch, rows, ctx, form", [
-    ("bf16 32 8 128", 1, 16, 512, "whole"), ("bf16 32 8 128", 1, 16, 513, "full"), ("bf16 32 8 128", 1, 17, 768, "whole"), ("bf16 8 2 64", 1, 32, 768, "whole"), ("bf16 8 2 64", 1, 32, 769, "full"),
-    ("bf16 8 2 64", 1, 36, 1024, "whole"), ("bf16 14 2 256", 3, 5, 210, "full"), ("bf16 14 2 256", 3, 5, 192, "whole"), ("bf16 14 2 256", 6, 5, 210, "whole"), ("f32 12 4 128", 1, 12, 232, "full"),
-    ("f32 12 4 128", 1, 12, 144, "whole"), ("f32 4 2 64", 1, 9, 224, "whole"), ("f32 4 2 64", 1, 9, 225, "full"), ("bf16 32 8 128", 1, 16, 2048, "full"),
+    ("bf16 32 8 128", 1, 16, 512, "whole"), ("bf16 32 8 128", 1, 16, 513, "full"), ("bf16 32 8 128", 1, 17, 768, "whole"), ("bf16 8 2 64", 1, 32, 1024, "whole"), ("bf16 8 2 64", 1, 32, 1025, "full"),
+    ("bf16 14 2 256", 3, 5, 210, "full"), ("bf16 14 2 256", 3, 5, 192, "whole"), ("bf16 14 2 256", 6, 5, 210, "whole"), ("f32 12 4 128", 1, 12, 232, "full"),
+    ("f32 12 4 128", 1, 12, 144, "whole"), ("f32 4 2 64", 1, 9, 256, "whole"), ("f32 4 2 64", 1, 9, 257, "full"), ("bf16 32 8 128", 1, 16, 2048, "full"),
     ("bf16 32 8 128", 2, 16, 769, "other")])
 def test_tiles_that_leave_the_chip_idle_are_split(recorder, shape, batch, rows, ctx, form):
     assert _form(recorder, "%s prefill %d 0 %s" % (shape, rows, " ".join([str(ctx)] * batch))) == form
