@@ -181,13 +181,52 @@ struct Rows {
     f32x16 o[NB];                // O^T: dim 32 db + 8 (r / 4) + 4 hi + r % 4
 };
 
-template <typename T, int DW>
-__device__ __forceinline__ void clear_rows(Rows<T, DW>& st) {
+// The same where fp32 is multiplied in three bf16 pieces (below).
+template <int DP>
+struct SplitRows {
+    static constexpr int NQ = DP / 16, NB = DP / 32;
+    u32x4 q[3][NQ];              // piece, dims 16 i + 8 hi .. +7
+    float m, l;
+    f32x16 o[NB];
+};
+
+template <typename ROWS>
+__device__ __forceinline__ void clear_rows(ROWS& st) {
     st.m = kNone; st.l = 0.f;
 #pragma unroll
-    for (int db = 0; db < Rows<T, DW>::NB; ++db)
+    for (int db = 0; db < ROWS::NB; ++db)
 #pragma unroll
         for (int r = 0; r < 16; ++r) st.o[db][r] = 0.f;
+}
+
+// fp32 in three bf16 pieces.  x = x0 + x1 + x2: x0 the upper half of the bits (cut, not rounded: the lowest value of the type, with which callers
+// mask, stays finite), x1 the remainder rounded to bf16, x2 what is left, which 8 bits hold.  Exact, as long as x2 is not below what bf16 can say
+// (2^-133): x of 2^-109 and above.  Of the nine products of two such numbers three lie below 2^-23 of theirs together and of either sign and are left out; the other six
+// bf16 MFMAs take 192 cycles for what the fp32 MFMA takes 512 for (32x32x16), and round less: 16 products and a sum at once, off by 0.41 units of the last place, where the fp32 one is
+// off by 1.1 after its eight steps.
+__device__ __forceinline__ void split2(float a, float b, uint32_t& x0, uint32_t& x1, uint32_t& x2) {
+    const uint32_t ua = __float_as_uint(a), ub = __float_as_uint(b);
+    x0 = __builtin_amdgcn_perm(ub, ua, 0x07060302u);
+    const float ra = a - __uint_as_float(ua & 0xffff0000u), rb = b - __uint_as_float(ub & 0xffff0000u);
+    x1 = pack_bf16(ra, rb);
+    x2 = pack_bf16(ra - __uint_as_float(x1 << 16), rb - __uint_as_float(x1 & 0xffff0000u));
+}
+__device__ __forceinline__ void split8(const u32x4& lo, const u32x4& hi, u32x4 (&x)[3]) {
+#pragma unroll
+    for (int i = 0; i < 4; ++i) {
+        const u32x4& w = i < 2 ? lo : hi;
+        uint32_t x0, x1, x2;
+        split2(__uint_as_float(w[2 * i % 4]), __uint_as_float(w[2 * i % 4 + 1]), x0, x1, x2);
+        x[0][i] = x0; x[1][i] = x1; x[2][i] = x2;
+    }
+}
+// acc += a b but for the largest product
+__device__ __forceinline__ void split_mfma(const bf16x8 (&a)[3], const bf16x8 (&b)[3], f32x16& acc) {
+    acc = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a[2], b[0], acc, 0, 0, 0);
+    acc = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a[0], b[2], acc, 0, 0, 0);
+    acc = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a[1], b[1], acc, 0, 0, 0);
+    acc = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a[1], b[0], acc, 0, 0, 0);
+    acc = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a[0], b[1], acc, 0, 0, 0);
 }
 
 // One run of 32 tokens.  S^T = K Q^T over the dims of part `wd`.  RUNS: 64 dims at a time.
@@ -260,8 +299,9 @@ __device__ __forceinline__ f32x16 sum_scores(const char* sums) {
 }
 
 // The softmax of the run's scores and O^T += V^T P^T.  `nvis`: how many of the tokens this lane's row sees.
-template <typename T, int DP, int WD>
-__device__ __forceinline__ void update(f32x16 s, const char* vpart, int wd, const ScoreScale<T>& sc, int nvis, Rows<T, DP / WD>& st) {
+// PLANE > 0: fp32 in three pieces, of which `vpart` holds the first's rows, the others' that many bytes behind each other.
+template <typename T, int DP, int WD, int PLANE = 0, typename ROWS>
+__device__ __forceinline__ void update(f32x16 s, const char* vpart, int wd, const ScoreScale<T>& sc, int nvis, ROWS& st) {
     constexpr int PITCH = DP * (int)sizeof(T), DW = DP / WD, NB = DW / 32;
     const int lane = threadIdx.x & 63, l32 = lane & 31, hi = lane >> 5;
     // register r holds token 8 (r / 4) + 4 hi + r % 4
@@ -304,7 +344,32 @@ __device__ __forceinline__ void update(f32x16 s, const char* vpart, int wd, cons
         if (__builtin_expect(__builtin_amdgcn_ballot_w64(!finite(sum0 + sum1)) != 0, 0)) { drop(); add_up(); }
     }
     st.l += sum0 + sum1;
-    if constexpr (sizeof(T) == 2) {
+    if constexpr (PLANE > 0) {
+        static_assert(sizeof(T) == 4 && WD == 1, "fp32, all dims");
+        constexpr int PITCH2 = 2 * DP;
+        // (k-slots and V^T fragments as for bf16, below)
+        const int g16 = lane >> 4, s16 = lane & 15, row0 = 4 * (g16 >> 1) + (s16 >> 2);
+        int voff = row0 * PITCH2 + (((2 * (g16 & 1) + ((s16 & 3) >> 1)) ^ swz_v<__bf16, DP>(row0)) << 4) + (s16 & 1) * 8;
+        asm volatile("" : "+v"(voff));
+#pragma unroll
+        for (int sl = 0; sl < 2; ++sl) {
+            u32x4 ps[3];
+            split8(u32x4{__float_as_uint(p[8 * sl]), __float_as_uint(p[8 * sl + 1]), __float_as_uint(p[8 * sl + 2]), __float_as_uint(p[8 * sl + 3])},
+                   u32x4{__float_as_uint(p[8 * sl + 4]), __float_as_uint(p[8 * sl + 5]), __float_as_uint(p[8 * sl + 6]), __float_as_uint(p[8 * sl + 7])}, ps);
+            const bf16x8 b[3] = {__builtin_bit_cast(bf16x8, ps[0]), __builtin_bit_cast(bf16x8, ps[1]), __builtin_bit_cast(bf16x8, ps[2])};
+#pragma unroll
+            for (int db = 0; db < NB; ++db) {
+                bf16x8 a[3];
+#pragma unroll
+                for (int x = 0; x < 3; ++x) {
+                    const char* at = vpart + x * PLANE + (voff ^ (64 * (db % 4))) + 16 * sl * PITCH2;
+                    a[x] = __builtin_shufflevector(lds_read_tr(at), lds_read_tr(at + 8 * PITCH2), 0, 1, 2, 3, 4, 5, 6, 7);
+                }
+                split_mfma(a, b, st.o[db]);
+                st.o[db] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a[0], b[0], st.o[db], 0, 0, 0);
+            }
+        }
+    } else if constexpr (sizeof(T) == 2) {
         // k-slot e of slab sl is token 16 sl + (e < 4 ? 4 hi + e : 8 + 4 hi + e - 4): the registers 8 sl .. 8 sl + 7
         u32x4 ph[2], pl[2];
 #pragma unroll
@@ -396,11 +461,11 @@ __device__ __forceinline__ void init_rows(Rows<T, DP / WD>& st, const T* q, int 
 
 // The partial results of a row's WK wavefronts become one, held by the wavefront of the first (others:
 // return false).  Every lane keeps its own dims and its own share of l.
-template <typename T, int DP, int WR, int WK>
-__device__ __forceinline__ bool combine(char* lds, Rows<T, DP>& st) {
+template <typename T, int DP, int WR, int WK, int ROOM = Tile<T, DP, WR, WK, 1>::LDS, typename ROWS>
+__device__ __forceinline__ bool combine(char* lds, ROWS& st) {
     if constexpr (WK == 1) return true;                      // (with WD > 1 every wavefront holds its own dims, and all hold m and l)
     constexpr int NV = DP / 2 + 2;                          // values per lane
-    static_assert((WK - 1) * WR * NV * 256 <= Tile<T, DP, WR, WK, 1>::LDS, "the ring holds the partial results");
+    static_assert((WK - 1) * WR * NV * 256 <= ROOM, "the ring holds the partial results");
     const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6, kw = wave % WK, wr = wave / WK;
     float* box = (float*)lds + lane;
     stage_barrier();                                         // every wavefront is done with the last stage
@@ -444,11 +509,11 @@ __device__ __forceinline__ void scale_contexts(Rows<T, DW>& st, float scale) {
         for (int r = 0; r < 16; ++r) st.o[db][r] *= inv;
 }
 
-template <typename T, int DP, int WD, typename OUT>
-__device__ __forceinline__ void store_row(const Rows<T, DP / WD>& st, float inv, int d, int wd, OUT* o) {
+template <typename T, int DP, int WD, typename OUT, typename ROWS>
+__device__ __forceinline__ void store_row(const ROWS& st, float inv, int d, int wd, OUT* o) {
     const int hi = (threadIdx.x & 63) >> 5;
 #pragma unroll
-    for (int db = 0; db < Rows<T, DP / WD>::NB; ++db)
+    for (int db = 0; db < ROWS::NB; ++db)
 #pragma unroll
         for (int q4 = 0; q4 < 4; ++q4) {
             const int c = DP / WD * wd + 32 * db + 8 * q4 + 4 * hi;
@@ -456,6 +521,8 @@ __device__ __forceinline__ void store_row(const Rows<T, DP / WD>& st, float inv,
             if (c < d) store4(o + c, x);
         }
 }
+
+constexpr uint32_t kSplitLeast = (127 - 100) << 23;         // bits of 2^-100
 
 // Rows that the products above cannot give are computed again, one at a time on the vector ALUs, where every score is rounded
 // once and a token counts only if the row sees it.  Which rows, the results tell: a reference so large that its own
@@ -465,14 +532,15 @@ __device__ __forceinline__ void store_row(const Rows<T, DP / WD>& st, float inv,
 // Nothing of this runs for ordinary inputs.  A wavefront does its own rows (a bit of the mask each): the fp32 encode of eight
 // contexts of about 512 tokens takes 7.4 ms, and not 0.22, with a value that is none in the eleventh token of each (the vector-ALU
 // kernels 2.6 whatever the values); 64 bf16 rows over 20 x 512 tokens, 16/8 heads of 256, 1.7 ms with one such token (14).
-template <typename T, int DW>
-__device__ __forceinline__ uint32_t rows_to_redo(const Rows<T, DW>& st, float sum, bool valid, bool hidden) {
+// SPLIT (fp32 in three pieces): also values that are all so small that bf16 does not hold their pieces.
+template <bool SPLIT = false, typename ROWS>
+__device__ __forceinline__ uint32_t rows_to_redo(const ROWS& st, float sum, bool valid, bool hidden) {
     bool odd = (fabsf(st.m) > kFar && st.m > kNone) || !finite(sum);
     if (hidden) {
         int32_t pos = 0;                                     // as whole numbers, an infinity or a NaN is above every number of its sign
         uint32_t neg = 0;
 #pragma unroll
-        for (int db = 0; db < Rows<T, DW>::NB; ++db)
+        for (int db = 0; db < ROWS::NB; ++db)
 #pragma unroll
             for (int r = 0; r < 16; ++r) {
                 const uint32_t bits = __float_as_uint(st.o[db][r]);
@@ -480,6 +548,8 @@ __device__ __forceinline__ uint32_t rows_to_redo(const Rows<T, DW>& st, float su
                 neg = max(neg, bits);
             }
         odd |= pos >= 0x7f800000 || neg >= 0xff800000u;
+        // (the row's sum is 1 or more; zeros alone are exact)
+        if (SPLIT) { const uint32_t most = max((uint32_t)pos, neg >= 0x80000000u ? neg & 0x7fffffffu : 0u); odd |= most != 0 && most < kSplitLeast; }
     }
     const uint64_t lanes = __builtin_amdgcn_ballot_w64(valid && odd);
     return (uint32_t)lanes | (uint32_t)(lanes >> 32);        // (a row lives in lanes l and l ^ 32)
@@ -653,14 +723,10 @@ __device__ __forceinline__ bool listed_tile(int tiles, int most, int w, int& con
     return true;
 }
 
-template <typename T, int DP, int WR, int WK, int WD>
-__global__ __launch_bounds__(64 * WR * WK * WD) __attribute__((amdgpu_waves_per_eu(Tile<T, DP, WR, WK, WD>::WAVES, Tile<T, DP, WR, WK, WD>::MOST)))
-void tile_encode_kernel(const EncodeArgs a, int n_qtiles, const Listing list) {
-    using X = Tile<T, DP, WR, WK, WD>;
-    extern __shared__ __attribute__((aligned(16))) char lds[];
-    const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), l32 = lane & 31, hi = lane >> 5, wd = wave % WD;
-    const int d = a.head_dim, hq = a.n_q_heads, hkv = a.n_kv_heads, G = hq / hkv;
-    int chunk, hk, qtile, c0, len;
+// The tile of this workgroup: `qtile` of the context whose rows start at c0, of KV head hk.  false: none.
+__device__ __forceinline__ bool encode_tile(const EncodeArgs& a, int n_qtiles, const Listing& list, int tile_rows, int& hk, int& qtile, int& c0, int& len) {
+    const int lane = threadIdx.x & 63, hkv = a.n_kv_heads, G = a.n_q_heads / hkv;
+    int chunk;
     if (list.n_groups > 0) {
         int w = blockIdx.x / hkv, g = 0;
         hk = blockIdx.x % hkv;
@@ -668,16 +734,37 @@ void tile_encode_kernel(const EncodeArgs a, int n_qtiles, const Listing list) {
         const int c = list.first_context[g] + lane;
         const bool there = c < list.first_context[g + 1];
         const int start = there && a.cu ? a.cu[c] : 0, n = !there ? 0 : a.cu ? a.cu[c + 1] - start : a.total_rows;
-        if (!listed_tile((int)(((long)n * G + X::ROWS - 1) / X::ROWS), n_qtiles, w - list.first_tile[g], chunk, qtile)) return;
+        if (!listed_tile((int)(((long)n * G + tile_rows - 1) / tile_rows), n_qtiles, w - list.first_tile[g], chunk, qtile)) return false;
         c0 = __builtin_amdgcn_readlane(start, chunk); len = __builtin_amdgcn_readlane(n, chunk);
     } else {
         int team, member;
         team_of_block(blockIdx.x, n_qtiles, team, member);
-        if (team >= a.n_chunks * hkv) return;
+        if (team >= a.n_chunks * hkv) return false;
         qtile = n_qtiles - 1 - member; chunk = team / hkv; hk = team % hkv;
         c0 = a.cu ? scalar_load_i32(a.cu + chunk) : 0;
         len = a.cu ? scalar_load_i32(a.cu + chunk + 1) - c0 : a.total_rows;
     }
+    return true;
+}
+template <typename T>
+__device__ __forceinline__ void encode_source(Source& src, const EncodeArgs& a, int c0, int len, long stride, long head) {
+    const long first = (long)c0 * a.n_kv_heads * a.head_dim;
+    src.init_seq(a.k_prefix, a.v_prefix, a.prefix_len, (const T*)a.k + first, (const T*)a.v + first, len, stride, head);
+    // (in scalar registers: left in vector registers, as c0 would have them, every near load costs a 64-bit addition there and two moves: 18
+    // vector instructions per pair; ragged bf16 encodes of 4 x 1000 tokens, 16/8 heads of 256, 111.0 / 108.0 us, 12/2 of 128 58.6 / 57.0; fp32 within 1 %)
+    src.ka = (const char*)uniform_address(src.ka); src.va = (const char*)uniform_address(src.va);
+    src.kb = (const char*)uniform_address(src.kb); src.vb = (const char*)uniform_address(src.vb);
+}
+
+template <typename T, int DP, int WR, int WK, int WD>
+__global__ __launch_bounds__(64 * WR * WK * WD) __attribute__((amdgpu_waves_per_eu(Tile<T, DP, WR, WK, WD>::WAVES, Tile<T, DP, WR, WK, WD>::MOST)))
+void tile_encode_kernel(const EncodeArgs a, int n_qtiles, const Listing list) {
+    using X = Tile<T, DP, WR, WK, WD>;
+    extern __shared__ __attribute__((aligned(16))) char lds[];
+    const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), l32 = lane & 31, hi = lane >> 5, wd = wave % WD;
+    const int d = a.head_dim, hq = a.n_q_heads, hkv = a.n_kv_heads, G = hq / hkv;
+    int hk, qtile, c0, len;
+    if (!encode_tile(a, n_qtiles, list, X::ROWS, hk, qtile, c0, len)) return;
     const long rows = (long)len * G;
     if ((long)qtile * X::ROWS >= rows) return;
     const long stride = (long)hkv * d * sizeof(T), head = (long)hk * d * sizeof(T);
@@ -686,11 +773,7 @@ void tile_encode_kernel(const EncodeArgs a, int n_qtiles, const Listing list) {
     const bool valid = R < rows;
     const long tile_last = (long)qtile * X::ROWS + X::ROWS - 1, wave_last = R0 + 31;
     Source src;
-    src.init_seq(a.k_prefix, a.v_prefix, a.prefix_len, (const T*)a.k + (long)c0 * hkv * d, (const T*)a.v + (long)c0 * hkv * d, len, stride, head);
-    // (in scalar registers: left in vector registers, as c0 would have them, every near load costs a 64-bit addition there and two moves: 18
-    // vector instructions per pair; ragged bf16 encodes of 4 x 1000 tokens, 16/8 heads of 256, 111.0 / 108.0 us, 12/2 of 128 58.6 / 57.0; fp32 within 1 %)
-    src.ka = (const char*)uniform_address(src.ka); src.va = (const char*)uniform_address(src.va);
-    src.kb = (const char*)uniform_address(src.kb); src.vb = (const char*)uniform_address(src.vb);
+    encode_source<T>(src, a, c0, len, stride, head);
     const int t_end = a.prefix_len + (int)((tile_last < rows ? tile_last : rows - 1) / G) + 1;
     const int lim = a.prefix_len + tok, lim_hi = a.prefix_len + (int)((wave_last < rows ? wave_last : rows - 1) / G);
     Rows<T, DP / WD> st;
@@ -708,6 +791,136 @@ void tile_encode_kernel(const EncodeArgs a, int n_qtiles, const Listing list) {
         if (a.lse && hi == 0 && wd == 0) a.lse[(long)h * a.total_rows + c0 + tok] = ScoreScale<T>::lse(st.m, lt);
     }
     if (__builtin_expect(redo != 0, 0)) redo_encode_rows<T>(kernarg_again<EncodeArgs>(), c0, hk, (int)R0, redo, DP / WD * wd, DP / WD * (wd + 1));
+}
+
+// ------------------------------------------------------------------------------------------
+// fp32 with every product in three bf16 pieces a factor (split2).  WR x WK wavefronts as above.  A stage's K and V are loaded as they are; the
+// wavefront that loaded a row splits it, once for all rows of the workgroup, and writes the rows of its pieces, in the bf16 kernels' layout, for all.
+// (One stage at a time and two barriers a stage, so that two workgroups fit a CU: 48 KB of pieces and 32 KB of rows.)
+//
+// What bounds it: power.  96 MFMAs of 32 cycles a run of 32 tokens and 32 rows of 128 dims, where the fp32 MFMA takes 8192 cycles; the matrix cores are 60 % busy, at 1.6 GHz
+// (eight contexts of 2048 tokens, 32/8 heads of 128, 200 TFLOP/s, six times that in bf16, where the flash kernels reach 1000 to 1200).
+// fp32 MFMA / this, us: that call 2270 / 1415, 64 x 512 tokens 1380 / 948, eight ragged of about 512 180 / 112; heads of 64, 60 x 256 328 / 168.  Errors against 64 bits:
+// outputs 2.74e-7 / 2.44e-7 on the eight, 3.60e-7 / 3.18e-7 on 3 x 1200 (tiles of 64 rows 2.46e-7), heads of 64 1.97e-7 / 2.00e-7 (1.62e-7); LogSumExps, root mean square, 2.22e-7 / 2.23e-7.
+// Fragments read a slab ahead: no difference.
+template <int DP, int WR, int WK>
+struct Split {
+    using Raw = Tile<float, DP, WR, WK, 1>;
+    static constexpr int PITCH = 2 * DP, PLANE = Raw::KS * PITCH, PART = 3 * PLANE;   // K's pieces; V's follow
+    static constexpr int LDS = Raw::STAGE + 2 * PART;
+    static constexpr int RPL = 64 / Raw::CPR, PAIRS = DP / 8;      // rows of a load; 8 values (32 bytes) of a row at a time,
+    static constexpr int GROUPS = Raw::LPT / 2;                    // so many times per lane and part
+    static constexpr int WAVES = 160 * 1024 / LDS * Raw::NW / 4;
+    static_assert(LDS <= 160 * 1024, "stage size");
+};
+
+template <int DP, int WR, int WK>
+__device__ __forceinline__ void split_stream(Source& src, int t_beg, int t_end, int d, const ScoreScale<float>& sc, int lim, int lim_hi, bool active, char* lds, SplitRows<DP>& st) {
+    using X = Split<DP, WR, WK>;
+    using Raw = typename X::Raw;
+    const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), kw = wave % WK, l32 = lane & 31, hi = lane >> 5;
+    char* const planes = lds + Raw::STAGE;
+    start_stage<float, DP, WR, WK, 1, true>(src, t_beg, t_end, d, lds);
+    auto bring = [&](int t) {                                // the pieces of stage t are in LDS, the loads of the next under way
+        wait_loads<0>();
+        stage_barrier();                                     // every wavefront is done with the stage before
+        uint32_t ln = lane;
+        asm volatile("" : "+v"(ln));                         // (offsets recomputed here, not kept over the loop)
+        const uint32_t pair = ln % X::PAIRS;
+        // the rows that this wavefront has loaded: RPL of every load
+#pragma unroll
+        for (int g = 0; g < X::GROUPS; ++g)
+#pragma unroll
+            for (int kv = 0; kv < 2; ++kv) {
+                const uint32_t lr = ln / X::PAIRS + 64 / X::PAIRS * g, row = X::RPL * (Raw::NW * (lr / X::RPL) + wave) + lr % X::RPL;
+                const int swz = kv ? swz_v<float, DP>(row) : swz_k<float, DP>(row);
+                const char* from = lds + kv * Raw::PART + row * Raw::PITCH;
+                u32x4 x[3];
+                split8(*(const u32x4*)(from + (((2 * pair) ^ swz) << 4)), *(const u32x4*)(from + (((2 * pair + 1) ^ swz) << 4)), x);
+                char* to = planes + kv * X::PART + row * X::PITCH + ((pair ^ (kv ? swz_v<__bf16, DP>(row) : swz_k<__bf16, DP>(row))) << 4);
+#pragma unroll
+                for (int i = 0; i < 3; ++i) *(u32x4*)(to + i * X::PLANE) = x[i];
+            }
+        asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
+        if (t + Raw::KS < t_end) start_stage<float, DP, WR, WK, 1, true>(src, t + Raw::KS, t_end, d, lds);
+        stage_barrier();
+    };
+    // (two loops: one in which the accumulators move or not keeps two copies of them, 64 moves a run and Q in scratch)
+    int t = t_beg;
+    if (active) {
+        for (const int last = min(lim_hi, t_end - 1) - 32 * kw; t <= last; t += Raw::KS) {
+            bring(t);
+            const char* part = planes + 32 * kw * X::PITCH;
+            // The largest products last, on top of the sum of the others: that one is off by little then, and one accumulator does.
+            f32x16 sum;
+#pragma unroll
+            for (int r = 0; r < 16; ++r) sum[r] = 0.f;
+            int koff = l32 * X::PITCH + ((hi ^ swz_k<__bf16, DP>(l32)) << 4);
+            asm volatile("" : "+v"(koff));
+            auto piece = [&](int p, int i) { return *(const bf16x8*)(part + p * X::PLANE + (koff ^ (32 * i))); };
+            auto q = [&](int p, int i) { return __builtin_bit_cast(bf16x8, st.q[p][i]); };
+#pragma unroll
+            for (int i = 0; i < SplitRows<DP>::NQ; ++i) {
+                const bf16x8 a[3] = {piece(0, i), piece(1, i), piece(2, i)}, b[3] = {q(0, i), q(1, i), q(2, i)};
+                split_mfma(a, b, sum);
+            }
+#pragma unroll
+            for (int i = 0; i < SplitRows<DP>::NQ; ++i) sum = __builtin_amdgcn_mfma_f32_32x32x16_bf16(piece(0, i), q(0, i), sum, 0, 0, 0);
+            update<float, DP, 1, X::PLANE>(sum, part + X::PART, 0, sc, min(lim, t_end - 1) - t - 32 * kw + 1, st);
+        }
+    }
+    for (; t < t_end; t += Raw::KS) bring(t);                // for the other wavefronts
+}
+
+// The query rows and the empty state.  `q`: the row's first element.
+template <int DP>
+__device__ __forceinline__ void init_rows(SplitRows<DP>& st, const float* q, int d) {
+    const int hi = (threadIdx.x & 63) >> 5;
+#pragma unroll
+    for (int i = 0; i < SplitRows<DP>::NQ; ++i) {
+        const int c = 16 * i + 8 * hi;                       // zeros beyond head_dim
+        u32x4 lo = *(const u32x4*)(q + (c < d ? c : 0)), up = *(const u32x4*)(q + (c < d ? c + 4 : 0)), x[3];
+#pragma unroll
+        for (int e = 0; e < 4; ++e) { lo[e] = c < d ? lo[e] : 0; up[e] = c < d ? up[e] : 0; }
+        split8(lo, up, x);
+#pragma unroll
+        for (int p = 0; p < 3; ++p) st.q[p][i] = x[p];
+    }
+    clear_rows(st);
+}
+
+template <int DP, int WR, int WK>
+__global__ __launch_bounds__(64 * WR * WK) __attribute__((amdgpu_waves_per_eu(2, Split<DP, WR, WK>::WAVES < 2 ? 2 : Split<DP, WR, WK>::WAVES)))
+void split_encode_kernel(const EncodeArgs a, int n_qtiles, const Listing list) {
+    constexpr int ROWS = 32 * WR;
+    extern __shared__ __attribute__((aligned(16))) char lds[];
+    const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), l32 = lane & 31, hi = lane >> 5;
+    const int d = a.head_dim, hq = a.n_q_heads, hkv = a.n_kv_heads, G = hq / hkv;
+    int hk, qtile, c0, len;
+    if (!encode_tile(a, n_qtiles, list, ROWS, hk, qtile, c0, len)) return;
+    const long rows = (long)len * G;
+    if ((long)qtile * ROWS >= rows) return;
+    const long stride = (long)hkv * d * sizeof(float), head = (long)hk * d * sizeof(float);
+    const long R0 = (long)qtile * ROWS + wave / WK * 32, R = R0 + l32, Rc = R < rows ? R : rows - 1;
+    const int tok = (int)(Rc / G), h = hk * G + (int)(Rc % G);
+    const bool valid = R < rows;
+    const long tile_last = (long)qtile * ROWS + ROWS - 1, wave_last = R0 + 31;
+    Source src;
+    encode_source<float>(src, a, c0, len, stride, head);
+    const int t_end = a.prefix_len + (int)((tile_last < rows ? tile_last : rows - 1) / G) + 1;
+    const int lim = a.prefix_len + tok, lim_hi = a.prefix_len + (int)((wave_last < rows ? wave_last : rows - 1) / G);
+    SplitRows<DP> st;
+    init_rows(st, (const float*)a.q + ((long)(c0 + tok) * hq + h) * d, d);
+    split_stream<DP, WR, WK>(src, 0, t_end, d, ScoreScale<float>(d, 1.f), lim, lim_hi, R0 < rows, lds, st);
+    if (!combine<float, DP, WR, WK, Split<DP, WR, WK>::LDS>(lds, st)) return;
+
+    const float lt = sum_halves(st.l);
+    const uint32_t redo = rows_to_redo<true>(st, lt, valid, true);
+    if (valid && !(redo >> l32 & 1)) {
+        store_row<float, DP, 1>(st, 1.f / lt, d, 0, (float*)a.out + ((long)(c0 + tok) * hq + h) * d);   // (a row always sees itself)
+        if (a.lse && hi == 0) a.lse[(long)h * a.total_rows + c0 + tok] = ScoreScale<float>::lse(st.m, lt);
+    }
+    if (__builtin_expect(redo != 0, 0)) redo_encode_rows<float>(kernarg_again<EncodeArgs>(), c0, hk, (int)R0, redo, 0, DP);
 }
 
 template <typename T, int DP, int WR, int WK, int WD, bool WHOLE>
@@ -763,28 +976,38 @@ Listing list_tiles(const EncodeArgs& a, int rows, size_t elem) {
     return l;
 }
 
+using EncodeKernel = void (*)(EncodeArgs, int, Listing);
+hipError_t run_encode(EncodeKernel kernel, const EncodeArgs& a, int tile_rows, int threads, int lds, size_t elem, hipStream_t s) {
+    const long rows = (long)a.max_chunk_len * (a.n_q_heads / a.n_kv_heads);
+    const int n_qtiles = (int)((rows + tile_rows - 1) / tile_rows);
+    hipError_t e = hipFuncSetAttribute((const void*)kernel, hipFuncAttributeMaxDynamicSharedMemorySize, lds);
+    if (e != hipSuccess) return e;
+    long blocks = ((long)a.n_chunks * a.n_kv_heads + 7) / 8 * 8 * n_qtiles;
+    const Listing list = list_tiles(a, tile_rows, elem);
+    if (list.n_groups > 0) blocks = (long)list.first_tile[list.n_groups] * a.n_kv_heads;
+    kernel<<<(unsigned)blocks, threads, lds, s>>>(a, n_qtiles, list);
+    return hipGetLastError();
+}
 template <typename T, int DP, int WR, int WK, int WD>
 hipError_t encode_as(const EncodeArgs& a, hipStream_t s) {
     using X = Tile<T, DP, WR, WK, WD>;
-    auto kernel = tile_encode_kernel<T, DP, WR, WK, WD>;
-    const long rows = (long)a.max_chunk_len * (a.n_q_heads / a.n_kv_heads);
-    const int n_qtiles = (int)((rows + X::ROWS - 1) / X::ROWS);
-    hipError_t e = hipFuncSetAttribute((const void*)kernel, hipFuncAttributeMaxDynamicSharedMemorySize, X::LDS);
-    if (e != hipSuccess) return e;
-    long blocks = ((long)a.n_chunks * a.n_kv_heads + 7) / 8 * 8 * n_qtiles;
-    const Listing list = list_tiles(a, X::ROWS, sizeof(T));
-    if (list.n_groups > 0) blocks = (long)list.first_tile[list.n_groups] * a.n_kv_heads;
-    kernel<<<(unsigned)blocks, X::NT, X::LDS, s>>>(a, n_qtiles, list);
-    return hipGetLastError();
+    return run_encode(tile_encode_kernel<T, DP, WR, WK, WD>, a, X::ROWS, X::NT, X::LDS, sizeof(T), s);
 }
+// fp32 of up to 128 dims has tiles of 64 and 128 rows in the split kernels alone.
 template <typename T, int DP>
 hipError_t encode_with(const EncodeArgs& a, int block_rows, hipStream_t s) {
     constexpr bool WIDE = DP * (int)sizeof(T) > 256;
     constexpr int K2 = WIDE ? 1 : 2, D2 = WIDE ? 2 : 1, K4 = WIDE ? 1 : 4, D4 = WIDE ? 4 : 1;
-    if constexpr (DP <= 128) {
-        if (block_rows == 128) return encode_as<T, DP, 4, 1, 1>(a, s);
+    if constexpr (sizeof(T) == 4 && DP <= 128) {
+        if (block_rows == 128) return run_encode(split_encode_kernel<DP, 4, 1>, a, 128, 256, Split<DP, 4, 1>::LDS, sizeof(T), s);
+        if (block_rows == 64) return run_encode(split_encode_kernel<DP, 2, 2>, a, 64, 256, Split<DP, 2, 2>::LDS, sizeof(T), s);
+    } else {
+        if constexpr (DP <= 128) {
+            if (block_rows == 128) return encode_as<T, DP, 4, 1, 1>(a, s);
+        }
+        if (block_rows == 64) return encode_as<T, DP, 2, K2, D2>(a, s);
     }
-    return block_rows == 64 ? encode_as<T, DP, 2, K2, D2>(a, s) : encode_as<T, DP, 1, K4, D4>(a, s);
+    return encode_as<T, DP, 1, K4, D4>(a, s);
 }
 
 }  // namespace
@@ -843,9 +1066,31 @@ int tile_encode_groups(const EncodeArgs& a, int dtype, int32_t* first_context) {
     return l.n_groups;
 }
 
+// fp32 of up to 128 dims: what runs, in place of the tile kernels that the rule above would take.  128, 64: split kernels (4 x 1 and 2 x 2 wavefronts); 32: the tile
+// kernel, whose four wavefronts share 32 rows and so have the shortest chain where tiles are few (a split one of 1 x 4 was slower everywhere).
+// Start / 32 / 64 / 128 rows, us:
+//   heads of 128: a few tiles per CU, where the chain of the last one counts, 32/8 heads, 1 x 300 tokens 31.1 / 31.4 / 33.1 / 40.1, 1 x 1000 129 / 127 / 96 / 110, 16 x 60 ragged
+//   29.2 / 27.3 / 37.3 / 25.0, 8 x 120 37.9 / 43.2 / 46.9 / 34.0; 8/8, 1 x 2000 191 / 157 / 139 / 206, 16 x 256 59.1 / 44.4 / 55.9 / 55.2, 4 x 1000 197 / 156 / 135 / 177; more of them,
+//   32/8, 40 x 30 32.8 / 32.5 / 39.0 / 22.4, 8 x 500 231 / 310 / 275 / 150, 1 x 2000 363 / 404 / 302 / 237;
+//   of 64: 4/2, 40 x 60 15.8 / 16.0 / 12.9 / 14.6, 16 x 256 32.7 / 22.4 / 28.1 / 32.3, 6/2 of 40, 8 x 500 49.4 / 51.2 / 38.9 / 51.8; 32/8, 2 x 200 16.0 / 18.8 / 15.1 / 18.9,
+//   1 x 1000 77.6 / 80.0 / 51.0 / 65.3, 16 x 60 19.3 / 29.5 / 17.8 / 15.0, 3 x 700 79.2 / 125 / 61.7 / 56.0, 60 x 256 328 / 664 / 256 / 168.
+int split_encode_rows(const EncodeArgs& a) {
+    const long group = a.n_q_heads / a.n_kv_heads, longest = a.max_chunk_len;
+    const long tiles = ((long)a.total_rows * group + 63) / 64 * a.n_kv_heads;   // of 64 rows
+    if (a.head_dim > 64) {
+        if (tiles >= 576) return 128;
+        if (tiles < 192) return 32;
+        return longest >= 560 ? 64 : tiles >= 400 ? 128 : 32;
+    }
+    if (tiles >= 900 || (tiles >= 320 && longest <= 200)) return 128;
+    if (tiles >= 320) return 64;
+    if ((long)a.n_chunks * a.n_kv_heads >= 64 && longest * group <= 256) return 64;   // many short contexts
+    return tiles >= 176 && longest < 400 ? 64 : 32;
+}
+
 hipError_t launch_tile_encode(const EncodeArgs& a, int dtype, hipStream_t s) {
     if (a.total_rows == 0) return hipSuccess;
-    const int d = a.head_dim, br = tile_encode_block_rows(a, dtype);
+    const int d = a.head_dim, br = dtype == APE_F32 && d <= 128 ? split_encode_rows(a) : tile_encode_block_rows(a, dtype);
     // The grid is contexts x KV heads x tiles of the longest context: where uneven lengths make it too large, it goes out a run of
     // contexts at a time (one context always fits: the outputs of a call are fewer than 2^26).
     const long per_context = (long)a.n_kv_heads * (((long)a.max_chunk_len * (a.n_q_heads / a.n_kv_heads) + br - 1) / br);

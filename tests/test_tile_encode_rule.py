@@ -64,3 +64,16 @@ def _ragged(n, mean):
     ("f32", (32, 8, 128), _ragged(8, 512), 128), ("f32", (32, 8, 128), _ragged(4, 512), 64)])
 def test_rows(dtype, heads, lens, expect):
     assert rows(dtype, heads, lens) == expect
+
+
+def split_rows(heads, lens):
+    a, _ = _args(heads, lens)
+    return B.load()._ZN3ape17split_encode_rowsERKNS_10EncodeArgsE(ctypes.byref(a))
+
+
+@pytest.mark.parametrize("heads, lens, expect", [
+    ((32, 8, 128), [300], 32), ((32, 8, 128), [1000], 64), ((32, 8, 128), _ragged(8, 512), 128), ((8, 8, 128), _ragged(12, 256), 32), ((8, 8, 72), [2000], 64),
+    ((4, 2, 64), [1000], 32), ((4, 2, 64), _ragged(40, 60), 64), ((32, 8, 64), [1000], 64), ((32, 8, 64), _ragged(16, 100), 128), ((6, 2, 40), _ragged(15, 300), 64)])
+def test_rows_in_three_pieces(heads, lens, expect):
+    """fp32 of up to 128 dims: 32 rows on the tile kernel, more on the kernels that multiply in three bf16 pieces."""
+    assert split_rows(heads, lens) == expect
