@@ -209,17 +209,24 @@ __global__ __launch_bounds__(kWave) void generic_encode_kernel(const EncodeArgs 
 // Whole calls, against a workgroup per unit that read the LogSumExps and then the rows of one group after the other (us): a decode
 // step over 20 x 512 tokens, 32 units of 33 splits, 17.8 -> 15.3; 80 units of 33 splits of a 20-row query 25.9 -> 23.6; 64 rows,
 // 32/8 bf16 heads of 64, 30.7 -> 27.4; 256 rows over 128K tokens, 8192 units of 9 splits, 481 -> 480.
-template <typename T, int NV, int H, bool UNEVEN, bool ONE>
-__device__ __forceinline__ void merge_units(const MergeArgs& a) {
+// XCD: workgroup b, which runs on XCD b % 8, takes rows of that XCD's KV heads (see launch_merge_t).
+struct XcdHeads { uint32_t heads, inv, group; };              // query heads per XCD, 2^32 divided by that and rounded up, query heads per KV head
+template <typename T, int NV, int H, bool UNEVEN, bool ONE, bool XCD = false>
+__device__ __forceinline__ void merge_units(const MergeArgs& a, const XcdHeads x = {}) {
     constexpr int UN = 8;
     __shared__ float4 part[H > 1 ? 8 : 1][32 * NV];
     const int lane = threadIdx.x & (kWave - 1), wave = threadIdx.x / kWave;
     const int half = lane >> 5, j = lane & 31, hw = 2 * wave + half, share = hw % H;
     const long n_units = (long)a.n_req * a.q_len * a.n_q_heads;
-    const long unit_raw = (long)blockIdx.x * (8 / H) + hw / H;
+    const int hq = a.n_q_heads, d = a.head_dim;
+    long unit_raw = (long)blockIdx.x * (8 / H) + hw / H;
+    if constexpr (XCD) {
+        const uint32_t u = (blockIdx.x >> 3) * (8 / H) + hw / H, row = __umulhi(u, x.inv), h = u - row * x.heads;   // unit u of the XCD's
+        unit_raw = u < (uint32_t)(n_units >> 3) ? (long)row * hq + (blockIdx.x & 7) * x.group + h : n_units;
+        if (x.heads > x.group) unit_raw += h / x.group * (7 * x.group);              // (KV heads b % 8, b % 8 + 8 ..)
+    }
     const bool valid = unit_raw < n_units;
     const long unit = valid ? unit_raw : n_units - 1;                // (a spare half-wavefront recomputes the last unit and stores nothing)
-    const int hq = a.n_q_heads, d = a.head_dim;
     const int rq = ONE ? 0 : (int)((uint32_t)unit / (uint32_t)(hq * a.q_len));     // (fewer than 2^24 units)
     const long gunit = (long)a.req_base * a.q_len * hq + unit;
     auto ka = kernarg<MergeArgs>();
@@ -344,6 +351,13 @@ __global__ __launch_bounds__(256) void pool_single_kernel(const MergeArgs a) { m
 // requests with splits of their own (a kernel of its own: the look-ups would cost the others 0.5 us)
 template <typename T, int NV, int H>
 __global__ __launch_bounds__(256) void pool_uneven_kernel(const MergeArgs a) { merge_units<T, NV, H, true, false>(a); }
+// The three by XCD (kernels of their own: the unit's division would cost small calls 0.4 us).
+template <typename T, int H>
+__global__ __launch_bounds__(256) void merge_units_kernel_by_xcd(const MergeArgs a, const XcdHeads x) { merge_units<T, 1, H, false, false, true>(a, x); }
+template <typename T, int H>
+__global__ __launch_bounds__(256) void pool_single_kernel_by_xcd(const MergeArgs a, const XcdHeads x) { merge_units<T, 1, H, false, true, true>(a, x); }
+template <typename T, int H>
+__global__ __launch_bounds__(256) void pool_uneven_kernel_by_xcd(const MergeArgs a, const XcdHeads x) { merge_units<T, 1, H, true, false, true>(a, x); }
 
 // ------------------------------------------------------------------------------------------
 // Tree of contexts (Appendix C.2 applied at every node, Appendix C.5).
@@ -770,6 +784,23 @@ hipError_t launch_merge_t(const MergeArgs& a, hipStream_t s) {
     const int h = units >= 4096 || slots <= 8 ? 1 : slots <= 16 ? 2 : slots <= 32 ? 4 : 8;
     const unsigned blocks = (unsigned)((units * h + 7) / 8);
     const bool un = a.n_own_splits > 0, one = a.n_req == 1 && !un;
+    // Where the attention kernel gave every KV head to one XCD, a row is merged on the XCD that wrote its partial results, if they are 4 MB or more
+    // (in turn / by XCD, us, whole calls, 32/8 heads of 128: 8 / 16 / 24 / 32 rows over 20 x 512 tokens, 4.3 / 8.6 / 13 / 17 MB, 15.9 / 15.5, 19.4 / 17.5, 23.7 / 19.4, 27.4 / 21.3,
+    // 4 rows over 8 x 512, 2 MB, 9.9 / 10.4; 16/8 heads, 64 rows over 20 x 512 27.0 / 22.5, 32 over 8 x 512 13.9 / 14.3).  Rows of more than 128 dims: no difference.
+    if constexpr (NV == 1) {
+        const long heads = a.n_q_heads / 8;
+        if (a.xcd_group > 0 && (heads >= 4 || slots > 32 || units > 1024) && units * slots * a.head_dim >= 1L << 20 && heads > 1 && heads <= 256) {
+            const XcdHeads x{(uint32_t)heads, (uint32_t)(((1ull << 32) + heads - 1) / heads), (uint32_t)a.xcd_group};   // (exact: fewer than 2^21 units, times 256)
+            auto pick = [&](auto n) {
+                constexpr int H = n();
+                return un ? pool_uneven_kernel_by_xcd<T, H> : one ? pool_single_kernel_by_xcd<T, H> : merge_units_kernel_by_xcd<T, H>;
+            };
+            auto kernel = h == 1 ? pick(std::integral_constant<int, 1>()) : h == 2 ? pick(std::integral_constant<int, 2>())
+                        : h == 4 ? pick(std::integral_constant<int, 4>()) : pick(std::integral_constant<int, 8>());
+            kernel<<<(unsigned)((units / 8 * h + 7) / 8 * 8), 256, 0, s>>>(a, x);
+            return hipGetLastError();
+        }
+    }
     auto pick = [&](auto n) {
         constexpr int H = n();
         return un ? pool_uneven_kernel<T, NV, H> : one ? pool_single_kernel<T, NV, H> : merge_units_kernel<T, NV, H>;

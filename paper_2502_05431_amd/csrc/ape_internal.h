@@ -30,6 +30,16 @@ struct KvView {
 constexpr int kWsAlign = 256;
 constexpr long kMaxEncodeBlocks = 1L << 24;     // workgroups of a matrix-core encode launch (256 threads each)
 
+// Whether the flash kernels give every KV head an XCD of its own, for several row tiles or requests too (`rows`: per KV head, of all requests): the merge then finds
+// a row's partial results in the L2 that wrote them (launch_merge_t).  For short calls, where that counts: over long contexts the splits go round the XCDs, each
+// of which then reads whole tokens.  By splits / by heads, us, 32/8 heads: 64 rows over 4 / 8 / 20 x 512 tokens 18.9 / 15.9, 23.8 / 20.7, 26.4 / 26.6, 200 over 4 x 512 27.9 / 22.9,
+// 12 x 600 48.6 / 46.7; 40 over 16 x 2048 42.1 / 46.3; batches of 3 x 64 rows over 2 x 512 22.6 / 17.5, 4 x 64 over 8 x 900 49.3 / 50.1, 4 x 128 over 6 x 512 43.3 / 44.3, 4 x 200 over
+// 2 x 512 41.5 / 42.6.
+__host__ __device__ inline bool flash_heads_by_xcd(int n_kv_heads, long rows, int n_ctx_splits, int ctx_split_len) {
+    const long ctx = (long)n_ctx_splits * ctx_split_len;
+    return n_kv_heads == 8 && ctx <= 8192 && rows <= 2048 && rows * ctx < 6L << 20;
+}
+
 // Kernel-argument block of the query-time kernels (prefill and decode).
 struct QueryArgs {
     static constexpr int kRequests = kMaxReqPerLaunch;
@@ -103,6 +113,7 @@ struct MergeArgs {
     int32_t lse_head_major;     // 1: lse_out[h*q_len + r] (prefill); 0: lse_out[unit] (decode)
     int32_t dtype;
     int32_t n_own_splits;       // as in QueryArgs (n_ctx_splits: the most splits of a request)
+    int32_t xcd_group;          // (host) query heads per KV head where every KV head was worked on by one XCD, hk % 8; or 0
 };
 
 // Device-side plan of a tree call, written into the workspace by the plan kernel and read by the

@@ -1,0 +1,42 @@
+"""GPU parity of the merge by XCD (KV heads a multiple of eight, partial results of 4 MB and more): one, two and more KV heads per XCD, numbers of heads whose
+division is not exact in binary, single requests, even and uneven batches, and calls on both sides of the line.  The units that a wrong map would miss
+keep the NaN that the outputs start from."""
+import numpy as np
+import pytest
+
+from paper_2502_05431_amd import workloads as W
+
+import helpers as H
+from test_gpu_parity import _check_prefill_batch
+
+pytestmark = pytest.mark.gpu
+DEV = "cuda:0"
+
+
+def _spec(dtype, hq, hkv, d, lens, rows):
+    return W.WorkloadSpec(name="xcd", cfg=6, dtype=dtype, n_q_heads=hq, n_kv_heads=hkv, head_dim=d, prefix_len=7, chunk_lens=tuple(lens), q_len=rows,
+                          decode_steps=0, temperature=0.8, scale=0.9)
+
+
+@pytest.mark.parametrize("dtype, hq, hkv, d, lens, rows", [
+    ("bf16", 32, 8, 128, (512, 511, 900), 33), ("bf16", 32, 8, 128, (700, 500), 97),      # a tile and more per KV head
+    ("bf16", 32, 8, 128, (512,) * 9, 24), ("bf16", 16, 8, 128, (512,) * 20, 31), ("bf16", 64, 8, 128, (600, 700), 40),
+    ("bf16", 64, 16, 128, (512, 333, 600), 32), ("bf16", 96, 32, 64, (700, 600), 33), ("bf16", 24, 8, 96, (512,) * 8, 50),
+    ("bf16", 72, 24, 40, (600,) * 4, 64), ("f32", 24, 8, 64, (512, 300) * 4, 40), ("bf16", 8, 8, 128, (512,) * 12, 130),
+])
+def test_one_request(dtype, hq, hkv, d, lens, rows):
+    spec = _spec(dtype, hq, hkv, d, lens, rows)
+    r = W.make_request(spec, DEV)
+    out, lse = H.run_prefill(spec, r, rows, rows)
+    ref, ref_lse, _ = H.oracle_prefill(H.HostArrays(r), rows, rows, r.temperature, r.scale)
+    H.check_close(H.f64(out).reshape(-1, d), ref, dtype, str(spec))
+    assert np.abs(H.f64(lse).T.reshape(-1) - ref_lse).max() <= H.lse_tol(dtype)
+
+
+@pytest.mark.parametrize("hq, hkv, d, rows, chunks", [
+    (32, 8, 128, 40, ((700, 300),) * 2), (32, 8, 128, 21, ((700, 300), (500,) * 5, (64,))), (64, 16, 128, 20, ((600, 40), (900, 800))),
+    (24, 8, 96, 33, ((500, 500),) * 3), (24, 8, 96, 33, ((500, 500), (90,), (600,) * 3)),
+])
+def test_batches(hq, hkv, d, rows, chunks):
+    specs = [_spec("bf16", hq, hkv, d, c, rows) for c in chunks]
+    _check_prefill_batch(specs, rows, [rows] * len(specs), what=str(specs[0]))
