@@ -11,6 +11,7 @@
 
 #include <cmath>
 #include <mutex>
+#include <numeric>
 
 namespace ape {
 namespace {
@@ -169,6 +170,16 @@ hipError_t launch_swiglu(const void* gate_up, void* act, long rows, int inter, i
     return hipGetLastError();
 }
 
+// Rows of a bf16 product that go out first, the rest behind them in a product of their own.  The library's products are tiles of 256 x 256, 256 at a time on this chip;
+// a last round that is not full costs it up to as much as two full ones, on long rows (k > n) most, where whole rounds and a small product behind them do not
+// (one product / so, us: n = 4096, k = 14336, 8300 rows 1013 / 651, 10240 1133 / 804, 7000 664 / 565; k = 4096, 9000 344 / 220, 10240 370 / 242; n = 28672, k = 4096, 5000 and 11500
+// rows, with 0.75 and 0.69 of a round left, 883 / 788 and 1836 / 1932, 10240 1725 / 1566; n = 6144, 8300 402 / 283, 10000, 0.75 left, 339 / 339; over 13 shapes of up to 20480 rows 1.10
+// times as fast; slower by more than 2 %: n = 10240, k = 8192, 12288 rows 1346 / 1516).  fp32 has other tiles (n = 6144, 12288 rows 4170 / 4562 by these).
+long rows_of_whole_rounds(long rows, int n, int k) {
+    const long across = (n + 255) / 256, block = 256 * (256 / std::gcd(256L, across)), left = (rows + 255) / 256 * across % 256;
+    return rows % block == 0 || left == 0 || (left > 128 && k <= n) || rows < block ? rows : rows / block * block;
+}
+
 // y[rows, n] = x[rows, k] W[n, k]^T (+ residual[rows, n]); all row-major, leading dimensions given in
 // elements.  In the column-major terms of the library: y^T = W^T(op T) x^T.
 int gemm_xwT(const void* x, long ldx, const void* w, const void* residual, void* y, long ldy, long rows, int n, int k,
@@ -179,10 +190,16 @@ int gemm_xwT(const void* x, long ldx, const void* w, const void* residual, void*
     if (rows == 0) return 0;
     const float alpha = 1.f, beta = residual ? 1.f : 0.f;
     const rocblas_datatype t = dtype == APE_F32 ? rocblas_datatype_f32_r : rocblas_datatype_bf16_r;
-    const rocblas_status st = rocblas_gemm_ex(h, rocblas_operation_transpose, rocblas_operation_none, n, (rocblas_int)rows, k, &alpha,
-                                              w, t, k, x, t, (rocblas_int)ldx, &beta, residual ? residual : y, t, (rocblas_int)ldy,
-                                              y, t, (rocblas_int)ldy, rocblas_datatype_f32_r, rocblas_gemm_algo_standard, 0, 0);
-    return st == rocblas_status_success ? 0 : -1;
+    const size_t size = dtype == APE_F32 ? 4 : 2;
+    const long first = dtype == APE_F32 ? rows : rows_of_whole_rounds(rows, n, k);
+    for (long r0 = 0, nr = first; r0 < rows; r0 += nr, nr = rows - first) {
+        const char* const xr = (const char*)x + (size_t)r0 * ldx * size;
+        char* const yr = (char*)y + (size_t)r0 * ldy * size;
+        const char* const cr = residual ? (const char*)residual + (size_t)r0 * ldy * size : yr;
+        if (rocblas_gemm_ex(h, rocblas_operation_transpose, rocblas_operation_none, n, (rocblas_int)nr, k, &alpha, w, t, k, xr, t, (rocblas_int)ldx, &beta,
+                            cr, t, (rocblas_int)ldy, yr, t, (rocblas_int)ldy, rocblas_datatype_f32_r, rocblas_gemm_algo_standard, 0, 0) != rocblas_status_success) return -1;
+    }
+    return 0;
 }
 
 }  // namespace ape

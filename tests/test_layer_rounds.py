@@ -1,0 +1,43 @@
+"""Which rows of a projection go out as whole rounds of tiles, and that the two products of one make up the whole."""
+import ctypes
+
+import pytest
+import torch
+
+from paper_2502_05431_amd import binding as B
+
+DEV = "cuda:0"
+
+
+def first(rows, n, k):
+    f = B.load_layer()._ZN3ape20rows_of_whole_roundsElii
+    f.restype = ctypes.c_long
+    return f(ctypes.c_long(rows), n, k)
+
+
+@pytest.mark.parametrize("n, k, rows, expect", [
+    (4096, 4096, 1, 1), (4096, 14336, 4095, 4095), (4096, 4096, 4096, 4096), (4096, 4096, 4097, 4096), (4096, 4096, 6145, 6145),   # more than half a round left
+    (4096, 14336, 7000, 4096), (4096, 4096, 12300, 12288), (28672, 4096, 10240, 8192), (6144, 4096, 8191, 8191), (6144, 4096, 8300, 8192),
+    (8192, 8192, 6000, 6000), (11008, 4096, 20000, 20000), (100, 300, 70000, 65536)])
+def test_rows_of_whole_rounds(n, k, rows, expect):
+    assert first(rows, n, k) == expect
+
+
+@pytest.mark.gpu
+@pytest.mark.parametrize("rows, n, k, residual", [(4097, 4096, 264, True), (4200, 4096, 4104, False), (8201, 6144, 128, True)])
+def test_both_products(rows, n, k, residual):
+    """Row strides wider than the rows; nothing but the rows is written."""
+    assert first(rows, n, k) < rows
+    g = torch.Generator(device=DEV)
+    g.manual_seed(3)
+    rnd = lambda *s: torch.randn(s, generator=g, device=DEV).bfloat16()
+    x, w, r = rnd(rows, k + 8), rnd(n, k) * k ** -0.5, rnd(rows, n + 16)
+    y = torch.full((rows, n + 16), 7.0, device=DEV, dtype=torch.bfloat16)
+    f = B.load_layer()._ZN3ape8gemm_xwTEPKvlS1_S1_PvlliiiP12ihipStream_t
+    p, c = ctypes.c_void_p, ctypes.c_long
+    assert f(p(x.data_ptr()), c(k + 8), p(w.data_ptr()), p(r.data_ptr() if residual else None), p(y.data_ptr()), c(n + 16), c(rows), n, k, B.APE_BF16,
+             p(torch.cuda.current_stream().cuda_stream)) == 0
+    ref = x[:, :k].float() @ w.float().T + (r[:, :n].float() if residual else 0.0)
+    # one rounding to bf16 of sums of order 1 to 5, fp32 sums
+    assert ((y[:, :n].float() - ref).abs() <= 2 ** -8 * ref.abs() + 1e-3).all()
+    assert (y[:, n:] == 7.0).all()
