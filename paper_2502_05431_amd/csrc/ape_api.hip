@@ -354,6 +354,18 @@ TreePlan plan_tree(const ShapeInfo& si, long total_ctx, int n_nodes, int q_len) 
     return p;
 }
 
+// Tokens of a run of nodes (tree_plan_kernel), 0: no runs.  As many runs as fill the slots of the chip once, two workgroups a CU, whole teams of row tiles per XCD (16/2 heads, 200 query
+// tokens over 64 x 512: 19 runs, 38 teams of 13 tiles, 140 us, 16 runs 97, a result per node 99).  Four nodes a run and more: before / with runs, us, 32/8 heads, 64 query tokens, two
+// nodes a run (64 x 512) 73 / 80, six (200 x 200) 161 / 136; 128 over 24 ragged of 1000, 1.5 a run, 87 / 93.  Not with one row tile per KV head, whose loads are
+// non-temporal without runs (32 over 256 x 512 180 / 193).
+int tree_run_len(const ShapeInfo& si, const ape_tree_node* nodes, int n_nodes, long total_ctx, int q_len, const TreePlan& plan) {
+    if (!si.mfma || q_len == 1 || plan.block_rows != 128 || total_ctx < 1) return 0;
+    long groups = 0;
+    for (int n = 0; n < n_nodes; ++n) groups += nodes[n].leaf_children != 0;
+    const long tiles = ceil_div((long)q_len * si.group, 128), teams = 8 * (tiles >= 64 ? 1 : 64 / tiles), runs = teams < si.hkv ? 1 : teams / si.hkv;
+    return tiles > 1 && groups >= 4 * runs ? ceil_div(total_ctx, runs) : 0;
+}
+
 // Checks the numbering rules of ape_tree_node and finds the level ranges.
 int check_tree(const ape_tree_node* nodes, int n_nodes, int n_chunks, int* n_levels, int32_t* level_start) {
     if (!nodes) return fail(APE_ERR_INVALID_ARG, "tree nodes are NULL");
@@ -762,7 +774,7 @@ int ape_attention_tree(const ape_shape* shape, const ape_request* req,
 
     TreePlanArgs tp{};
     tp.nodes = nodes_dev; tp.cu = req->cu_chunk_lens; tp.plan = plan_dev;
-    tp.n_nodes = n_nodes; tp.max_splits = plan.max_splits; tp.split_len = plan.len;
+    tp.n_nodes = n_nodes; tp.max_splits = plan.max_splits; tp.split_len = plan.len; tp.run_len = tree_run_len(si, nodes_host, n_nodes, req->total_ctx_len, q_len, plan);
     hipError_t he = launch_tree_plan(tp, st);
     if (he != hipSuccess) return fail(APE_ERR_DEVICE, "tree plan kernel: %s", hipGetErrorString(he));
 
@@ -779,7 +791,7 @@ int ape_attention_tree(const ape_shape* shape, const ape_request* req,
     // The prefix and own tokens' workgroup has a CU of its own where they are many (half of one / this, 20 contexts of 43 tokens behind 3489 own ones, 32/8 heads of 128, 59.5 / 49.6 us, the flash
     // kernel 57.9; 8 of 36 behind 1225, fp32, 76.8 / 46.9; over 93 sizes behind 500 and more 1.15 times as fast, none slower), as long as the splits leave it one.
     const FewForm form = own >= 500 && (plan.max_splits + 1L) * si.hkv <= 256 ? FewForm::full : FewForm::half;
-    he = few ? launch_few_rows(a, si.dtype, form, st) : launch_query(si, a, plan.block_rows, st);
+    he = few ? launch_few_rows(a, si.dtype, form, st) : tp.run_len > 0 ? launch_flash_tree(a, nodes_dev, st) : launch_query(si, a, plan.block_rows, st);
     if (he != hipSuccess) return fail(APE_ERR_DEVICE, "attention kernel: %s", hipGetErrorString(he));
 
     m.part_o = part_o; m.part_lse = part_lse; m.out = out; m.lse_out = lse_out; m.nodes = nodes_dev; m.plan = plan_dev;

@@ -1100,6 +1100,129 @@ __global__ __launch_bounds__(NT) void flash_uneven_kernel(const QueryArgs a, int
 }
 
 // ------------------------------------------------------------------------------------------
+// Query rows under a tree whose plan has runs of nodes (tree_plan_kernel): the same teams and narrow tiles.  A workgroup takes the nodes of a run one after the other.  Behind
+// each, the node's block result (V, L) and what its slot holds become one: weights S L and the slot's LogSumExp so far, Appendix C.2 at the parent.  The slot is the
+// accumulator: every lane reads and writes its own values of it, 64 KB a workgroup and node, where a result per node would be written and read again by the merge,
+// and the 64 registers that a second accumulator takes are there between two streams only.
+// Whole calls, 32/8 heads, 256 query tokens, a result per node / this, us: 64 nodes of 2048 tokens (65 partial results a row, 275 MB, become 9; merge 67 / 13) 610 / 593, 256 of 512
+// 968 / 856, 200 of 200 620 / 429; 64 query tokens over 256 of 512 278 / 257.  What bounds it: the flash loop, one node's wind-down and fold at a time beside the other workgroup of the CU.
+// (The next node's first loads start in front of the fold: 604 without.  Wide tiles, one workgroup a CU: the first two 577, 936.)
+struct TreeNode { int t0, t1; float scale; };
+__device__ __forceinline__ TreeNode tree_node(const ape_tree_node* n, const int32_t* cu) {
+    static_assert(sizeof(ape_tree_node) == 16, "scale, first, count, leaf_children");
+    const int first = scalar_load_i32(&n->first), count = scalar_load_i32(&n->count);
+    return {scalar_load_i32(cu + first), scalar_load_i32(cu + first + count), __uint_as_float((uint32_t)scalar_load_i32((const int32_t*)&n->scale))};
+}
+template <int G>
+__global__ __launch_bounds__(NT) __attribute__((amdgpu_waves_per_eu(2, 2))) void flash_tree_kernel(const OneQuery a, const int n_qtiles, const ape_tree_node* const nodes) {
+    extern __shared__ __attribute__((aligned(16))) char lds[];
+    constexpr int BM = NW * 32, RB = 1;
+    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6, l32 = lane & 31, hi = lane >> 5;
+    const int ctx_teams = a.n_ctx_splits * a.n_kv_heads, ctx_blocks = (ctx_teams + 7) / 8 * 8 * n_qtiles;
+    int team, qtile, split, hk;
+    if ((int)blockIdx.x < ctx_blocks) {
+        team_of_block(blockIdx.x, n_qtiles, team, qtile);
+        if (team >= ctx_teams) return;
+        hk = team % a.n_kv_heads; split = team / a.n_kv_heads;
+    } else {
+        team_of_block(blockIdx.x - ctx_blocks, n_qtiles, team, qtile);
+        if (team >= a.n_kv_heads) return;
+        split = a.n_ctx_splits; hk = team;
+    }
+    const KvView kv = load_view<OneQuery>(0);
+    const int hq = a.n_q_heads, q_len = a.q_len;
+    const long stride_b = (long)a.n_kv_heads * ROWB, head_b = (long)hk * ROWB;
+    const float inv_sqrt_d = 0.08838834764831845f;      // 1/sqrt(128)
+    const bool own = split >= a.n_ctx_splits;
+    const int causal_off = kv.self_len - q_len;
+    const int R = qtile * BM + wave * 32 + l32, tok = R / G, g = R % G;
+    const bool valid = tok < q_len, idle = __builtin_amdgcn_readfirstlane(qtile * BM + wave * 32) / G >= q_len;
+    const int lim[RB] = {(valid ? tok : q_len - 1) + causal_off};
+    const long slot = (long)split * a.units_total + (long)tok * hq + hk * G + g;
+    float* const o = a.part_o + slot * D + 4 * hi;
+
+    long t0 = 0, t1 = 0;
+    if (!own) { ctx_split_range(a, kv, split, t0, t1); if (t0 == t1) return; }     // (a slot that is not in use)
+    const int node0 = t0 < 0 ? (int)(-1 - t0) : -1, n_nodes = node0 < 0 ? 1 : (int)t1;
+    float lse = -INFINITY;                              // of the slot so far
+    bool any = false;
+    // starts the loads of the next node from n on that has tokens (the prefix and own tokens: of them); false: there is none
+    RingStart<Ring<RB>::slots, false, false> rs;
+    float next_scale = 1.f;
+    int n = 0;
+    auto start_next = [&]() {
+        Stream walk;
+        int vis_lo = 0;
+        if (own) {
+            if (n++ > 0) return false;
+            const int tok_lo = min(qtile * BM + wave * 32, q_len * G - 1) / G, wg_tok_hi = min((qtile * BM + BM - 1) / G, q_len - 1);
+            walk.init_seq((const char*)kv.k_prefix + head_b, (const char*)kv.v_prefix + head_b, kv.prefix_len,
+                          (const char*)kv.k_self + head_b, (const char*)kv.v_self + head_b, wg_tok_hi + causal_off + 1, stride_b);
+            vis_lo = tok_lo + causal_off;
+        } else {
+            TreeNode x{(int)t0, (int)t1, 1.f};
+            do {
+                if (n >= n_nodes) return false;
+                if (node0 >= 0) x = tree_node(nodes + node0 + n, kv.cu);
+                ++n;
+            } while (x.t0 >= x.t1);                     // (for all wavefronts)
+            walk.init_ctx(kv.cu, kv.k_chunks, kv.v_chunks, kv.n_chunks, x.t0, x.t1, stride_b, head_b);
+            next_scale = x.scale;
+        }
+        start_stream(rs, walk, lds, __builtin_amdgcn_readfirstlane(vis_lo), tid);
+        return true;
+    };
+    bool more = start_next();
+    bf16x8 qf[RB][8];
+    {
+        const char* qp = (const char*)a.q + ((long)tok * hq + hk * G + g) * ROWB + hi * 16;
+#pragma unroll
+        for (int ks = 0; ks < 8; ++ks) {
+            u32x4 w = {0, 0, 0, 0};
+            if (valid) w = *(const u32x4*)(qp + ks * 32);
+            qf[0][ks] = __builtin_bit_cast(bf16x8, w);
+        }
+    }
+    const float sc2 = own ? inv_sqrt_d * LOG2E : inv_sqrt_d / kv.temperature * LOG2E;
+#pragma unroll 1
+    while (more) {
+        const float scale = next_scale;
+        WaveState<RB> st;
+        init_state<RB>(st);
+        if (idle) run_blocks_idle<RB>(rs, lds); else run_blocks<RB>(rs, lds, qf, st, sc2, lim);
+        asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
+        ring_barrier();                                 // every wavefront has read its last block: the next node's first ones go where it was
+        more = start_next();
+
+        const float lt = st.l[0] + __shfl_xor(st.l[0], 32);
+        const float v = lt > 0.f ? scale * ((st.m[0] + __builtin_amdgcn_logf(lt)) * LN2) : -INFINITY;
+        // new values: those of the slot times e^(lse - sum) and the node's times e^(v - sum) / lt
+        const float most = fmaxf(lse, v), ea = any && lse > -INFINITY ? __builtin_amdgcn_exp2f((lse - most) * LOG2E) : 0.f;
+        const float eb = lt > 0.f ? __builtin_amdgcn_exp2f((v - most) * LOG2E) : 0.f, z = ea + eb;
+        const float wa = z > 0.f ? ea / z : 0.f, wb = z > 0.f ? eb / (z * lt) : 0.f;
+        if (valid) {
+#pragma unroll
+            for (int db = 0; db < 4; ++db)
+#pragma unroll
+                for (int q4 = 0; q4 < 4; ++q4) {
+                    f32x4* const at = (f32x4*)(o + 32 * db + 8 * q4);
+                    f32x4 w = {0.f, 0.f, 0.f, 0.f};
+                    if (any) w = *at;
+#pragma unroll
+                    for (int e = 0; e < 4; ++e) {       // (a weight of zero takes nothing, be the value infinite)
+                        const float x = wb > 0.f ? st.o[0][db][4 * q4 + e] * wb : 0.f;
+                        w[e] = wa > 0.f ? fmaf(w[e], wa, x) : x;
+                    }
+                    *at = w;
+                }
+        }
+        if (z > 0.f) lse = most + __builtin_amdgcn_logf(z) * LN2;
+        any = true;
+    }
+    if (valid && hi == 0) a.part_lse[slot] = lse;
+}
+
+// ------------------------------------------------------------------------------------------
 // Block-diagonal causal encode: team = (chunk, KV head), members = query tiles of the chunk,
 // heaviest (last) tile first.  Writes the final bf16 output.  `vblock` is the tile's index in the
 // order team_of_block() defines.
@@ -1311,6 +1434,24 @@ hipError_t launch_flash_prefill(const QueryArgs& a, int block_rows, hipStream_t 
     if (bm == 256) return launch_prefill_g<2, false>(group, a, grid, n_qtiles, s);
     // one row tile: every K/V block is fetched by one workgroup and never again -> non-temporal loads
     return n_qtiles == 1 ? launch_prefill_g<1, true>(group, a, grid, n_qtiles, s) : launch_prefill_g<1, false>(group, a, grid, n_qtiles, s);
+}
+
+template <int G>
+static hipError_t launch_tree_t(const QueryArgs& a, dim3 grid, int n_qtiles, const ape_tree_node* nodes, hipStream_t s) {
+    hipError_t e = hipFuncSetAttribute((const void*)flash_tree_kernel<G>, hipFuncAttributeMaxDynamicSharedMemorySize, Ring<1>::slots * SLOTB);
+    if (e != hipSuccess) return e;
+    flash_tree_kernel<G><<<grid, NT, Ring<1>::slots * SLOTB, s>>>(OneQuery(a), n_qtiles, nodes);
+    return hipGetLastError();
+}
+hipError_t launch_flash_tree(const QueryArgs& a, const ape_tree_node* nodes, hipStream_t s) {
+    const int group = a.n_q_heads / a.n_kv_heads, n_qtiles = (a.q_len * group + 127) / 128;
+    const dim3 grid((unsigned)((((long)a.n_ctx_splits * a.n_kv_heads + 7) / 8 * 8 + (a.n_kv_heads + 7) / 8 * 8) * n_qtiles));
+    switch (group) {
+        case 1: return launch_tree_t<1>(a, grid, n_qtiles, nodes, s);
+        case 2: return launch_tree_t<2>(a, grid, n_qtiles, nodes, s);
+        case 4: return launch_tree_t<4>(a, grid, n_qtiles, nodes, s);
+        default: return launch_tree_t<8>(a, grid, n_qtiles, nodes, s);
+    }
 }
 
 hipError_t launch_flash_encode(const EncodeArgs& a, hipStream_t s) {

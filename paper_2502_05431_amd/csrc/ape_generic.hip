@@ -367,43 +367,95 @@ __global__ __launch_bounds__(256) void pool_uneven_kernel_by_xcd(const MergeArgs
 // Appendix C.1, so they need no boundary between them) and gets ceil(tokens / split_len) splits.
 // An exclusive scan over the nodes gives every such node its first split; the ranges of the
 // splits in use are written out, the slots behind them are left empty.
+// Runs of nodes (run_len > 0): where all children of a node hold contexts of one split or none each, consecutive ones are put into runs of about run_len tokens.  A
+// run is one slot: the attention kernel merges its nodes' results, each weighted by its scaling factor, as it goes, and the merge takes the runs for the parent's splits.
 constexpr int kPlanThreads = 1024;
 constexpr int kMergeWaves = 4;
+// Exclusive scan of v[0 .. n) in place by one wavefront, v[n] the total; lane l owns a run of consecutive values.  (v has room for n + 1, a multiple of 64 and one more.)
+__device__ __forceinline__ void wave_scan(int* v, int n) {
+    const int lane = threadIdx.x & (kWave - 1), each = (n + kWave - 1) / kWave, first = min(lane * each, n), last = min(first + each, n);
+    int sum = 0;
+    for (int j = first; j < last; ++j) sum += v[j];
+    int incl = sum;
+#pragma unroll
+    for (int o = 1; o < kWave; o <<= 1) {
+        const int x = __shfl_up(incl, o);
+        if (lane >= o) incl += x;
+    }
+    int run = incl - sum;
+    for (int j = first; j < last; ++j) { const int x = v[j]; v[j] = run; run += x; }
+    if (lane == kWave - 1) v[n] = incl;
+}
 __global__ __launch_bounds__(kPlanThreads) void tree_plan_kernel(const TreePlanArgs a) {
-    __shared__ int cnt[APE_TREE_MAX_NODES];
-    __shared__ int off[APE_TREE_MAX_NODES];
-    const int tid = threadIdx.x, lane = tid & (kWave - 1);
+    __shared__ int cnt[APE_TREE_MAX_NODES];                  // slots that start at a node
+    __shared__ int off[APE_TREE_MAX_NODES + 1];
+    const int tid = threadIdx.x;
     const TreePlanLayout lay{a.n_nodes, a.max_splits};
     int32_t* first_split = a.plan + lay.first_split_at();
     int32_t* n_splits = a.plan + lay.n_splits_at();
     int32_t* ranges = a.plan + lay.ranges_at();
     for (int i = tid; i < 2 * a.max_splits; i += kPlanThreads) ranges[i] = 0;
-    for (int n = tid; n < APE_TREE_MAX_NODES; n += kPlanThreads) {
-        int c = 0;
-        if (n < a.n_nodes) {
-            const ape_tree_node me = a.nodes[n];
-            if (me.leaf_children) c = (a.cu[me.first + me.count] - a.cu[me.first] + a.split_len - 1) / a.split_len;
-        }
-        cnt[n] = c;
-    }
-    __syncthreads();
-    if (tid < kWave) {
-        // lane owns a run of consecutive nodes; wavefront scan of the run sums, then the runs
-        const int run_len = (a.n_nodes + kWave - 1) / kWave;         // (no counts behind the last node)
-        int sum = 0;
-        for (int j = 0; j < run_len; ++j) sum += cnt[lane * run_len + j];
-        int incl = sum;
-#pragma unroll
-        for (int o = 1; o < kWave; o <<= 1) {
-            const int v = __shfl_up(incl, o);
-            if (lane >= o) incl += v;
-        }
-        int run = incl - sum;
-        for (int j = 0; j < run_len; ++j) { off[lane * run_len + j] = run; run += cnt[lane * run_len + j]; }
-        if (lane == kWave - 1) a.plan[0] = min(incl, a.max_splits);
-    }
-    __syncthreads();
     for (int n = tid; n < a.n_nodes; n += kPlanThreads) {
+        const ape_tree_node me = a.nodes[n];
+        cnt[n] = me.leaf_children ? (a.cu[me.first + me.count] - a.cu[me.first] + a.split_len - 1) / a.split_len : 0;
+        off[n] = cnt[n];
+    }
+    __syncthreads();
+    if (a.run_len > 0) {
+        __shared__ int before[APE_TREE_MAX_NODES + 1];       // tokens of the nodes in front
+        __shared__ int odd[APE_TREE_MAX_NODES + 1];          // nodes in front that no run takes
+        __shared__ int parent[APE_TREE_MAX_NODES];           // of a node in a run: its parent; otherwise -1
+        for (int n = tid; n < a.n_nodes; n += kPlanThreads) {
+            const ape_tree_node me = a.nodes[n];
+            before[n] = me.leaf_children ? a.cu[me.first + me.count] - a.cu[me.first] : 0;
+            odd[n] = !me.leaf_children || cnt[n] > 1;
+            parent[n] = -1;
+        }
+        __syncthreads();
+        if (tid < kWave) wave_scan(before, a.n_nodes); else if (tid < 2 * kWave) wave_scan(odd, a.n_nodes);
+        __syncthreads();
+        auto in_runs = [&](const ape_tree_node& p) {         // (a parent without a token has no run)
+            return !p.leaf_children && p.count > 1 && odd[p.first + p.count] == odd[p.first] && before[p.first + p.count] > before[p.first];
+        };
+        for (int n = tid / kWave; n < a.n_nodes; n += kPlanThreads / kWave) {
+            const ape_tree_node me = a.nodes[n];
+            if (!in_runs(me)) continue;
+            for (int c = me.first + (tid & (kWave - 1)); c < me.first + me.count; c += kWave) {
+                parent[c] = n;
+                const int at = (before[c] - before[me.first]) / a.run_len;
+                cnt[c] = c == me.first || at != (before[c - 1] - before[me.first]) / a.run_len;
+                off[c] = cnt[c];
+            }
+        }
+        __syncthreads();
+        if (tid < kWave) wave_scan(off, a.n_nodes);
+        __syncthreads();
+        for (int n = tid; n < a.n_nodes; n += kPlanThreads) {
+            const ape_tree_node me = a.nodes[n];
+            if (in_runs(me)) {
+                first_split[n] = off[me.first];
+                n_splits[n] = off[me.first + me.count] - off[me.first];
+                cnt[n] = -1;                                 // (written; no slot of its own starts here)
+            } else if (parent[n] >= 0) {
+                first_split[n] = off[n];
+                n_splits[n] = 0;
+                if (cnt[n] > 0 && off[n] < a.max_splits) {
+                    int end = n + 1;
+                    while (end < a.n_nodes && parent[end] == parent[n] && off[end + 1] == off[end]) ++end;   // (off[end + 1] > off[end]: a run starts at `end`)
+                    ranges[2 * off[n]] = -1 - n;
+                    ranges[2 * off[n] + 1] = end - n;
+                }
+            }
+        }
+        __syncthreads();
+        for (int n = tid; n < a.n_nodes; n += kPlanThreads) if (parent[n] >= 0) cnt[n] = -1;
+    } else if (tid < kWave) {
+        wave_scan(off, a.n_nodes);
+    }
+    __syncthreads();
+    if (tid == 0) a.plan[0] = min(off[a.n_nodes], a.max_splits);
+    for (int n = tid; n < a.n_nodes; n += kPlanThreads) {
+        if (cnt[n] < 0) continue;
         first_split[n] = off[n];
         n_splits[n] = cnt[n];
         if (cnt[n] > 0) {
@@ -466,9 +518,10 @@ __global__ __launch_bounds__(kWave * kMergeWaves) void tree_merge_kernel(const T
     float* split_v = (float*)(n_splits + n_nodes);                 // [max_splits] LogSumExp, later log-weight
 
     for (int n = tid; n < n_nodes; n += NT) {
-        nd[n] = a.nodes[n];
         first_split[n] = a.plan[lay.first_split_at() + n];
         n_splits[n] = a.plan[lay.n_splits_at() + n];
+        nd[n] = a.nodes[n];
+        if (n_splits[n] > 0) nd[n].leaf_children = 1;        // (also a node whose children are in runs: the runs are its splits)
     }
     for (int s = tid; s < n_used; s += NT) split_v[s] = a.part_lse[(long)s * U + unit];
     const float l_other = a.part_lse[(long)a.max_splits * U + unit];
@@ -629,9 +682,10 @@ __global__ __launch_bounds__(kWave * kTreeUnitsPerBlock) void tree_merge_wave_ke
     float* split_v = node_w + n_nodes;                             // [max_splits] LogSumExp, later log-weight
 
     for (int n = tid; n < n_nodes; n += NT) {
-        nd[n] = a.nodes[n];
         first_split[n] = a.plan[lay.first_split_at() + n];
         n_splits[n] = a.plan[lay.n_splits_at() + n];
+        nd[n] = a.nodes[n];
+        if (n_splits[n] > 0) nd[n].leaf_children = 1;        // (also a node whose children are in runs: the runs are its splits)
     }
     for (int s = lane; s < n_used; s += kWave) split_v[s] = a.part_lse[(long)s * U + unit];
     const float l_other = a.part_lse[(long)a.max_splits * U + unit];

@@ -122,6 +122,8 @@ struct MergeArgs {
 // merge exactly (Appendix C.1), so no split ever needs to stop at a context boundary inside a group.
 // Layout in int32 words: [0] number of splits in use, [1..3] unused, then first_split[n_nodes],
 // n_splits[n_nodes] (0 for nodes whose children are nodes), split_ranges[2 * max_splits].
+// A run of nodes (run_len) is one slot, which holds their merged result; its range is (-1 - first node, nodes).  Its slots are the parent's splits, whose
+// n_splits then is not 0, and the nodes themselves have none.
 struct TreePlanLayout {
     int n_nodes, max_splits;
     __host__ __device__ long first_split_at() const { return 4; }
@@ -137,6 +139,7 @@ struct TreePlanArgs {
     int32_t n_nodes;
     int32_t max_splits;
     int32_t split_len;
+    int32_t run_len;            // > 0: nodes of one split each under one parent go in runs of about so many tokens (see tree_plan_kernel)
 };
 
 // Kernel-argument block of the tree merge (Appendix C.2 per node, C.5).
@@ -404,6 +407,7 @@ hipError_t launch_merge(const MergeArgs& a, hipStream_t s);
 hipError_t launch_rope_write(const RopeArgs& a, int dtype, hipStream_t s);
 hipError_t launch_tree_plan(const TreePlanArgs& a, hipStream_t s);
 hipError_t launch_tree_merge(const TreeMergeArgs& a, hipStream_t s);
+hipError_t launch_flash_tree(const QueryArgs& a, const ape_tree_node* nodes, hipStream_t s);   // as below, narrow tiles, runs of nodes in the plan
 hipError_t launch_flash_prefill(const QueryArgs& a, int block_rows, hipStream_t s);     // bf16, d = 128; block_rows from the plan
 hipError_t launch_flash_encode(const EncodeArgs& a, hipStream_t s);     // bf16, d = 128
 hipError_t launch_encode_walk(const EncodeArgs& a, int parts, hipStream_t s);   // the same shapes, short contexts

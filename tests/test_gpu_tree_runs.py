@@ -1,0 +1,74 @@
+"""GPU parity of trees whose nodes go in runs (flash shapes, many nodes of one split each): runs of equal and of ragged nodes, empty nodes at their ends and a parent
+without a token, several parents, parents that no run takes (a node among their children, a node of several splits, a single child), nodes whose contexts lie anywhere,
+scaling factors far apart, and values that are infinite where the weight is zero."""
+import numpy as np
+import pytest
+import torch
+
+from paper_2502_05431_amd import workloads as W
+
+import helpers as H
+from test_gpu_tree import _check_tree
+
+pytestmark = pytest.mark.gpu
+DEV = "cuda:0"
+
+
+def _request(hq, hkv, lens, rows, prefix=9, own=3):
+    spec = W.WorkloadSpec(name="runs", cfg=6, dtype="bf16", n_q_heads=hq, n_kv_heads=hkv, head_dim=128, prefix_len=prefix, chunk_lens=tuple(lens), q_len=rows,
+                          decode_steps=own, temperature=0.8, scale=0.9)
+    return spec, W.make_request(spec, DEV)
+
+
+def _mixed():
+    """Root over: a parent of 30 nodes, a parent of one, a parent of a node and of a parent of 20, a node of contexts."""
+    nodes = [(1.0, 1, 4, False)]
+    nodes += [(0.9, 5, 30, False), (0.8, 35, 1, False), (1.1, 36, 2, False), (0.7, 0, 3, True)]
+    at = 3
+    for i in range(30):
+        nodes.append((0.6 + 0.02 * i, at, 1 + i % 2, True)); at += 1 + i % 2
+    nodes.append((0.95, at, 2, True)); at += 2
+    nodes += [(0.85, at, 1, True), (0.9, 38, 20, False)]; at += 1
+    for i in range(20):
+        nodes.append((1.2 - 0.03 * i, at, 1, True)); at += 1
+    return nodes, at
+
+
+# (five tiles of 128 rows per KV head: 12 runs, for which 48 nodes are needed)
+@pytest.mark.parametrize("hq, hkv, rows", [(32, 8, 160), (16, 8, 290), (64, 8, 70), (8, 8, 530), (16, 2, 330)])
+@pytest.mark.parametrize("what", ["equal", "ragged", "mixed"])
+def test_runs(hq, hkv, rows, what):
+    if what == "mixed":
+        nodes, n = _mixed()
+        lens = [(37 * i + 5) % 70 for i in range(n)]
+        lens[40] = 1500                                      # (several splits: its parent's nodes are no run)
+    else:
+        n = 60
+        lens = [32] * n if what == "equal" else [(53 * i) % 90 for i in range(n - 4)] + [0] * 4
+        nodes = W.tree_per_context(n, 0.85)
+    spec, r = _request(hq, hkv, lens, rows)
+    _check_tree(spec, r, H.HostArrays(r), nodes, rows, rows + 3, what="%s %d/%d" % (what, hq, hkv))
+
+
+def test_empty_parent_and_contexts_out_of_order():
+    lens = [40] * 50 + [0] * 10
+    nodes = [(1.0, 1, 2, False), (0.8, 3, 50, False), (0.9, 53, 10, False)]
+    nodes += [(0.7 + 0.005 * i, 49 - i, 1, True) for i in range(50)] + [(0.9, 50 + i, 1, True) for i in range(10)]
+    spec, r = _request(32, 8, lens, 150)
+    _check_tree(spec, r, H.HostArrays(r), nodes, 150, 150, what="empty parent")
+
+
+def test_weights_far_apart():
+    """Scores that make a node's weight vanish beside another's, before and behind it in a run; the infinite values of such a node take no part."""
+    spec, r = _request(32, 8, [64] * 60, 150)
+    r.k_ctx[64 * 7:64 * 8] *= 40.0
+    nodes = W.tree_per_context(60, 0.9)
+    _check_tree(spec, r, H.HostArrays(r), nodes, 150, 150, what="far apart")
+    nodes[21] = (60.0, 20, 1, True)                          # A = 60 times its LogSumExp, about 250: the others' weights are zero in fp32
+    out, lse = H.run_tree(spec, r, nodes, 150, 150)
+    ok = torch.isfinite(out).all()
+    r.v_ctx[64 * 30:64 * 31, :, 5] = float("inf")
+    again, lse2 = H.run_tree(spec, r, nodes, 150, 150)
+    assert ok and torch.equal(lse, lse2)
+    gone = (lse.T.reshape(150, 32) > 200.0)[..., None].expand(150, 32, 128)
+    assert gone.any() and torch.equal(out.reshape(150, 32, 128)[gone], again.reshape(150, 32, 128)[gone])
