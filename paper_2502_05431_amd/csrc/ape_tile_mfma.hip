@@ -5,7 +5,8 @@
 // Math (arXiv 2502.05431): as in the flash kernels -- block results of Appendix C.1, context scores
 // q.k/(T sqrt d) (Section 4.4), the scaling factor applied later by the merge kernel.
 //
-// Precision.  fp32 storage runs on the fp32 MFMA (32x32x2): fp32 scores, probabilities and sums.  bf16 storage runs on the bf16
+// Precision.  fp32 storage runs on the fp32 MFMA (32x32x2): fp32 scores, probabilities and sums; most encodes of up to 128 dims in three bf16 pieces
+// a factor on the bf16 MFMA, exact as those ("fp32 in three bf16 pieces" below).  bf16 storage runs on the bf16
 // MFMA (32x32x16): fp32 scores and sums, every probability taken as the sum of two bf16 values, 16 significant bits, i.e. two
 // MFMAs per V fragment.  exp and log are the hardware's, of base 2.  Against 64 bits, this / the vector-ALU kernels (fp32
 // probabilities, the library's exp), mean of 220 calls over head_dims 40 .. 256 and up to 10240 tokens: outputs fp32 2.1e-7 .. 3.1e-7 /
@@ -26,7 +27,7 @@
 // attention's own count for bf16), the fixed chain of a launch, first loads and merge for a short query.  Against the
 // vector-ALU kernels, which give a wavefront one row and read every K/V byte once per row (same card, same inputs):
 // fp32 encode of eight contexts of about 512 tokens, 32/8 heads of 128: 2754 -> 180 us (94 TFLOP/s; the vendor's fp32 GEMM
-// reaches 154); 64 bf16 rows over 20 x 512 tokens, 16/8 heads of 256: 14200 -> 43 us (2.0 TB/s, on inputs that change); a fp32 decode step over 4096
+// reaches 153), 116 in bf16 pieces; 64 bf16 rows over 20 x 512 tokens, 16/8 heads of 256: 14200 -> 43 us (2.0 TB/s, on inputs that change); a fp32 decode step over 4096
 // tokens, 16/8 heads of 256: 28 us, 88 by one wavefront per workgroup; 16 fp32 rows over 4 x 32 tokens, 4/2 heads of 64: 47.8 -> 14.8 us (on the few-row kernels 7.3).
 #include "ape_exact_row.h"
 
